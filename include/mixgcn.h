@@ -385,6 +385,12 @@ int mixgcn_softmax_xent(int dtype, const void* logits, int64_t ldl, const int32_
 int mixgcn_graph_info(const mixgcn_graph* g, mixgcn_graph_view* out);
 int mixgcn_graph_free(mixgcn_graph* g);
 /*
+ * Device and pinned host memory of freed graphs and of the work arrays of mixgcn_build_csr and
+ * mixgcn_reorder_rcm stays cached for the next such call, up to 4 GiB per device (256 MiB pinned).
+ * mixgcn_release_memory gives all of it back to the driver.  Thread safe.
+ */
+int mixgcn_release_memory(void);
+/*
  * A stream whose kernels run on a subset of the compute units, for splitting the GPU between
  * the sparse and the dense half of the pipeline: CU c is enabled iff (c / 8) % groups lies in
  * [lo, hi).  Default priority.  Destroy with mixgcn_stream_destroy (after its work is done).

@@ -11,7 +11,7 @@ from .binding import (  # noqa: F401
     apply_bitmap,
     backward_pipelined, bandwidth, build_csr, dropout_bitmap, forward_pipelined, pipeline_window,
     cu_subset_stream,
-    layer_bwd, layer_fwd, lib_path, load_library, measure_peaks, normalize, permute_rows, pipeline_stages, relabel_edges,
+    layer_bwd, layer_fwd, lib_path, load_library, measure_peaks, normalize, permute_rows, pipeline_stages, relabel_edges, release_memory,
     relu_bitmap, reorder_rcm, set_aggregate_whole_rows, set_update_arith, softmax_xent, update, version,
 )
 from .model import GCNDropoutStep, GCNStep, GINStep, SAGEStep  # noqa: F401

@@ -120,7 +120,7 @@ def load_library():
     lib.mixgcn_pipeline_timing.argtypes = [vp, ctypes.c_int]
     lib.mixgcn_pipeline_timing_read.argtypes = [vp, ctypes.c_int, ctypes.POINTER(ctypes.c_double),
                                                 ctypes.POINTER(ctypes.c_int64)]
-    for name in ("build_csr", "normalize", "aggregate", "aggregate_masked", "relu_bitmap",
+    for name in ("release_memory", "build_csr", "normalize", "aggregate", "aggregate_masked", "relu_bitmap",
                  "measure_peaks", "reorder_rcm", "bandwidth", "relabel_edges", "permute_rows",
                  "update", "layer_fwd", "layer_bwd",
                  "softmax_xent", "graph_info", "graph_free", "pipeline_create", "pipeline_destroy",
@@ -239,6 +239,11 @@ class Graph:
             self.free()
         except Exception:
             pass
+
+
+def release_memory() -> None:
+    """Gives the device memory that the library keeps for later graphs back to the driver."""
+    _check(load_library().mixgcn_release_memory(), "release_memory")
 
 
 def cu_subset_stream(lo: int, hi: int, groups: int):

@@ -96,7 +96,7 @@ static int acquire_agg_slot(const mixgcn_graph* g, hipStream_t stream, float** o
                 if (slots[i].last_use < pick->last_use) pick = &slots[i];
             MIXGCN_HIP_TRY(hipDeviceSynchronize());
         }
-        if (!pick->p) MIXGCN_HIP_TRY(hipMalloc((void**)&pick->p, g->agg_slot_bytes));
+        if (!pick->p) MIXGCN_TRY(pool_alloc_unordered((void**)&pick->p, g->agg_slot_bytes));
         pick->stream = stream;
         pick->bound = true;
     }
@@ -200,11 +200,9 @@ int mixgcn_build_csr(const uint32_t* src, const uint32_t* dst, uint64_t n_edges,
     do {
         if (hipGetDevice(&g->device) != hipSuccess) { rc = fail(MIXGCN_EHIP, "hipGetDevice"); break; }
         if ((flags & MIXGCN_INPUT_ON_HOST) && n_edges > 0) {
-            if (hipMalloc((void**)&d_src, n_edges * 4) != hipSuccess ||
-                hipMalloc((void**)&d_dst, n_edges * 4) != hipSuccess) {
-                rc = fail(MIXGCN_ENOMEM, "build_csr: staging the host edge list");
-                break;
-            }
+            rc = pool_alloc_unordered((void**)&d_src, n_edges * 4);
+            if (rc == MIXGCN_OK) rc = pool_alloc_unordered((void**)&d_dst, n_edges * 4);
+            if (rc != MIXGCN_OK) break;
             if (hipMemcpy(d_src, src, n_edges * 4, hipMemcpyHostToDevice) != hipSuccess ||
                 hipMemcpy(d_dst, dst, n_edges * 4, hipMemcpyHostToDevice) != hipSuccess) {
                 rc = fail(MIXGCN_EHIP, "build_csr: copying the host edge list");
@@ -223,8 +221,8 @@ int mixgcn_build_csr(const uint32_t* src, const uint32_t* dst, uint64_t n_edges,
             g->has_transpose = true;
         }
     } while (0);
-    if (d_src) (void)hipFree(d_src);
-    if (d_dst) (void)hipFree(d_dst);
+    pool_free_on(d_src, s);
+    pool_free_on(d_dst, s);
     if (rc != MIXGCN_OK) {
         mixgcn_graph_free(g);
         return rc;
@@ -236,13 +234,24 @@ int mixgcn_build_csr(const uint32_t* src, const uint32_t* dst, uint64_t n_edges,
 int mixgcn_graph_free(mixgcn_graph* g)
 {
     if (!g) return MIXGCN_OK;
+    // work on the arrays may be queued on any stream of the graph's device
+    int dev = g->device;
+    (void)hipGetDevice(&dev);
+    if (dev != g->device) (void)hipSetDevice(g->device);
+    (void)hipDeviceSynchronize();
+    if (dev != g->device) (void)hipSetDevice(dev);
     csr_free(&g->fwd);
     csr_free(&g->tr);
-    if (g->deg) (void)hipFree(g->deg);
-    if (g->dinv) (void)hipFree(g->dinv);
-    for (AggSlot& slot : g->agg_slots)
-        if (slot.p) (void)hipFree(slot.p);
+    pool_free(g->deg);
+    pool_free(g->dinv);
+    for (AggSlot& slot : g->agg_slots) pool_free(slot.p);
     delete g;
+    return MIXGCN_OK;
+}
+
+int mixgcn_release_memory(void)
+{
+    pool_release();
     return MIXGCN_OK;
 }
 
@@ -262,7 +271,7 @@ int mixgcn_normalize_mode(mixgcn_graph* g, int mode, float eps, void* stream)
     // the row-piece scratch of the aggregation: sized once from the entry count, first slot here
     if (!g->agg_slot_bytes) g->agg_slot_bytes = agg_scratch_bound(g->fwd.nnz);
     if (!g->agg_slots[0].p)
-        MIXGCN_HIP_TRY(hipMalloc((void**)&g->agg_slots[0].p, g->agg_slot_bytes));
+        MIXGCN_TRY(pool_alloc_unordered((void**)&g->agg_slots[0].p, g->agg_slot_bytes));
     return MIXGCN_OK;
 }
 
@@ -284,7 +293,7 @@ int mixgcn_graph_reserve_streams(mixgcn_graph* g, int32_t n_streams)
     for (int i = 0; i < kAggSlots && ready < n_streams; ++i) {
         AggSlot& slot = g->agg_slots[i];
         if (slot.bound || slot.p) continue;
-        MIXGCN_HIP_TRY(hipMalloc((void**)&slot.p, g->agg_slot_bytes));
+        MIXGCN_TRY(pool_alloc_unordered((void**)&slot.p, g->agg_slot_bytes));
         ++ready;
     }
     return MIXGCN_OK;

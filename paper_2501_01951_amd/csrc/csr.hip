@@ -194,25 +194,25 @@ __global__ __launch_bounds__(kBlock) void copy_entries_kernel(const uint2* __res
 }
 
 template <typename T>
-int dmalloc(T** p, size_t count)
+int dmalloc(T** p, size_t count, hipStream_t s)
 {
-    *p = nullptr;
-    if (count == 0) count = 1;
-    MIXGCN_HIP_TRY(hipMalloc((void**)p, count * sizeof(T)));
-    return MIXGCN_OK;
+    return pool_alloc((void**)p, (count ? count : 1) * sizeof(T), s);
 }
 
+// Work arrays of a build, released on its stream.
 struct TmpBufs {
+    explicit TmpBufs(hipStream_t stream) : s(stream) {}
+    hipStream_t s;
     uint64_t* keys = nullptr;
     uint64_t* alt = nullptr;
     void* tmp = nullptr;
     uint32_t* flags = nullptr;
     ~TmpBufs()
     {
-        if (keys) (void)hipFree(keys);
-        if (alt) (void)hipFree(alt);
-        if (tmp) (void)hipFree(tmp);
-        if (flags) (void)hipFree(flags);
+        pool_free_on(keys, s);
+        pool_free_on(alt, s);
+        pool_free_on(tmp, s);
+        pool_free_on(flags, s);
     }
 };
 
@@ -220,13 +220,13 @@ struct TmpBufs {
 
 void csr_free(Csr* c)
 {
-    if (c->rowptr) (void)hipFree(c->rowptr);
-    if (c->col) (void)hipFree(c->col);
-    if (c->cv) (void)hipFree(c->cv);
-    if (c->val) (void)hipFree(c->val);
-    if (c->cv_t) (void)hipFree(c->cv_t);
-    if (c->val_t) (void)hipFree(c->val_t);
-    if (c->grp_row) (void)hipFree(c->grp_row);
+    pool_free(c->rowptr);
+    pool_free(c->col);
+    pool_free(c->cv);
+    pool_free(c->val);
+    pool_free(c->cv_t);
+    pool_free(c->val_t);
+    pool_free(c->grp_row);
     *c = Csr();
 }
 
@@ -239,17 +239,17 @@ int csr_from_edges(const uint32_t* d_src, const uint32_t* d_dst, uint64_t n_edge
     const int sort_bits = 2 * bits + (self_loops ? 0 : 1);  // the drop marker needs one more bit
     const int64_t n_keys = (int64_t)((symmetrize ? 2 : 1) * n_edges + (self_loops ? n : 0));
 
-    TmpBufs t;
-    MIXGCN_TRY(dmalloc(&t.keys, (size_t)n_keys));
-    MIXGCN_TRY(dmalloc(&t.alt, (size_t)n_keys));
+    TmpBufs t(s);
+    MIXGCN_TRY(dmalloc(&t.keys, (size_t)n_keys, s));
+    MIXGCN_TRY(dmalloc(&t.alt, (size_t)n_keys, s));
     const int64_t n_ctiles = ceil_div(n_keys > 0 ? n_keys : 1, kCompactTile);
     size_t tmp_bytes = sort_tmp_bytes(n_keys);
     const size_t compact_bytes =
         ((size_t)n_ctiles * 4 + 255) / 256 * 256 + ((size_t)n_ctiles * 8 + 255) / 256 * 256 +
         scan_tmp_bytes(n_ctiles) + 256;
     if (compact_bytes > tmp_bytes) tmp_bytes = compact_bytes;
-    MIXGCN_HIP_TRY(hipMalloc(&t.tmp, tmp_bytes));
-    MIXGCN_TRY(dmalloc(&t.flags, 4));  // [0] bad endpoint, [1] empty rows, [2..3] total (u64)
+    MIXGCN_TRY(pool_alloc(&t.tmp, tmp_bytes, s));
+    MIXGCN_TRY(dmalloc(&t.flags, 4, s));  // [0] bad endpoint, [1] empty rows, [2..3] total (u64)
     MIXGCN_HIP_TRY(hipMemsetAsync(t.flags, 0, 16, s));
 
     if (n_keys > 0) {
@@ -290,10 +290,10 @@ int csr_from_edges(const uint32_t* d_src, const uint32_t* d_dst, uint64_t n_edge
     c.nnz_padded = (c.n_groups + 1) * kGroupNnz + kEntryPad;
     int rc = MIXGCN_OK;
     do {
-        if ((rc = dmalloc(&c.rowptr, (size_t)n + 1)) != MIXGCN_OK) break;
-        if ((rc = dmalloc(&c.col, (size_t)nnz)) != MIXGCN_OK) break;
-        if ((rc = dmalloc(&c.cv, (size_t)c.nnz_padded)) != MIXGCN_OK) break;
-        if ((rc = dmalloc(&c.grp_row, (size_t)c.n_groups + 1)) != MIXGCN_OK) break;
+        if ((rc = dmalloc(&c.rowptr, (size_t)n + 1, s)) != MIXGCN_OK) break;
+        if ((rc = dmalloc(&c.col, (size_t)nnz, s)) != MIXGCN_OK) break;
+        if ((rc = dmalloc(&c.cv, (size_t)c.nnz_padded, s)) != MIXGCN_OK) break;
+        if ((rc = dmalloc(&c.grp_row, (size_t)c.n_groups + 1, s)) != MIXGCN_OK) break;
         if (hipMemsetAsync(c.cv, 0, (size_t)c.nnz_padded * 8, s) != hipSuccess) {
             rc = fail(MIXGCN_EHIP, "hipMemsetAsync(cv)");
             break;
@@ -319,6 +319,7 @@ int csr_from_edges(const uint32_t* d_src, const uint32_t* d_dst, uint64_t n_edge
         c.has_empty_rows = h_flags[1] != 0;
     } while (0);
     if (rc != MIXGCN_OK) {
+        (void)hipStreamSynchronize(s);  // the arrays may have work queued on them
         csr_free(&c);
         return rc;
     }
@@ -329,15 +330,15 @@ int csr_from_edges(const uint32_t* d_src, const uint32_t* d_dst, uint64_t n_edge
 int normalize_graph(mixgcn_graph* g, int mode, float eps, hipStream_t s)
 {
     const uint32_t n = g->n;
-    if (!g->deg) MIXGCN_TRY(dmalloc(&g->deg, n));
-    if (!g->dinv) MIXGCN_TRY(dmalloc(&g->dinv, n));
+    if (!g->deg) MIXGCN_TRY(dmalloc(&g->deg, n, s));
+    if (!g->dinv) MIXGCN_TRY(dmalloc(&g->dinv, n, s));
     if (n > 0)
         hipLaunchKernelGGL(degree_kernel, dim3((unsigned)ceil_div(n, kBlock)), dim3(kBlock), 0, s,
                            g->fwd.rowptr, n, mode, g->deg, g->dinv);
     Csr* mats[2] = {&g->fwd, g->has_transpose ? &g->tr : nullptr};
     for (Csr* c : mats) {
         if (!c) continue;
-        if (!c->val) MIXGCN_TRY(dmalloc(&c->val, (size_t)c->nnz));
+        if (!c->val) MIXGCN_TRY(dmalloc(&c->val, (size_t)c->nnz, s));
         if (c->nnz > 0)
             hipLaunchKernelGGL(values_kernel, dim3((unsigned)ceil_div(c->nnz, kBlock)),
                                dim3(kBlock), 0, s, c->rowptr, c->col, g->dinv, n, c->nnz, mode, eps,
@@ -347,8 +348,8 @@ int normalize_graph(mixgcn_graph* g, int mode, float eps, hipStream_t s)
     // weights are not symmetric, so the transpose gets value arrays of its own on that pattern.
     Csr& f = g->fwd;
     if (mode == MIXGCN_NORM_MEAN && (g->flags & MIXGCN_SYMMETRIZE)) {
-        if (!f.val_t) MIXGCN_TRY(dmalloc(&f.val_t, (size_t)f.nnz));
-        if (!f.cv_t) MIXGCN_TRY(dmalloc(&f.cv_t, (size_t)f.nnz_padded));
+        if (!f.val_t) MIXGCN_TRY(dmalloc(&f.val_t, (size_t)f.nnz, s));
+        if (!f.cv_t) MIXGCN_TRY(dmalloc(&f.cv_t, (size_t)f.nnz_padded, s));
         hipLaunchKernelGGL(copy_entries_kernel, dim3((unsigned)ceil_div(f.nnz_padded, kBlock)),
                            dim3(kBlock), 0, s, f.cv, f.cv_t, f.nnz_padded);
         if (f.nnz > 0)

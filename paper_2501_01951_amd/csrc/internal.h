@@ -157,6 +157,17 @@ size_t sort_tmp_bytes(int64_t n);
 int radix_sort_u64(uint64_t* keys, uint64_t* alt, int64_t n, int n_bits, uint64_t** sorted,
                    void* tmp, hipStream_t s);
 
+// ---- memory for the library's own arrays (pool.hip) ------------------------------------------
+// pool_alloc: work that the caller queues on `s` may use the block at once.  pool_alloc_unordered:
+// any stream may (no stream is made to wait, so it can be called while one is being recorded).
+// pool_free: no work on the block is queued any more; pool_free_on: only work on `s` may be.
+int pool_alloc(void** p, size_t bytes, hipStream_t s);
+int pool_alloc_unordered(void** p, size_t bytes);
+int pool_alloc_pinned(void** p, size_t bytes);
+void pool_free(void* p);
+void pool_free_on(void* p, hipStream_t s);
+void pool_release();
+
 // ---- scratch shared by entry points without a handle --------------------------------------------
 int get_scratch(int which, size_t bytes, void** out);
 

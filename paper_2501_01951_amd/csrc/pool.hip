@@ -1,0 +1,195 @@
+// Device memory and pinned host memory for the library's own arrays (graphs, their scratch, the
+// work arrays of a build or a reordering), kept for reuse after their release.
+//
+// Building the matrix of a 10^6-node graph takes about 4 ms of kernels and allocates 13 arrays for
+// it.  Allocating and freeing them through the driver costs 2 ms at its best and 45 to 115 ms once
+// a process has cycled a few tens of gigabytes that way (a free of more than 128 MB then takes tens
+// of milliseconds).  A released block therefore stays here and goes to the next request it fits.
+//
+//  - Bounded: at most kMaxCachedDevice bytes per device and kMaxCachedPinned of pinned memory stay
+//    cached; the oldest blocks go back to the driver first, blocks larger than half the bound at
+//    once, and all of them when an allocation fails or when mixgcn_release_memory is called.
+//  - A block is released either on a stream that may still have work on it queued (the next owner's
+//    stream waits for an event recorded there), or after the device has been synchronised.
+//  - Thread safe: one mutex.
+#include <list>
+#include <mutex>
+#include <unordered_map>
+
+#include "internal.h"
+
+namespace mixgcn {
+namespace {
+
+constexpr size_t kMaxCachedDevice = (size_t)4 << 30;
+constexpr size_t kMaxCachedPinned = (size_t)256 << 20;
+constexpr int kPinned = -1;  // in the place of the device of a block: pinned host memory
+constexpr int kPoolDevices = 16;
+
+struct Block {
+    void* p = nullptr;
+    size_t bytes = 0;
+    int device = 0;
+    hipEvent_t ev = nullptr;  // recorded at the release, if work could still be queued then
+};
+
+struct Pool {
+    std::mutex mu;
+    std::list<Block> cached;  // oldest first
+    std::unordered_map<void*, Block> in_use;
+    std::vector<hipEvent_t> events[kPoolDevices];  // spare events of each device
+};
+Pool& pool()
+{
+    static Pool* p = new Pool;  // never destroyed: graphs may be freed while the process exits
+    return *p;
+}
+
+// Multiples of between 1/16 and 1/8 of the size, so that slightly different requests share blocks.
+size_t round_size(size_t bytes)
+{
+    size_t step = 512;
+    while (step * 16 <= bytes) step *= 2;
+    return bytes < step ? step : (bytes + step - 1) / step * step;
+}
+
+void to_driver(Pool& P, Block& b)
+{
+    if (b.ev) {
+        (void)hipEventSynchronize(b.ev);
+        P.events[b.device].push_back(b.ev);
+    }
+    if (b.device == kPinned) (void)hipHostFree(b.p);
+    else (void)hipFree(b.p);
+}
+
+// Gives cached blocks back, oldest first, until at most `keep` bytes of their kind are left.
+void trim(Pool& P, int device, size_t keep)
+{
+    size_t have = 0;
+    for (const Block& b : P.cached)
+        if (b.device == device) have += b.bytes;
+    for (auto it = P.cached.begin(); it != P.cached.end() && have > keep;) {
+        if (it->device != device) {
+            ++it;
+            continue;
+        }
+        have -= it->bytes;
+        to_driver(P, *it);
+        it = P.cached.erase(it);
+    }
+}
+
+// ordered = false: the caller cannot make a stream wait (it may be recording one), so only blocks
+// without pending work are taken from the cache.
+int take(void** out, size_t bytes, int device, bool ordered, hipStream_t s)
+{
+    *out = nullptr;
+    Pool& P = pool();
+    const size_t want = round_size(bytes);
+    std::lock_guard<std::mutex> lock(P.mu);
+    // the smallest block that fits and is not more than a quarter larger; the newest of equals
+    auto best = P.cached.end();
+    for (auto it = P.cached.begin(); it != P.cached.end(); ++it) {
+        if (it->device != device || it->bytes < want || it->bytes > want + want / 4) continue;
+        if (it->ev && !ordered) continue;
+        if (best == P.cached.end() || it->bytes <= best->bytes) best = it;
+    }
+    Block b;
+    if (best != P.cached.end()) {
+        if (best->ev) {
+            MIXGCN_HIP_TRY(hipStreamWaitEvent(s, best->ev, 0));
+            P.events[device].push_back(best->ev);
+            best->ev = nullptr;
+        }
+        b = *best;
+        P.cached.erase(best);
+    } else {
+        b.bytes = want;
+        b.device = device;
+        const auto from_driver = [&] {
+            return device == kPinned ? hipHostMalloc(&b.p, want, hipHostMallocDefault) : hipMalloc(&b.p, want);
+        };
+        hipError_t e = from_driver();
+        if (e == hipErrorOutOfMemory) {
+            (void)hipGetLastError();
+            trim(P, device, 0);
+            e = from_driver();
+        }
+        MIXGCN_HIP_TRY(e);
+    }
+    P.in_use[b.p] = b;
+    *out = b.p;
+    return MIXGCN_OK;
+}
+
+int device_of_caller(int* dev)
+{
+    MIXGCN_HIP_TRY(hipGetDevice(dev));
+    if (*dev < 0 || *dev >= kPoolDevices) return fail(MIXGCN_EINVAL, "memory pool: device index");
+    return MIXGCN_OK;
+}
+
+void put_back(void* p, bool queued, hipStream_t s)
+{
+    if (!p) return;
+    Pool& P = pool();
+    std::lock_guard<std::mutex> lock(P.mu);
+    const auto it = P.in_use.find(p);
+    if (it == P.in_use.end()) return;
+    Block b = it->second;
+    P.in_use.erase(it);
+    const size_t most = b.device == kPinned ? kMaxCachedPinned : kMaxCachedDevice;
+    if (queued) {
+        std::vector<hipEvent_t>& spare = P.events[b.device];
+        if (!spare.empty()) {
+            b.ev = spare.back();
+            spare.pop_back();
+        } else if (hipEventCreateWithFlags(&b.ev, hipEventDisableTiming) != hipSuccess) {
+            b.ev = nullptr;
+        }
+        if (!b.ev || hipEventRecord(b.ev, s) != hipSuccess) {
+            // nothing to order a reuse by: finish the work instead
+            (void)hipStreamSynchronize(s);
+            if (b.ev) (void)hipEventDestroy(b.ev);
+            b.ev = nullptr;
+        }
+    }
+    if (b.bytes > most / 2) {
+        to_driver(P, b);
+        return;
+    }
+    P.cached.push_back(b);
+    trim(P, b.device, most);
+}
+
+}  // namespace
+
+int pool_alloc(void** p, size_t bytes, hipStream_t s)
+{
+    int dev = 0;
+    MIXGCN_TRY(device_of_caller(&dev));
+    return take(p, bytes, dev, true, s);
+}
+
+int pool_alloc_unordered(void** p, size_t bytes)
+{
+    int dev = 0;
+    MIXGCN_TRY(device_of_caller(&dev));
+    return take(p, bytes, dev, false, nullptr);
+}
+
+int pool_alloc_pinned(void** p, size_t bytes) { return take(p, bytes, kPinned, false, nullptr); }
+
+void pool_free(void* p) { put_back(p, false, nullptr); }
+void pool_free_on(void* p, hipStream_t s) { put_back(p, true, s); }
+
+void pool_release()
+{
+    Pool& P = pool();
+    std::lock_guard<std::mutex> lock(P.mu);
+    for (Block& b : P.cached) to_driver(P, b);
+    P.cached.clear();
+}
+
+}  // namespace mixgcn

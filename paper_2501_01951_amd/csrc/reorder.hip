@@ -25,18 +25,21 @@ namespace {
 
 constexpr uint32_t kNone = 0xFFFFFFFFu;
 
+// Work arrays, released on the stream that uses them.
 struct DevMem {
+    explicit DevMem(hipStream_t stream) : s(stream) {}
+    hipStream_t s;
     std::vector<void*> ptrs;
     ~DevMem()
     {
-        for (void* p : ptrs) (void)hipFree(p);
+        for (void* p : ptrs) pool_free_on(p, s);
     }
     template <typename T>
     int alloc(T** out, size_t count)
     {
         *out = nullptr;
         void* p = nullptr;
-        MIXGCN_HIP_TRY(hipMalloc(&p, (count ? count : 1) * sizeof(T)));
+        MIXGCN_TRY(pool_alloc(&p, (count ? count : 1) * sizeof(T), s));
         ptrs.push_back(p);
         *out = (T*)p;
         return MIXGCN_OK;
@@ -471,7 +474,7 @@ int mixgcn_reorder_rcm(const mixgcn_graph* g, uint32_t* pos, void* stream)
     const uint32_t n = g->n;
     if (n == 0) return MIXGCN_OK;
     const Csr& m = g->fwd;
-    DevMem mem;
+    DevMem mem(s);
     uint64_t *keys, *alt;
     uint32_t *bydeg, *degrank, *single, *cm_idx, *parent, *order, *next_list, *counters;
     void* tmp;
