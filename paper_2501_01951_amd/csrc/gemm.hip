@@ -739,10 +739,7 @@ int update_typed(int op, const T* A, int64_t lda, const void* B_, int64_t ldb, v
         const int bm = 128, bn = wide ? 128 : 32;
         const int nit = (int)ceil_div(k, bm), njt = (int)ceil_div(m, bn);
         const int tiles = nit * njt;
-        int64_t n_slabs = ceil_div(n, 1024);
-        const int64_t cap = tiles >= 1024 ? 1 : 1024 / tiles;
-        if (n_slabs > cap) n_slabs = cap;
-        if (n_slabs < 1) n_slabs = 1;
+        int64_t n_slabs = wgrad_slabs(n, tiles, 1024);
         int64_t rows_per_slab = ceil_div(ceil_div(n, n_slabs), BK) * BK;
         if (rows_per_slab < BK) rows_per_slab = BK;
         n_slabs = n > 0 ? ceil_div(n, rows_per_slab) : 1;

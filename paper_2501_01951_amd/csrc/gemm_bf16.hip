@@ -891,10 +891,7 @@ int launch_update_bf16(int op, const uint16_t* A, int64_t lda, const void* B_, i
         const int64_t n_main = pitches_ok ? n - n % BKB : 0;
         if (timer) MIXGCN_TRY(timer->begin(kTimeUpdateWgrad, s));
         auto part = [&](bool transposing_reads, int64_t row0, int64_t rows, float beta_part) -> int {
-            int64_t n_slabs = ceil_div(rows, 2048);
-            const int64_t cap = tiles >= 1024 ? 1 : 1024 / tiles;
-            if (n_slabs > cap) n_slabs = cap;
-            if (n_slabs < 1) n_slabs = 1;
+            int64_t n_slabs = wgrad_slabs(rows, tiles, 2048);
             int64_t rows_per_slab = ceil_div(ceil_div(rows, n_slabs), BKB) * BKB;
             if (rows_per_slab < BKB) rows_per_slab = BKB;
             n_slabs = rows > 0 ? ceil_div(rows, rows_per_slab) : 1;

@@ -553,10 +553,7 @@ static int launch_wgrad_split(const float* A, int64_t lda, const float* B, int64
                               int64_t ldr, float beta, hipStream_t s, Timer* timer)
 {
     const int nit = k / 128, njt = m / 128, tiles = nit * njt;
-    int64_t n_slabs = ceil_div(n, 1024);
-    const int64_t cap = tiles >= 1024 ? 1 : 1024 / tiles;
-    if (n_slabs > cap) n_slabs = cap;
-    if (n_slabs < 1) n_slabs = 1;
+    int64_t n_slabs = wgrad_slabs(n, tiles, 1024);
     const int64_t rows_per_slab = ceil_div(ceil_div(n, n_slabs), BKS) * BKS;
     n_slabs = ceil_div(n, rows_per_slab);
     const int64_t cells = (int64_t)k * m;

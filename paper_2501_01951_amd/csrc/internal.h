@@ -224,6 +224,20 @@ int launch_update_split(int op, const float* A, int64_t lda, const float* W, int
                         int64_t ldc, int64_t n, int32_t k, int32_t m, const float* R, int64_t ldr,
                         float beta, hipStream_t s, Timer* timer);
 
+// Row slabs of a weight gradient of `tiles` output tiles over n rows: slabs of at most `most_rows`
+// rows (1024 workgroups at most), and on small inputs shorter ones until every compute unit has a
+// workgroup, but never below 128 rows: a slab costs its partial tile once more in the reduction, and
+// a workgroup its start.  (64 x 32 over 4096 rows: 4 slabs of 1024 rows took 49 us.)
+inline int64_t wgrad_slabs(int64_t n, int64_t tiles, int64_t most_rows)
+{
+    int64_t slabs = ceil_div(n, most_rows);
+    const int64_t fill = ceil_div(256, tiles), finest = ceil_div(n, 128);
+    if (slabs < fill) slabs = fill < finest ? fill : finest;
+    const int64_t cap = tiles >= 1024 ? 1 : 1024 / tiles;
+    if (slabs > cap) slabs = cap;
+    return slabs < 1 ? 1 : slabs;
+}
+
 // dW = beta dW + sum of the slab partials P[slab][cells], in slab order in fp64
 int launch_wgrad_reduce(const float* P, int64_t n_slabs, int64_t cells, int32_t m, float* dW,
                         int64_t ldw, float beta, hipStream_t s);
