@@ -269,7 +269,13 @@ int mixgcn_normalize_mode(mixgcn_graph* g, int mode, float eps, void* stream)
     if (!(eps == eps) || fabsf(eps) > 3.0e38f) return fail(MIXGCN_EINVAL, "normalize: eps");
     MIXGCN_TRY(normalize_graph(g, mode, mode == MIXGCN_NORM_SUM ? eps : 0.f, (hipStream_t)stream));
     // the row-piece scratch of the aggregation: sized once from the entry count, first slot here
-    if (!g->agg_slot_bytes) g->agg_slot_bytes = agg_scratch_bound(g->fwd.nnz);
+    if (!g->agg_slot_bytes) {
+        g->agg_slot_bytes = agg_scratch_bound(g->fwd.nnz);
+        for (const mixgcn::Csr* m : {&g->fwd, &g->tr}) {
+            const size_t b = rowgroups_scratch(m->groups, g->n, MIXGCN_BF16, kAggMaxPassCols);
+            if (b > g->agg_slot_bytes) g->agg_slot_bytes = b;
+        }
+    }
     if (!g->agg_slots[0].p)
         MIXGCN_TRY(pool_alloc_unordered((void**)&g->agg_slots[0].p, g->agg_slot_bytes));
     return MIXGCN_OK;
@@ -374,18 +380,17 @@ static int aggregate_impl(const mixgcn_graph* g, int transpose, int dtype, const
         }
     }
     const mixgcn::Csr* m = &g->fwd;
-    const uint2* cv = g->fwd.cv;
+    bool values_t = false;
     if (transpose) {
         if (g->flags & MIXGCN_SYMMETRIZE) {
-            if (g->norm_mode == MIXGCN_NORM_MEAN) cv = g->fwd.cv_t;
+            values_t = g->norm_mode == MIXGCN_NORM_MEAN;
         } else {
             if (!g->has_transpose)
                 return fail(MIXGCN_ESTATE, "aggregate: transpose needs MIXGCN_BUILD_TRANSPOSE");
             m = &g->tr;
-            cv = g->tr.cv;
         }
     }
-    if (!cv) return fail(MIXGCN_ESTATE, "aggregate: values of the transpose are missing");
+    if (!(values_t ? m->cv_t : m->cv)) return fail(MIXGCN_ESTATE, "aggregate: values of the transpose are missing");
     if (mask && ld_mask < ((int64_t)col_end + 31) / 32)
         return fail(MIXGCN_EINVAL, "aggregate: ld_mask shorter than ceil(col_end / 32) words");
     if (row_end == row_begin || col_end == col_begin) return MIXGCN_OK;
@@ -393,7 +398,7 @@ static int aggregate_impl(const mixgcn_graph* g, int transpose, int dtype, const
     size_t partials_bytes = g->agg_slot_bytes;
     if (static_scratch) MIXGCN_TRY(static_agg_scratch(&partials, &partials_bytes));
     else MIXGCN_TRY(acquire_agg_slot(g, stream, &partials));
-    return launch_aggregate(g, *m, cv, dtype, H, ldh, Z, ldz, col_begin, col_end, row_begin,
+    return launch_aggregate(g, *m, values_t, dtype, H, ldh, Z, ldz, col_begin, col_end, row_begin,
                             row_end, epilogue, mask, ld_mask, partials, partials_bytes, stream,
                             timer);
 }

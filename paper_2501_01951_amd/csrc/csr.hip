@@ -153,12 +153,7 @@ __global__ __launch_bounds__(kBlock) void degree_kernel(const int64_t* __restric
     else dinv[r] = d ? (float)(1.0 / sqrt((double)d)) : 0.0f;
 }
 
-// One thread per stored entry (r, c) of the CSR at hand, its row found by binary search in
-// rowptr.  `swapped`: the CSR holds the transpose of the aggregation matrix, so its entry
-// (r, c) carries the value of entry (c, r).
-//   symmetric: dinv[r] * dinv[c] - a single fp32 multiply, so val(u,v) == val(v,u) bit for bit;
-//   mean:      dinv[row of the aggregation matrix] = 1 / deg;
-//   sum:       1, and 1 + eps on the diagonal.
+// One thread per stored entry, its row found by binary search in rowptr.
 __global__ __launch_bounds__(kBlock) void values_kernel(const int64_t* __restrict__ rowptr,
                                                         const uint32_t* __restrict__ col,
                                                         const float* __restrict__ dinv,
@@ -175,12 +170,8 @@ __global__ __launch_bounds__(kBlock) void values_kernel(const int64_t* __restric
         if (rowptr[mid] <= e) lo = mid + 1;
         else hi = mid;
     }
-    const int64_t row = lo - 1;
-    const uint32_t c = col[e];
-    float v;
-    if (mode == MIXGCN_NORM_MEAN) v = swapped ? dinv[c] : dinv[row];
-    else if (mode == MIXGCN_NORM_SUM) v = ((int64_t)c == row) ? 1.0f + eps : 1.0f;
-    else v = dinv[row] * dinv[c];
+    const uint32_t row = (uint32_t)(lo - 1);
+    const float v = entry_value(mode, eps, swapped, row, col[e], dinv[row], dinv);
     val[e] = v;
     cv[e].y = __float_as_uint(v);
 }
@@ -227,6 +218,7 @@ void csr_free(Csr* c)
     pool_free(c->cv_t);
     pool_free(c->val_t);
     pool_free(c->grp_row);
+    rowgroups_free(&c->groups);
     *c = Csr();
 }
 
@@ -327,6 +319,27 @@ int csr_from_edges(const uint32_t* d_src, const uint32_t* d_dst, uint64_t n_edge
     return MIXGCN_OK;
 }
 
+namespace {
+
+// Matrices of up to 2^31 entries also get the row-grouped form.  Above that the two forms together
+// (16 bytes per entry) would not leave room for the features, and a graph of that size gathers from
+// memory anyway: both kernels run at the device's random-gather rate.
+constexpr int64_t kMostGroupedEntries = 1ll << 31;
+
+// Values of the matrix (swapped: of its transpose on the same pattern) in all stored forms.
+int fill_values(const Csr& c, uint32_t n, const float* dinv, int mode, float eps, int swapped,
+                bool transposed, float* val, uint2* cv, hipStream_t s)
+{
+    if (c.nnz == 0) return MIXGCN_OK;
+    if (!c.groups.bands.empty())
+        return rowgroups_fill(c, c.groups, dinv, mode, eps, swapped, transposed, val, cv, s);
+    hipLaunchKernelGGL(values_kernel, dim3((unsigned)ceil_div(c.nnz, kBlock)), dim3(kBlock), 0, s,
+                       c.rowptr, c.col, dinv, n, c.nnz, mode, eps, swapped, val, cv);
+    return MIXGCN_OK;
+}
+
+}  // namespace
+
 int normalize_graph(mixgcn_graph* g, int mode, float eps, hipStream_t s)
 {
     const uint32_t n = g->n;
@@ -339,10 +352,9 @@ int normalize_graph(mixgcn_graph* g, int mode, float eps, hipStream_t s)
     for (Csr* c : mats) {
         if (!c) continue;
         if (!c->val) MIXGCN_TRY(dmalloc(&c->val, (size_t)c->nnz, s));
-        if (c->nnz > 0)
-            hipLaunchKernelGGL(values_kernel, dim3((unsigned)ceil_div(c->nnz, kBlock)),
-                               dim3(kBlock), 0, s, c->rowptr, c->col, g->dinv, n, c->nnz, mode, eps,
-                               c == &g->tr ? 1 : 0, c->val, c->cv);
+        if (c->groups.bands.empty() && c->nnz > 0 && c->nnz <= kMostGroupedEntries && n < kEntryColMask)
+            MIXGCN_TRY(rowgroups_build(*c, n, g->flags & MIXGCN_SYMMETRIZE, &c->groups, s));
+        MIXGCN_TRY(fill_values(*c, n, g->dinv, mode, eps, c == &g->tr ? 1 : 0, false, c->val, c->cv, s));
     }
     // A symmetrised graph stores one pattern for the matrix and its transpose.  The mean
     // weights are not symmetric, so the transpose gets value arrays of its own on that pattern.
@@ -350,11 +362,10 @@ int normalize_graph(mixgcn_graph* g, int mode, float eps, hipStream_t s)
     if (mode == MIXGCN_NORM_MEAN && (g->flags & MIXGCN_SYMMETRIZE)) {
         if (!f.val_t) MIXGCN_TRY(dmalloc(&f.val_t, (size_t)f.nnz, s));
         if (!f.cv_t) MIXGCN_TRY(dmalloc(&f.cv_t, (size_t)f.nnz_padded, s));
+        MIXGCN_TRY(rowgroups_alloc_transpose(&f.groups, s));
         hipLaunchKernelGGL(copy_entries_kernel, dim3((unsigned)ceil_div(f.nnz_padded, kBlock)),
                            dim3(kBlock), 0, s, f.cv, f.cv_t, f.nnz_padded);
-        if (f.nnz > 0)
-            hipLaunchKernelGGL(values_kernel, dim3((unsigned)ceil_div(f.nnz, kBlock)), dim3(kBlock), 0,
-                               s, f.rowptr, f.col, g->dinv, n, f.nnz, mode, eps, 1, f.val_t, f.cv_t);
+        MIXGCN_TRY(fill_values(f, n, g->dinv, mode, eps, 1, true, f.val_t, f.cv_t, s));
     }
     MIXGCN_HIP_TRY(hipGetLastError());
     g->normalized = true;

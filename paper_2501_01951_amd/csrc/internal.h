@@ -57,6 +57,28 @@ struct AggSlot {
     uint64_t last_use = 0;
 };
 
+// The entries of a matrix with its rows grouped by length (rowgroups.hip), for aggregations over all
+// rows: per band of columns a stream of batches of eight {column, value} entries.
+struct Band {
+    int64_t piece = 0;      // entries of a piece of a very long row
+    int64_t n_batches = 0, n_groups = 0, n_tab = 0;
+    int64_t n_cut = 0, n_pieces = 0;
+    uint2* ent = nullptr;         // [8 n_batches + pad]
+    uint2* ent_t = nullptr;       // the same pattern with the values of the transpose (see cv_t)
+    uint32_t* rows = nullptr;     // [8 (n_groups + 16)] rows of each group
+    uint32_t* kind = nullptr;     // [n_groups]
+    uint64_t* start = nullptr;    // [n_groups] first batch of each group
+    uint2* tab = nullptr;         // [n_tab] {group, batch} at every 8th batch
+    uint32_t* cut_row = nullptr;  // [n_cut] rows that were cut into pieces
+    uint64_t* piece0 = nullptr;   // [n_cut] first piece of each
+    int64_t* rowptr = nullptr;    // [n + 1] of the band (null: the only band)
+    int64_t src0 = 0;             // its first entry in RowGroups::src
+};
+struct RowGroups {
+    std::vector<Band> bands;  // empty: not built
+    uint32_t* src = nullptr;  // [nnz] entry indices band by band (null: one band)
+};
+
 struct Csr {
     int64_t nnz = 0;
     int64_t nnz_padded = 0;          // allocation length of cv
@@ -71,6 +93,7 @@ struct Csr {
     uint2* cv_t = nullptr;           // [nnz_padded]
     float* val_t = nullptr;          // [nnz]
     uint32_t* grp_row = nullptr;     // [n_groups + 1] row that holds entry g * kGroupNnz
+    RowGroups groups;                // empty where the rule of csr.hip leaves it out
     std::vector<int64_t> h_rowptr;   // host copy of rowptr
     bool has_empty_rows = false;
 };
@@ -177,12 +200,25 @@ int csr_from_edges(const uint32_t* d_src, const uint32_t* d_dst, uint64_t n_edge
 void csr_free(Csr* c);
 int normalize_graph(mixgcn_graph* g, int mode, float eps, hipStream_t s);
 
+int rowgroups_build(const Csr& m, uint32_t n, bool symmetric, RowGroups* out, hipStream_t s);
+int rowgroups_alloc_transpose(RowGroups* g, hipStream_t s);
+int rowgroups_fill(const Csr& m, const RowGroups& g, const float* dinv, int mode, float eps,
+                   int swapped, bool transposed, float* val, uint2* cv, hipStream_t s);
+void rowgroups_free(RowGroups* g);
+// Bytes of scratch that a pass of `width` columns over the n rows uses.
+size_t rowgroups_scratch(const RowGroups& g, int64_t n, int dtype, int width);
+// One pass over all rows: columns [c0, c0 + width), of which [c_lo, c_hi) are written.
+int launch_groups_pass(const RowGroups& g, bool values_t, int64_t n_nodes, int dtype,
+                       const void* H, int64_t ldh, void* Z, int64_t ldz, int c0, int width, float* P,
+                       int epi, const uint32_t* mask, int64_t ldm, int c_lo, int c_hi, hipStream_t s,
+                       Timer* timer, int timer_kind);
+
 // mask: optional bitmap applied to the written outputs (bit c % 32 of mask[r * ldm + c / 32])
-// cv: the entry array to walk (m.cv, or m.cv_t for the transpose of a symmetrised graph with
-// unsymmetric weights); epilogue: MIXGCN_EPI_* flags
+// values_t: walk the values of the transpose on the same pattern (m.cv_t: the transpose of a
+// symmetrised graph with unsymmetric weights); epilogue: MIXGCN_EPI_* flags
 // partials / partials_bytes: scratch for the row pieces (device); a call that would need more is
 // refused with MIXGCN_EINVAL before anything is launched
-int launch_aggregate(const mixgcn_graph* g, const Csr& m, const uint2* cv, int dtype, const void* H,
+int launch_aggregate(const mixgcn_graph* g, const Csr& m, bool values_t, int dtype, const void* H,
                      int64_t ldh, void* Z, int64_t ldz, int32_t c0, int32_t c1, int64_t r0,
                      int64_t r1, int epilogue, const uint32_t* mask, int64_t ldm, float* partials,
                      size_t partials_bytes, hipStream_t s, Timer* timer);

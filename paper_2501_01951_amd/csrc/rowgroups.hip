@@ -1,0 +1,1067 @@
+// Neighbor aggregation over whole matrices: rows grouped by length.
+//
+// The entry-balanced kernel (spmm.hip) closes one row at a time: three rounds of lane exchanges and
+// a store by an eighth of the lanes for every row, which is what it spends its time on as soon as
+// rows are short or the gathers hit the L2 (a 302 k-entry graph at 256 bf16 columns: 50 us, where
+// the gathers alone take 6).  Here the rows are laid out so that eight of them end together:
+//
+//   short rows (1 to 64 entries)  are sorted by length, longest first, and taken eight at a time:
+//                                 a *group*.  Batch j of a group holds entry j of each of its eight
+//                                 rows, so the eight lanes of a sub-group own one row from its first
+//                                 entry to its last, add in registers and write it themselves.
+//   longer rows                   are a group each: batch j holds entries 8 j .. 8 j + 7 of the row,
+//                                 and the eight sub-group sums are combined once at its end.
+//   very long rows                are cut into pieces, a group each, whose sums go to scratch slots
+//                                 that a second kernel adds in order (deterministic, no atomics).
+//
+// The groups are stored one after the other as one stream of batches of eight {column, value}
+// entries.  A wavefront takes the groups that start in its part of the stream, for one column slice
+// of 8 lanes, so nothing crosses from one wavefront to the next.  The sort works within windows of
+// 4096 consecutive rows: the padding of a group is the spread of eight neighbors in sorted order
+// (below 1 % of the entries in all), while the rows written at the same time stay close together (rows
+// sorted over the whole graph: 3 % slower with plain stores, 12 % with an epilogue that reads).
+//
+// Bands.  What is left is the L2: every XCD's 4 MiB hold 32 k of the 128-byte lines that a column
+// slice has per node, a gather that misses costs four times one that hits, and an LRU cache keeps
+// far less than the most popular lines (R-MAT, 2^20 nodes: 44 % hits, where the 26 k most popular
+// columns alone are 64 % of the gathers).  So the columns are dealt to bands by popularity, 26 k
+// columns each and the rest in the last, and the bands are aggregated one after the other: the
+// gathers of a band all hit once its lines are in, and the later bands add to what the earlier ones
+// left in Z.  How many bands pay is estimated from the degree histogram (plan_bands).
+#include <cmath>
+
+#include "agg_common.h"
+
+namespace mixgcn {
+namespace {
+
+constexpr int kGroupRows = 8;   // rows of a group, sub-groups of a wavefront
+constexpr int kMostShort = 64;  // longest row that may share a group with others
+constexpr int kWindowItems = 16;
+constexpr int kWindow = kBlock * kWindowItems;  // rows sorted together
+// Stream positions for which the first group that starts there is tabulated (batches).
+constexpr int kTabBatches = 8;
+constexpr int kRowPad = 2 * kGroupRows;  // groups whose rows may be read past the end
+constexpr int kStreamPad = 128 * kGroupRows;  // entries that the pipeline may read past the end
+
+// Marks in bits 30 and 31 of the column word of the first entry of a group's last batch.
+constexpr uint32_t kEndGroup = 1u << 30;  // every sub-group closes its own row
+constexpr uint32_t kEndRow = 2u << 30;    // the sub-groups close one row together
+constexpr uint32_t kEndPiece = 3u << 30;  // they close a piece of a row
+constexpr uint32_t kPadValue = 0x80000000u;  // value word (-0.0) of an entry that stands for nothing
+// A row of a group: its index and what the band is to it.
+constexpr uint32_t kRowMask = 0x3FFFFFFFu;
+constexpr uint32_t kNoRow = kRowMask;
+constexpr uint32_t kRowAdds = 1u << 31;   // an earlier band has written the row
+constexpr uint32_t kRowMore = 1u << 30;   // a later band will add to it: no epilogue yet
+
+// Classes of the row sort: pieces, single long rows, short rows by falling length, empty rows.
+constexpr int kClassPieces = 0;
+constexpr int kClassLong = 1;
+constexpr int kClassEmpty = kMostShort + 2;
+
+__device__ inline int row_class(int64_t len, int64_t piece, int short_row)
+{
+    if (len > piece) return kClassPieces;
+    if (len > short_row) return kClassLong;
+    return kClassEmpty - (int)len;
+}
+
+// ---- bands ----------------------------------------------------------------------------------------
+
+constexpr int kBandColumns = 26000;  // columns of a band: 4/5 of the lines of an XCD's L2
+constexpr int kMostBands = 16;
+// Popularity bins, most popular first: exact up to 64 entries, 16 bins per factor of two above.
+constexpr int kBins = 256;
+
+__device__ inline int popularity_bin(int64_t len)
+{
+    if (len < 64) return kBins - 1 - (int)len;
+    const int e = 63 - __clzll((long long)len);  // 2^e <= len
+    const int b = 64 + (e - 6) * 16 + (int)((len >> (e - 4)) & 15);
+    return b > kBins - 1 ? 0 : kBins - 1 - b;
+}
+
+// Rows and entries per bin, and the sort keys (row << 8 | bin).
+__global__ __launch_bounds__(kBlock) void popularity_kernel(const int64_t* __restrict__ rowptr,
+                                                            uint32_t n, uint64_t* __restrict__ keys,
+                                                            unsigned long long* __restrict__ rows,
+                                                            unsigned long long* __restrict__ entries)
+{
+    __shared__ unsigned long long hr[kBins], he[kBins];
+    hr[threadIdx.x] = 0;
+    he[threadIdx.x] = 0;
+    __syncthreads();
+    for (int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x; r < n; r += (int64_t)gridDim.x * kBlock) {
+        const int64_t len = rowptr[r + 1] - rowptr[r];
+        const int b = popularity_bin(len);
+        keys[r] = (uint64_t)r << 8 | (uint64_t)b;
+        atomicAdd(&hr[b], 1ull);
+        atomicAdd(&he[b], (unsigned long long)len);
+    }
+    __syncthreads();
+    if (hr[threadIdx.x]) {
+        atomicAdd(&rows[threadIdx.x], hr[threadIdx.x]);
+        atomicAdd(&entries[threadIdx.x], he[threadIdx.x]);
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void band_of_column_kernel(const uint64_t* __restrict__ sorted,
+                                                                uint32_t n, uint32_t per_band,
+                                                                int n_bands, uint8_t* __restrict__ band)
+{
+    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+    if (i >= n) return;
+    const uint32_t b = i / per_band;
+    band[sorted[i] >> 8] = (uint8_t)(b < (uint32_t)n_bands ? b : n_bands - 1);
+}
+
+// Entries of every row in every band, one wavefront per row.  FILL: pos[b][r] is where the row's
+// entries of band b start, and the entry indices are written there in their order in the row;
+// otherwise their counts go to count[b][r].
+template <bool FILL>
+__global__ __launch_bounds__(kBlock) void deal_entries_kernel(
+    const int64_t* __restrict__ rowptr, const uint32_t* __restrict__ col,
+    const uint8_t* __restrict__ band, uint32_t n, int n_bands, uint32_t* __restrict__ count,
+    const uint64_t* __restrict__ pos, uint32_t* __restrict__ src)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t r = (int64_t)blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6);
+    if (r >= n) return;
+    const int64_t e0 = rowptr[r], e1 = rowptr[r + 1];
+    // lane b keeps the running count (or position) of band b
+    uint64_t run = FILL && lane < n_bands ? pos[(int64_t)lane * n + r] : 0;
+    for (int64_t e = e0; e < e1; e += kWave) {
+        const bool valid = e + lane < e1;
+        const int mine = valid ? band[col[e + lane]] : -1;
+        for (int b = 0; b < n_bands; ++b) {
+            const uint64_t m = __ballot(mine == b);
+            if (FILL) {
+                const uint64_t at = __shfl((unsigned long long)run, b, kWave);
+                if (mine == b) src[at + __popcll(m & ((1ull << lane) - 1))] = (uint32_t)(e + lane);
+            }
+            if (lane == b) run += __popcll(m);
+        }
+    }
+    if (!FILL && lane < n_bands) count[(int64_t)lane * n + r] = (uint32_t)run;
+}
+
+// rowptr of a band relative to its own entries
+__global__ __launch_bounds__(kBlock) void band_rowptr_kernel(const uint64_t* __restrict__ pos,
+                                                             int64_t n, int b, int n_bands,
+                                                             int64_t nnz, int64_t* __restrict__ rowptr)
+{
+    const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (r > n) return;
+    const uint64_t* p = pos + (int64_t)b * n;
+    const int64_t end = b + 1 < n_bands ? (int64_t)p[n] : nnz;
+    rowptr[r] = (r < n ? (int64_t)p[r] : end) - (int64_t)p[0];
+}
+
+// Share of gathers that miss an LRU cache of `lines` lines when column classes of `count` columns
+// with `entries` gathers in all are hit independently (Che's approximation: a line stays for a
+// fixed number of gathers T, chosen so that the cache is full).
+struct Popular {
+    double count, entries;
+};
+double lru_misses(const Popular* c, int n, double lines)
+{
+    double total = 0, columns = 0;
+    for (int i = 0; i < n; ++i) {
+        total += c[i].entries;
+        columns += c[i].count;
+    }
+    if (columns <= lines || total <= 0) return 0;
+    double lo = 0, hi = total * 1e6;
+    for (int it = 0; it < 100; ++it) {
+        const double T = 0.5 * (lo + hi);
+        double full = 0;
+        for (int i = 0; i < n; ++i)
+            if (c[i].count > 0) full += c[i].count * -expm1(-c[i].entries / c[i].count / total * T);
+        (full < lines ? lo : hi) = T;
+    }
+    double miss = 0;
+    for (int i = 0; i < n; ++i)
+        if (c[i].count > 0) miss += c[i].entries * exp(-c[i].entries / c[i].count / total * lo);
+    return miss / total;
+}
+
+// Number of bands for a matrix with the given rows and entries per bin (most popular first).  In
+// units of a gather that misses (18 ps per line over the chip), a hit measured 0.3 to 0.38 and a row
+// that a later band adds to 3 to 6 lines: its old line is read with a miss that the gathers queued
+// behind it wait for, and written again.
+int plan_bands(const unsigned long long* rows, const unsigned long long* entries, double n, double nnz)
+{
+    constexpr double kHit = 0.35, kInBand = 0.03, kRow = 5, kLines = 29000;
+    int best = 1;
+    double best_cost = 0;
+    for (int k = 1; k <= kMostBands && (k - 1) * (double)kBandColumns < n; ++k) {
+        double cost = 0;
+        Popular rest[kBins];
+        int n_rest = 0;
+        double share[kMostBands] = {};
+        double rank = 0;
+        for (int i = 0; i < kBins; ++i) {
+            double left = (double)rows[i];
+            if (left <= 0) continue;
+            const double each = (double)entries[i] / left;
+            while (left > 0) {
+                int b = (int)(rank / kBandColumns);
+                if (b > k - 1) b = k - 1;
+                double take = left;
+                if (b < k - 1 && rank + take > (b + 1) * (double)kBandColumns)
+                    take = (b + 1) * (double)kBandColumns - rank;
+                share[b] += take * each / nnz;
+                if (b == k - 1) rest[n_rest++] = Popular{take, take * each};
+                rank += take;
+                left -= take;
+            }
+        }
+        for (int b = 0; b < k; ++b) {
+            const double miss = b < k - 1 ? kInBand : lru_misses(rest, n_rest, kLines);
+            cost += share[b] * (miss + (1 - miss) * kHit);
+            if (b == 0) continue;
+            for (int i = 0; i < kBins; ++i)  // rows that have an entry in the band
+                if (rows[i])
+                    cost += kRow * (double)rows[i] / nnz *
+                            -expm1(-(double)entries[i] / (double)rows[i] * share[b]);
+        }
+        // Bands have to promise a fifth: the estimate takes columns and rows for independent, and
+        // where popular rows prefer popular columns (R-MAT) it promises up to 15 % that are not
+        // there.  Uniform columns, 100 k nodes, 100 entries per row: 566 -> 373 us with 4 bands
+        // (estimate 0.81 -> 0.51); power law, 233 k nodes, 492 per row: 7.2 -> 3.5 ms with 9.
+        if (k == 1) best_cost = 0.8 * cost;
+        else if (cost < best_cost) {
+            best_cost = cost;
+            best = k;
+        }
+    }
+    return best;
+}
+
+// ---- layout ---------------------------------------------------------------------------------------
+
+// What a window of rows contributes.
+struct WindowPlan {
+    uint32_t cut, pieces, groups, batches;
+};
+
+// Sorts the rows of a window by class (stable) and counts what they need; one block per window.
+__global__ __launch_bounds__(kBlock) void window_sort_kernel(const int64_t* __restrict__ rowptr,
+                                                             uint32_t n, int64_t piece, int short_row,
+                                                             uint32_t* __restrict__ sorted,
+                                                             uint2* __restrict__ long_short,
+                                                             WindowPlan* __restrict__ plan)
+{
+    __shared__ uint32_t whist[kBlock / kWave][256];
+    __shared__ uint32_t base[256];
+    __shared__ uint64_t scan[4];
+    __shared__ uint32_t pieces, batches;
+#pragma unroll
+    for (int i = 0; i < kBlock / kWave; ++i) whist[i][threadIdx.x] = 0;
+    if (threadIdx.x == 0) pieces = batches = 0;
+    __syncthreads();
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x >> 6;
+    const int64_t first = (int64_t)blockIdx.x * kWindow;
+    const int64_t row0 = first + (int64_t)w * kWindowItems * kWave + lane;
+    uint32_t digit[kWindowItems], rank[kWindowItems];
+    bool valid[kWindowItems];
+#pragma unroll
+    for (int i = 0; i < kWindowItems; ++i) {
+        const int64_t r = row0 + (int64_t)i * kWave;
+        valid[i] = r < n;
+        const int64_t len = valid[i] ? rowptr[r + 1] - rowptr[r] : 0;
+        digit[i] = (uint32_t)row_class(len, piece, short_row);
+        if (valid[i] && digit[i] == kClassPieces) {
+            const int64_t full = len / piece, rest = len % piece;
+            atomicAdd(&pieces, (uint32_t)(full + (rest ? 1 : 0)));
+            atomicAdd(&batches, (uint32_t)(full * (piece / kGroupRows) + (rest + kGroupRows - 1) / kGroupRows));
+        } else if (valid[i] && digit[i] == kClassLong) {
+            atomicAdd(&batches, (uint32_t)((len + kGroupRows - 1) / kGroupRows));
+        }
+    }
+    wave_digit_ranks(digit, valid, whist, rank);
+    __syncthreads();
+    const int d = threadIdx.x;  // thread d: class d
+    uint32_t total = 0;
+#pragma unroll
+    for (int i = 0; i < kBlock / kWave; ++i) {
+        const uint32_t c = whist[i][d];
+        whist[i][d] = total;
+        total += c;
+    }
+    uint64_t all;
+    const uint32_t b = (uint32_t)block_exclusive_scan_u64(total, &all, scan);
+    base[d] = b;
+    __syncthreads();
+    const uint32_t short0 = base[kClassLong + 1];
+    if (d > kClassLong && d < kClassEmpty && total > 0) {
+        // a group of short rows is as long as its first row
+        const uint32_t g0 = (b - short0 + kGroupRows - 1) / kGroupRows;
+        const uint32_t g1 = (b - short0 + total + kGroupRows - 1) / kGroupRows;
+        atomicAdd(&batches, (g1 - g0) * (uint32_t)(kClassEmpty - d));
+    }
+#pragma unroll
+    for (int i = 0; i < kWindowItems; ++i)
+        if (valid[i])
+            sorted[first + base[digit[i]] + whist[w][digit[i]] + rank[i]] =
+                (uint32_t)(row0 + (int64_t)i * kWave);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t n_cut = base[kClassLong], n_long = short0 - n_cut, n_short = base[kClassEmpty] - short0;
+        long_short[blockIdx.x] = make_uint2(n_long, n_short);
+        plan[blockIdx.x] = WindowPlan{n_cut, pieces, pieces + n_long + (n_short + kGroupRows - 1) / kGroupRows,
+                                      batches};
+    }
+}
+
+struct WindowStart {
+    uint64_t cut, pieces, groups, batches;
+};
+
+// Exclusive prefix sums over the windows; start[n_windows] = totals.  One block.
+__global__ __launch_bounds__(kBlock) void window_scan_kernel(const WindowPlan* __restrict__ plan,
+                                                             int64_t n_windows,
+                                                             WindowStart* __restrict__ start)
+{
+    __shared__ uint64_t lds[4];
+    WindowStart run{0, 0, 0, 0};
+    for (int64_t i0 = 0; i0 < n_windows; i0 += kBlock) {
+        const int64_t i = i0 + threadIdx.x;
+        const WindowPlan p = i < n_windows ? plan[i] : WindowPlan{0, 0, 0, 0};
+        WindowStart o;
+        uint64_t t;
+        o.cut = run.cut + block_exclusive_scan_u64(p.cut, &t, lds);
+        run.cut += t;
+        o.pieces = run.pieces + block_exclusive_scan_u64(p.pieces, &t, lds);
+        run.pieces += t;
+        o.groups = run.groups + block_exclusive_scan_u64(p.groups, &t, lds);
+        run.groups += t;
+        o.batches = run.batches + block_exclusive_scan_u64(p.batches, &t, lds);
+        run.batches += t;
+        if (i < n_windows) start[i] = o;
+    }
+    if (threadIdx.x == 0) start[n_windows] = run;
+}
+
+// Whether a row has entries in an earlier or a later band.
+__device__ inline uint32_t band_marks(const uint32_t* __restrict__ count, int64_t n, int64_t row,
+                                      int band, int n_bands)
+{
+    uint32_t marks = 0;
+    for (int b = 0; b < n_bands; ++b)
+        if (b != band && count[b * n + row]) marks |= b < band ? kRowAdds : kRowMore;
+    return marks;
+}
+
+// Kinds of groups.  The eight row words of a group hold its rows; those of a long row hold the row and
+// seven times kNoRow, those of a piece kNoRow alone.
+constexpr uint32_t kKindShort = 0;
+constexpr uint32_t kKindLong = 1;
+constexpr uint32_t kKindPiece = 2;  // + slot of the piece
+
+// Lays out the groups of a window: rows, kinds and lengths in batches; one block per window.
+__global__ __launch_bounds__(kBlock) void window_groups_kernel(
+    const int64_t* __restrict__ rowptr, const uint32_t* __restrict__ sorted,
+    const uint2* __restrict__ long_short, const WindowStart* __restrict__ start, int64_t piece,
+    const uint32_t* __restrict__ band_count, int64_t n, int band, int n_bands,
+    uint32_t* __restrict__ rows, uint32_t* __restrict__ kind, uint32_t* __restrict__ len,
+    uint32_t* __restrict__ cut_row, uint64_t* __restrict__ piece0)
+{
+    const WindowStart at = start[blockIdx.x], next = start[blockIdx.x + 1];
+    const int n_cut = (int)(next.cut - at.cut);
+    const int n_long = (int)long_short[blockIdx.x].x, n_short = (int)long_short[blockIdx.x].y;
+    const uint32_t* const mine = sorted + (int64_t)blockIdx.x * kWindow;
+    int64_t k = (int64_t)at.groups;
+    int64_t slot = (int64_t)at.pieces;
+    for (int i = 0; i < n_cut; ++i) {
+        const uint32_t r = mine[i];
+        const int64_t entries = rowptr[r + 1] - rowptr[r], count = (entries + piece - 1) / piece;
+        if (threadIdx.x == 0) {
+            cut_row[at.cut + i] = r | band_marks(band_count, n, r, band, n_bands);
+            piece0[at.cut + i] = (uint64_t)slot;
+        }
+        for (int64_t p = threadIdx.x; p < count; p += kBlock) {
+            const int64_t left = entries - p * piece;
+            for (int j = 0; j < kGroupRows; ++j) rows[(k + p) * kGroupRows + j] = kNoRow;
+            kind[k + p] = kKindPiece + (uint32_t)(slot + p);
+            len[k + p] = (uint32_t)(((left < piece ? left : piece) + kGroupRows - 1) / kGroupRows);
+        }
+        k += count;
+        slot += count;
+    }
+    for (int i = threadIdx.x; i < n_long; i += kBlock) {
+        const uint32_t r = mine[n_cut + i];
+        rows[(k + i) * kGroupRows] = r | band_marks(band_count, n, r, band, n_bands);
+        for (int j = 1; j < kGroupRows; ++j) rows[(k + i) * kGroupRows + j] = kNoRow;
+        kind[k + i] = kKindLong;
+        len[k + i] = (uint32_t)((rowptr[r + 1] - rowptr[r] + kGroupRows - 1) / kGroupRows);
+    }
+    k += n_long;
+    const int padded = (n_short + kGroupRows - 1) / kGroupRows * kGroupRows;
+    for (int i = threadIdx.x; i < padded; i += kBlock) {
+        uint32_t r = kNoRow;
+        if (i < n_short) {
+            r = mine[n_cut + n_long + i];
+            if (i % kGroupRows == 0) {  // the first row of a group is its longest
+                kind[k + i / kGroupRows] = kKindShort;
+                len[k + i / kGroupRows] = (uint32_t)(rowptr[r + 1] - rowptr[r]);
+            }
+            r |= band_marks(band_count, n, r, band, n_bands);
+        }
+        rows[k * kGroupRows + i] = r;
+    }
+}
+
+// tab[i] = {first group that starts at batch kTabBatches * i or later, batch where it starts}
+__global__ __launch_bounds__(kBlock) void group_table_kernel(const uint64_t* __restrict__ start,
+                                                             int64_t n_groups, int64_t n_batches,
+                                                             int64_t n_tab, uint2* __restrict__ tab,
+                                                             uint32_t* __restrict__ rows)
+{
+    const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (k > n_groups) return;
+    const int64_t b = k < n_groups ? (int64_t)start[k] : n_batches;
+    const int64_t i0 = k == 0 ? 0 : (int64_t)start[k - 1] / kTabBatches + 1;
+    const int64_t i1 = k < n_groups ? b / kTabBatches : n_tab - 1;
+    for (int64_t i = i0; i <= i1; ++i) tab[i] = make_uint2((uint32_t)k, (uint32_t)b);
+    if (k == n_groups)  // the padding stands for no rows
+        for (int i = 0; i < kRowPad * kGroupRows; ++i) rows[k * kGroupRows + i] = kNoRow;
+}
+
+// ---- values ---------------------------------------------------------------------------------------
+
+// One wavefront per group: computes the matrix values of its rows (rule of the normalisation mode,
+// see entry_value) and writes them to the public array, to the entry-balanced form and, with the
+// columns and the end marks, to the group's batches.  rowptr and src are those of the band: its entry
+// `at` is entry src[at] of the matrix (src null: the only band).  64 consecutive entries of the stream per
+// step: the lane with position i of the step handles entry i / 8 of row i % 8 of a short group.
+__global__ __launch_bounds__(kBlock) void fill_groups_kernel(
+    const int64_t* __restrict__ rowptr, const uint32_t* __restrict__ col,
+    const float* __restrict__ dinv, int mode, float eps, int swapped,
+    const uint32_t* __restrict__ rows, const uint32_t* __restrict__ kind,
+    const uint64_t* __restrict__ start, const uint32_t* __restrict__ cut_row,
+    const uint64_t* __restrict__ piece0, int64_t n_cut, int64_t n_groups, int64_t n_batches,
+    int64_t piece,
+    const uint32_t* __restrict__ src,
+    float* __restrict__ val, uint2* __restrict__ cv, uint2* __restrict__ ent)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t k = (int64_t)blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6);
+    if (k >= n_groups) {
+        if (k == n_groups)
+            for (int i = lane; i < kStreamPad; i += kWave)
+                ent[n_batches * kGroupRows + i] = make_uint2(0u, kPadValue);
+        return;
+    }
+    const int64_t b0 = (int64_t)start[k];
+    const int64_t b1 = k + 1 < n_groups ? (int64_t)start[k + 1] : n_batches;
+    const uint32_t what = kind[k];
+    const bool is_short = what == kKindShort, is_piece = what >= kKindPiece;
+    uint32_t row = rows[k * kGroupRows + (is_short ? lane % kGroupRows : 0)] & kRowMask;
+    int64_t skip = 0;
+    if (is_piece) {  // of the last cut row whose pieces start at this slot or earlier
+        const int64_t slot = what - kKindPiece;
+        int64_t lo = 0, hi = n_cut;
+        while (lo + 1 < hi) {
+            const int64_t mid = (lo + hi) / 2;
+            if ((int64_t)piece0[mid] <= slot) lo = mid;
+            else hi = mid;
+        }
+        row = cut_row[lo] & kRowMask;
+        skip = (slot - (int64_t)piece0[lo]) * piece;
+    }
+    int64_t e0 = 0, e1 = 0;
+    if (row != kNoRow) {
+        e0 = rowptr[row];
+        e1 = rowptr[row + 1];
+    }
+    if (is_piece) {
+        e0 += skip;
+        if (e1 - e0 > piece) e1 = e0 + piece;
+    }
+    const float drow = (mode == MIXGCN_NORM_SUM || row == kNoRow) ? 0.f : dinv[row];
+    const uint32_t end = is_piece ? kEndPiece : is_short ? kEndGroup : kEndRow;
+    for (int64_t b = b0; b < b1; b += kWave / kGroupRows) {
+        const int64_t bb = b + lane / kGroupRows;  // the lane's batch
+        if (bb >= b1) break;
+        const int64_t at = e0 + (is_short ? bb - b0 : (b - b0) * kGroupRows + lane);
+        uint2 out = make_uint2(0u, kPadValue);
+        if (at < e1) {
+            const int64_t e = src ? (int64_t)src[at] : at;
+            const uint32_t c = col[e];
+            const float v = entry_value(mode, eps, swapped, row, c, drow, dinv);
+            val[e] = v;
+            cv[e].y = __float_as_uint(v);
+            out = make_uint2(c, __float_as_uint(v));
+        } else if (e1 > e0) {
+            out.x = col[src ? (int64_t)src[e1 - 1] : e1 - 1];  // a line that has just been gathered
+        }
+        if (bb == b1 - 1 && lane % kGroupRows == 0) out.x |= end;
+        ent[bb * kGroupRows + lane % kGroupRows] = out;
+    }
+}
+
+// ---- aggregation ----------------------------------------------------------------------------------
+
+// Closes a row, or what one band adds to it.  zraw and mbits are what Z and the mask hold for the
+// lane's columns, where they are wanted (wants_z, mask).  Between bands an fp32 row waits in Z itself;
+// a bf16 row waits unrounded in `sums` (fp32, [row][sum_stride], the lane's columns at j).
+template <int DT>
+__device__ inline bool wants_z(uint32_t row, int epi)
+{
+    if (DT == MIXGCN_BF16) return (epi & kEpiAccumulate) && !(row & kRowMore);
+    return (epi & kEpiAccumulate) || (row & kRowAdds);
+}
+
+template <int DT, int VB, bool EPI>
+__device__ inline void finish_row(float* t, void* Z, int64_t ldz, uint32_t row, int64_t c, int epi,
+                                  const typename Feat<DT, VB>::Raw& zraw, bool masked, uint32_t mbits,
+                                  int c_lo, int c_hi, float* sums, int sum_stride, int j)
+{
+    using F = Feat<DT, VB>;
+    constexpr int VEC = F::VEC;
+    const int64_t r = (int64_t)(row & kRowMask);
+    if (EPI) {
+        if (DT == MIXGCN_BF16 && (row & (kRowAdds | kRowMore))) {
+            float* const p = sums + r * sum_stride + j;
+            if (row & kRowAdds) {
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) t[i] += p[i];
+            }
+            if (row & kRowMore) {
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) p[i] = t[i];
+                return;
+            }
+        }
+        if (wants_z<DT>(row, epi)) {
+            float o[VEC];
+            F::widen(zraw, o);
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) t[i] += o[i];
+        }
+        if (!(row & kRowMore)) {
+            if (epi & kEpiRelu) {
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) t[i] = fmaxf(t[i], 0.f);
+            }
+            if (masked) {
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) t[i] = ((mbits >> i) & 1u) ? t[i] : 0.f;
+            }
+        }
+    }
+    store_in_range<DT, VB>(Z, r * ldz, c, t, c_lo, c_hi);
+}
+
+// LPR lanes of 16 bytes hold a feature row's slice: 8 for the 128-byte slices of wide passes; for
+// passes of at most 64 bytes 4, and one gather instruction then takes two batches (sixteen rows), the
+// first in the lower half of the wavefront, the second in the upper (with 8 lanes of 8 bytes such a
+// pass took twice as long: the L1 answers by the row).
+// The pipeline is that of the entry-balanced kernel: the entries of four gathers arrive with one
+// coalesced load two rounds ahead and are handed out with lane shuffles, the feature rows are
+// gathered one round (four loads) ahead, two rounds are written out per trip so that no register
+// of a load in flight is copied, and the loop has no side exit.
+// EPI: an epilogue other than a plain store is wanted.  OFF32: offsets into H fit 32 bits and
+// column indices 24 bits.
+template <int DT, int LPR, bool EPI, bool OFF32>
+__global__ __launch_bounds__(kBlock, DT == MIXGCN_BF16 && (EPI || LPR == 4) ? 6 : 8) void aggregate_groups_kernel(
+    const uint2* __restrict__ ent, const uint32_t* __restrict__ rows,
+    const uint32_t* __restrict__ kind, const uint2* __restrict__ tab, int64_t n_tab, int tab_per_wave, int64_t n_waves, const void* __restrict__ H, int64_t ldh,
+    void* __restrict__ Z, int64_t ldz, int c0, int width, int n_slices,
+    float* __restrict__ partials, int part_stride, int epi, const uint32_t* __restrict__ mask,
+    int64_t ldm, int c_lo, int c_hi, float* sums)
+{
+    using F = Feat<DT>;
+    constexpr int VEC = F::VEC;
+    constexpr int PW = LPR * VEC;              // columns of a slice
+    constexpr int BPG = 8 / LPR;               // batches per gather instruction
+    constexpr int EPG = BPG * kGroupRows;      // entries per gather instruction
+    constexpr int D = 4;                       // gathers in flight per wavefront
+    const int lane = threadIdx.x & (kWave - 1);
+    const int sub = lane / LPR % kGroupRows, lj = lane % LPR;
+    const int half = BPG == 2 ? lane / 32 : 0;
+    // Workgroups are dealt round-robin to the 8 XCDs.  1, 2, 4 or 8 slices are dealt with them, so
+    // that an XCD's L2 holds lines of one slice only; any other number is taken one after the other.
+    const bool dealt = (n_slices & (n_slices - 1)) == 0;
+    const unsigned per_slice = gridDim.x / (unsigned)n_slices;
+    const int slice = (int)(dealt ? blockIdx.x % (unsigned)n_slices : blockIdx.x / per_slice);
+    const unsigned block = dealt ? blockIdx.x / (unsigned)n_slices : blockIdx.x % per_slice;
+    const int64_t w = uniform64((int64_t)block * (kBlock / kWave) + (threadIdx.x >> 6));
+    if (w >= n_waves) return;
+    const int64_t i0 = w * tab_per_wave;
+    const int64_t i1 = i0 + tab_per_wave < n_tab ? i0 + tab_per_wave : n_tab - 1;
+    const uint2 t0 = tab[i0], t1 = tab[i1];
+    const int nb = uniform32((int)(t1.y - t0.y));  // batches of this wavefront
+    if (nb == 0) return;
+    int64_t k = (int64_t)(uint32_t)uniform32((int)t0.x);
+    const int64_t b0 = (int64_t)(uint32_t)uniform32((int)t0.y);
+    const int cs = slice * PW;  // first column of the slice within the pass
+    const bool active = cs + lj * VEC < width;
+    const int64_t c = (int64_t)c0 + cs + lj * VEC;
+    const int64_t c_load = active ? c : (int64_t)c0 + cs;  // idle lanes re-read the first column
+    const uint32_t pitch = (uint32_t)(ldh * F::ES);
+    const uint32_t lane_off = (uint32_t)(c_load * F::ES);
+    const char* const hbase = reinterpret_cast<const char*>(H) + c_load * F::ES;
+
+    float acc[VEC];
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
+    constexpr int RE = D * EPG;  // entries per round
+    static_assert(RE <= kWave, "a round's entries must fit one load per lane");
+    const uint2* const rent = ent + b0 * kGroupRows + (lane & (RE - 1));
+    uint32_t cw[D];
+    uint32_t a[D];
+    typename F::Raw h[D];
+    auto fill = [&](int u, const uint2& en) __attribute__((always_inline)) {  // slot u <- gather u of the round `en`
+        cw[u] = __shfl(en.x, u * EPG + lane / LPR, kWave);
+        a[u] = __shfl(en.y, u * EPG + lane / LPR, kWave);
+        if (OFF32)  // the 24-bit multiply ignores the marks
+            h[u] = *reinterpret_cast<const typename F::Raw*>(
+                reinterpret_cast<const char*>(H) + (__umul24(cw[u], pitch) + lane_off));
+        else
+            h[u] = *reinterpret_cast<const typename F::Raw*>(
+                hbase + (uint64_t)(cw[u] & kEntryColMask) * pitch);
+    };
+    // The rows of eight groups at a time, a word per lane, and those of the next eight in flight;
+    // `row` is the lane's row of the open group.  An epilogue that reads Z or a mask gets its words
+    // when the group is opened, not when it ends.
+    const uint32_t* row_words = rows + k * kGroupRows + lane;
+    uint32_t rv = row_words[0], rv_next = row_words[kWave];
+    int g = 0;  // group within the eight
+    uint32_t row = kNoRow, mbits = 0;
+    typename F::Raw zraw = {};
+    auto open = [&]() __attribute__((always_inline)) {
+        row = __shfl(rv, g * kGroupRows + sub, kWave);
+        if (EPI && row != kNoRow && active && half == 0) {
+            const int64_t r = (int64_t)(row & kRowMask);
+            if (wants_z<DT>(row, epi)) zraw = *F::ptr(Z, r * ldz + c);
+            if (mask) mbits = mask[r * ldm + (c >> 5)] >> (c & 31);
+        }
+    };
+    open();
+    auto finish = [&](uint32_t end) __attribute__((always_inline)) {
+        if (end == kEndGroup) {
+            if (BPG == 2) {
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) acc[i] += __shfl_xor(acc[i], 32, kWave);
+            }
+        } else {
+            reduce_subgroups<LPR, VEC>(acc);
+            if (end == kEndPiece && lane < LPR && active) {
+                float* p = partials + (size_t)(kind[k] - kKindPiece) * part_stride + cs + lj * VEC;
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) p[i] = acc[i];
+            }
+        }
+        if (row != kNoRow && active && half == 0)
+            finish_row<DT, 16, EPI>(acc, Z, ldz, row, c, epi, zraw, mask != nullptr, mbits, c_lo, c_hi, sums,
+                                    part_stride, cs + lj * VEC);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
+        ++k;
+        if (++g == kGroupRows) {
+            g = 0;
+            rv = rv_next;
+            row_words += kWave;
+            rv_next = row_words[kWave];
+        }
+        open();
+    };
+    auto round = [&](int b, const uint2& en) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            float x[VEC];
+            F::widen(h[u], x);
+            const float av = __uint_as_float(a[u]);
+            const bool real = a[u] != kPadValue;
+            // marks of the batches of this gather, if they belong to this wavefront
+            const int bu = b + u * BPG;
+            uint32_t end0 = (uint32_t)uniform32((int)cw[u]) & ~kEntryColMask;
+            if (bu >= nb) end0 = 0;
+            if (BPG == 1) {
+                if (real) {
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) acc[i] = fmaf(av, x[i], acc[i]);
+                }
+                if (__builtin_expect(end0 != 0, 0)) finish(end0);
+            } else {
+                uint32_t end1 = (uint32_t)__builtin_amdgcn_readlane((int)cw[u], 32) & ~kEntryColMask;
+                if (bu + 1 >= nb) end1 = 0;
+                if (__builtin_expect(end0 != 0, 0)) {  // the lower half belongs to the closing group, the upper to the next
+                    if (real && half == 0) {
+#pragma unroll
+                        for (int i = 0; i < VEC; ++i) acc[i] = fmaf(av, x[i], acc[i]);
+                    }
+                    finish(end0);
+                }
+                if (real && !(end0 && half == 0)) {
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) acc[i] = fmaf(av, x[i], acc[i]);
+                }
+                if (__builtin_expect(end1 != 0, 0)) finish(end1);
+            }
+            fill(u, en);
+        }
+    };
+    uint2 ea = rent[0];
+    uint2 eb = rent[RE];
+#pragma unroll
+    for (int u = 0; u < D; ++u) fill(u, ea);
+    constexpr int RB = D * BPG;  // batches per round
+    for (int b = 0; b < nb; b += 2 * RB) {
+        ea = rent[(int64_t)(b + 2 * RB) * kGroupRows];
+        round(b, eb);
+        eb = rent[(int64_t)(b + 3 * RB) * kGroupRows];
+        round(b + RB, ea);
+    }
+}
+
+// Adds the pieces of the rows that were cut: one block per row, its lanes along the columns.
+template <int DT>
+__global__ __launch_bounds__(kWave) void sum_pieces_kernel(
+    const uint32_t* __restrict__ cut_row, const uint64_t* __restrict__ piece0, int64_t n_cut,
+    int64_t n_pieces, void* __restrict__ Z, int64_t ldz, int c0, int width,
+    const float* __restrict__ partials, int part_stride, int epi, const uint32_t* __restrict__ mask,
+    int64_t ldm, int c_lo, int c_hi, float* sums)
+{
+    constexpr int VB = 4 * Feat<DT, 4>::ES;  // four columns per lane
+    constexpr int VEC = Feat<DT, VB>::VEC;
+    const int64_t i = blockIdx.x;
+    const int j = threadIdx.x * VEC;
+    if (j >= width) return;
+    const int64_t k0 = (int64_t)piece0[i], k1 = i + 1 < n_cut ? (int64_t)piece0[i + 1] : n_pieces;
+    float t[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) t[v] = 0.f;
+    const float4* p = reinterpret_cast<const float4*>(partials + (size_t)k0 * part_stride + j);
+    const size_t step = (size_t)part_stride / 4;
+    int64_t k = k0;
+    for (; k + 8 <= k1; k += 8) {  // eight loads in flight, added in order
+        float4 q[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) q[u] = p[u * step];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            t[0] += q[u].x; t[1] += q[u].y; t[2] += q[u].z; t[3] += q[u].w;
+        }
+        p += 8 * step;
+    }
+    for (; k < k1; ++k, p += step) {
+        const float4 q = *p;
+        t[0] += q.x; t[1] += q.y; t[2] += q.z; t[3] += q.w;
+    }
+    using F = Feat<DT, VB>;
+    const uint32_t row = cut_row[i];
+    const int64_t r = (int64_t)(row & kRowMask), c = (int64_t)c0 + j;
+    typename F::Raw zraw = {};
+    if (wants_z<DT>(row, epi)) zraw = *F::ptr(Z, r * ldz + c);
+    const uint32_t mbits = mask ? mask[r * ldm + (c >> 5)] >> (c & 31) : 0;
+    finish_row<DT, VB, true>(t, Z, ldz, row, c, epi, zraw, mask != nullptr, mbits, c_lo, c_hi, sums,
+                             part_stride, j);
+}
+
+template <typename T>
+int dmalloc(T** p, size_t count, hipStream_t s)
+{
+    return pool_alloc((void**)p, (count ? count : 1) * sizeof(T), s);
+}
+
+// Work arrays of one call, released on its stream.
+struct Tmp {
+    explicit Tmp(hipStream_t stream) : s(stream) {}
+    hipStream_t s;
+    uint64_t* keys = nullptr;
+    uint64_t* alt = nullptr;
+    void* sort = nullptr;
+    unsigned long long* hist = nullptr;
+    uint32_t* sorted = nullptr;
+    uint2* long_short = nullptr;
+    WindowPlan* plan = nullptr;
+    WindowStart* start = nullptr;
+    uint32_t* len = nullptr;
+    uint32_t* count = nullptr;
+    uint64_t* pos = nullptr;
+    uint8_t* band = nullptr;
+    ~Tmp()
+    {
+        pool_free_on(keys, s);
+        pool_free_on(alt, s);
+        pool_free_on(sort, s);
+        pool_free_on(hist, s);
+        pool_free_on(sorted, s);
+        pool_free_on(long_short, s);
+        pool_free_on(plan, s);
+        pool_free_on(start, s);
+        pool_free_on(len, s);
+        pool_free_on(count, s);
+        pool_free_on(pos, s);
+        pool_free_on(band, s);
+    }
+};
+
+inline unsigned blocks(int64_t threads) { return (unsigned)ceil_div(threads, kBlock); }
+
+}  // namespace
+
+void rowgroups_free(RowGroups* g)
+{
+    for (Band& b : g->bands) {
+        pool_free(b.ent);
+        pool_free(b.ent_t);
+        pool_free(b.rows);
+        pool_free(b.kind);
+        pool_free(b.start);
+        pool_free(b.tab);
+        pool_free(b.cut_row);
+        pool_free(b.piece0);
+        pool_free(b.rowptr);
+    }
+    pool_free(g->src);
+    *g = RowGroups();
+}
+
+int rowgroups_alloc_transpose(RowGroups* g, hipStream_t s)
+{
+    for (Band& b : g->bands)
+        if (!b.ent_t) MIXGCN_TRY(dmalloc(&b.ent_t, (size_t)b.n_batches * kGroupRows + kStreamPad, s));
+    return MIXGCN_OK;
+}
+
+namespace {
+
+// Groups of one band, whose rows are given by rowptr.
+int build_band(const int64_t* rowptr, uint32_t n, int64_t nnz, const uint32_t* band_count, int band,
+               int n_bands, Band* out, hipStream_t s)
+{
+    Band& g = *out;
+    // Pieces of 256 entries and groups of at most 32 batches keep the longest wavefront of a small
+    // graph short; on large ones 1024 keep the number of slots low, and groups of up to 64 batches
+    // the padding of the rows that do not fill whole batches of their own.
+    const bool small = nnz < (4ll << 20);
+    g.piece = small ? 256 : 1024;
+    const int short_row = small ? 32 : kMostShort;
+    const int64_t n_windows = ceil_div(n, kWindow);
+    Tmp t(s);
+    MIXGCN_TRY(dmalloc(&t.sorted, n, s));
+    MIXGCN_TRY(dmalloc(&t.long_short, (size_t)n_windows, s));
+    MIXGCN_TRY(dmalloc(&t.plan, (size_t)n_windows, s));
+    MIXGCN_TRY(dmalloc(&t.start, (size_t)n_windows + 1, s));
+    hipLaunchKernelGGL(window_sort_kernel, dim3((unsigned)n_windows), dim3(kBlock), 0, s, rowptr, n, g.piece,
+                       short_row, t.sorted, t.long_short, t.plan);
+    hipLaunchKernelGGL(window_scan_kernel, dim3(1), dim3(kBlock), 0, s, t.plan, n_windows, t.start);
+    WindowStart h;
+    MIXGCN_HIP_TRY(hipMemcpyAsync(&h, t.start + n_windows, sizeof(h), hipMemcpyDeviceToHost, s));
+    MIXGCN_HIP_TRY(hipStreamSynchronize(s));
+    g.n_cut = (int64_t)h.cut;
+    g.n_pieces = (int64_t)h.pieces;
+    g.n_groups = (int64_t)h.groups;
+    g.n_batches = (int64_t)h.batches;
+    g.n_tab = g.n_batches / kTabBatches + 2;
+
+    MIXGCN_TRY(pool_alloc(&t.sort, scan_tmp_bytes(g.n_groups), s));
+    MIXGCN_TRY(dmalloc(&t.len, (size_t)g.n_groups, s));
+    MIXGCN_TRY(dmalloc(&g.rows, (size_t)(g.n_groups + kRowPad) * kGroupRows, s));
+    MIXGCN_TRY(dmalloc(&g.kind, (size_t)g.n_groups, s));
+    MIXGCN_TRY(dmalloc(&g.start, (size_t)g.n_groups, s));
+    MIXGCN_TRY(dmalloc(&g.tab, (size_t)g.n_tab, s));
+    MIXGCN_TRY(dmalloc(&g.cut_row, (size_t)g.n_cut, s));
+    MIXGCN_TRY(dmalloc(&g.piece0, (size_t)g.n_cut, s));
+    MIXGCN_TRY(dmalloc(&g.ent, (size_t)g.n_batches * kGroupRows + kStreamPad, s));
+    hipLaunchKernelGGL(window_groups_kernel, dim3((unsigned)n_windows), dim3(kBlock), 0, s, rowptr, t.sorted,
+                       t.long_short, t.start, g.piece, band_count, (int64_t)n, band, n_bands, g.rows, g.kind,
+                       t.len, g.cut_row, g.piece0);
+    MIXGCN_TRY(exclusive_scan_u32_to_u64(t.len, g.start, g.n_groups, nullptr, t.sort, s));
+    hipLaunchKernelGGL(group_table_kernel, dim3(blocks(g.n_groups + 1)), dim3(kBlock), 0, s, g.start,
+                       g.n_groups, g.n_batches, g.n_tab, g.tab, g.rows);
+    MIXGCN_HIP_TRY(hipGetLastError());
+    return MIXGCN_OK;
+}
+
+int build_bands(const Csr& m, uint32_t n, bool symmetric, RowGroups* out, hipStream_t s)
+{
+    int n_bands = 1;
+    Tmp t(s);
+    uint64_t* sorted = nullptr;
+    // Row lengths are column popularities only where the pattern is symmetric.
+    if (symmetric && n > (uint32_t)kBandColumns) {
+        MIXGCN_TRY(dmalloc(&t.keys, n, s));
+        MIXGCN_TRY(dmalloc(&t.hist, 2 * kBins, s));
+        MIXGCN_HIP_TRY(hipMemsetAsync(t.hist, 0, 2 * kBins * sizeof(unsigned long long), s));
+        hipLaunchKernelGGL(popularity_kernel, dim3(blocks(n) < 512u ? blocks(n) : 512u), dim3(kBlock), 0, s,
+                           m.rowptr, n, t.keys, t.hist, t.hist + kBins);
+        unsigned long long h[2 * kBins];
+        MIXGCN_HIP_TRY(hipMemcpyAsync(h, t.hist, sizeof(h), hipMemcpyDeviceToHost, s));
+        MIXGCN_HIP_TRY(hipStreamSynchronize(s));
+        n_bands = plan_bands(h, h + kBins, (double)n, (double)m.nnz);
+    }
+    out->bands.resize((size_t)n_bands);
+    if (n_bands == 1) return build_band(m.rowptr, n, m.nnz, nullptr, 0, 1, &out->bands[0], s);
+
+    size_t tmp_bytes = sort_tmp_bytes(n);
+    const int64_t counts = (int64_t)n_bands * n;
+    if (scan_tmp_bytes(counts) > tmp_bytes) tmp_bytes = scan_tmp_bytes(counts);
+    MIXGCN_TRY(dmalloc(&t.alt, n, s));
+    MIXGCN_TRY(pool_alloc(&t.sort, tmp_bytes, s));
+    MIXGCN_TRY(dmalloc(&t.band, n, s));
+    MIXGCN_TRY(dmalloc(&t.count, (size_t)counts, s));
+    MIXGCN_TRY(dmalloc(&t.pos, (size_t)counts, s));
+    MIXGCN_TRY(dmalloc(&out->src, (size_t)m.nnz, s));
+    MIXGCN_TRY(radix_sort_u64(t.keys, t.alt, n, 8, &sorted, t.sort, s));
+    uint32_t per_band = kBandColumns;
+    if ((int64_t)n_bands * kBandColumns >= n) per_band = (uint32_t)ceil_div(n, n_bands);
+    hipLaunchKernelGGL(band_of_column_kernel, dim3(blocks(n)), dim3(kBlock), 0, s, sorted, n, per_band,
+                       n_bands, t.band);
+    const dim3 grid((unsigned)ceil_div(n, kBlock / kWave));
+    hipLaunchKernelGGL(deal_entries_kernel<false>, grid, dim3(kBlock), 0, s, m.rowptr, m.col, t.band, n,
+                       n_bands, t.count, (const uint64_t*)nullptr, (uint32_t*)nullptr);
+    MIXGCN_TRY(exclusive_scan_u32_to_u64(t.count, t.pos, counts, nullptr, t.sort, s));
+    hipLaunchKernelGGL(deal_entries_kernel<true>, grid, dim3(kBlock), 0, s, m.rowptr, m.col, t.band, n,
+                       n_bands, (uint32_t*)nullptr, t.pos, out->src);
+    std::vector<uint64_t> first((size_t)n_bands + 1);
+    for (int b = 0; b < n_bands; ++b)
+        MIXGCN_HIP_TRY(hipMemcpyAsync(&first[(size_t)b], t.pos + (int64_t)b * n, 8, hipMemcpyDeviceToHost, s));
+    MIXGCN_HIP_TRY(hipStreamSynchronize(s));
+    first[(size_t)n_bands] = (uint64_t)m.nnz;
+    for (int b = 0; b < n_bands; ++b) {
+        Band& band = out->bands[(size_t)b];
+        band.src0 = (int64_t)first[(size_t)b];
+        MIXGCN_TRY(dmalloc(&band.rowptr, (size_t)n + 1, s));
+        hipLaunchKernelGGL(band_rowptr_kernel, dim3(blocks((int64_t)n + 1)), dim3(kBlock), 0, s, t.pos,
+                           (int64_t)n, b, n_bands, m.nnz, band.rowptr);
+        MIXGCN_TRY(build_band(band.rowptr, n, (int64_t)first[(size_t)b + 1] - band.src0, t.count, b, n_bands,
+                              &band, s));
+    }
+    return MIXGCN_OK;
+}
+
+}  // namespace
+
+// The groups of a matrix: everything that depends on its pattern only.
+int rowgroups_build(const Csr& m, uint32_t n, bool symmetric, RowGroups* out, hipStream_t s)
+{
+    RowGroups g;
+    const int rc = build_bands(m, n, symmetric, &g, s);
+    if (rc != MIXGCN_OK) {
+        (void)hipStreamSynchronize(s);  // the arrays may have work queued on them
+        rowgroups_free(&g);
+        return rc;
+    }
+    *out = std::move(g);
+    return MIXGCN_OK;
+}
+
+// Values of the matrix (mode, eps; transposed: those of its transpose on the same pattern, into
+// ent_t) into val, the value words of cv, and the streams.
+int rowgroups_fill(const Csr& m, const RowGroups& g, const float* dinv, int mode, float eps,
+                   int swapped, bool transposed, float* val, uint2* cv, hipStream_t s)
+{
+    for (const Band& b : g.bands)
+        hipLaunchKernelGGL(fill_groups_kernel, dim3((unsigned)ceil_div(b.n_groups + 1, kBlock / kWave)),
+                           dim3(kBlock), 0, s, b.rowptr ? b.rowptr : m.rowptr, m.col, dinv, mode, eps,
+                           swapped, b.rows, b.kind, b.start, b.cut_row, b.piece0, b.n_cut, b.n_groups,
+                           b.n_batches, b.piece, b.rowptr ? g.src + b.src0 : nullptr, val, cv,
+                           transposed ? b.ent_t : b.ent);
+    MIXGCN_HIP_TRY(hipGetLastError());
+    return MIXGCN_OK;
+}
+
+namespace {
+
+template <int DT, int LPR>
+int launch_groups(const Band& g, const uint2* ent, int64_t n_nodes, const void* H, int64_t ldh,
+                  void* Z, int64_t ldz, int c0, int width, float* P, int part_stride, int epi,
+                  const uint32_t* mask, int64_t ldm, int c_lo, int c_hi, hipStream_t s, Timer* timer,
+                  int timer_kind, bool epilogue, float* sums)
+{
+    using F = Feat<DT>;
+    if (g.n_batches == 0) return MIXGCN_OK;
+    const int n_slices = (int)ceil_div(width, F::VEC * LPR);
+    // A wavefront walks up to 1024 batches: its start is four dependent loads (2.45 M nodes, 256 bf16
+    // columns: 6.14 ms with 256 batches each, 6.08 with 1024).  Half, a quarter .. of that, down to
+    // 256, until the chip's 8192 wavefronts are filled seven times over (a last partial filling then
+    // costs little); on small inputs further, until they are filled once.
+    int per_wave = 1024 / kTabBatches;
+    while (per_wave > 1) {
+        const int64_t waves = ceil_div(g.n_tab, per_wave) * n_slices;
+        if (waves >= (per_wave > 256 / kTabBatches ? 7 * 8192 : 8192)) break;
+        per_wave /= 2;
+    }
+    const int64_t n_waves = ceil_div(g.n_tab - 1, per_wave);
+    const int64_t grid = ceil_div(n_waves, kBlock / kWave) * n_slices;
+    if (grid > 0x7FFFFFFF) return fail(MIXGCN_EINVAL, "aggregate: grid too large");
+    const bool off32 = n_nodes * ldh * F::ES + (int64_t)(c0 + width) * F::ES < (1ll << 32) &&
+                       ldh * F::ES < (1ll << 24) && n_nodes <= (1ll << 24);
+    if (timer) MIXGCN_TRY(timer->begin(timer_kind, s));
+#define MIXGCN_GROUPS(EPI, O32)                                                                   \
+    hipLaunchKernelGGL((aggregate_groups_kernel<DT, LPR, EPI, O32>), dim3((unsigned)grid),         \
+                       dim3(kBlock), 0, s, ent, g.rows, g.kind, g.tab, g.n_tab, per_wave, n_waves, H, ldh, Z, \
+                       ldz, c0, width, n_slices, P, part_stride, epi, mask, ldm, c_lo, c_hi, sums)
+    if (epilogue) {
+        if (off32) MIXGCN_GROUPS(true, true);
+        else MIXGCN_GROUPS(true, false);
+    } else {
+        if (off32) MIXGCN_GROUPS(false, true);
+        else MIXGCN_GROUPS(false, false);
+    }
+#undef MIXGCN_GROUPS
+    if (timer) MIXGCN_TRY(timer->end(s));
+    if (g.n_cut > 0)
+        hipLaunchKernelGGL((sum_pieces_kernel<DT>), dim3((unsigned)g.n_cut), dim3(kWave), 0, s,
+                           g.cut_row, g.piece0, g.n_cut, g.n_pieces, Z, ldz, c0, width, P, part_stride,
+                           epi, mask, ldm, c_lo, c_hi, sums);
+    return MIXGCN_OK;
+}
+
+// Columns of a slot: the pass, rounded up to whole slices.
+inline int slot_columns(int width) { return (width + 63) / 64 * 64; }
+
+template <int DT>
+int launch_band(const Band& g, const uint2* ent, int64_t n_nodes, const void* H, int64_t ldh, void* Z,
+                int64_t ldz, int c0, int width, float* P, int epi, const uint32_t* mask, int64_t ldm,
+                int c_lo, int c_hi, hipStream_t s, Timer* timer, int timer_kind, bool epilogue, float* sums)
+{
+#define MIXGCN_GROUPS_LPR(LPR)                                                                    \
+    return launch_groups<DT, LPR>(g, ent, n_nodes, H, ldh, Z, ldz, c0, width, P, slot_columns(width), \
+                                  epi, mask, ldm, c_lo, c_hi, s, timer, timer_kind, epilogue, sums)
+    if (width * Feat<DT>::ES <= 64) MIXGCN_GROUPS_LPR(4);
+    MIXGCN_GROUPS_LPR(8);
+#undef MIXGCN_GROUPS_LPR
+}
+
+}  // namespace
+
+// Piece slots, and where bf16 rows wait between bands.
+size_t rowgroups_scratch(const RowGroups& g, int64_t n, int dtype, int width)
+{
+    int64_t slots = 0;
+    for (const Band& b : g.bands) slots = b.n_pieces > slots ? b.n_pieces : slots;
+    if (dtype == MIXGCN_BF16 && g.bands.size() > 1) slots += n;
+    return (size_t)slots * slot_columns(width) * sizeof(float);
+}
+
+int launch_groups_pass(const RowGroups& g, bool values_t, int64_t n_nodes, int dtype, const void* H,
+                       int64_t ldh, void* Z, int64_t ldz, int c0, int width, float* P, int epi,
+                       const uint32_t* mask, int64_t ldm, int c_lo, int c_hi, hipStream_t s,
+                       Timer* timer, int timer_kind)
+{
+    int64_t slots = 0;
+    for (const Band& b : g.bands) slots = b.n_pieces > slots ? b.n_pieces : slots;
+    float* const sums = P + slots * slot_columns(width);
+    for (size_t i = 0; i < g.bands.size(); ++i) {
+        const Band& b = g.bands[i];
+        const uint2* ent = values_t ? b.ent_t : b.ent;
+        // without an epilogue of its own the first band's fp32 rows are plain stores
+        const bool epilogue = epi || mask || (dtype == MIXGCN_F32 ? i > 0 : g.bands.size() > 1);
+        if (dtype == MIXGCN_F32)
+            MIXGCN_TRY(launch_band<MIXGCN_F32>(b, ent, n_nodes, H, ldh, Z, ldz, c0, width, P, epi, mask, ldm,
+                                               c_lo, c_hi, s, timer, timer_kind, epilogue, sums));
+        else
+            MIXGCN_TRY(launch_band<MIXGCN_BF16>(b, ent, n_nodes, H, ldh, Z, ldz, c0, width, P, epi, mask, ldm,
+                                                c_lo, c_hi, s, timer, timer_kind, epilogue, sums));
+    }
+    return MIXGCN_OK;
+}
+
+}  // namespace mixgcn

@@ -47,27 +47,16 @@ __global__ __launch_bounds__(kBlock) void radix_scatter_kernel(const uint64_t* _
     const int64_t base = (int64_t)blockIdx.x * kSortTile + (int64_t)w * kWaveKeys;
     uint64_t key[kSortItems];
     uint32_t rank[kSortItems];
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    uint32_t digit[kSortItems];
+    bool valid[kSortItems];
 #pragma unroll
     for (int r = 0; r < kSortItems; ++r) {
         const int64_t i = base + (int64_t)r * kWave + lane;
-        const bool valid = i < n;
-        key[r] = valid ? keys[i] : 0ull;
-        const uint32_t d = (uint32_t)(key[r] >> shift) & (kRadix - 1);
-        uint64_t m = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < kRadixBits; ++b) {
-            const bool bit = (d >> b) & 1u;
-            const uint64_t bal = __ballot(bit);
-            m &= bit ? bal : ~bal;
-        }
-        // m: valid lanes of this round with my digit (includes me when valid)
-        const int leader = m ? (__ffsll((unsigned long long)m) - 1) : 0;
-        uint32_t prior = 0;
-        if (valid && lane == leader) prior = atomicAdd(&whist[w][d], (uint32_t)__popcll(m));
-        prior = __shfl(prior, leader, kWave);
-        rank[r] = prior + (uint32_t)__popcll(m & lt_mask);
+        valid[r] = i < n;
+        key[r] = valid[r] ? keys[i] : 0ull;
+        digit[r] = (uint32_t)(key[r] >> shift) & (kRadix - 1);
     }
+    wave_digit_ranks(digit, valid, whist, rank);
     __syncthreads();
     {
         // thread t = digit t: turn per-wave counts into exclusive wave offsets

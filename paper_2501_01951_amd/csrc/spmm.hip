@@ -22,147 +22,13 @@
 // and each private L2 caches only its own part of the hot feature rows.
 #include <mutex>
 
-#include "device_utils.h"
-#include "internal.h"
+#include "agg_common.h"
 
 namespace mixgcn {
 namespace {
 
 constexpr int kBatchesPerSpan = 256;  // gather instructions per wavefront (fewer on small inputs)
 constexpr int kDepth = 4;             // gather instructions a wavefront keeps in flight
-
-// 16-byte feature vector: 4 fp32 or 8 bf16 (widened to fp32)
-template <int DT>
-struct Feat;
-
-template <>
-struct Feat<MIXGCN_F32> {
-    static constexpr int VEC = 4;
-    using Raw = float4;
-    __device__ static inline void widen(const Raw& r, float* o)
-    {
-        o[0] = r.x; o[1] = r.y; o[2] = r.z; o[3] = r.w;
-    }
-    __device__ static inline void store(void* base, int64_t elem_off, const float* a)
-    {
-        *reinterpret_cast<float4*>(reinterpret_cast<float*>(base) + elem_off) =
-            make_float4(a[0], a[1], a[2], a[3]);
-    }
-    __device__ static inline void store_one(void* base, int64_t elem_off, float a)
-    {
-        reinterpret_cast<float*>(base)[elem_off] = a;
-    }
-    __device__ static inline const Raw* ptr(const void* base, int64_t elem_off)
-    {
-        return reinterpret_cast<const Raw*>(reinterpret_cast<const float*>(base) + elem_off);
-    }
-};
-
-template <>
-struct Feat<MIXGCN_BF16> {
-    static constexpr int VEC = 8;
-    using Raw = uint4;
-    __device__ static inline void widen(const Raw& r, float* o)
-    {
-        const uint32_t w[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            o[2 * i] = __uint_as_float(w[i] << 16);
-            o[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
-        }
-    }
-    // two fp32 -> two bf16, round to nearest even, by the conversion instruction of this part
-    // (rounding in software made a row's end a third of the vector work of this kernel at bf16)
-    __device__ static inline uint32_t pack2(float lo, float hi)
-    {
-        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-        typedef float floatx2 __attribute__((ext_vector_type(2)));
-        const floatx2 v = {lo, hi};
-        const bf16x2 h = __builtin_convertvector(v, bf16x2);
-        uint32_t u;
-        __builtin_memcpy(&u, &h, 4);
-        return u;
-    }
-    __device__ static inline void store(void* base, int64_t elem_off, const float* a)
-    {
-        uint4 r;
-        r.x = pack2(a[0], a[1]);
-        r.y = pack2(a[2], a[3]);
-        r.z = pack2(a[4], a[5]);
-        r.w = pack2(a[6], a[7]);
-        *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(base) + elem_off) = r;
-    }
-    __device__ static inline void store_one(void* base, int64_t elem_off, float a)
-    {
-        reinterpret_cast<uint16_t*>(base)[elem_off] = (uint16_t)pack2(a, 0.f);
-    }
-    __device__ static inline const Raw* ptr(const void* base, int64_t elem_off)
-    {
-        return reinterpret_cast<const Raw*>(reinterpret_cast<const uint16_t*>(base) + elem_off);
-    }
-};
-
-// Writes a lane's VEC columns [c, c + VEC) of one output row: the whole 16-byte group when it
-// lies inside the call's column range [c_lo, c_hi), else only the elements that do, one by one
-// (a range need not start or end on a group; what lies outside it is never written).
-template <int DT>
-__device__ inline void store_in_range(void* Z, int64_t row_off, int64_t c, const float* t, int c_lo,
-                                      int c_hi)
-{
-    using F = Feat<DT>;
-    if (c >= c_lo && c + F::VEC <= c_hi) {
-        F::store(Z, row_off + c, t);
-    } else {
-#pragma unroll
-        for (int i = 0; i < F::VEC; ++i)
-            if (c + i >= c_lo && c + i < c_hi) F::store_one(Z, row_off + c + i, t[i]);
-    }
-}
-
-// A value that is the same in every lane, moved to scalar registers.
-__device__ inline int uniform32(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ inline int64_t uniform64(int64_t v)
-{
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
-    return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
-// Sum over the 64 / LPR sub-groups of a wavefront (lanes that hold the same columns).
-template <int LPR, int VEC>
-__device__ inline void reduce_subgroups(float* v)
-{
-#pragma unroll
-    for (int d = LPR; d < kWave; d <<= 1)
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) v[i] += __shfl_xor(v[i], d, kWave);
-}
-
-// Output mask of the S-SpMM (paper Eq. 4), a bitmap: column c of row r is bit c % 32 of word
-// mask[r * ldm + c / 32].  A lane's VEC consecutive columns start at a multiple of VEC, so
-// their bits lie in one word.
-template <int VEC>
-__device__ inline void apply_mask(float* t, const uint32_t* __restrict__ mask, int64_t ldm,
-                                  int64_t r, int64_t c)
-{
-    const uint32_t bits = mask[r * ldm + (c >> 5)] >> (c & 31);
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) t[i] = ((bits >> i) & 1u) ? t[i] : 0.f;
-}
-
-// Epilogue flags carried in the kernels' `relu` argument (MIXGCN_EPI_* of the ABI).
-constexpr int kEpiRelu = 1;        // Z = max(., 0)
-constexpr int kEpiAccumulate = 2;  // Z = Z + (.): the finished row sum is added to what Z holds
-
-template <int DT>
-__device__ inline void add_stored(float* t, const void* Z, int64_t elem_off)
-{
-    using F = Feat<DT>;
-    float o[F::VEC];
-    F::widen(*F::ptr(Z, elem_off), o);
-#pragma unroll
-    for (int i = 0; i < F::VEC; ++i) t[i] += o[i];
-}
 
 // Partial-sum slots: [span in call][head = 0 / tail = 1][part_stride] fp32, indexed by the
 // column offset within the pass.
@@ -567,7 +433,7 @@ size_t agg_scratch_need(int dtype, int32_t n_cols, int64_t e0, int64_t e1)
 namespace {
 
 template <int DT>
-int launch_dt(const mixgcn_graph* g, const Csr& m, const uint2* cv, const void* H, int64_t ldh,
+int launch_dt(const mixgcn_graph* g, const Csr& m, bool values_t, const void* H, int64_t ldh,
               void* Z, int64_t ldz, int32_t c0, int32_t c1, int64_t r0, int64_t r1, int relu,
               const uint32_t* mask, int64_t ldm, float* P, size_t P_bytes, hipStream_t s,
               Timer* timer)
@@ -592,12 +458,26 @@ int launch_dt(const mixgcn_graph* g, const Csr& m, const uint2* cv, const void* 
                            dim3(kBlock), 0, s, m.rowptr, Z, ldz, c_lo, c_hi - c_lo, r0, r1,
                            (relu & kEpiAccumulate) ? 1 : 0);
     if (e1 <= e0) return MIXGCN_OK;
+    // The row-grouped form takes the calls over all rows (its order of the rows is not theirs); the
+    // entry-balanced kernel takes row ranges, the whole-row measurement mode, and matrices too
+    // large to be stored twice.
+    const uint2* cv = values_t ? m.cv_t : m.cv;
+    const int widest = c1 - c0 < kAggMaxPassCols ? c1 - c0 : kAggMaxPassCols;
+    const bool grouped = !m.groups.bands.empty() && r0 == 0 && r1 == (int64_t)g->n && !g_aggregate_whole_rows &&
+                         rowgroups_scratch(m.groups, (int64_t)g->n, DT, widest) <= P_bytes;
     for (int32_t cbk = c0; cbk < c1; cbk += kAggMaxPassCols) {
         Pass p;
         plan_pass(VEC, cbk, (c1 - cbk) < kAggMaxPassCols ? (c1 - cbk) : kAggMaxPassCols, e1 - e0, &p);
         const int32_t cb = p.cb;
         const int w = p.w;
         const int64_t span = p.span;
+        if (grouped) {
+            const int kind = p.gf == 4 ? kTimeAggG4 : p.gf == 8 ? kTimeAggG8 : p.gf == 16 ? kTimeAggG16
+                             : p.gf == 32 ? kTimeAggG32 : kTimeAggG64;
+            MIXGCN_TRY(launch_groups_pass(m.groups, values_t, (int64_t)g->n, DT, H, ldh, Z, ldz, cb, w, P, relu,
+                                          mask, ldm, c_lo, c_hi, s, timer, kind));
+            continue;
+        }
 #define MIXGCN_AGG_PASS(GG)                                                                      \
     if (g_aggregate_whole_rows)                                                                  \
         MIXGCN_TRY((launch_main<GG, GG, DT>(m, cv, (int64_t)g->n, H, ldh, Z, ldz, cb, w, r0, r1, e0, \
@@ -754,15 +634,15 @@ int launch_relu_bitmap(int dtype, const void* X, int64_t ldx, int64_t n, int32_t
     return MIXGCN_OK;
 }
 
-int launch_aggregate(const mixgcn_graph* g, const Csr& m, const uint2* cv, int dtype, const void* H,
+int launch_aggregate(const mixgcn_graph* g, const Csr& m, bool values_t, int dtype, const void* H,
                      int64_t ldh, void* Z, int64_t ldz, int32_t c0, int32_t c1, int64_t r0,
                      int64_t r1, int epilogue, const uint32_t* mask, int64_t ldm, float* partials,
                      size_t partials_bytes, hipStream_t s, Timer* timer)
 {
     if (dtype == MIXGCN_F32)
-        return launch_dt<MIXGCN_F32>(g, m, cv, H, ldh, Z, ldz, c0, c1, r0, r1, epilogue, mask, ldm,
+        return launch_dt<MIXGCN_F32>(g, m, values_t, H, ldh, Z, ldz, c0, c1, r0, r1, epilogue, mask, ldm,
                                      partials, partials_bytes, s, timer);
-    return launch_dt<MIXGCN_BF16>(g, m, cv, H, ldh, Z, ldz, c0, c1, r0, r1, epilogue, mask, ldm,
+    return launch_dt<MIXGCN_BF16>(g, m, values_t, H, ldh, Z, ldz, c0, c1, r0, r1, epilogue, mask, ldm,
                                   partials, partials_bytes, s, timer);
 }
 
