@@ -6,11 +6,12 @@
 // rule - visit in queue order; the unvisited neighbors of the visited node join the queue in
 // increasing (degree, id) - puts the nodes of one breadth-first level in the order of
 // (queue index of the earliest visited neighbor, degree, id).  So per level: every frontier
-// node offers its queue index to its unvisited neighbors with an atomic minimum, the first
-// offer also appends the neighbor to the next level's list, and that list is sorted by
-// (winning index, rank of the node in the global (degree, id) order).  Components start from
+// node offers its queue index to its unvisited neighbors with an atomic minimum; a neighbor then
+// belongs to the frontier node whose offer stands, and each frontier node places its own, in the
+// (degree, id) order, behind those of the frontier nodes before it.  Components start from
 // the unvisited node of smallest (degree, id); runs of single-node components are appended in
-// one pass.  Wide levels run as grid-wide kernels with one counter read back per level; levels
+// one pass.  Wide levels run as grid-wide kernels that keep the state of the walk on the device,
+// up to 16 levels between two looks of the host; levels
 // whose frontier is small (at most kNarrowFrontier nodes with kNarrowEdges stored entries) are
 // walked by ONE workgroup that stays on the device from level to level, and from component to
 // component, until it meets a level too wide for it - a banded graph with tens of thousands of
@@ -46,12 +47,13 @@ struct DevMem {
     }
 };
 
+// The sort is stable and takes only the degree bits: nodes of one degree stay in the order of ids.
 __global__ __launch_bounds__(kBlock) void degree_keys_kernel(const int64_t* __restrict__ rowptr,
                                                              uint32_t n, uint64_t* __restrict__ keys)
 {
     const uint32_t v = blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= n) return;
-    keys[v] = ((uint64_t)(rowptr[v + 1] - rowptr[v]) << 32) | v;
+    keys[v] = (uint64_t)v << 32 | (uint32_t)(rowptr[v + 1] - rowptr[v]);
 }
 
 // bydeg[i] = i-th node in (degree, id) order; degrank = its inverse; single[v] = the row of v
@@ -67,7 +69,7 @@ __global__ __launch_bounds__(kBlock) void rank_kernel(const uint64_t* __restrict
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const uint32_t v = (uint32_t)sorted[i];
+    const uint32_t v = (uint32_t)(sorted[i] >> 32);
     bydeg[i] = v;
     degrank[v] = i;
     const int64_t a = rowptr[v], b = rowptr[v + 1];
@@ -334,41 +336,217 @@ __global__ __launch_bounds__(kBlock) void narrow_levels_kernel(
     }
 }
 
-// One wavefront per frontier node order[f_begin + i]: offers its queue index to every unvisited
-// neighbor; the first offer a node receives also puts it on the next level's list.
-__global__ __launch_bounds__(kBlock) void expand_kernel(
+// ---- wide levels ----------------------------------------------------------------------------
+// Three kernels and a scan per level, one wavefront per frontier node.  What bounds a level of a few
+// thousand nodes is the chain of dependent loads of each kernel (about 5 us) and the launches, so
+// the levels follow each other without the host: the state of the walk goes from one slot to the
+// next on the device, and launches behind the last wide level return at once.
+// A 64 x 64 x 64 grid (about 95 wide levels): 3.8 ms; with one counter read back and a radix sort of
+// seven passes per level it was 17.4 ms.
+constexpr int kMostChildren = 64;   // next-level nodes of one frontier node that a wavefront orders
+constexpr int kWideBlocks = 1024;
+constexpr int kScanThreads = 1024;
+constexpr int kScanPer = 16;        // counts per thread and step of the scan
+
+struct WideState {
+    uint32_t f_begin, f_count;  // the frontier is order[f_begin, f_begin + f_count)
+    uint32_t count;             // nodes placed so far
+    uint32_t m;                 // kWideSort: nodes of the next level
+    uint32_t stop;
+};
+constexpr uint32_t kWideGo = 0;
+constexpr uint32_t kWideEnd = 1;     // the component is complete
+constexpr uint32_t kWideNarrow = 2;  // the frontier is one for the resident workgroup
+constexpr uint32_t kWideSort = 3;    // a frontier node has too many next-level nodes: sort the level
+
+// Offers the queue indices of the frontier.  A placed node's parent is smaller than every index of
+// the frontier, or its own index (see narrow_levels_kernel).
+__global__ __launch_bounds__(kBlock) void wide_offer_kernel(
     const int64_t* __restrict__ rowptr, const uint32_t* __restrict__ col,
-    const uint32_t* __restrict__ order, uint32_t f_begin, uint32_t f_count,
-    const uint32_t* __restrict__ cm_idx, uint32_t* __restrict__ parent,
-    uint32_t* __restrict__ next_list, uint32_t* __restrict__ next_count)
+    const uint32_t* __restrict__ order, const WideState* __restrict__ st, uint32_t* parent,
+    uint32_t* __restrict__ many)
 {
-    const uint32_t i = blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6);
-    if (i >= f_count) return;
-    const uint32_t lane = threadIdx.x & 63;
-    const uint32_t qi = f_begin + i;
-    const uint32_t u = order[qi];
-    for (int64_t e = rowptr[u] + lane; e < rowptr[u + 1]; e += kWave) {
-        const uint32_t w = col[e];
-        if (cm_idx[w] != kNone) continue;
-        const uint32_t old = atomicMin(&parent[w], qi);
-        if (old == kNone) next_list[atomicAdd(next_count, 1u)] = w;
+    const WideState a = *st;
+    if (a.stop != kWideGo) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *many = 0;
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    for (uint32_t i = blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6); i < a.f_count;
+         i += gridDim.x * (kBlock / kWave)) {
+        const uint32_t qi = a.f_begin + i;
+        const uint32_t u = order[qi];
+        const int64_t e1 = rowptr[u + 1];
+        for (int64_t e = rowptr[u] + lane; e < e1; e += kWave) {
+            const uint32_t w = col[e];
+            // an outdated value is larger than the true one: the minimum decides
+            if (parent[w] > qi) atomicMin(&parent[w], qi);
+        }
     }
 }
 
-__global__ __launch_bounds__(kBlock) void level_keys_kernel(const uint32_t* __restrict__ next_list,
-                                                            uint32_t m,
-                                                            const uint32_t* __restrict__ parent,
-                                                            const uint32_t* __restrict__ degrank,
-                                                            uint64_t* __restrict__ keys)
+// Whether w, a neighbor of the frontier node u with queue index qi, is placed by it.  Only a root has
+// its own index for a parent.
+__device__ inline bool is_child(const uint32_t* __restrict__ parent, uint32_t w, uint32_t u, uint32_t qi)
 {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= m) return;
-    const uint32_t w = next_list[i];
-    keys[i] = ((uint64_t)parent[w] << 32) | degrank[w];
+    return w != u && parent[w] == qi;
+}
+
+// Next-level nodes of every frontier node.
+__global__ __launch_bounds__(kBlock) void wide_count_kernel(
+    const int64_t* __restrict__ rowptr, const uint32_t* __restrict__ col,
+    const uint32_t* __restrict__ order, const WideState* __restrict__ st,
+    const uint32_t* __restrict__ parent, uint32_t* __restrict__ cnt, uint32_t* __restrict__ many)
+{
+    const WideState a = *st;
+    if (a.stop != kWideGo) return;
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    for (uint32_t i = blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6); i < a.f_count;
+         i += gridDim.x * (kBlock / kWave)) {
+        const uint32_t qi = a.f_begin + i;
+        const uint32_t u = order[qi];
+        const int64_t e0 = rowptr[u], e1 = rowptr[u + 1];
+        uint32_t c = 0;
+        for (int64_t e = e0; e < e1; e += kWave)
+            c += (uint32_t)__popcll(__ballot(e + lane < e1 && is_child(parent, col[e + lane], u, qi)));
+        if (lane == 0) {
+            cnt[i] = c;
+            if (c > (uint32_t)kMostChildren) atomicOr(many, 1u);
+        }
+    }
+}
+
+// Exclusive prefix sums of the counts, and the state after the level.  One workgroup.
+__global__ __launch_bounds__(kScanThreads) void wide_scan_kernel(
+    const WideState* __restrict__ st, WideState* __restrict__ next, const uint32_t* __restrict__ cnt,
+    uint32_t* __restrict__ off, const uint32_t* __restrict__ many)
+{
+    __shared__ uint32_t sums[kScanThreads / kWave];
+    const WideState a = *st;
+    const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid >> 6;
+    if (a.stop != kWideGo) {
+        if (tid == 0) *next = a;
+        return;
+    }
+    uint32_t run = 0;
+    for (uint32_t i0 = 0; i0 < a.f_count; i0 += kScanThreads * kScanPer) {
+        const uint32_t first = i0 + tid * kScanPer;
+        uint32_t v[kScanPer], mine = 0;
+#pragma unroll
+        for (int j = 0; j < kScanPer; ++j) {
+            v[j] = first + j < a.f_count ? cnt[first + j] : 0;
+            mine += v[j];
+        }
+        uint32_t inc = mine;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const uint32_t t = (uint32_t)__shfl_up((int)inc, o, kWave);
+            if (lane >= (uint32_t)o) inc += t;
+        }
+        if (lane == kWave - 1) sums[wv] = inc;
+        __syncthreads();
+        uint32_t before = run, total = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < kScanThreads / kWave; ++k) {
+            const uint32_t x = sums[k];
+            if (k < wv) before += x;
+            total += x;
+        }
+        __syncthreads();
+        before += inc - mine;
+#pragma unroll
+        for (int j = 0; j < kScanPer; ++j) {
+            if (first + j < a.f_count) off[first + j] = before;
+            before += v[j];
+        }
+        run += total;
+    }
+    if (tid == 0) {
+        WideState b;
+        if (*many) {
+            b = a;
+            b.m = run;
+            b.stop = kWideSort;
+        } else {
+            b.f_begin = a.count;
+            b.f_count = run;
+            b.count = a.count + run;
+            b.m = 0;
+            b.stop = run == 0 ? kWideEnd : run <= (uint32_t)kNarrowFrontier ? kWideNarrow : kWideGo;
+        }
+        *next = b;
+    }
+}
+
+// Every frontier node places its next-level nodes in their (degree, id) order.
+__global__ __launch_bounds__(kBlock) void wide_place_kernel(
+    const int64_t* __restrict__ rowptr, const uint32_t* __restrict__ col,
+    const uint32_t* __restrict__ bydeg, const uint32_t* __restrict__ degrank, uint32_t* order,
+    const WideState* __restrict__ st, const WideState* __restrict__ next,
+    const uint32_t* __restrict__ parent, const uint32_t* __restrict__ cnt,
+    const uint32_t* __restrict__ off, uint32_t* __restrict__ cm_idx)
+{
+    __shared__ uint32_t ranks[kBlock / kWave][kMostChildren];
+    const WideState a = *st;
+    if (a.stop != kWideGo || next->stop == kWideSort) return;
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    volatile uint32_t* const mine = ranks[threadIdx.x >> 6];
+    for (uint32_t i = blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6); i < a.f_count;
+         i += gridDim.x * (kBlock / kWave)) {
+        const uint32_t c = cnt[i];  // at most kMostChildren
+        if (c == 0) continue;
+        const uint32_t qi = a.f_begin + i;
+        const uint32_t u = order[qi];
+        const int64_t e0 = rowptr[u], e1 = rowptr[u + 1];
+        uint32_t found = 0;
+        for (int64_t e = e0; e < e1 && found < c; e += kWave) {
+            const uint32_t w = e + lane < e1 ? col[e + lane] : u;
+            const bool child = is_child(parent, w, u, qi);
+            const uint64_t m = __ballot(child);
+            if (child) mine[found + __popcll(m & ((1ull << lane) - 1))] = degrank[w];
+            found += (uint32_t)__popcll(m);
+        }
+        __builtin_amdgcn_wave_barrier();  // LDS operations of a wavefront complete in order
+        const uint32_t key = lane < c ? mine[lane] : 0;
+        uint32_t rank = 0;
+        for (uint32_t j = 0; j < c; ++j) rank += mine[j] < key ? 1u : 0u;
+        if (lane < c) {
+            const uint32_t w = bydeg[key], at = a.count + off[i] + rank;
+            order[at] = w;
+            cm_idx[w] = at;
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// A level with a hub: keys (frontier node, rank in the (degree, id) order) of its nodes for the
+// radix sort.
+__global__ __launch_bounds__(kBlock) void level_keys_kernel(
+    const int64_t* __restrict__ rowptr, const uint32_t* __restrict__ col,
+    const uint32_t* __restrict__ order, uint32_t f_begin, uint32_t f_count,
+    const uint32_t* __restrict__ parent, const uint32_t* __restrict__ degrank,
+    const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ off, int rank_bits,
+    uint64_t* __restrict__ keys)
+{
+    const uint32_t i = blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6);
+    if (i >= f_count) return;
+    const uint32_t c = cnt[i];
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const uint32_t qi = f_begin + i;
+    const uint32_t u = order[qi];
+    const int64_t e0 = rowptr[u], e1 = rowptr[u + 1];
+    uint32_t found = 0;
+    for (int64_t e = e0; e < e1 && found < c; e += kWave) {
+        const uint32_t w = e + lane < e1 ? col[e + lane] : u;
+        const bool child = is_child(parent, w, u, qi);
+        const uint64_t m = __ballot(child);
+        if (child)
+            keys[off[i] + found + __popcll(m & ((1ull << lane) - 1))] =
+                (uint64_t)i << rank_bits | degrank[w];
+        found += (uint32_t)__popcll(m);
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void level_assign_kernel(const uint64_t* __restrict__ sorted,
-                                                              uint32_t m,
+                                                              uint32_t m, int rank_bits,
                                                               const uint32_t* __restrict__ bydeg,
                                                               uint32_t base,
                                                               uint32_t* __restrict__ cm_idx,
@@ -376,7 +554,7 @@ __global__ __launch_bounds__(kBlock) void level_assign_kernel(const uint64_t* __
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= m) return;
-    const uint32_t w = bydeg[(uint32_t)sorted[i]];
+    const uint32_t w = bydeg[sorted[i] & ((1ull << rank_bits) - 1)];
     cm_idx[w] = base + i;
     order[base + i] = w;
 }
@@ -476,7 +654,8 @@ int mixgcn_reorder_rcm(const mixgcn_graph* g, uint32_t* pos, void* stream)
     const Csr& m = g->fwd;
     DevMem mem(s);
     uint64_t *keys, *alt;
-    uint32_t *bydeg, *degrank, *single, *cm_idx, *parent, *order, *next_list, *counters;
+    uint32_t *bydeg, *degrank, *single, *cm_idx, *parent, *order, *cnt, *off, *many;
+    WideState* wide;
     void* tmp;
     MIXGCN_TRY(mem.alloc(&keys, n));
     MIXGCN_TRY(mem.alloc(&alt, n));
@@ -486,8 +665,10 @@ int mixgcn_reorder_rcm(const mixgcn_graph* g, uint32_t* pos, void* stream)
     MIXGCN_TRY(mem.alloc(&cm_idx, n));
     MIXGCN_TRY(mem.alloc(&parent, n));
     MIXGCN_TRY(mem.alloc(&order, n));
-    MIXGCN_TRY(mem.alloc(&next_list, n));
-    MIXGCN_TRY(mem.alloc(&counters, 2));  // [0] next-level count
+    MIXGCN_TRY(mem.alloc(&cnt, n));
+    MIXGCN_TRY(mem.alloc(&off, n));
+    MIXGCN_TRY(mem.alloc(&many, 1));
+    MIXGCN_TRY(mem.alloc(&wide, 2));
     const size_t tmp_bytes = sort_tmp_bytes(n) > scan_tmp_bytes(n) ? sort_tmp_bytes(n) : scan_tmp_bytes(n);
     {
         char* t;
@@ -498,11 +679,11 @@ int mixgcn_reorder_rcm(const mixgcn_graph* g, uint32_t* pos, void* stream)
     // global (degree, id) order
     hipLaunchKernelGGL(degree_keys_kernel, dim3(blocks_for(n)), dim3(kBlock), 0, s, m.rowptr, n, keys);
     uint64_t* sorted = nullptr;
-    const uint64_t max_deg_key = ((uint64_t)(m.nnz > 0 ? m.nnz : 1) << 32) | 0xFFFFFFFFull;
-    MIXGCN_TRY(radix_sort_u64(keys, alt, n, bits_for(max_deg_key), &sorted, tmp, s));
+    MIXGCN_TRY(radix_sort_u64(keys, alt, n, bits_for(n), &sorted, tmp, s));  // a degree is at most n
     hipLaunchKernelGGL(rank_kernel, dim3(blocks_for(n)), dim3(kBlock), 0, s, sorted, m.rowptr, m.col,
                        n, bydeg, degrank, single, cm_idx, parent);
 
+    const int id_bits = bits_for(n - 1);
     // The resident workgroup walks narrow levels and finds roots until it meets a level too
     // wide for it; the host then runs that one level with the grid-wide kernels and hands back.
     RcmState* d_state;
@@ -517,36 +698,43 @@ int mixgcn_reorder_rcm(const mixgcn_graph* g, uint32_t* pos, void* stream)
         if (st.done) break;
         if (st.f_count == 0 || st.count >= n + 1)
             return fail(MIXGCN_EHIP, "reorder_rcm: the level walk stopped without a frontier");
-        // wide levels, until the frontier is narrow again or the component ends
-        uint32_t count = st.count, f_begin = st.f_begin, f_count = st.f_count;
-        bool first = true;  // the level the workgroup refused is run here whatever its node count
-        while (f_count > 0 && (first || f_count > (uint32_t)kNarrowFrontier)) {
-            first = false;
-            MIXGCN_HIP_TRY(hipMemsetAsync(counters, 0, 4, s));
-            hipLaunchKernelGGL(expand_kernel, dim3((unsigned)ceil_div(f_count, kBlock / kWave)),
-                               dim3(kBlock), 0, s, m.rowptr, m.col, order, f_begin, f_count, cm_idx,
-                               parent, next_list, counters);
-            uint32_t mcount = 0;
-            MIXGCN_TRY(read_u32(counters, &mcount, s));
-            if (mcount == 0) {
-                f_count = 0;
+        // wide levels, until the frontier is narrow again or the component ends; the level the
+        // workgroup refused is run here whatever its node count
+        WideState w = {st.f_begin, st.f_count, st.count, 0, kWideGo};
+        MIXGCN_HIP_TRY(hipMemcpyAsync(wide, &w, sizeof(w), hipMemcpyHostToDevice, s));
+        int at = 0;  // slot of the current state
+        for (int levels = 1;; levels = levels < 16 ? 2 * levels : 16) {
+            for (int l = 0; l < levels; ++l, at ^= 1) {
+                const dim3 grid(kWideBlocks), block(kBlock);
+                hipLaunchKernelGGL(wide_offer_kernel, grid, block, 0, s, m.rowptr, m.col, order,
+                                   wide + at, parent, many);
+                hipLaunchKernelGGL(wide_count_kernel, grid, block, 0, s, m.rowptr, m.col, order,
+                                   wide + at, parent, cnt, many);
+                hipLaunchKernelGGL(wide_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, wide + at,
+                                   wide + (at ^ 1), cnt, off, many);
+                hipLaunchKernelGGL(wide_place_kernel, grid, block, 0, s, m.rowptr, m.col, bydeg, degrank,
+                                   order, wide + at, wide + (at ^ 1), parent, cnt, off, cm_idx);
+            }
+            MIXGCN_HIP_TRY(hipMemcpyAsync(&w, wide + at, sizeof(w), hipMemcpyDeviceToHost, s));
+            MIXGCN_HIP_TRY(hipStreamSynchronize(s));
+            if (w.stop == kWideSort) {
+                hipLaunchKernelGGL(level_keys_kernel, dim3((unsigned)ceil_div(w.f_count, kBlock / kWave)),
+                                   dim3(kBlock), 0, s, m.rowptr, m.col, order, w.f_begin, w.f_count,
+                                   parent, degrank, cnt, off, id_bits, keys);
+                const int key_bits = id_bits + bits_for(w.f_count - 1);
+                MIXGCN_TRY(radix_sort_u64(keys, alt, w.m, key_bits, &sorted, tmp, s));
+                hipLaunchKernelGGL(level_assign_kernel, dim3(blocks_for(w.m)), dim3(kBlock), 0, s, sorted,
+                                   w.m, id_bits, bydeg, w.count, cm_idx, order);
+                w = {w.count, w.m, w.count + w.m, 0, kWideGo};
+                if (w.f_count <= (uint32_t)kNarrowFrontier) break;
+                MIXGCN_HIP_TRY(hipMemcpyAsync(wide + at, &w, sizeof(w), hipMemcpyHostToDevice, s));
+            } else if (w.stop != kWideGo) {
                 break;
             }
-            hipLaunchKernelGGL(level_keys_kernel, dim3(blocks_for(mcount)), dim3(kBlock), 0, s,
-                               next_list, mcount, parent, degrank, keys);
-            const uint64_t max_key = ((uint64_t)(count - 1) << 32) | (uint64_t)(n - 1);
-            // the low word only needs the bits of n - 1, the high word those of count - 1, but
-            // the sort works on a contiguous bit range: [0, 32 + bits(count - 1))
-            MIXGCN_TRY(radix_sort_u64(keys, alt, mcount, bits_for(max_key), &sorted, tmp, s));
-            hipLaunchKernelGGL(level_assign_kernel, dim3(blocks_for(mcount)), dim3(kBlock), 0, s,
-                               sorted, mcount, bydeg, count, cm_idx, order);
-            f_begin = count;
-            f_count = mcount;
-            count += mcount;
         }
-        st.count = count;
-        st.f_begin = f_begin;
-        st.f_count = f_count;
+        st.count = w.count;
+        st.f_begin = w.f_begin;
+        st.f_count = w.f_count;  // 0: the component is complete
         MIXGCN_HIP_TRY(hipMemcpyAsync(d_state, &st, sizeof(st), hipMemcpyHostToDevice, s));
     }
     if (st.count != n) return fail(MIXGCN_EHIP, "reorder_rcm: not every node was placed");
