@@ -42,25 +42,52 @@ __global__ __launch_bounds__(kBlock) void emit_keys_kernel(
     }
 }
 
-__device__ inline bool is_first_of_run(const uint64_t* keys, int64_t i, uint64_t drop)
+// Keys of a wavefront for the removal of duplicates: kCompactItems * 64 consecutive ones, 64 at a time,
+// with their neighbors on both sides (kNoKey past the ends).
+constexpr uint64_t kNoKey = ~0ull;
+struct WaveKeys {
+    uint64_t key[kCompactItems];
+    uint64_t prev[kCompactItems];
+    uint64_t first[kCompactItems];  // lanes that hold the first key of a run of equal ones
+    uint32_t count;                 // runs that start here
+};
+
+__device__ inline void load_wave_keys(const uint64_t* __restrict__ keys, int64_t n_keys, uint64_t drop,
+                                      int64_t base, int lane, WaveKeys& k)
 {
-    const uint64_t k = keys[i];
-    return k < drop && (i == 0 || keys[i - 1] != k);
+#pragma unroll
+    for (int j = 0; j < kCompactItems; ++j) {
+        const int64_t i = base + j * kWave + lane;
+        k.key[j] = i < n_keys ? keys[i] : kNoKey;
+    }
+    uint64_t before = base > 0 && base <= n_keys ? keys[base - 1] : kNoKey;
+    k.count = 0;
+#pragma unroll
+    for (int j = 0; j < kCompactItems; ++j) {
+        const uint64_t left = __shfl_up((unsigned long long)k.key[j], 1, kWave);
+        k.prev[j] = lane == 0 ? before : left;
+        before = __shfl((unsigned long long)k.key[j], kWave - 1, kWave);
+        k.first[j] = __ballot(k.key[j] < drop && k.key[j] != k.prev[j]);
+        k.count += (uint32_t)__popcll(k.first[j]);
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void unique_count_kernel(const uint64_t* __restrict__ keys,
                                                               int64_t n_keys, uint64_t drop,
                                                               uint32_t* __restrict__ tile_cnt)
 {
-    __shared__ uint64_t lds[4];
-    const int64_t base = (int64_t)blockIdx.x * kCompactTile + (int64_t)threadIdx.x * kCompactItems;
-    uint64_t c = 0;
-#pragma unroll
-    for (int j = 0; j < kCompactItems; ++j)
-        if (base + j < n_keys && is_first_of_run(keys, base + j, drop)) ++c;
-    uint64_t total;
-    block_exclusive_scan_u64(c, &total, lds);
-    if (threadIdx.x == 0) tile_cnt[blockIdx.x] = (uint32_t)total;
+    __shared__ uint32_t count[kBlock / kWave];
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x >> 6;
+    WaveKeys k;
+    load_wave_keys(keys, n_keys, drop, (int64_t)blockIdx.x * kCompactTile + w * kCompactItems * kWave,
+                   lane, k);
+    if (lane == 0) count[w] = k.count;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t total = 0;
+        for (int i = 0; i < kBlock / kWave; ++i) total += count[i];
+        tile_cnt[blockIdx.x] = total;
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void fill_i64_kernel(int64_t* p, int64_t n, int64_t v)
@@ -69,50 +96,54 @@ __global__ __launch_bounds__(kBlock) void fill_i64_kernel(int64_t* p, int64_t n,
     if (i < n) p[i] = v;
 }
 
-// Writes col/cv for every distinct key and rowptr[q] = (index of the first entry with row >= q)
-// for every q up to the last non-empty row; later rows keep the preset value nnz.
+// Writes col/cv for every distinct key, with the mark of the last entry of a row, and rowptr[q] =
+// (index of the first entry with row >= q) for every q up to the last non-empty row; later rows
+// keep the preset value nnz.  Reports empty rows.  Bound by memory.  Consecutive lanes take consecutive
+// keys: 33.5 M keys 0.13 ms (with eight keys per lane and the marks in a pass of their own 0.70).
 __global__ __launch_bounds__(kBlock) void unique_fill_kernel(
-    const uint64_t* __restrict__ keys, int64_t n_keys, uint64_t drop, int bits,
+    const uint64_t* __restrict__ keys, int64_t n_keys, uint64_t drop, int bits, uint32_t n,
     const uint64_t* __restrict__ tile_off, uint32_t* __restrict__ col,
-    uint2* __restrict__ cv, int64_t* __restrict__ rowptr)
+    uint2* __restrict__ cv, int64_t* __restrict__ rowptr, uint32_t* __restrict__ any_empty)
 {
-    __shared__ uint64_t lds[4];
-    const int64_t base = (int64_t)blockIdx.x * kCompactTile + (int64_t)threadIdx.x * kCompactItems;
-    bool f[kCompactItems];
-    uint64_t c = 0;
-#pragma unroll
-    for (int j = 0; j < kCompactItems; ++j) {
-        f[j] = (base + j < n_keys) && is_first_of_run(keys, base + j, drop);
-        c += f[j] ? 1 : 0;
-    }
-    uint64_t total;
-    uint64_t pos = block_exclusive_scan_u64(c, &total, lds) + tile_off[blockIdx.x];
+    __shared__ uint32_t count[kBlock / kWave];
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x >> 6;
+    const int64_t base = (int64_t)blockIdx.x * kCompactTile + w * kCompactItems * kWave;
+    WaveKeys k;
+    load_wave_keys(keys, n_keys, drop, base, lane, k);
+    const int64_t after = base + kCompactItems * kWave;
+    uint64_t next_step = after < n_keys ? keys[after] : kNoKey;  // the key behind the last step
+    if (lane == 0) count[w] = k.count;
+    __syncthreads();
+    uint64_t pos = tile_off[blockIdx.x];  // runs that start before the wave's keys
+    for (int i = 0; i < w; ++i) pos += count[i];
     const uint64_t cmask = (1ull << bits) - 1;
+    const uint64_t upto = ~0ull >> (kWave - 1 - lane);  // this lane and those before it
 #pragma unroll
     for (int j = 0; j < kCompactItems; ++j) {
-        if (!f[j]) continue;
-        const int64_t i = base + j;
-        const uint64_t k = keys[i];
-        const uint32_t c32 = (uint32_t)(k & cmask);
-        col[pos] = c32;
-        cv[pos] = make_uint2(c32, 0u);
-        const int64_t row = (int64_t)(k >> bits);
-        const int64_t prev = (i == 0) ? -1 : (int64_t)(keys[i - 1] >> bits);
-        for (int64_t q = prev + 1; q <= row; ++q) rowptr[q] = (int64_t)pos;
-        ++pos;
+        const uint64_t key = k.key[j];
+        const uint64_t right = __shfl_down((unsigned long long)key, 1, kWave);
+        const uint64_t behind =
+            j + 1 < kCompactItems ? __shfl((unsigned long long)k.key[j + 1 < kCompactItems ? j + 1 : j], 0, kWave)
+                                  : next_step;
+        const uint64_t next = lane == kWave - 1 ? behind : right;
+        if (key < drop) {
+            const int64_t row = (int64_t)(key >> bits);
+            const uint64_t at = pos + __popcll(k.first[j] & upto) - 1;  // index of the key's run
+            if ((k.first[j] >> lane) & 1) {
+                const int64_t prev = k.prev[j] == kNoKey ? -1 : (int64_t)(k.prev[j] >> bits);
+                for (int64_t q = prev + 1; q <= row; ++q) rowptr[q] = (int64_t)at;
+                if (row > prev + 1) *any_empty = 1u;
+            }
+            if (key != next) {  // the last key of the run writes the entry
+                const bool last = next >= drop || (int64_t)(next >> bits) != row;
+                const uint32_t c = (uint32_t)(key & cmask);
+                col[at] = c;
+                cv[at] = make_uint2(last ? c | kEntryEndBit : c, 0u);
+                if (next >= drop && row + 1 < (int64_t)n) *any_empty = 1u;
+            }
+        }
+        pos += __popcll(k.first[j]);
     }
-}
-
-// Marks the last stored entry of every non-empty row in cv and reports empty rows.
-__global__ __launch_bounds__(kBlock) void mark_row_ends_kernel(const int64_t* __restrict__ rowptr,
-                                                               uint32_t n, uint2* cv,
-                                                               uint32_t* __restrict__ any_empty)
-{
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n) return;
-    const int64_t a = rowptr[r], b = rowptr[r + 1];
-    if (b > a) cv[b - 1].x |= kEntryEndBit;
-    else atomicOr(any_empty, 1u);
 }
 
 // grp_row[g] = the row that holds stored entry g * kGroupNnz (last row with rowptr <= that).
@@ -286,7 +317,7 @@ int csr_from_edges(const uint32_t* d_src, const uint32_t* d_dst, uint64_t n_edge
         if ((rc = dmalloc(&c.col, (size_t)nnz, s)) != MIXGCN_OK) break;
         if ((rc = dmalloc(&c.cv, (size_t)c.nnz_padded, s)) != MIXGCN_OK) break;
         if ((rc = dmalloc(&c.grp_row, (size_t)c.n_groups + 1, s)) != MIXGCN_OK) break;
-        if (hipMemsetAsync(c.cv, 0, (size_t)c.nnz_padded * 8, s) != hipSuccess) {
+        if (hipMemsetAsync(c.cv + nnz, 0, (size_t)(c.nnz_padded - nnz) * 8, s) != hipSuccess) {
             rc = fail(MIXGCN_EHIP, "hipMemsetAsync(cv)");
             break;
         }
@@ -294,10 +325,8 @@ int csr_from_edges(const uint32_t* d_src, const uint32_t* d_dst, uint64_t n_edge
                            dim3(kBlock), 0, s, c.rowptr, (int64_t)n + 1, nnz);
         if (n_keys > 0)
             hipLaunchKernelGGL(unique_fill_kernel, dim3((unsigned)n_ctiles), dim3(kBlock), 0, s,
-                               sorted, n_keys, drop, bits, tile_off, c.col, c.cv, c.rowptr);
-        if (n > 0)
-            hipLaunchKernelGGL(mark_row_ends_kernel, dim3((unsigned)ceil_div(n, kBlock)),
-                               dim3(kBlock), 0, s, c.rowptr, n, c.cv, t.flags + 1);
+                               sorted, n_keys, drop, bits, n, tile_off, c.col, c.cv, c.rowptr,
+                               t.flags + 1);
         hipLaunchKernelGGL(group_rows_kernel, dim3((unsigned)ceil_div(c.n_groups + 1, kBlock)),
                            dim3(kBlock), 0, s, c.rowptr, n, nnz, c.n_groups, c.grp_row);
         c.h_rowptr.resize((size_t)n + 1);
@@ -308,7 +337,7 @@ int csr_from_edges(const uint32_t* d_src, const uint32_t* d_dst, uint64_t n_edge
             rc = fail(MIXGCN_EHIP, "CSR fill failed");
             break;
         }
-        c.has_empty_rows = h_flags[1] != 0;
+        c.has_empty_rows = h_flags[1] != 0 || (nnz == 0 && n > 0);
     } while (0);
     if (rc != MIXGCN_OK) {
         (void)hipStreamSynchronize(s);  // the arrays may have work queued on them
