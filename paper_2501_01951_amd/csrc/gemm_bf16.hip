@@ -879,7 +879,7 @@ int launch_update_bf16(int op, const uint16_t* A, int64_t lda, const void* B_, i
         if (timer) MIXGCN_TRY(timer->end(s));
     } else if (op == MIXGCN_OP_WGRAD) {
         // C[k x m] = beta C + A[n x k]^T (B (.) mask)[n x m]: whole steps of 32 rows with the
-        // transposing LDS reads, the last n % 32 rows with the scattering kernel, added on top
+        // transposing LDS reads, the last n % 32 rows with the scattering kernel
         const uint16_t* B = (const uint16_t*)B_;
         float* C = (float*)C_;
         const bool wide = m > 64;
@@ -889,15 +889,32 @@ int launch_update_bf16(int op, const uint16_t* A, int64_t lda, const void* B_, i
         const int64_t cells = (int64_t)k * m;
         const bool pitches_ok = lda < (1 << 25) && ldb < (1 << 25) && ldr < (1 << 25);
         const int64_t n_main = pitches_ok ? n - n % BKB : 0;
+        struct Part {
+            int64_t rows = 0, slabs = 0, rows_per_slab = BKB;
+        };
+        auto plan = [&](int64_t rows) {
+            Part p;
+            p.rows = rows;
+            p.rows_per_slab = ceil_div(ceil_div(rows, wgrad_slabs(rows, tiles, 2048)), BKB) * BKB;
+            if (p.rows_per_slab < BKB) p.rows_per_slab = BKB;
+            p.slabs = rows > 0 ? ceil_div(rows, p.rows_per_slab) : 1;
+            return p;
+        };
+        Part main_part, rest;
+        if (n_main > 0) main_part = plan(n_main);
+        if (n_main < n || n == 0) rest = plan(n - n_main);
+        // One reduction adds the slabs of both where they fit the buffer's default size together (a
+        // call recorded into a graph must not make it grow): six products over 100003 rows take 11 us
+        // less than with a reduction of their own for the last 3 rows.
+        const int64_t all = main_part.slabs + rest.slabs;
+        const bool together = (size_t)all * cells * sizeof(float) <= ((size_t)64 << 20);
+        const int64_t most = main_part.slabs > rest.slabs ? main_part.slabs : rest.slabs;
+        void* scratch = nullptr;
+        MIXGCN_TRY(get_scratch(0, (size_t)(together ? all : most) * cells * sizeof(float), &scratch));
+        float* const P0 = (float*)scratch;
         if (timer) MIXGCN_TRY(timer->begin(kTimeUpdateWgrad, s));
-        auto part = [&](bool transposing_reads, int64_t row0, int64_t rows, float beta_part) -> int {
-            int64_t n_slabs = wgrad_slabs(rows, tiles, 2048);
-            int64_t rows_per_slab = ceil_div(ceil_div(rows, n_slabs), BKB) * BKB;
-            if (rows_per_slab < BKB) rows_per_slab = BKB;
-            n_slabs = rows > 0 ? ceil_div(rows, rows_per_slab) : 1;
-            void* scratch = nullptr;
-            MIXGCN_TRY(get_scratch(0, (size_t)n_slabs * cells * sizeof(float), &scratch));
-            float* P = (float*)scratch;
+        auto slabs = [&](bool transposing_reads, int64_t row0, const Part& p, float* P) {
+            const int64_t rows = p.rows, rows_per_slab = p.rows_per_slab, n_slabs = p.slabs;
             const unsigned grid = (unsigned)(n_slabs * tiles);
             const uint16_t* a = A + row0 * lda;
             const uint16_t* b = B + row0 * ldb;
@@ -919,10 +936,17 @@ int launch_update_bf16(int op, const uint16_t* A, int64_t lda, const void* B_, i
             else MIXGCN_WGRAD_SHAPES(wgrad_bf16_kernel);
 #undef MIXGCN_WGRAD_SHAPES
 #undef MIXGCN_WGRAD
-            return launch_wgrad_reduce(P, n_slabs, cells, m, C, ldc, beta_part, s);
         };
-        if (n_main > 0) MIXGCN_TRY(part(true, 0, n_main, beta));
-        if (n_main < n || n == 0) MIXGCN_TRY(part(false, n_main, n - n_main, n_main > 0 ? 1.f : beta));
+        if (main_part.slabs) {
+            slabs(true, 0, main_part, P0);
+            if (!together) {
+                MIXGCN_TRY(launch_wgrad_reduce(P0, main_part.slabs, cells, m, C, ldc, beta, s));
+                beta = 1.f;
+            }
+        }
+        if (rest.slabs) slabs(false, n_main, rest, together ? P0 + main_part.slabs * cells : P0);
+        if (together || rest.slabs)
+            MIXGCN_TRY(launch_wgrad_reduce(P0, together ? all : rest.slabs, cells, m, C, ldc, beta, s));
         if (timer) MIXGCN_TRY(timer->end(s));
     } else {
         return fail(MIXGCN_EINVAL, "update: unknown op");
