@@ -77,6 +77,9 @@ struct Band {
 struct RowGroups {
     std::vector<Band> bands;  // empty: not built
     uint32_t* src = nullptr;  // [nnz] entry indices band by band (null: one band)
+    // estimated cost of a gathered line, in units of one that misses the L2: with the columns in one
+    // band, and in these
+    float line_cost = 0, band_cost = 0;
 };
 
 struct Csr {
@@ -205,6 +208,7 @@ int rowgroups_alloc_transpose(RowGroups* g, hipStream_t s);
 int rowgroups_fill(const Csr& m, const RowGroups& g, const float* dinv, int mode, float eps,
                    int swapped, bool transposed, float* val, uint2* cv, hipStream_t s);
 void rowgroups_free(RowGroups* g);
+bool rowgroups_pay(const RowGroups& g, int64_t nnz, int64_t n, int dtype, int width);
 // Bytes of scratch that a pass of `width` columns over the n rows uses.
 size_t rowgroups_scratch(const RowGroups& g, int64_t n, int dtype, int width);
 // One pass over all rows: columns [c0, c0 + width), of which [c_lo, c_hi) are written.

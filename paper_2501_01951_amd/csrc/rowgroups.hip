@@ -190,9 +190,11 @@ double lru_misses(const Popular* c, int n, double lines)
 // units of a gather that misses (18 ps per line over the chip), a hit measured 0.3 to 0.38 and a row
 // that a later band adds to 3 to 6 lines: its old line is read with a miss that the gathers queued
 // behind it wait for, and written again.
-int plan_bands(const unsigned long long* rows, const unsigned long long* entries, double n, double nnz)
+constexpr double kHit = 0.35, kLines = 29000;
+int plan_bands(const unsigned long long* rows, const unsigned long long* entries, double n, double nnz,
+               RowGroups* out)
 {
-    constexpr double kHit = 0.35, kInBand = 0.03, kRow = 5, kLines = 29000;
+    constexpr double kInBand = 0.03, kRow = 5;
     int best = 1;
     double best_cost = 0;
     for (int k = 1; k <= kMostBands && (k - 1) * (double)kBandColumns < n; ++k) {
@@ -230,10 +232,13 @@ int plan_bands(const unsigned long long* rows, const unsigned long long* entries
         // where popular rows prefer popular columns (R-MAT) it promises up to 15 % that are not
         // there.  Uniform columns, 100 k nodes, 100 entries per row: 566 -> 373 us with 4 bands
         // (estimate 0.81 -> 0.51); power law, 233 k nodes, 492 per row: 7.2 -> 3.5 ms with 9.
-        if (k == 1) best_cost = 0.8 * cost;
-        else if (cost < best_cost) {
+        if (k == 1) {
+            out->line_cost = (float)cost;
+            best_cost = 0.8 * cost;
+        } else if (cost < best_cost) {
             best_cost = cost;
             best = k;
+            out->band_cost = (float)cost;
         }
     }
     return best;
@@ -894,7 +899,10 @@ int build_bands(const Csr& m, uint32_t n, bool symmetric, RowGroups* out, hipStr
         unsigned long long h[2 * kBins];
         MIXGCN_HIP_TRY(hipMemcpyAsync(h, t.hist, sizeof(h), hipMemcpyDeviceToHost, s));
         MIXGCN_HIP_TRY(hipStreamSynchronize(s));
-        n_bands = plan_bands(h, h + kBins, (double)n, (double)m.nnz);
+        n_bands = plan_bands(h, h + kBins, (double)n, (double)m.nnz, out);
+    } else {  // columns of equal popularity
+        const double miss = (double)n > kLines ? 1 - kLines / (double)n : 0;
+        out->line_cost = (float)(miss + (1 - miss) * kHit);
     }
     out->bands.resize((size_t)n_bands);
     if (n_bands == 1) return build_band(m.rowptr, n, m.nnz, nullptr, 0, 1, &out->bands[0], s);
@@ -1031,6 +1039,29 @@ int launch_band(const Band& g, const uint2* ent, int64_t n_nodes, const void* H,
 }
 
 }  // namespace
+
+// Whether a pass of `width` columns over all rows is faster on the groups than with the entry-balanced
+// kernel, by the estimates of plan_bands (line_cost, band_cost; 18 ps each).  Measured in both ways on
+// R-MAT, uniform and power-law graphs of 150 k to 2.45 M nodes and 12 to 90 entries per row, at 16 to
+// 256 columns:
+//  - One band.  Where gathers that miss bound both kernels, the groups cost 1 to 5 % more: their
+//    padding, and eight output rows per close (2.45 M nodes, 50 per row, 256 bf16 columns: 5.96
+//    entry-balanced, 6.06 ms).  The entry-balanced kernel is bound by closing rows instead, about
+//    0.2 ns (narrow passes 0.3, bf16 0.4) per row and slice plus 3.6 ps per line, where rows are
+//    short or gathers hit (1 M nodes, 25 per row, 256 bf16 columns: 1.42 ms, groups 1.14).
+//  - Several bands.  What they save is of wide fp32 passes.  Against those, bf16 rows waiting in
+//    fp32 between bands cost 1.3 times as much, half lines 1.65 times: half of a band's L2 stays
+//    empty (power law, 150 k nodes, 90 per row: 128 fp32 columns 737 -> 567 us, but 128 bf16 columns
+//    375 -> 392 and 16 fp32 columns 151 -> 187).
+bool rowgroups_pay(const RowGroups& g, int64_t nnz, int64_t n, int dtype, int width)
+{
+    const bool bf16 = dtype == MIXGCN_BF16;
+    const bool narrow = width * (bf16 ? 2 : 4) <= 64;
+    if (g.bands.size() > 1) return g.band_cost * (narrow ? 1.65f : bf16 ? 1.3f : 1.f) < g.line_cost;
+    const double len = (double)nnz / (double)(n > 0 ? n : 1);
+    const double close = narrow ? 300 : bf16 ? 400 : 200;  // ps per row and slice
+    return 18.0 * g.line_cost * len < 1.1 * (close + 3.6 * len);
+}
 
 // Piece slots, and where bf16 rows wait between bands.
 size_t rowgroups_scratch(const RowGroups& g, int64_t n, int dtype, int width)

@@ -81,3 +81,35 @@ def test_dense_graph_whose_columns_form_bands(mg, mean):
     for f, bf in ((16, False), (40, False), (72, True)):
         check(mg, g, og, f, bf, mean, f"bands n={n} nnz={og.nnz}")
     g.free()
+
+
+@pytest.mark.parametrize("mean_len", [85, 105, 160, 200])
+def test_both_sides_of_the_dispatch(mg, mean_len):
+    """28 k columns fit an L2, so the groups pay up to about 93 (fp32), 140 (narrow passes) and 188 (bf16)
+    entries per row; all of these have more than 4 M entries or come close, and rows in pieces."""
+    n = 28_000
+    lens = np.full(n, 3, dtype=np.int64)
+    long_rows = np.random.default_rng(mean_len).permutation(n)[:n * (mean_len - 3) // 5000]
+    lens[long_rows] = 5000
+    src = np.repeat(np.arange(n), lens)
+    dst = (src * 7 + np.arange(len(src)) - np.repeat(np.cumsum(lens) - lens, lens)) % n
+    src, dst = src.astype(np.uint32), dst.astype(np.uint32)
+    g = mg.build_csr(dev(src.view(np.int32)), dev(dst.view(np.int32)), n, 0)
+    mg.normalize(g, mg.NORM_MEAN)
+    og = oracle.normalize_mean(oracle.build_csr(src, dst, n, False, False))
+    for f, bf in ((16, False), (33, False), (40, True)):
+        check(mg, g, og, f, bf, False, f"mean length {mean_len} nnz={og.nnz}")
+    g.free()
+
+
+def test_bands_of_narrow_and_bf16_passes(mg):
+    """Dense enough that bands pay for bf16 rows, which wait in fp32 between them, and for half lines."""
+    n, degree = 80_000, 300
+    rng = np.random.default_rng(6)
+    src, dst = (rng.integers(0, n, n * degree // 2).astype(np.uint32) for _ in range(2))
+    g = mg.build_csr(dev(src.view(np.int32)), dev(dst.view(np.int32)), n)
+    mg.normalize(g)
+    og = oracle.normalize(oracle.build_csr(src, dst, n, True, True))
+    for f, bf in ((16, False), (72, True)):
+        check(mg, g, og, f, bf, False, f"bands n={n} nnz={og.nnz}")
+    g.free()
