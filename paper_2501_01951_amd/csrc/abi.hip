@@ -271,10 +271,15 @@ int mixgcn_normalize_mode(mixgcn_graph* g, int mode, float eps, void* stream)
     // the row-piece scratch of the aggregation: sized once from the entry count, first slot here
     if (!g->agg_slot_bytes) {
         g->agg_slot_bytes = agg_scratch_bound(g->fwd.nnz);
-        for (const mixgcn::Csr* m : {&g->fwd, &g->tr}) {
-            const size_t b = rowgroups_scratch(m->groups, g->n, MIXGCN_BF16, kAggMaxPassCols);
-            if (b > g->agg_slot_bytes) g->agg_slot_bytes = b;
-        }
+        for (const mixgcn::Csr* m : {&g->fwd, &g->tr})
+            for (const int dtype : {MIXGCN_F32, MIXGCN_BF16}) {
+                const size_t b = rowgroups_scratch(m->groups, g->n, dtype, kAggMaxPassCols);
+                // Where bf16 rows wait between bands takes 1 KB per node in every stream's slot, which
+                // is not spent on fewer than 64 entries per row: 1.3 times the cost of the bands is
+                // hardly ever below that of one band there (rowgroups_pay), and a call whose slot is
+                // too small takes the entry-balanced kernel.
+                if (b <= (size_t)m->nnz * 16 + (1u << 20) && b > g->agg_slot_bytes) g->agg_slot_bytes = b;
+            }
     }
     if (!g->agg_slots[0].p)
         MIXGCN_TRY(pool_alloc_unordered((void**)&g->agg_slots[0].p, g->agg_slot_bytes));

@@ -381,8 +381,12 @@ int normalize_graph(mixgcn_graph* g, int mode, float eps, hipStream_t s)
     for (Csr* c : mats) {
         if (!c) continue;
         if (!c->val) MIXGCN_TRY(dmalloc(&c->val, (size_t)c->nnz, s));
-        if (c->groups.bands.empty() && c->nnz > 0 && c->nnz <= kMostGroupedEntries && n < kEntryColMask)
-            MIXGCN_TRY(rowgroups_build(*c, n, g->flags & MIXGCN_SYMMETRIZE, &c->groups, s));
+        if (c->groups.bands.empty() && c->nnz > 0 && c->nnz <= kMostGroupedEntries && n < kEntryColMask) {
+            // without memory for it the matrix stays with the entry-balanced kernel
+            const int rc = rowgroups_build(*c, n, g->flags & MIXGCN_SYMMETRIZE, &c->groups, s);
+            if (rc == MIXGCN_ENOMEM) (void)hipGetLastError();
+            else MIXGCN_TRY(rc);
+        }
         MIXGCN_TRY(fill_values(*c, n, g->dinv, mode, eps, c == &g->tr ? 1 : 0, false, c->val, c->cv, s));
     }
     // A symmetrised graph stores one pattern for the matrix and its transpose.  The mean
@@ -391,7 +395,14 @@ int normalize_graph(mixgcn_graph* g, int mode, float eps, hipStream_t s)
     if (mode == MIXGCN_NORM_MEAN && (g->flags & MIXGCN_SYMMETRIZE)) {
         if (!f.val_t) MIXGCN_TRY(dmalloc(&f.val_t, (size_t)f.nnz, s));
         if (!f.cv_t) MIXGCN_TRY(dmalloc(&f.cv_t, (size_t)f.nnz_padded, s));
-        MIXGCN_TRY(rowgroups_alloc_transpose(&f.groups, s));
+        const int rc = rowgroups_alloc_transpose(&f.groups, s);
+        if (rc == MIXGCN_ENOMEM) {
+            (void)hipGetLastError();
+            MIXGCN_HIP_TRY(hipDeviceSynchronize());  // work on the groups may be queued on any stream
+            rowgroups_free(&f.groups);
+        } else {
+            MIXGCN_TRY(rc);
+        }
         hipLaunchKernelGGL(copy_entries_kernel, dim3((unsigned)ceil_div(f.nnz_padded, kBlock)),
                            dim3(kBlock), 0, s, f.cv, f.cv_t, f.nnz_padded);
         MIXGCN_TRY(fill_values(f, n, g->dinv, mode, eps, 1, true, f.val_t, f.cv_t, s));
