@@ -350,9 +350,8 @@ int csr_from_edges(const uint32_t* d_src, const uint32_t* d_dst, uint64_t n_edge
 
 namespace {
 
-// Matrices of up to 2^31 entries also get the row-grouped form.  Above that the two forms together
-// (16 bytes per entry) would not leave room for the features, and a graph of that size gathers from
-// memory anyway: both kernels run at the device's random-gather rate.
+// Matrices of up to 2^31 entries may have bands.  Above that the two forms together (20 bytes per
+// entry) would not leave room for the features.
 constexpr int64_t kMostGroupedEntries = 1ll << 31;
 
 // Values of the matrix (swapped: of its transpose on the same pattern) in all stored forms.
@@ -381,11 +380,12 @@ int normalize_graph(mixgcn_graph* g, int mode, float eps, hipStream_t s)
     for (Csr* c : mats) {
         if (!c) continue;
         if (!c->val) MIXGCN_TRY(dmalloc(&c->val, (size_t)c->nnz, s));
-        if (c->groups.bands.empty() && c->nnz > 0 && c->nnz <= kMostGroupedEntries && n < kEntryColMask) {
-            // without memory for it the matrix stays with the entry-balanced kernel
+        if (!c->groups.planned && c->nnz > 0 && c->nnz <= kMostGroupedEntries && n < kEntryColMask) {
+            // without memory for them the matrix stays with the entry-balanced kernel
             const int rc = rowgroups_build(*c, n, g->flags & MIXGCN_SYMMETRIZE, &c->groups, s);
             if (rc == MIXGCN_ENOMEM) (void)hipGetLastError();
             else MIXGCN_TRY(rc);
+            c->groups.planned = true;
         }
         MIXGCN_TRY(fill_values(*c, n, g->dinv, mode, eps, c == &g->tr ? 1 : 0, false, c->val, c->cv, s));
     }

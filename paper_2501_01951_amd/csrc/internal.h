@@ -57,8 +57,8 @@ struct AggSlot {
     uint64_t last_use = 0;
 };
 
-// The entries of a matrix with its rows grouped by length (rowgroups.hip), for aggregations over all
-// rows: per band of columns a stream of batches of eight {column, value} entries.
+// The entries of a matrix whose columns are dealt to bands (rowgroups.hip), for aggregations over all
+// rows: per band a stream of batches of eight {column, value} entries, its rows grouped by length.
 struct Band {
     int64_t piece = 0;      // entries of a piece of a very long row
     int64_t n_batches = 0, n_groups = 0, n_tab = 0;
@@ -71,12 +71,13 @@ struct Band {
     uint2* tab = nullptr;         // [n_tab] {group, batch} at every 8th batch
     uint32_t* cut_row = nullptr;  // [n_cut] rows that were cut into pieces
     uint64_t* piece0 = nullptr;   // [n_cut] first piece of each
-    int64_t* rowptr = nullptr;    // [n + 1] of the band (null: the only band)
+    int64_t* rowptr = nullptr;    // [n + 1] of the band
     int64_t src0 = 0;             // its first entry in RowGroups::src
 };
 struct RowGroups {
-    std::vector<Band> bands;  // empty: not built
-    uint32_t* src = nullptr;  // [nnz] entry indices band by band (null: one band)
+    std::vector<Band> bands;  // empty: the columns stay in one band
+    bool planned = false;
+    uint32_t* src = nullptr;  // [nnz] entry indices band by band
     // estimated cost of a gathered line, in units of one that misses the L2: with the columns in one
     // band, and in these
     float line_cost = 0, band_cost = 0;
@@ -96,7 +97,7 @@ struct Csr {
     uint2* cv_t = nullptr;           // [nnz_padded]
     float* val_t = nullptr;          // [nnz]
     uint32_t* grp_row = nullptr;     // [n_groups + 1] row that holds entry g * kGroupNnz
-    RowGroups groups;                // empty where the rule of csr.hip leaves it out
+    RowGroups groups;
     std::vector<int64_t> h_rowptr;   // host copy of rowptr
     bool has_empty_rows = false;
 };
@@ -208,7 +209,7 @@ int rowgroups_alloc_transpose(RowGroups* g, hipStream_t s);
 int rowgroups_fill(const Csr& m, const RowGroups& g, const float* dinv, int mode, float eps,
                    int swapped, bool transposed, float* val, uint2* cv, hipStream_t s);
 void rowgroups_free(RowGroups* g);
-bool rowgroups_pay(const RowGroups& g, int64_t nnz, int64_t n, int dtype, int width);
+bool rowgroups_pay(const RowGroups& g, int dtype, int width);
 // Bytes of scratch that a pass of `width` columns over the n rows uses.
 size_t rowgroups_scratch(const RowGroups& g, int64_t n, int dtype, int width);
 // One pass over all rows: columns [c0, c0 + width), of which [c_lo, c_hi) are written.

@@ -1,9 +1,15 @@
-// Neighbor aggregation over whole matrices: rows grouped by length.
+// Neighbor aggregation over whole matrices: columns dealt to bands, rows grouped by length.
 //
-// The entry-balanced kernel (spmm.hip) closes one row at a time: three rounds of lane exchanges and
-// a store by an eighth of the lanes for every row, which is what it spends its time on as soon as
-// rows are short or the gathers hit the L2 (a 302 k-entry graph at 256 bf16 columns: 50 us, where
-// the gathers alone take 6).  Here the rows are laid out so that eight of them end together:
+// Bands.  Every XCD's 4 MiB of L2 hold 32 k of the 128-byte lines that a column slice has per node, a
+// gather that misses costs four times one that hits, and an LRU cache keeps far less than the most
+// popular lines.  So where a graph is dense enough the columns are dealt to bands by popularity, 26 k
+// columns each and the rest in the last, and the bands are aggregated one after the other: the
+// gathers of a band all hit once its lines are in, and the later bands add to what the earlier ones
+// left in Z.  How many bands pay is estimated from the degree histogram (plan_bands).
+//
+// Groups.  Within a band rows are short, and closing them one at a time (three rounds of lane
+// exchanges and a store by an eighth of the lanes, as the entry-balanced kernel of spmm.hip does)
+// would take most of the time.  So they are laid out such that eight of them end together:
 //
 //   short rows (1 to 64 entries)  are sorted by length, longest first, and taken eight at a time:
 //                                 a *group*.  Batch j of a group holds entry j of each of its eight
@@ -17,17 +23,12 @@
 // The groups are stored one after the other as one stream of batches of eight {column, value}
 // entries.  A wavefront takes the groups that start in its part of the stream, for one column slice
 // of 8 lanes, so nothing crosses from one wavefront to the next.  The sort works within windows of
-// 4096 consecutive rows: the padding of a group is the spread of eight neighbors in sorted order
-// (below 1 % of the entries in all), while the rows written at the same time stay close together (rows
-// sorted over the whole graph: 3 % slower with plain stores, 12 % with an epilogue that reads).
+// 4096 consecutive rows: the padding of a group is the spread of eight neighbors in sorted order,
+// while the rows written at the same time stay close together (rows sorted over the whole graph: 3 %
+// slower with plain stores, 12 % with an epilogue that reads).
 //
-// Bands.  What is left is the L2: every XCD's 4 MiB hold 32 k of the 128-byte lines that a column
-// slice has per node, a gather that misses costs four times one that hits, and an LRU cache keeps
-// far less than the most popular lines (R-MAT, 2^20 nodes: 44 % hits, where the 26 k most popular
-// columns alone are 64 % of the gathers).  So the columns are dealt to bands by popularity, 26 k
-// columns each and the rest in the last, and the bands are aggregated one after the other: the
-// gathers of a band all hit once its lines are in, and the later bands add to what the earlier ones
-// left in Z.  How many bands pay is estimated from the degree histogram (plan_bands).
+// A matrix with one band has no groups: its aggregations are those of the entry-balanced kernel, which
+// adds a row in eight chains and a tree where a short row here is one chain.
 #include <cmath>
 
 #include "agg_common.h"
@@ -439,8 +440,8 @@ __global__ __launch_bounds__(kBlock) void group_table_kernel(const uint64_t* __r
 // One wavefront per group: computes the matrix values of its rows (rule of the normalisation mode,
 // see entry_value) and writes them to the public array, to the entry-balanced form and, with the
 // columns and the end marks, to the group's batches.  rowptr and src are those of the band: its entry
-// `at` is entry src[at] of the matrix (src null: the only band).  64 consecutive entries of the stream per
-// step: the lane with position i of the step handles entry i / 8 of row i % 8 of a short group.
+// `at` is entry src[at] of the matrix.  64 consecutive entries of the stream per step: the lane with
+// position i of the step handles entry i / 8 of row i % 8 of a short group.
 __global__ __launch_bounds__(kBlock) void fill_groups_kernel(
     const int64_t* __restrict__ rowptr, const uint32_t* __restrict__ col,
     const float* __restrict__ dinv, int mode, float eps, int swapped,
@@ -493,14 +494,14 @@ __global__ __launch_bounds__(kBlock) void fill_groups_kernel(
         const int64_t at = e0 + (is_short ? bb - b0 : (b - b0) * kGroupRows + lane);
         uint2 out = make_uint2(0u, kPadValue);
         if (at < e1) {
-            const int64_t e = src ? (int64_t)src[at] : at;
+            const int64_t e = src[at];
             const uint32_t c = col[e];
             const float v = entry_value(mode, eps, swapped, row, c, drow, dinv);
             val[e] = v;
             cv[e].y = __float_as_uint(v);
             out = make_uint2(c, __float_as_uint(v));
         } else if (e1 > e0) {
-            out.x = col[src ? (int64_t)src[e1 - 1] : e1 - 1];  // a line that has just been gathered
+            out.x = col[src[e1 - 1]];  // a line that has just been gathered
         }
         if (bb == b1 - 1 && lane % kGroupRows == 0) out.x |= end;
         ent[bb * kGroupRows + lane % kGroupRows] = out;
@@ -513,10 +514,9 @@ __global__ __launch_bounds__(kBlock) void fill_groups_kernel(
 // lane's columns, where they are wanted (wants_z, mask).  Between bands an fp32 row waits in Z itself;
 // a bf16 row waits unrounded in `sums` (fp32, [row][sum_stride], the lane's columns at j).
 template <int DT>
-__device__ inline bool wants_z(uint32_t row, int epi)
+__device__ inline bool wants_z(uint32_t row)
 {
-    if (DT == MIXGCN_BF16) return (epi & kEpiAccumulate) && !(row & kRowMore);
-    return (epi & kEpiAccumulate) || (row & kRowAdds);
+    return DT == MIXGCN_F32 && (row & kRowAdds);
 }
 
 template <int DT, int VB, bool EPI>
@@ -540,7 +540,7 @@ __device__ inline void finish_row(float* t, void* Z, int64_t ldz, uint32_t row, 
                 return;
             }
         }
-        if (wants_z<DT>(row, epi)) {
+        if (wants_z<DT>(row)) {
             float o[VEC];
             F::widen(zraw, o);
 #pragma unroll
@@ -641,7 +641,7 @@ __global__ __launch_bounds__(kBlock, DT == MIXGCN_BF16 && (EPI || LPR == 4) ? 6 
         row = __shfl(rv, g * kGroupRows + sub, kWave);
         if (EPI && row != kNoRow && active && half == 0) {
             const int64_t r = (int64_t)(row & kRowMask);
-            if (wants_z<DT>(row, epi)) zraw = *F::ptr(Z, r * ldz + c);
+            if (wants_z<DT>(row)) zraw = *F::ptr(Z, r * ldz + c);
             if (mask) mbits = mask[r * ldm + (c >> 5)] >> (c & 31);
         }
     };
@@ -761,7 +761,7 @@ __global__ __launch_bounds__(kWave) void sum_pieces_kernel(
     const uint32_t row = cut_row[i];
     const int64_t r = (int64_t)(row & kRowMask), c = (int64_t)c0 + j;
     typename F::Raw zraw = {};
-    if (wants_z<DT>(row, epi)) zraw = *F::ptr(Z, r * ldz + c);
+    if (wants_z<DT>(row)) zraw = *F::ptr(Z, r * ldz + c);
     const uint32_t mbits = mask ? mask[r * ldm + (c >> 5)] >> (c & 31) : 0;
     finish_row<DT, VB, true>(t, Z, ldz, row, c, epi, zraw, mask != nullptr, mbits, c_lo, c_hi, sums,
                              part_stride, j);
@@ -900,12 +900,9 @@ int build_bands(const Csr& m, uint32_t n, bool symmetric, RowGroups* out, hipStr
         MIXGCN_HIP_TRY(hipMemcpyAsync(h, t.hist, sizeof(h), hipMemcpyDeviceToHost, s));
         MIXGCN_HIP_TRY(hipStreamSynchronize(s));
         n_bands = plan_bands(h, h + kBins, (double)n, (double)m.nnz, out);
-    } else {  // columns of equal popularity
-        const double miss = (double)n > kLines ? 1 - kLines / (double)n : 0;
-        out->line_cost = (float)(miss + (1 - miss) * kHit);
     }
+    if (n_bands == 1) return MIXGCN_OK;
     out->bands.resize((size_t)n_bands);
-    if (n_bands == 1) return build_band(m.rowptr, n, m.nnz, nullptr, 0, 1, &out->bands[0], s);
 
     size_t tmp_bytes = sort_tmp_bytes(n);
     const int64_t counts = (int64_t)n_bands * n;
@@ -946,7 +943,8 @@ int build_bands(const Csr& m, uint32_t n, bool symmetric, RowGroups* out, hipStr
 
 }  // namespace
 
-// The groups of a matrix: everything that depends on its pattern only.
+// The bands and groups of a matrix (none: its columns stay in one band): everything that depends on
+// its pattern only.
 int rowgroups_build(const Csr& m, uint32_t n, bool symmetric, RowGroups* out, hipStream_t s)
 {
     RowGroups g;
@@ -967,9 +965,9 @@ int rowgroups_fill(const Csr& m, const RowGroups& g, const float* dinv, int mode
 {
     for (const Band& b : g.bands)
         hipLaunchKernelGGL(fill_groups_kernel, dim3((unsigned)ceil_div(b.n_groups + 1, kBlock / kWave)),
-                           dim3(kBlock), 0, s, b.rowptr ? b.rowptr : m.rowptr, m.col, dinv, mode, eps,
+                           dim3(kBlock), 0, s, b.rowptr, m.col, dinv, mode, eps,
                            swapped, b.rows, b.kind, b.start, b.cut_row, b.piece0, b.n_cut, b.n_groups,
-                           b.n_batches, b.piece, b.rowptr ? g.src + b.src0 : nullptr, val, cv,
+                           b.n_batches, b.piece, g.src + b.src0, val, cv,
                            transposed ? b.ent_t : b.ent);
     MIXGCN_HIP_TRY(hipGetLastError());
     return MIXGCN_OK;
@@ -1040,27 +1038,17 @@ int launch_band(const Band& g, const uint2* ent, int64_t n_nodes, const void* H,
 
 }  // namespace
 
-// Whether a pass of `width` columns over all rows is faster on the groups than with the entry-balanced
-// kernel, by the estimates of plan_bands (line_cost, band_cost; 18 ps each).  Measured in both ways on
-// R-MAT, uniform and power-law graphs of 150 k to 2.45 M nodes and 12 to 90 entries per row, at 16 to
-// 256 columns:
-//  - One band.  Where gathers that miss bound both kernels, the groups cost 1 to 5 % more: their
-//    padding, and eight output rows per close (2.45 M nodes, 50 per row, 256 bf16 columns: 5.96
-//    entry-balanced, 6.06 ms).  The entry-balanced kernel is bound by closing rows instead, about
-//    0.2 ns (narrow passes 0.3, bf16 0.4) per row and slice plus 3.6 ps per line, where rows are
-//    short or gathers hit (1 M nodes, 25 per row, 256 bf16 columns: 1.42 ms, groups 1.14).
-//  - Several bands.  What they save is of wide fp32 passes.  Against those, bf16 rows waiting in
-//    fp32 between bands cost 1.3 times as much, half lines 1.65 times: half of a band's L2 stays
-//    empty (power law, 150 k nodes, 90 per row: 128 fp32 columns 737 -> 567 us, but 128 bf16 columns
-//    375 -> 392 and 16 fp32 columns 151 -> 187).
-bool rowgroups_pay(const RowGroups& g, int64_t nnz, int64_t n, int dtype, int width)
+// Whether a pass of `width` columns over all rows is faster in bands than with the entry-balanced
+// kernel, by the estimates of plan_bands (line_cost, band_cost).  What bands save is of wide fp32
+// passes.  Against those, bf16 rows waiting in fp32 between bands cost 1.3 times as much, half lines
+// 1.65 times: half of a band's L2 stays empty (power law, 150 k nodes, 90 per row: 128 fp32 columns
+// 737 -> 567 us, but 128 bf16 columns 375 -> 392 and 16 fp32 columns 151 -> 187).
+bool rowgroups_pay(const RowGroups& g, int dtype, int width)
 {
+    if (g.bands.empty()) return false;
     const bool bf16 = dtype == MIXGCN_BF16;
     const bool narrow = width * (bf16 ? 2 : 4) <= 64;
-    if (g.bands.size() > 1) return g.band_cost * (narrow ? 1.65f : bf16 ? 1.3f : 1.f) < g.line_cost;
-    const double len = (double)nnz / (double)(n > 0 ? n : 1);
-    const double close = narrow ? 300 : bf16 ? 400 : 200;  // ps per row and slice
-    return 18.0 * g.line_cost * len < 1.1 * (close + 3.6 * len);
+    return g.band_cost * (narrow ? 1.65f : bf16 ? 1.3f : 1.f) < g.line_cost;
 }
 
 // Piece slots, and where bf16 rows wait between bands.
@@ -1084,7 +1072,7 @@ int launch_groups_pass(const RowGroups& g, bool values_t, int64_t n_nodes, int d
         const Band& b = g.bands[i];
         const uint2* ent = values_t ? b.ent_t : b.ent;
         // without an epilogue of its own the first band's fp32 rows are plain stores
-        const bool epilogue = epi || mask || (dtype == MIXGCN_F32 ? i > 0 : g.bands.size() > 1);
+        const bool epilogue = epi || mask || dtype != MIXGCN_F32 || i > 0;
         if (dtype == MIXGCN_F32)
             MIXGCN_TRY(launch_band<MIXGCN_F32>(b, ent, n_nodes, H, ldh, Z, ldz, c0, width, P, epi, mask, ldm,
                                                c_lo, c_hi, s, timer, timer_kind, epilogue, sums));
