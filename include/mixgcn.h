@@ -212,6 +212,13 @@ int mixgcn_aggregate_static(const mixgcn_graph* g, int transpose, int dtype, con
                             int64_t row_begin, int64_t row_end, void* stream);
 
 /*
+ * Bands that a plain aggregation of n_cols columns over all rows of the graph takes its columns in (on
+ * dense symmetrised graphs, fp32), or 0 where it does not: host arithmetic on the graph, the type and the
+ * width alone.  -1 for bad arguments or a graph that is not normalised.
+ */
+int mixgcn_aggregate_bands(const mixgcn_graph* g, int transpose, int dtype, int32_t n_cols);
+
+/*
  * mixgcn_aggregate with an epilogue (MIXGCN_EPI_* flags, 0 = none), for the layer forms that
  * combine a node's own features with the aggregate (GraphSAGE's concatenation, whose backward
  * pass is dH = dX_self + A_hat^T dX_neigh):

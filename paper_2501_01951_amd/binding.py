@@ -77,6 +77,7 @@ def load_library():
     lib.mixgcn_graph_reserve_streams.restype = ctypes.c_int
     lib.mixgcn_aggregate_scratch_bytes.argtypes = [i64]
     lib.mixgcn_aggregate_scratch_bytes.restype = i64
+    lib.mixgcn_aggregate_bands.argtypes = [vp, ctypes.c_int, ctypes.c_int, i32]
     lib.mixgcn_aggregate_scratch_need.argtypes = [ctypes.c_int, i32, i64, i64]
     lib.mixgcn_aggregate_scratch_need.restype = i64
     lib.mixgcn_aggregate_static.argtypes = lib.mixgcn_aggregate.argtypes

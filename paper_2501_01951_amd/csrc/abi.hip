@@ -269,18 +269,7 @@ int mixgcn_normalize_mode(mixgcn_graph* g, int mode, float eps, void* stream)
     if (!(eps == eps) || fabsf(eps) > 3.0e38f) return fail(MIXGCN_EINVAL, "normalize: eps");
     MIXGCN_TRY(normalize_graph(g, mode, mode == MIXGCN_NORM_SUM ? eps : 0.f, (hipStream_t)stream));
     // the row-piece scratch of the aggregation: sized once from the entry count, first slot here
-    if (!g->agg_slot_bytes) {
-        g->agg_slot_bytes = agg_scratch_bound(g->fwd.nnz);
-        for (const mixgcn::Csr* m : {&g->fwd, &g->tr})
-            for (const int dtype : {MIXGCN_F32, MIXGCN_BF16}) {
-                const size_t b = rowgroups_scratch(m->groups, g->n, dtype, kAggMaxPassCols);
-                // Where bf16 rows wait between bands takes 1 KB per node in every stream's slot, which
-                // is not spent on fewer than 64 entries per row: 1.3 times the cost of the bands is
-                // hardly ever below that of one band there (rowgroups_pay), and a call whose slot is
-                // too small takes the entry-balanced kernel.
-                if (b <= (size_t)m->nnz * 16 + (1u << 20) && b > g->agg_slot_bytes) g->agg_slot_bytes = b;
-            }
-    }
+    if (!g->agg_slot_bytes) g->agg_slot_bytes = agg_scratch_bound(g->fwd.nnz);
     if (!g->agg_slots[0].p)
         MIXGCN_TRY(pool_alloc_unordered((void**)&g->agg_slots[0].p, g->agg_slot_bytes));
     return MIXGCN_OK;
@@ -414,6 +403,17 @@ int mixgcn_aggregate(const mixgcn_graph* g, int transpose, int dtype, const void
 {
     return aggregate_impl(g, transpose, dtype, H, ldh, Z, ldz, col_begin, col_end, row_begin,
                           row_end, 0, (hipStream_t)stream, nullptr);
+}
+
+int mixgcn_aggregate_bands(const mixgcn_graph* g, int transpose, int dtype, int32_t n_cols)
+{
+    if (!g || n_cols < 0 || (dtype != MIXGCN_F32 && dtype != MIXGCN_BF16)) return -1;
+    const bool symmetric = g->flags & MIXGCN_SYMMETRIZE;
+    if (!g->normalized || (transpose && !symmetric && !g->has_transpose)) return -1;
+    const mixgcn::Csr& m = transpose && !symmetric ? g->tr : g->fwd;
+    const bool values_t = transpose && symmetric && g->norm_mode == MIXGCN_NORM_MEAN;
+    return aggregate_bands(g, m, values_t, dtype, n_cols < kAggMaxPassCols ? n_cols : kAggMaxPassCols, 0,
+                           (int64_t)g->n, 0, agg_scratch_need(dtype, n_cols, 0, m.nnz));
 }
 
 int mixgcn_aggregate_static(const mixgcn_graph* g, int transpose, int dtype, const void* H,

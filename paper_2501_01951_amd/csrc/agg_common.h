@@ -6,23 +6,17 @@
 namespace mixgcn {
 namespace {
 
-// VB consecutive bytes of a feature row (16, 8 or 4) as one load: fp32, or bf16 widened to fp32.
-template <int VB>
-struct RawVec;
-template <> struct RawVec<16> { using T = uint4; };
-template <> struct RawVec<8> { using T = uint2; };
-template <> struct RawVec<4> { using T = uint32_t; };
-
-template <int DT, int VB = 16>
+// 16-byte feature vector: 4 fp32, or 8 bf16 widened to fp32.
+template <int DT>
 struct Feat {
     static constexpr int ES = DT == MIXGCN_F32 ? 4 : 2;  // bytes per stored element
-    static constexpr int VEC = VB / ES;
-    static constexpr int WORDS = VB / 4;
-    using Raw = typename RawVec<VB>::T;
+    static constexpr int VEC = 16 / ES;
+    static constexpr int WORDS = 4;
+    using Raw = uint4;
     __device__ static inline void widen(const Raw& r, float* o)
     {
         uint32_t w[WORDS];
-        __builtin_memcpy(w, &r, VB);
+        __builtin_memcpy(w, &r, 16);
 #pragma unroll
         for (int i = 0; i < WORDS; ++i) {
             if (DT == MIXGCN_F32) {
@@ -52,7 +46,7 @@ struct Feat {
         for (int i = 0; i < WORDS; ++i)
             w[i] = DT == MIXGCN_F32 ? __float_as_uint(a[i]) : pack2(a[2 * i], a[(2 * i + 1) % VEC]);
         Raw r;
-        __builtin_memcpy(&r, w, VB);
+        __builtin_memcpy(&r, w, 16);
         *reinterpret_cast<Raw*>(reinterpret_cast<char*>(base) + elem_off * ES) = r;
     }
     __device__ static inline void store_one(void* base, int64_t elem_off, float a)
@@ -69,11 +63,11 @@ struct Feat {
 // Writes a lane's VEC columns [c, c + VEC) of one output row: the whole group when it
 // lies inside the call's column range [c_lo, c_hi), else only the elements that do, one by one
 // (a range need not start or end on a group; what lies outside it is never written).
-template <int DT, int VB = 16>
+template <int DT>
 __device__ inline void store_in_range(void* Z, int64_t row_off, int64_t c, const float* t, int c_lo,
                                       int c_hi)
 {
-    using F = Feat<DT, VB>;
+    using F = Feat<DT>;
     if (c >= c_lo && c + F::VEC <= c_hi) {
         F::store(Z, row_off + c, t);
     } else {
@@ -118,10 +112,10 @@ __device__ inline void apply_mask(float* t, const uint32_t* __restrict__ mask, i
 constexpr int kEpiRelu = 1;        // Z = max(., 0)
 constexpr int kEpiAccumulate = 2;  // Z = Z + (.): the finished row sum is added to what Z holds
 
-template <int DT, int VB = 16>
+template <int DT>
 __device__ inline void add_stored(float* t, const void* Z, int64_t elem_off)
 {
-    using F = Feat<DT, VB>;
+    using F = Feat<DT>;
     float o[F::VEC];
     F::widen(*F::ptr(Z, elem_off), o);
 #pragma unroll

@@ -209,14 +209,16 @@ int rowgroups_alloc_transpose(RowGroups* g, hipStream_t s);
 int rowgroups_fill(const Csr& m, const RowGroups& g, const float* dinv, int mode, float eps,
                    int swapped, bool transposed, float* val, uint2* cv, hipStream_t s);
 void rowgroups_free(RowGroups* g);
-bool rowgroups_pay(const RowGroups& g, int dtype, int width);
-// Bytes of scratch that a pass of `width` columns over the n rows uses.
-size_t rowgroups_scratch(const RowGroups& g, int64_t n, int dtype, int width);
-// One pass over all rows: columns [c0, c0 + width), of which [c_lo, c_hi) are written.
-int launch_groups_pass(const RowGroups& g, bool values_t, int64_t n_nodes, int dtype,
-                       const void* H, int64_t ldh, void* Z, int64_t ldz, int c0, int width, float* P,
-                       int epi, const uint32_t* mask, int64_t ldm, int c_lo, int c_hi, hipStream_t s,
-                       Timer* timer, int timer_kind);
+bool rowgroups_take(const RowGroups& g, bool values_t, int dtype, int width, size_t scratch_need);
+// One fp32 pass over all rows: columns [c0, c0 + width), of which [c_lo, c_hi) are written.
+int launch_groups_pass(const RowGroups& g, bool values_t, int64_t n_nodes, const void* H, int64_t ldh,
+                       void* Z, int64_t ldz, int c0, int width, float* P, int epi, const uint32_t* mask,
+                       int64_t ldm, int c_lo, int c_hi, hipStream_t s, Timer* timer, int timer_kind);
+
+// Bands of the pass of `width` columns in a call whose row pieces need scratch_need bytes; 0: the
+// entry-balanced kernel takes it.
+int aggregate_bands(const mixgcn_graph* g, const Csr& m, bool values_t, int dtype, int width, int64_t r0,
+                    int64_t r1, int epilogue, size_t scratch_need);
 
 // mask: optional bitmap applied to the written outputs (bit c % 32 of mask[r * ldm + c / 32])
 // values_t: walk the values of the transpose on the same pattern (m.cv_t: the transpose of a

@@ -1,4 +1,4 @@
-// Neighbor aggregation over whole matrices: columns dealt to bands, rows grouped by length.
+// fp32 neighbor aggregation over whole matrices: columns dealt to bands, rows grouped by length.
 //
 // Bands.  Every XCD's 4 MiB of L2 hold 32 k of the 128-byte lines that a column slice has per node, a
 // gather that misses costs four times one that hits, and an LRU cache keeps far less than the most
@@ -510,54 +510,34 @@ __global__ __launch_bounds__(kBlock) void fill_groups_kernel(
 
 // ---- aggregation ----------------------------------------------------------------------------------
 
-// Closes a row, or what one band adds to it.  zraw and mbits are what Z and the mask hold for the
-// lane's columns, where they are wanted (wants_z, mask).  Between bands an fp32 row waits in Z itself;
-// a bf16 row waits unrounded in `sums` (fp32, [row][sum_stride], the lane's columns at j).
-template <int DT>
-__device__ inline bool wants_z(uint32_t row)
-{
-    return DT == MIXGCN_F32 && (row & kRowAdds);
-}
+constexpr int kVec = 4;  // columns per lane, 16 bytes
+using F = Feat<MIXGCN_F32>;
 
-template <int DT, int VB, bool EPI>
+// Closes a row, or what one band adds to it: between bands a row waits in Z.  zraw and mbits are what Z
+// and the mask hold for the lane's columns, where they are wanted (kRowAdds, mask).
+template <bool EPI>
 __device__ inline void finish_row(float* t, void* Z, int64_t ldz, uint32_t row, int64_t c, int epi,
-                                  const typename Feat<DT, VB>::Raw& zraw, bool masked, uint32_t mbits,
-                                  int c_lo, int c_hi, float* sums, int sum_stride, int j)
+                                  const F::Raw& zraw, bool masked, uint32_t mbits, int c_lo, int c_hi)
 {
-    using F = Feat<DT, VB>;
-    constexpr int VEC = F::VEC;
-    const int64_t r = (int64_t)(row & kRowMask);
     if (EPI) {
-        if (DT == MIXGCN_BF16 && (row & (kRowAdds | kRowMore))) {
-            float* const p = sums + r * sum_stride + j;
-            if (row & kRowAdds) {
-#pragma unroll
-                for (int i = 0; i < VEC; ++i) t[i] += p[i];
-            }
-            if (row & kRowMore) {
-#pragma unroll
-                for (int i = 0; i < VEC; ++i) p[i] = t[i];
-                return;
-            }
-        }
-        if (wants_z<DT>(row)) {
-            float o[VEC];
+        if (row & kRowAdds) {
+            float o[kVec];
             F::widen(zraw, o);
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) t[i] += o[i];
+            for (int i = 0; i < kVec; ++i) t[i] += o[i];
         }
         if (!(row & kRowMore)) {
             if (epi & kEpiRelu) {
 #pragma unroll
-                for (int i = 0; i < VEC; ++i) t[i] = fmaxf(t[i], 0.f);
+                for (int i = 0; i < kVec; ++i) t[i] = fmaxf(t[i], 0.f);
             }
             if (masked) {
 #pragma unroll
-                for (int i = 0; i < VEC; ++i) t[i] = ((mbits >> i) & 1u) ? t[i] : 0.f;
+                for (int i = 0; i < kVec; ++i) t[i] = ((mbits >> i) & 1u) ? t[i] : 0.f;
             }
         }
     }
-    store_in_range<DT, VB>(Z, r * ldz, c, t, c_lo, c_hi);
+    store_in_range<MIXGCN_F32>(Z, (int64_t)(row & kRowMask) * ldz, c, t, c_lo, c_hi);
 }
 
 // LPR lanes of 16 bytes hold a feature row's slice: 8 for the 128-byte slices of wide passes; for
@@ -570,17 +550,15 @@ __device__ inline void finish_row(float* t, void* Z, int64_t ldz, uint32_t row, 
 // of a load in flight is copied, and the loop has no side exit.
 // EPI: an epilogue other than a plain store is wanted.  OFF32: offsets into H fit 32 bits and
 // column indices 24 bits.
-template <int DT, int LPR, bool EPI, bool OFF32>
-__global__ __launch_bounds__(kBlock, DT == MIXGCN_BF16 && (EPI || LPR == 4) ? 6 : 8) void aggregate_groups_kernel(
+template <int LPR, bool EPI, bool OFF32>
+__global__ __launch_bounds__(kBlock, 8) void aggregate_groups_kernel(
     const uint2* __restrict__ ent, const uint32_t* __restrict__ rows,
     const uint32_t* __restrict__ kind, const uint2* __restrict__ tab, int64_t n_tab, int tab_per_wave, int64_t n_waves, const void* __restrict__ H, int64_t ldh,
     void* __restrict__ Z, int64_t ldz, int c0, int width, int n_slices,
     float* __restrict__ partials, int part_stride, int epi, const uint32_t* __restrict__ mask,
-    int64_t ldm, int c_lo, int c_hi, float* sums)
+    int64_t ldm, int c_lo, int c_hi)
 {
-    using F = Feat<DT>;
-    constexpr int VEC = F::VEC;
-    constexpr int PW = LPR * VEC;              // columns of a slice
+    constexpr int PW = LPR * kVec;             // columns of a slice
     constexpr int BPG = 8 / LPR;               // batches per gather instruction
     constexpr int EPG = BPG * kGroupRows;      // entries per gather instruction
     constexpr int D = 4;                       // gathers in flight per wavefront
@@ -603,30 +581,30 @@ __global__ __launch_bounds__(kBlock, DT == MIXGCN_BF16 && (EPI || LPR == 4) ? 6 
     int64_t k = (int64_t)(uint32_t)uniform32((int)t0.x);
     const int64_t b0 = (int64_t)(uint32_t)uniform32((int)t0.y);
     const int cs = slice * PW;  // first column of the slice within the pass
-    const bool active = cs + lj * VEC < width;
-    const int64_t c = (int64_t)c0 + cs + lj * VEC;
+    const bool active = cs + lj * kVec < width;
+    const int64_t c = (int64_t)c0 + cs + lj * kVec;
     const int64_t c_load = active ? c : (int64_t)c0 + cs;  // idle lanes re-read the first column
     const uint32_t pitch = (uint32_t)(ldh * F::ES);
     const uint32_t lane_off = (uint32_t)(c_load * F::ES);
     const char* const hbase = reinterpret_cast<const char*>(H) + c_load * F::ES;
 
-    float acc[VEC];
+    float acc[kVec];
 #pragma unroll
-    for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
+    for (int i = 0; i < kVec; ++i) acc[i] = 0.f;
     constexpr int RE = D * EPG;  // entries per round
     static_assert(RE <= kWave, "a round's entries must fit one load per lane");
     const uint2* const rent = ent + b0 * kGroupRows + (lane & (RE - 1));
     uint32_t cw[D];
     uint32_t a[D];
-    typename F::Raw h[D];
+    F::Raw h[D];
     auto fill = [&](int u, const uint2& en) __attribute__((always_inline)) {  // slot u <- gather u of the round `en`
         cw[u] = __shfl(en.x, u * EPG + lane / LPR, kWave);
         a[u] = __shfl(en.y, u * EPG + lane / LPR, kWave);
         if (OFF32)  // the 24-bit multiply ignores the marks
-            h[u] = *reinterpret_cast<const typename F::Raw*>(
+            h[u] = *reinterpret_cast<const F::Raw*>(
                 reinterpret_cast<const char*>(H) + (__umul24(cw[u], pitch) + lane_off));
         else
-            h[u] = *reinterpret_cast<const typename F::Raw*>(
+            h[u] = *reinterpret_cast<const F::Raw*>(
                 hbase + (uint64_t)(cw[u] & kEntryColMask) * pitch);
     };
     // The rows of eight groups at a time, a word per lane, and those of the next eight in flight;
@@ -636,12 +614,12 @@ __global__ __launch_bounds__(kBlock, DT == MIXGCN_BF16 && (EPI || LPR == 4) ? 6 
     uint32_t rv = row_words[0], rv_next = row_words[kWave];
     int g = 0;  // group within the eight
     uint32_t row = kNoRow, mbits = 0;
-    typename F::Raw zraw = {};
+    F::Raw zraw = {};
     auto open = [&]() __attribute__((always_inline)) {
         row = __shfl(rv, g * kGroupRows + sub, kWave);
         if (EPI && row != kNoRow && active && half == 0) {
             const int64_t r = (int64_t)(row & kRowMask);
-            if (wants_z<DT>(row)) zraw = *F::ptr(Z, r * ldz + c);
+            if (row & kRowAdds) zraw = *F::ptr(Z, r * ldz + c);
             if (mask) mbits = mask[r * ldm + (c >> 5)] >> (c & 31);
         }
     };
@@ -650,21 +628,20 @@ __global__ __launch_bounds__(kBlock, DT == MIXGCN_BF16 && (EPI || LPR == 4) ? 6 
         if (end == kEndGroup) {
             if (BPG == 2) {
 #pragma unroll
-                for (int i = 0; i < VEC; ++i) acc[i] += __shfl_xor(acc[i], 32, kWave);
+                for (int i = 0; i < kVec; ++i) acc[i] += __shfl_xor(acc[i], 32, kWave);
             }
         } else {
-            reduce_subgroups<LPR, VEC>(acc);
+            reduce_subgroups<LPR, kVec>(acc);
             if (end == kEndPiece && lane < LPR && active) {
-                float* p = partials + (size_t)(kind[k] - kKindPiece) * part_stride + cs + lj * VEC;
+                float* p = partials + (size_t)(kind[k] - kKindPiece) * part_stride + cs + lj * kVec;
 #pragma unroll
-                for (int i = 0; i < VEC; ++i) p[i] = acc[i];
+                for (int i = 0; i < kVec; ++i) p[i] = acc[i];
             }
         }
         if (row != kNoRow && active && half == 0)
-            finish_row<DT, 16, EPI>(acc, Z, ldz, row, c, epi, zraw, mask != nullptr, mbits, c_lo, c_hi, sums,
-                                    part_stride, cs + lj * VEC);
+            finish_row<EPI>(acc, Z, ldz, row, c, epi, zraw, mask != nullptr, mbits, c_lo, c_hi);
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
+        for (int i = 0; i < kVec; ++i) acc[i] = 0.f;
         ++k;
         if (++g == kGroupRows) {
             g = 0;
@@ -677,7 +654,7 @@ __global__ __launch_bounds__(kBlock, DT == MIXGCN_BF16 && (EPI || LPR == 4) ? 6 
     auto round = [&](int b, const uint2& en) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < D; ++u) {
-            float x[VEC];
+            float x[kVec];
             F::widen(h[u], x);
             const float av = __uint_as_float(a[u]);
             const bool real = a[u] != kPadValue;
@@ -688,7 +665,7 @@ __global__ __launch_bounds__(kBlock, DT == MIXGCN_BF16 && (EPI || LPR == 4) ? 6 
             if (BPG == 1) {
                 if (real) {
 #pragma unroll
-                    for (int i = 0; i < VEC; ++i) acc[i] = fmaf(av, x[i], acc[i]);
+                    for (int i = 0; i < kVec; ++i) acc[i] = fmaf(av, x[i], acc[i]);
                 }
                 if (__builtin_expect(end0 != 0, 0)) finish(end0);
             } else {
@@ -697,13 +674,13 @@ __global__ __launch_bounds__(kBlock, DT == MIXGCN_BF16 && (EPI || LPR == 4) ? 6 
                 if (__builtin_expect(end0 != 0, 0)) {  // the lower half belongs to the closing group, the upper to the next
                     if (real && half == 0) {
 #pragma unroll
-                        for (int i = 0; i < VEC; ++i) acc[i] = fmaf(av, x[i], acc[i]);
+                        for (int i = 0; i < kVec; ++i) acc[i] = fmaf(av, x[i], acc[i]);
                     }
                     finish(end0);
                 }
                 if (real && !(end0 && half == 0)) {
 #pragma unroll
-                    for (int i = 0; i < VEC; ++i) acc[i] = fmaf(av, x[i], acc[i]);
+                    for (int i = 0; i < kVec; ++i) acc[i] = fmaf(av, x[i], acc[i]);
                 }
                 if (__builtin_expect(end1 != 0, 0)) finish(end1);
             }
@@ -724,22 +701,19 @@ __global__ __launch_bounds__(kBlock, DT == MIXGCN_BF16 && (EPI || LPR == 4) ? 6 
 }
 
 // Adds the pieces of the rows that were cut: one block per row, its lanes along the columns.
-template <int DT>
 __global__ __launch_bounds__(kWave) void sum_pieces_kernel(
     const uint32_t* __restrict__ cut_row, const uint64_t* __restrict__ piece0, int64_t n_cut,
     int64_t n_pieces, void* __restrict__ Z, int64_t ldz, int c0, int width,
     const float* __restrict__ partials, int part_stride, int epi, const uint32_t* __restrict__ mask,
-    int64_t ldm, int c_lo, int c_hi, float* sums)
+    int64_t ldm, int c_lo, int c_hi)
 {
-    constexpr int VB = 4 * Feat<DT, 4>::ES;  // four columns per lane
-    constexpr int VEC = Feat<DT, VB>::VEC;
     const int64_t i = blockIdx.x;
-    const int j = threadIdx.x * VEC;
+    const int j = threadIdx.x * kVec;
     if (j >= width) return;
     const int64_t k0 = (int64_t)piece0[i], k1 = i + 1 < n_cut ? (int64_t)piece0[i + 1] : n_pieces;
-    float t[VEC];
+    float t[kVec];
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) t[v] = 0.f;
+    for (int v = 0; v < kVec; ++v) t[v] = 0.f;
     const float4* p = reinterpret_cast<const float4*>(partials + (size_t)k0 * part_stride + j);
     const size_t step = (size_t)part_stride / 4;
     int64_t k = k0;
@@ -757,14 +731,12 @@ __global__ __launch_bounds__(kWave) void sum_pieces_kernel(
         const float4 q = *p;
         t[0] += q.x; t[1] += q.y; t[2] += q.z; t[3] += q.w;
     }
-    using F = Feat<DT, VB>;
     const uint32_t row = cut_row[i];
     const int64_t r = (int64_t)(row & kRowMask), c = (int64_t)c0 + j;
-    typename F::Raw zraw = {};
-    if (wants_z<DT>(row)) zraw = *F::ptr(Z, r * ldz + c);
+    F::Raw zraw = {};
+    if (row & kRowAdds) zraw = *F::ptr(Z, r * ldz + c);
     const uint32_t mbits = mask ? mask[r * ldm + (c >> 5)] >> (c & 31) : 0;
-    finish_row<DT, VB, true>(t, Z, ldz, row, c, epi, zraw, mask != nullptr, mbits, c_lo, c_hi, sums,
-                             part_stride, j);
+    finish_row<true>(t, Z, ldz, row, c, epi, zraw, mask != nullptr, mbits, c_lo, c_hi);
 }
 
 template <typename T>
@@ -975,19 +947,17 @@ int rowgroups_fill(const Csr& m, const RowGroups& g, const float* dinv, int mode
 
 namespace {
 
-template <int DT, int LPR>
+template <int LPR>
 int launch_groups(const Band& g, const uint2* ent, int64_t n_nodes, const void* H, int64_t ldh,
                   void* Z, int64_t ldz, int c0, int width, float* P, int part_stride, int epi,
                   const uint32_t* mask, int64_t ldm, int c_lo, int c_hi, hipStream_t s, Timer* timer,
-                  int timer_kind, bool epilogue, float* sums)
+                  int timer_kind, bool epilogue)
 {
-    using F = Feat<DT>;
     if (g.n_batches == 0) return MIXGCN_OK;
-    const int n_slices = (int)ceil_div(width, F::VEC * LPR);
-    // A wavefront walks up to 1024 batches: its start is four dependent loads (2.45 M nodes, 256 bf16
-    // columns: 6.14 ms with 256 batches each, 6.08 with 1024).  Half, a quarter .. of that, down to
-    // 256, until the chip's 8192 wavefronts are filled seven times over (a last partial filling then
-    // costs little); on small inputs further, until they are filled once.
+    const int n_slices = (int)ceil_div(width, kVec * LPR);
+    // A wavefront walks up to 1024 batches: its start is four dependent loads.  Half, a quarter .. of
+    // that, down to 256, until the chip's 8192 wavefronts are filled seven times over (a last partial
+    // filling then costs little); on small inputs further, until they are filled once.
     int per_wave = 1024 / kTabBatches;
     while (per_wave > 1) {
         const int64_t waves = ceil_div(g.n_tab, per_wave) * n_slices;
@@ -1001,9 +971,9 @@ int launch_groups(const Band& g, const uint2* ent, int64_t n_nodes, const void* 
                        ldh * F::ES < (1ll << 24) && n_nodes <= (1ll << 24);
     if (timer) MIXGCN_TRY(timer->begin(timer_kind, s));
 #define MIXGCN_GROUPS(EPI, O32)                                                                   \
-    hipLaunchKernelGGL((aggregate_groups_kernel<DT, LPR, EPI, O32>), dim3((unsigned)grid),         \
-                       dim3(kBlock), 0, s, ent, g.rows, g.kind, g.tab, g.n_tab, per_wave, n_waves, H, ldh, Z, \
-                       ldz, c0, width, n_slices, P, part_stride, epi, mask, ldm, c_lo, c_hi, sums)
+    hipLaunchKernelGGL((aggregate_groups_kernel<LPR, EPI, O32>), dim3((unsigned)grid), dim3(kBlock), 0, s, \
+                       ent, g.rows, g.kind, g.tab, g.n_tab, per_wave, n_waves, H, ldh, Z, ldz, c0, width, \
+                       n_slices, P, part_stride, epi, mask, ldm, c_lo, c_hi)
     if (epilogue) {
         if (off32) MIXGCN_GROUPS(true, true);
         else MIXGCN_GROUPS(true, false);
@@ -1014,71 +984,59 @@ int launch_groups(const Band& g, const uint2* ent, int64_t n_nodes, const void* 
 #undef MIXGCN_GROUPS
     if (timer) MIXGCN_TRY(timer->end(s));
     if (g.n_cut > 0)
-        hipLaunchKernelGGL((sum_pieces_kernel<DT>), dim3((unsigned)g.n_cut), dim3(kWave), 0, s,
-                           g.cut_row, g.piece0, g.n_cut, g.n_pieces, Z, ldz, c0, width, P, part_stride,
-                           epi, mask, ldm, c_lo, c_hi, sums);
+        hipLaunchKernelGGL(sum_pieces_kernel, dim3((unsigned)g.n_cut), dim3(kWave), 0, s, g.cut_row, g.piece0,
+                           g.n_cut, g.n_pieces, Z, ldz, c0, width, P, part_stride, epi, mask, ldm, c_lo,
+                           c_hi);
     return MIXGCN_OK;
 }
 
-// Columns of a slot: the pass, rounded up to whole slices.
-inline int slot_columns(int width) { return (width + 63) / 64 * 64; }
+// Passes of at most 64 bytes.
+inline bool is_narrow(int width) { return width * F::ES <= 64; }
 
-template <int DT>
-int launch_band(const Band& g, const uint2* ent, int64_t n_nodes, const void* H, int64_t ldh, void* Z,
-                int64_t ldz, int c0, int width, float* P, int epi, const uint32_t* mask, int64_t ldm,
-                int c_lo, int c_hi, hipStream_t s, Timer* timer, int timer_kind, bool epilogue, float* sums)
+// Columns of a slot: the pass, rounded up to whole slices.
+inline int slot_columns(int width) { return is_narrow(width) ? 16 : (width + 31) / 32 * 32; }
+
+// Bytes of scratch of a pass: the slots of the pieces.
+size_t pieces_scratch(const RowGroups& g, int width)
 {
-#define MIXGCN_GROUPS_LPR(LPR)                                                                    \
-    return launch_groups<DT, LPR>(g, ent, n_nodes, H, ldh, Z, ldz, c0, width, P, slot_columns(width), \
-                                  epi, mask, ldm, c_lo, c_hi, s, timer, timer_kind, epilogue, sums)
-    if (width * Feat<DT>::ES <= 64) MIXGCN_GROUPS_LPR(4);
-    MIXGCN_GROUPS_LPR(8);
-#undef MIXGCN_GROUPS_LPR
+    int64_t slots = 0;
+    for (const Band& b : g.bands) slots = b.n_pieces > slots ? b.n_pieces : slots;
+    return (size_t)slots * slot_columns(width) * sizeof(float);
 }
 
 }  // namespace
 
-// Whether a pass of `width` columns over all rows is faster in bands than with the entry-balanced
-// kernel, by the estimates of plan_bands (line_cost, band_cost).  What bands save is of wide fp32
-// passes.  Against those, bf16 rows waiting in fp32 between bands cost 1.3 times as much, half lines
-// 1.65 times: half of a band's L2 stays empty (power law, 150 k nodes, 90 per row: 128 fp32 columns
-// 737 -> 567 us, but 128 bf16 columns 375 -> 392 and 16 fp32 columns 151 -> 187).
-bool rowgroups_pay(const RowGroups& g, int dtype, int width)
+// Whether a pass over all rows takes the bands: they are there, for the values at hand too, and
+//  - the pass is fp32.  bf16 rows would have to wait in fp32 between bands, in scratch of 1 KB per row,
+//    which cost 1.3 times the bands of fp32;
+//  - the bands promise to be faster than the entry-balanced kernel by the estimates of plan_bands.  In
+//    passes of at most 64 bytes they cost 1.65 times as much, half of a band's L2 stays empty (power law,
+//    150 k nodes, 90 per row: 128 columns 737 -> 567 us, but 16 columns 151 -> 187);
+//  - the pieces need no more scratch than the entry-balanced kernel would, so that every caller's scratch
+//    holds them.  Nothing here depends on the caller: the same call gives the same bits whatever
+//    scratch it brings.
+bool rowgroups_take(const RowGroups& g, bool values_t, int dtype, int width, size_t scratch_need)
 {
-    if (g.bands.empty()) return false;
-    const bool bf16 = dtype == MIXGCN_BF16;
-    const bool narrow = width * (bf16 ? 2 : 4) <= 64;
-    return g.band_cost * (narrow ? 1.65f : bf16 ? 1.3f : 1.f) < g.line_cost;
+    if (g.bands.empty() || dtype != MIXGCN_F32 || (values_t && !g.bands.back().ent_t)) return false;
+    if (g.band_cost * (is_narrow(width) ? 1.65f : 1.f) >= g.line_cost) return false;
+    return pieces_scratch(g, width) <= scratch_need;
 }
 
-// Piece slots, and where bf16 rows wait between bands.
-size_t rowgroups_scratch(const RowGroups& g, int64_t n, int dtype, int width)
+int launch_groups_pass(const RowGroups& g, bool values_t, int64_t n_nodes, const void* H, int64_t ldh,
+                       void* Z, int64_t ldz, int c0, int width, float* P, int epi, const uint32_t* mask,
+                       int64_t ldm, int c_lo, int c_hi, hipStream_t s, Timer* timer, int timer_kind)
 {
-    int64_t slots = 0;
-    for (const Band& b : g.bands) slots = b.n_pieces > slots ? b.n_pieces : slots;
-    if (dtype == MIXGCN_BF16 && g.bands.size() > 1) slots += n;
-    return (size_t)slots * slot_columns(width) * sizeof(float);
-}
-
-int launch_groups_pass(const RowGroups& g, bool values_t, int64_t n_nodes, int dtype, const void* H,
-                       int64_t ldh, void* Z, int64_t ldz, int c0, int width, float* P, int epi,
-                       const uint32_t* mask, int64_t ldm, int c_lo, int c_hi, hipStream_t s,
-                       Timer* timer, int timer_kind)
-{
-    int64_t slots = 0;
-    for (const Band& b : g.bands) slots = b.n_pieces > slots ? b.n_pieces : slots;
-    float* const sums = P + slots * slot_columns(width);
     for (size_t i = 0; i < g.bands.size(); ++i) {
         const Band& b = g.bands[i];
         const uint2* ent = values_t ? b.ent_t : b.ent;
-        // without an epilogue of its own the first band's fp32 rows are plain stores
-        const bool epilogue = epi || mask || dtype != MIXGCN_F32 || i > 0;
-        if (dtype == MIXGCN_F32)
-            MIXGCN_TRY(launch_band<MIXGCN_F32>(b, ent, n_nodes, H, ldh, Z, ldz, c0, width, P, epi, mask, ldm,
-                                               c_lo, c_hi, s, timer, timer_kind, epilogue, sums));
-        else
-            MIXGCN_TRY(launch_band<MIXGCN_BF16>(b, ent, n_nodes, H, ldh, Z, ldz, c0, width, P, epi, mask, ldm,
-                                                c_lo, c_hi, s, timer, timer_kind, epilogue, sums));
+        // without an epilogue of its own the rows of the first band are plain stores
+        const bool epilogue = epi || mask || i > 0;
+#define MIXGCN_GROUPS_LPR(LPR)                                                                    \
+    MIXGCN_TRY(launch_groups<LPR>(b, ent, n_nodes, H, ldh, Z, ldz, c0, width, P, slot_columns(width), epi, \
+                                  mask, ldm, c_lo, c_hi, s, timer, timer_kind, epilogue))
+        if (is_narrow(width)) MIXGCN_GROUPS_LPR(4);
+        else MIXGCN_GROUPS_LPR(8);
+#undef MIXGCN_GROUPS_LPR
     }
     return MIXGCN_OK;
 }

@@ -430,6 +430,16 @@ size_t agg_scratch_need(int dtype, int32_t n_cols, int64_t e0, int64_t e1)
     return need;
 }
 
+// The bands take the calls over all rows that they pay for (rowgroups_take); the entry-balanced kernel
+// takes the others, row ranges, the whole-row measurement mode, and the accumulating calls: what Z held
+// would be rounded once per band.
+int aggregate_bands(const mixgcn_graph* g, const Csr& m, bool values_t, int dtype, int width, int64_t r0,
+                    int64_t r1, int epilogue, size_t scratch_need)
+{
+    if (r0 != 0 || r1 != (int64_t)g->n || g_aggregate_whole_rows || (epilogue & kEpiAccumulate)) return 0;
+    return rowgroups_take(m.groups, values_t, dtype, width, scratch_need) ? (int)m.groups.bands.size() : 0;
+}
+
 namespace {
 
 template <int DT>
@@ -458,25 +468,18 @@ int launch_dt(const mixgcn_graph* g, const Csr& m, bool values_t, const void* H,
                            dim3(kBlock), 0, s, m.rowptr, Z, ldz, c_lo, c_hi - c_lo, r0, r1,
                            (relu & kEpiAccumulate) ? 1 : 0);
     if (e1 <= e0) return MIXGCN_OK;
-    // The bands take the calls over all rows that they pay for; the entry-balanced kernel takes the
-    // others, row ranges, the whole-row measurement mode, and the accumulating calls: what Z held
-    // would be rounded once per band.
     const uint2* cv = values_t ? m.cv_t : m.cv;
-    const int widest = c1 - c0 < kAggMaxPassCols ? c1 - c0 : kAggMaxPassCols;
-    const bool grouped = !m.groups.bands.empty() && r0 == 0 && r1 == (int64_t)g->n && !g_aggregate_whole_rows &&
-                         !(relu & kEpiAccumulate) &&
-                         rowgroups_scratch(m.groups, (int64_t)g->n, DT, widest) <= P_bytes;
     for (int32_t cbk = c0; cbk < c1; cbk += kAggMaxPassCols) {
         Pass p;
         plan_pass(VEC, cbk, (c1 - cbk) < kAggMaxPassCols ? (c1 - cbk) : kAggMaxPassCols, e1 - e0, &p);
         const int32_t cb = p.cb;
         const int w = p.w;
         const int64_t span = p.span;
-        if (grouped && rowgroups_pay(m.groups, DT, w)) {
+        if (aggregate_bands(g, m, values_t, DT, w, r0, r1, relu, need) > 0) {
             const int kind = p.gf == 4 ? kTimeAggG4 : p.gf == 8 ? kTimeAggG8 : p.gf == 16 ? kTimeAggG16
                              : p.gf == 32 ? kTimeAggG32 : kTimeAggG64;
-            MIXGCN_TRY(launch_groups_pass(m.groups, values_t, (int64_t)g->n, DT, H, ldh, Z, ldz, cb, w, P, relu,
-                                          mask, ldm, c_lo, c_hi, s, timer, kind));
+            MIXGCN_TRY(launch_groups_pass(m.groups, values_t, (int64_t)g->n, H, ldh, Z, ldz, cb, w, P, relu, mask,
+                                          ldm, c_lo, c_hi, s, timer, kind));
             continue;
         }
 #define MIXGCN_AGG_PASS(GG)                                                                      \

@@ -1,0 +1,59 @@
+"""Aggregations of dense graphs whose columns are dealt to bands: which calls take them, and what holds
+for their results."""
+import numpy as np
+import pytest
+
+import oracle
+from parity import say
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def mg():
+    import paper_2501_01951_amd as m
+
+    assert torch.cuda.is_available()
+    m.load_library()
+    return m
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def bands(mg, g, f, dtype=None, transpose=0):
+    return mg.load_library().mixgcn_aggregate_bands(g._h, transpose, mg.F32 if dtype is None else dtype, f)
+
+
+def edges(n, degree, seed, hubs=0):
+    """Uniform columns; hubs > 0: a part of the edges ends in that many nodes."""
+    rng = np.random.default_rng(seed)
+    src, dst = (rng.integers(0, n, n * degree // 2).astype(np.uint32) for _ in range(2))
+    if hubs:
+        dst[:n // 2] = rng.integers(0, hubs, n // 2)
+    return src, dst
+
+
+def graph(mg, src, dst, n, mean=False):
+    g = mg.build_csr(dev(src.view(np.int32)), dev(dst.view(np.int32)), n,
+                     mg.SYMMETRIZE | (0 if mean else mg.ADD_SELF_LOOPS))
+    mg.normalize(g, mg.NORM_MEAN if mean else mg.NORM_SYM)
+    return g
+
+
+@pytest.mark.parametrize("n,degree,f,bf", [(60_000, 61, 72, True), (80_000, 300, 256, True),
+                                           (80_000, 300, 256, False), (80_000, 300, 300, False)])
+def test_fixed_scratch_gives_the_same_bits(mg, n, degree, f, bf):
+    """mixgcn_aggregate_static takes the same kernel whatever scratch the graph's own slots have."""
+    g = graph(mg, *edges(n, degree, 5, 40), n)
+    say(f"static and own scratch n={n} nnz={g.nnz} f={f} bf16={bf}")
+    assert (bands(mg, g, f, mg.BF16 if bf else mg.F32) > 1) == (not bf)
+    h = torch.randn(n, (f + 7) // 8 * 8, device="cuda").to(torch.bfloat16 if bf else torch.float32)
+    z, z_static = torch.zeros_like(h), torch.zeros_like(h)
+    mg.aggregate(g, h, z, col_end=f)
+    mg.aggregate_static(g, h, z_static, col_end=f)
+    assert torch.equal(z, z_static)
+    g.free()
