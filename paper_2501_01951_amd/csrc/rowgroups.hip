@@ -27,8 +27,16 @@
 // while the rows written at the same time stay close together (rows sorted over the whole graph: 3 %
 // slower with plain stores, 12 % with an epilogue that reads).
 //
-// A matrix with one band has no groups: its aggregations are those of the entry-balanced kernel, which
-// adds a row in eight chains and a tree where a short row here is one chain.
+// A matrix with one band has no groups: its aggregations are those of the entry-balanced kernel.
+//
+// Rounding.  The entry-balanced kernel adds a row of n entries in eight chains and a tree, with an error
+// variance of about n^2 / 16 + 3 n (in units of that of one addition to a sum of one entry).  A short row
+// has one sub-group here, whose lanes keep four chains, one per gather in flight: over k bands
+// n^2 / 8 k + (k + 3) n / 2, less from n = 9 k on.  plan_bands asks for 12 k.  Measured against 64 bits,
+// the rms error of 128 columns is 0.995 of the entry-balanced kernel's for 2 bands of 30 entries per row
+// (one chain: 1.26), 0.92 for 4 bands of 25 (1.19), 0.90 for 5 of 18 on a power law (1.08), 0.93 for 7 of
+// 14 (1.10) and 0.64 for 9 of 55 (0.82).  The chains cost nothing (100 k nodes, 100 per row, 4 bands: 399
+// us with one chain and 8 wavefronts per SIMD, 385 with four and 6; 4 and 8 wavefronts spill).
 #include <cmath>
 
 #include "agg_common.h"
@@ -196,9 +204,11 @@ int plan_bands(const unsigned long long* rows, const unsigned long long* entries
                RowGroups* out)
 {
     constexpr double kInBand = 0.03, kRow = 5;
+    // at least 12 entries of a row per band on average: with fewer the sums lose precision (see the top)
+    const int most = nnz / n / 12 < kMostBands ? (int)(nnz / n / 12) : kMostBands;
     int best = 1;
     double best_cost = 0;
-    for (int k = 1; k <= kMostBands && (k - 1) * (double)kBandColumns < n; ++k) {
+    for (int k = 1; k <= most && (k - 1) * (double)kBandColumns < n; ++k) {
         double cost = 0;
         Popular rest[kBins];
         int n_rest = 0;
@@ -551,7 +561,7 @@ __device__ inline void finish_row(float* t, void* Z, int64_t ldz, uint32_t row, 
 // EPI: an epilogue other than a plain store is wanted.  OFF32: offsets into H fit 32 bits and
 // column indices 24 bits.
 template <int LPR, bool EPI, bool OFF32>
-__global__ __launch_bounds__(kBlock, 8) void aggregate_groups_kernel(
+__global__ __launch_bounds__(kBlock, 6) void aggregate_groups_kernel(
     const uint2* __restrict__ ent, const uint32_t* __restrict__ rows,
     const uint32_t* __restrict__ kind, const uint2* __restrict__ tab, int64_t n_tab, int tab_per_wave, int64_t n_waves, const void* __restrict__ H, int64_t ldh,
     void* __restrict__ Z, int64_t ldz, int c0, int width, int n_slices,
@@ -588,9 +598,11 @@ __global__ __launch_bounds__(kBlock, 8) void aggregate_groups_kernel(
     const uint32_t lane_off = (uint32_t)(c_load * F::ES);
     const char* const hbase = reinterpret_cast<const char*>(H) + c_load * F::ES;
 
-    float acc[kVec];
+    float acc[D][kVec];  // of the gathers of a slot
 #pragma unroll
-    for (int i = 0; i < kVec; ++i) acc[i] = 0.f;
+    for (int u = 0; u < D; ++u)
+#pragma unroll
+        for (int i = 0; i < kVec; ++i) acc[u][i] = 0.f;
     constexpr int RE = D * EPG;  // entries per round
     static_assert(RE <= kWave, "a round's entries must fit one load per lane");
     const uint2* const rent = ent + b0 * kGroupRows + (lane & (RE - 1));
@@ -625,23 +637,28 @@ __global__ __launch_bounds__(kBlock, 8) void aggregate_groups_kernel(
     };
     open();
     auto finish = [&](uint32_t end) __attribute__((always_inline)) {
+        float t[kVec];
+#pragma unroll
+        for (int i = 0; i < kVec; ++i) t[i] = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
         if (end == kEndGroup) {
             if (BPG == 2) {
 #pragma unroll
-                for (int i = 0; i < kVec; ++i) acc[i] += __shfl_xor(acc[i], 32, kWave);
+                for (int i = 0; i < kVec; ++i) t[i] += __shfl_xor(t[i], 32, kWave);
             }
         } else {
-            reduce_subgroups<LPR, kVec>(acc);
+            reduce_subgroups<LPR, kVec>(t);
             if (end == kEndPiece && lane < LPR && active) {
                 float* p = partials + (size_t)(kind[k] - kKindPiece) * part_stride + cs + lj * kVec;
 #pragma unroll
-                for (int i = 0; i < kVec; ++i) p[i] = acc[i];
+                for (int i = 0; i < kVec; ++i) p[i] = t[i];
             }
         }
         if (row != kNoRow && active && half == 0)
-            finish_row<EPI>(acc, Z, ldz, row, c, epi, zraw, mask != nullptr, mbits, c_lo, c_hi);
+            finish_row<EPI>(t, Z, ldz, row, c, epi, zraw, mask != nullptr, mbits, c_lo, c_hi);
 #pragma unroll
-        for (int i = 0; i < kVec; ++i) acc[i] = 0.f;
+        for (int u = 0; u < D; ++u)
+#pragma unroll
+            for (int i = 0; i < kVec; ++i) acc[u][i] = 0.f;
         ++k;
         if (++g == kGroupRows) {
             g = 0;
@@ -665,7 +682,7 @@ __global__ __launch_bounds__(kBlock, 8) void aggregate_groups_kernel(
             if (BPG == 1) {
                 if (real) {
 #pragma unroll
-                    for (int i = 0; i < kVec; ++i) acc[i] = fmaf(av, x[i], acc[i]);
+                    for (int i = 0; i < kVec; ++i) acc[u][i] = fmaf(av, x[i], acc[u][i]);
                 }
                 if (__builtin_expect(end0 != 0, 0)) finish(end0);
             } else {
@@ -674,13 +691,13 @@ __global__ __launch_bounds__(kBlock, 8) void aggregate_groups_kernel(
                 if (__builtin_expect(end0 != 0, 0)) {  // the lower half belongs to the closing group, the upper to the next
                     if (real && half == 0) {
 #pragma unroll
-                        for (int i = 0; i < kVec; ++i) acc[i] = fmaf(av, x[i], acc[i]);
+                        for (int i = 0; i < kVec; ++i) acc[u][i] = fmaf(av, x[i], acc[u][i]);
                     }
                     finish(end0);
                 }
                 if (real && !(end0 && half == 0)) {
 #pragma unroll
-                    for (int i = 0; i < kVec; ++i) acc[i] = fmaf(av, x[i], acc[i]);
+                    for (int i = 0; i < kVec; ++i) acc[u][i] = fmaf(av, x[i], acc[u][i]);
                 }
                 if (__builtin_expect(end1 != 0, 0)) finish(end1);
             }
