@@ -78,9 +78,9 @@ struct RowGroups {
     std::vector<Band> bands;  // empty: the columns stay in one band
     bool planned = false;
     uint32_t* src = nullptr;  // [nnz] entry indices band by band
-    // estimated cost of a gathered line, in units of one that misses the L2: with the columns in one
-    // band, and in these
-    float line_cost = 0, band_cost = 0;
+    // estimated cost of a gathered line, in units of one that misses the L2, and the most it may be for
+    // the bands to pay
+    double cost = 0, most_cost = 0;
 };
 
 struct Csr {
@@ -209,7 +209,8 @@ int rowgroups_alloc_transpose(RowGroups* g, hipStream_t s);
 int rowgroups_fill(const Csr& m, const RowGroups& g, const float* dinv, int mode, float eps,
                    int swapped, bool transposed, float* val, uint2* cv, hipStream_t s);
 void rowgroups_free(RowGroups* g);
-bool rowgroups_take(const RowGroups& g, bool values_t, int dtype, int width, size_t scratch_need);
+bool rowgroups_take(const RowGroups& g, int64_t n, int64_t nnz, bool values_t, int dtype, int width,
+                    size_t scratch_need);
 // One fp32 pass over all rows: columns [c0, c0 + width), of which [c_lo, c_hi) are written.
 int launch_groups_pass(const RowGroups& g, bool values_t, int64_t n_nodes, const void* H, int64_t ldh,
                        void* Z, int64_t ldz, int c0, int width, float* P, int epi, const uint32_t* mask,

@@ -244,12 +244,11 @@ int plan_bands(const unsigned long long* rows, const unsigned long long* entries
         // there.  Uniform columns, 100 k nodes, 100 entries per row: 566 -> 373 us with 4 bands
         // (estimate 0.81 -> 0.51); power law, 233 k nodes, 492 per row: 7.2 -> 3.5 ms with 9.
         if (k == 1) {
-            out->line_cost = (float)cost;
+            out->most_cost = 0.85 * cost;  // with the launches (rowgroups_take)
             best_cost = 0.8 * cost;
         } else if (cost < best_cost) {
-            best_cost = cost;
+            out->cost = best_cost = cost;
             best = k;
-            out->band_cost = (float)cost;
         }
     }
     return best;
@@ -520,7 +519,9 @@ __global__ __launch_bounds__(kBlock) void fill_groups_kernel(
 
 // ---- aggregation ----------------------------------------------------------------------------------
 
-constexpr int kVec = 4;  // columns per lane, 16 bytes
+constexpr int kVec = 4;         // columns per lane, 16 bytes
+constexpr int kSliceLanes = 8;  // lanes of a slice
+constexpr int kSliceColumns = kSliceLanes * kVec;
 using F = Feat<MIXGCN_F32>;
 
 // Closes a row, or what one band adds to it: between bands a row waits in Z.  zraw and mbits are what Z
@@ -550,17 +551,14 @@ __device__ inline void finish_row(float* t, void* Z, int64_t ldz, uint32_t row, 
     store_in_range<MIXGCN_F32>(Z, (int64_t)(row & kRowMask) * ldz, c, t, c_lo, c_hi);
 }
 
-// LPR lanes of 16 bytes hold a feature row's slice: 8 for the 128-byte slices of wide passes; for
-// passes of at most 64 bytes 4, and one gather instruction then takes two batches (sixteen rows), the
-// first in the lower half of the wavefront, the second in the upper (with 8 lanes of 8 bytes such a
-// pass took twice as long: the L1 answers by the row).
+// Eight lanes of 16 bytes hold a feature row's slice, one 128-byte line.
 // The pipeline is that of the entry-balanced kernel: the entries of four gathers arrive with one
 // coalesced load two rounds ahead and are handed out with lane shuffles, the feature rows are
 // gathered one round (four loads) ahead, two rounds are written out per trip so that no register
 // of a load in flight is copied, and the loop has no side exit.
 // EPI: an epilogue other than a plain store is wanted.  OFF32: offsets into H fit 32 bits and
 // column indices 24 bits.
-template <int LPR, bool EPI, bool OFF32>
+template <bool EPI, bool OFF32>
 __global__ __launch_bounds__(kBlock, 6) void aggregate_groups_kernel(
     const uint2* __restrict__ ent, const uint32_t* __restrict__ rows,
     const uint32_t* __restrict__ kind, const uint2* __restrict__ tab, int64_t n_tab, int tab_per_wave, int64_t n_waves, const void* __restrict__ H, int64_t ldh,
@@ -568,13 +566,9 @@ __global__ __launch_bounds__(kBlock, 6) void aggregate_groups_kernel(
     float* __restrict__ partials, int part_stride, int epi, const uint32_t* __restrict__ mask,
     int64_t ldm, int c_lo, int c_hi)
 {
-    constexpr int PW = LPR * kVec;             // columns of a slice
-    constexpr int BPG = 8 / LPR;               // batches per gather instruction
-    constexpr int EPG = BPG * kGroupRows;      // entries per gather instruction
-    constexpr int D = 4;                       // gathers in flight per wavefront
+    constexpr int D = 4;  // gathers in flight per wavefront, a batch each
     const int lane = threadIdx.x & (kWave - 1);
-    const int sub = lane / LPR % kGroupRows, lj = lane % LPR;
-    const int half = BPG == 2 ? lane / 32 : 0;
+    const int sub = lane / kSliceLanes, lj = lane % kSliceLanes;
     // Workgroups are dealt round-robin to the 8 XCDs.  1, 2, 4 or 8 slices are dealt with them, so
     // that an XCD's L2 holds lines of one slice only; any other number is taken one after the other.
     const bool dealt = (n_slices & (n_slices - 1)) == 0;
@@ -590,7 +584,7 @@ __global__ __launch_bounds__(kBlock, 6) void aggregate_groups_kernel(
     if (nb == 0) return;
     int64_t k = (int64_t)(uint32_t)uniform32((int)t0.x);
     const int64_t b0 = (int64_t)(uint32_t)uniform32((int)t0.y);
-    const int cs = slice * PW;  // first column of the slice within the pass
+    const int cs = slice * kSliceColumns;  // first column of the slice within the pass
     const bool active = cs + lj * kVec < width;
     const int64_t c = (int64_t)c0 + cs + lj * kVec;
     const int64_t c_load = active ? c : (int64_t)c0 + cs;  // idle lanes re-read the first column
@@ -603,15 +597,15 @@ __global__ __launch_bounds__(kBlock, 6) void aggregate_groups_kernel(
     for (int u = 0; u < D; ++u)
 #pragma unroll
         for (int i = 0; i < kVec; ++i) acc[u][i] = 0.f;
-    constexpr int RE = D * EPG;  // entries per round
+    constexpr int RE = D * kGroupRows;  // entries per round
     static_assert(RE <= kWave, "a round's entries must fit one load per lane");
     const uint2* const rent = ent + b0 * kGroupRows + (lane & (RE - 1));
     uint32_t cw[D];
     uint32_t a[D];
     F::Raw h[D];
     auto fill = [&](int u, const uint2& en) __attribute__((always_inline)) {  // slot u <- gather u of the round `en`
-        cw[u] = __shfl(en.x, u * EPG + lane / LPR, kWave);
-        a[u] = __shfl(en.y, u * EPG + lane / LPR, kWave);
+        cw[u] = __shfl(en.x, u * kGroupRows + sub, kWave);
+        a[u] = __shfl(en.y, u * kGroupRows + sub, kWave);
         if (OFF32)  // the 24-bit multiply ignores the marks
             h[u] = *reinterpret_cast<const F::Raw*>(
                 reinterpret_cast<const char*>(H) + (__umul24(cw[u], pitch) + lane_off));
@@ -629,7 +623,7 @@ __global__ __launch_bounds__(kBlock, 6) void aggregate_groups_kernel(
     F::Raw zraw = {};
     auto open = [&]() __attribute__((always_inline)) {
         row = __shfl(rv, g * kGroupRows + sub, kWave);
-        if (EPI && row != kNoRow && active && half == 0) {
+        if (EPI && row != kNoRow && active) {
             const int64_t r = (int64_t)(row & kRowMask);
             if (row & kRowAdds) zraw = *F::ptr(Z, r * ldz + c);
             if (mask) mbits = mask[r * ldm + (c >> 5)] >> (c & 31);
@@ -640,20 +634,15 @@ __global__ __launch_bounds__(kBlock, 6) void aggregate_groups_kernel(
         float t[kVec];
 #pragma unroll
         for (int i = 0; i < kVec; ++i) t[i] = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
-        if (end == kEndGroup) {
-            if (BPG == 2) {
-#pragma unroll
-                for (int i = 0; i < kVec; ++i) t[i] += __shfl_xor(t[i], 32, kWave);
-            }
-        } else {
-            reduce_subgroups<LPR, kVec>(t);
-            if (end == kEndPiece && lane < LPR && active) {
+        if (end != kEndGroup) {
+            reduce_subgroups<kSliceLanes, kVec>(t);
+            if (end == kEndPiece && lane < kSliceLanes && active) {
                 float* p = partials + (size_t)(kind[k] - kKindPiece) * part_stride + cs + lj * kVec;
 #pragma unroll
                 for (int i = 0; i < kVec; ++i) p[i] = t[i];
             }
         }
-        if (row != kNoRow && active && half == 0)
+        if (row != kNoRow && active)
             finish_row<EPI>(t, Z, ldz, row, c, epi, zraw, mask != nullptr, mbits, c_lo, c_hi);
 #pragma unroll
         for (int u = 0; u < D; ++u)
@@ -675,32 +664,13 @@ __global__ __launch_bounds__(kBlock, 6) void aggregate_groups_kernel(
             F::widen(h[u], x);
             const float av = __uint_as_float(a[u]);
             const bool real = a[u] != kPadValue;
-            // marks of the batches of this gather, if they belong to this wavefront
-            const int bu = b + u * BPG;
-            uint32_t end0 = (uint32_t)uniform32((int)cw[u]) & ~kEntryColMask;
-            if (bu >= nb) end0 = 0;
-            if (BPG == 1) {
-                if (real) {
+            uint32_t end = (uint32_t)uniform32((int)cw[u]) & ~kEntryColMask;
+            if (b + u >= nb) end = 0;  // a batch of the next wavefront
+            if (real) {
 #pragma unroll
-                    for (int i = 0; i < kVec; ++i) acc[u][i] = fmaf(av, x[i], acc[u][i]);
-                }
-                if (__builtin_expect(end0 != 0, 0)) finish(end0);
-            } else {
-                uint32_t end1 = (uint32_t)__builtin_amdgcn_readlane((int)cw[u], 32) & ~kEntryColMask;
-                if (bu + 1 >= nb) end1 = 0;
-                if (__builtin_expect(end0 != 0, 0)) {  // the lower half belongs to the closing group, the upper to the next
-                    if (real && half == 0) {
-#pragma unroll
-                        for (int i = 0; i < kVec; ++i) acc[u][i] = fmaf(av, x[i], acc[u][i]);
-                    }
-                    finish(end0);
-                }
-                if (real && !(end0 && half == 0)) {
-#pragma unroll
-                    for (int i = 0; i < kVec; ++i) acc[u][i] = fmaf(av, x[i], acc[u][i]);
-                }
-                if (__builtin_expect(end1 != 0, 0)) finish(end1);
+                for (int i = 0; i < kVec; ++i) acc[u][i] = fmaf(av, x[i], acc[u][i]);
             }
+            if (__builtin_expect(end != 0, 0)) finish(end);
             fill(u, en);
         }
     };
@@ -708,12 +678,11 @@ __global__ __launch_bounds__(kBlock, 6) void aggregate_groups_kernel(
     uint2 eb = rent[RE];
 #pragma unroll
     for (int u = 0; u < D; ++u) fill(u, ea);
-    constexpr int RB = D * BPG;  // batches per round
-    for (int b = 0; b < nb; b += 2 * RB) {
-        ea = rent[(int64_t)(b + 2 * RB) * kGroupRows];
+    for (int b = 0; b < nb; b += 2 * D) {
+        ea = rent[(int64_t)(b + 2 * D) * kGroupRows];
         round(b, eb);
-        eb = rent[(int64_t)(b + 3 * RB) * kGroupRows];
-        round(b + RB, ea);
+        eb = rent[(int64_t)(b + 3 * D) * kGroupRows];
+        round(b + D, ea);
     }
 }
 
@@ -964,14 +933,13 @@ int rowgroups_fill(const Csr& m, const RowGroups& g, const float* dinv, int mode
 
 namespace {
 
-template <int LPR>
 int launch_groups(const Band& g, const uint2* ent, int64_t n_nodes, const void* H, int64_t ldh,
                   void* Z, int64_t ldz, int c0, int width, float* P, int part_stride, int epi,
                   const uint32_t* mask, int64_t ldm, int c_lo, int c_hi, hipStream_t s, Timer* timer,
                   int timer_kind, bool epilogue)
 {
     if (g.n_batches == 0) return MIXGCN_OK;
-    const int n_slices = (int)ceil_div(width, kVec * LPR);
+    const int n_slices = (int)ceil_div(width, kSliceColumns);
     // A wavefront walks up to 1024 batches: its start is four dependent loads.  Half, a quarter .. of
     // that, down to 256, until the chip's 8192 wavefronts are filled seven times over (a last partial
     // filling then costs little); on small inputs further, until they are filled once.
@@ -988,7 +956,7 @@ int launch_groups(const Band& g, const uint2* ent, int64_t n_nodes, const void* 
                        ldh * F::ES < (1ll << 24) && n_nodes <= (1ll << 24);
     if (timer) MIXGCN_TRY(timer->begin(timer_kind, s));
 #define MIXGCN_GROUPS(EPI, O32)                                                                   \
-    hipLaunchKernelGGL((aggregate_groups_kernel<LPR, EPI, O32>), dim3((unsigned)grid), dim3(kBlock), 0, s, \
+    hipLaunchKernelGGL((aggregate_groups_kernel<EPI, O32>), dim3((unsigned)grid), dim3(kBlock), 0, s, \
                        ent, g.rows, g.kind, g.tab, g.n_tab, per_wave, n_waves, H, ldh, Z, ldz, c0, width, \
                        n_slices, P, part_stride, epi, mask, ldm, c_lo, c_hi)
     if (epilogue) {
@@ -1007,11 +975,8 @@ int launch_groups(const Band& g, const uint2* ent, int64_t n_nodes, const void* 
     return MIXGCN_OK;
 }
 
-// Passes of at most 64 bytes.
-inline bool is_narrow(int width) { return width * F::ES <= 64; }
-
 // Columns of a slot: the pass, rounded up to whole slices.
-inline int slot_columns(int width) { return is_narrow(width) ? 16 : (width + 31) / 32 * 32; }
+inline int slot_columns(int width) { return (int)ceil_div(width, kSliceColumns) * kSliceColumns; }
 
 // Bytes of scratch of a pass: the slots of the pieces.
 size_t pieces_scratch(const RowGroups& g, int width)
@@ -1023,19 +988,27 @@ size_t pieces_scratch(const RowGroups& g, int width)
 
 }  // namespace
 
-// Whether a pass over all rows takes the bands: they are there, for the values at hand too, and
+// Whether a pass over all n rows takes the bands: they are there, for the values at hand too, and
 //  - the pass is fp32.  bf16 rows would have to wait in fp32 between bands, in scratch of 1 KB per row,
 //    which cost 1.3 times the bands of fp32;
-//  - the bands promise to be faster than the entry-balanced kernel by the estimates of plan_bands.  In
-//    passes of at most 64 bytes they cost 1.65 times as much, half of a band's L2 stays empty (power law,
-//    150 k nodes, 90 per row: 128 columns 737 -> 567 us, but 16 columns 151 -> 187);
+//  - its rows are longer than 64 bytes.  Shorter ones leave half of a band's L2 empty and miss less
+//    with the columns in one band, as two share a line (uniform columns, 60 k nodes, 300 per row: 107
+//    us at 8 columns, in bands 137; power law, 120 k nodes, 300 per row, 16 columns: 342 and 347);
+//  - a matrix of rows of up to one line does not nearly fit an L2 (uniform columns, 300 per row, 20
+//    columns: 45 k nodes 122 us, in bands 134; 60 k 178 and 183; 80 k 289 and 249);
+//  - there is enough of it to pay for a launch of its own per band, 10 us or 0.55 M lines with what the
+//    last wavefronts leave idle (uniform columns, 45 k nodes, 80 per row, 2 bands: 49 us at 20 columns,
+//    in bands 60; 145 and 146 at 128);
 //  - the pieces need no more scratch than the entry-balanced kernel would, so that every caller's scratch
 //    holds them.  Nothing here depends on the caller: the same call gives the same bits whatever
 //    scratch it brings.
-bool rowgroups_take(const RowGroups& g, bool values_t, int dtype, int width, size_t scratch_need)
+bool rowgroups_take(const RowGroups& g, int64_t n, int64_t nnz, bool values_t, int dtype, int width,
+                    size_t scratch_need)
 {
     if (g.bands.empty() || dtype != MIXGCN_F32 || (values_t && !g.bands.back().ent_t)) return false;
-    if (g.band_cost * (is_narrow(width) ? 1.65f : 1.f) >= g.line_cost) return false;
+    if (width <= 16 || (width <= kSliceColumns && n * width * F::ES < (6 << 20))) return false;
+    const double lines = (double)nnz * (double)ceil_div(width, kSliceColumns);
+    if (g.cost + 0.55e6 * (double)(g.bands.size() - 1) / lines >= g.most_cost) return false;
     return pieces_scratch(g, width) <= scratch_need;
 }
 
@@ -1048,12 +1021,8 @@ int launch_groups_pass(const RowGroups& g, bool values_t, int64_t n_nodes, const
         const uint2* ent = values_t ? b.ent_t : b.ent;
         // without an epilogue of its own the rows of the first band are plain stores
         const bool epilogue = epi || mask || i > 0;
-#define MIXGCN_GROUPS_LPR(LPR)                                                                    \
-    MIXGCN_TRY(launch_groups<LPR>(b, ent, n_nodes, H, ldh, Z, ldz, c0, width, P, slot_columns(width), epi, \
-                                  mask, ldm, c_lo, c_hi, s, timer, timer_kind, epilogue))
-        if (is_narrow(width)) MIXGCN_GROUPS_LPR(4);
-        else MIXGCN_GROUPS_LPR(8);
-#undef MIXGCN_GROUPS_LPR
+        MIXGCN_TRY(launch_groups(b, ent, n_nodes, H, ldh, Z, ldz, c0, width, P, slot_columns(width), epi,
+                                 mask, ldm, c_lo, c_hi, s, timer, timer_kind, epilogue));
     }
     return MIXGCN_OK;
 }

@@ -437,7 +437,8 @@ int aggregate_bands(const mixgcn_graph* g, const Csr& m, bool values_t, int dtyp
                     int64_t r1, int epilogue, size_t scratch_need)
 {
     if (r0 != 0 || r1 != (int64_t)g->n || g_aggregate_whole_rows || (epilogue & kEpiAccumulate)) return 0;
-    return rowgroups_take(m.groups, values_t, dtype, width, scratch_need) ? (int)m.groups.bands.size() : 0;
+    if (!rowgroups_take(m.groups, (int64_t)g->n, m.nnz, values_t, dtype, width, scratch_need)) return 0;
+    return (int)m.groups.bands.size();
 }
 
 namespace {

@@ -81,3 +81,21 @@ def test_rounding_error_is_that_of_the_row_ranges(mg, n, degree):
     ratio = (z.double() - exact).norm() / (z_ranges.double() - exact).norm()
     assert ratio < 1.002, float(ratio)
     g.free()
+
+
+def test_which_passes_take_the_bands(mg):
+    """Wide fp32 passes of dense symmetrised graphs; not rows of 64 bytes or less, which the bands slow
+    down, and not bf16."""
+    g = graph(mg, *edges(80_000, 300, 9), 80_000)
+    for f in (1, 8, 16, 19):
+        assert bands(mg, g, f) == 0
+    for f in (20, 128, 600):
+        assert bands(mg, g, f) > 1 and bands(mg, g, f, mg.BF16) == 0
+    sparse = graph(mg, *edges(80_000, 20, 9), 80_000)
+    assert bands(mg, sparse, 128) == 0
+    src, dst = edges(80_000, 150, 9)
+    directed = mg.build_csr(dev(src.view(np.int32)), dev(dst.view(np.int32)), 80_000, mg.BUILD_TRANSPOSE)
+    mg.normalize(directed)
+    assert bands(mg, directed, 128) == 0 and bands(mg, directed, 128, transpose=1) == 0
+    for x in (g, sparse, directed):
+        x.free()
