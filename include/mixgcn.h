@@ -129,7 +129,9 @@ enum { MIXGCN_AGG_FIRST = 0, MIXGCN_UPDATE_FIRST = 1 };
  *   src, dst  : [n_edges] node ids (device, or host with MIXGCN_INPUT_ON_HOST); not modified.
  *   out       : receives a new graph, released with mixgcn_graph_free.
  * Synchronises `stream` (nnz must be known to size the arrays).  An endpoint >= n_nodes gives
- * MIXGCN_EINVAL and no graph.
+ * MIXGCN_EINVAL and no graph.  A symmetrised graph of more than 26000 nodes and at least 24 entries per
+ * row may get a second layout of about 14 bytes per entry (22 with the weights of the mean), where
+ * aggregations in bands of columns pay (mixgcn_aggregate_bands).
  */
 int mixgcn_build_csr(const uint32_t* src, const uint32_t* dst, uint64_t n_edges, uint32_t n_nodes,
                      uint32_t flags, void* stream, mixgcn_graph** out);

@@ -214,6 +214,7 @@ int mixgcn_build_csr(const uint32_t* src, const uint32_t* dst, uint64_t n_edges,
         g->n = n_nodes;
         g->flags = flags;
         rc = csr_from_edges(use_src, use_dst, n_edges, n_nodes, sym, loops, false, &g->fwd, s);
+        if (rc == MIXGCN_OK && sym) rc = rowgroups_build(g->fwd, n_nodes, &g->fwd.groups, s);
         if (rc != MIXGCN_OK) break;
         if ((flags & MIXGCN_BUILD_TRANSPOSE) && !sym) {
             rc = csr_from_edges(use_src, use_dst, n_edges, n_nodes, false, loops, true, &g->tr, s);

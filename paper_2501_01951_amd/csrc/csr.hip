@@ -350,16 +350,12 @@ int csr_from_edges(const uint32_t* d_src, const uint32_t* d_dst, uint64_t n_edge
 
 namespace {
 
-// Matrices of up to 2^31 entries may have bands.  Above that the two forms together (20 bytes per
-// entry) would not leave room for the features.
-constexpr int64_t kMostGroupedEntries = 1ll << 31;
-
 // Values of the matrix (swapped: of its transpose on the same pattern) in all stored forms.
 int fill_values(const Csr& c, uint32_t n, const float* dinv, int mode, float eps, int swapped,
                 bool transposed, float* val, uint2* cv, hipStream_t s)
 {
     if (c.nnz == 0) return MIXGCN_OK;
-    if (!c.groups.bands.empty())
+    if (!c.groups.bands.empty() && (!transposed || c.groups.bands.back().ent_t))
         return rowgroups_fill(c, c.groups, dinv, mode, eps, swapped, transposed, val, cv, s);
     hipLaunchKernelGGL(values_kernel, dim3((unsigned)ceil_div(c.nnz, kBlock)), dim3(kBlock), 0, s,
                        c.rowptr, c.col, dinv, n, c.nnz, mode, eps, swapped, val, cv);
@@ -380,13 +376,6 @@ int normalize_graph(mixgcn_graph* g, int mode, float eps, hipStream_t s)
     for (Csr* c : mats) {
         if (!c) continue;
         if (!c->val) MIXGCN_TRY(dmalloc(&c->val, (size_t)c->nnz, s));
-        if (!c->groups.planned && c->nnz > 0 && c->nnz <= kMostGroupedEntries && n < kEntryColMask) {
-            // without memory for them the matrix stays with the entry-balanced kernel
-            const int rc = rowgroups_build(*c, n, g->flags & MIXGCN_SYMMETRIZE, &c->groups, s);
-            if (rc == MIXGCN_ENOMEM) (void)hipGetLastError();
-            else MIXGCN_TRY(rc);
-            c->groups.planned = true;
-        }
         MIXGCN_TRY(fill_values(*c, n, g->dinv, mode, eps, c == &g->tr ? 1 : 0, false, c->val, c->cv, s));
     }
     // A symmetrised graph stores one pattern for the matrix and its transpose.  The mean
@@ -395,14 +384,7 @@ int normalize_graph(mixgcn_graph* g, int mode, float eps, hipStream_t s)
     if (mode == MIXGCN_NORM_MEAN && (g->flags & MIXGCN_SYMMETRIZE)) {
         if (!f.val_t) MIXGCN_TRY(dmalloc(&f.val_t, (size_t)f.nnz, s));
         if (!f.cv_t) MIXGCN_TRY(dmalloc(&f.cv_t, (size_t)f.nnz_padded, s));
-        const int rc = rowgroups_alloc_transpose(&f.groups, s);
-        if (rc == MIXGCN_ENOMEM) {
-            (void)hipGetLastError();
-            MIXGCN_HIP_TRY(hipDeviceSynchronize());  // work on the groups may be queued on any stream
-            rowgroups_free(&f.groups);
-        } else {
-            MIXGCN_TRY(rc);
-        }
+        MIXGCN_TRY(rowgroups_alloc_transpose(&f.groups, s));
         hipLaunchKernelGGL(copy_entries_kernel, dim3((unsigned)ceil_div(f.nnz_padded, kBlock)),
                            dim3(kBlock), 0, s, f.cv, f.cv_t, f.nnz_padded);
         MIXGCN_TRY(fill_values(f, n, g->dinv, mode, eps, 1, true, f.val_t, f.cv_t, s));

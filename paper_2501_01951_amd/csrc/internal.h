@@ -76,7 +76,6 @@ struct Band {
 };
 struct RowGroups {
     std::vector<Band> bands;  // empty: the columns stay in one band
-    bool planned = false;
     uint32_t* src = nullptr;  // [nnz] entry indices band by band
     // estimated cost of a gathered line, in units of one that misses the L2, and the most it may be for
     // the bands to pay
@@ -204,7 +203,7 @@ int csr_from_edges(const uint32_t* d_src, const uint32_t* d_dst, uint64_t n_edge
 void csr_free(Csr* c);
 int normalize_graph(mixgcn_graph* g, int mode, float eps, hipStream_t s);
 
-int rowgroups_build(const Csr& m, uint32_t n, bool symmetric, RowGroups* out, hipStream_t s);
+int rowgroups_build(const Csr& m, uint32_t n, RowGroups* out, hipStream_t s);
 int rowgroups_alloc_transpose(RowGroups* g, hipStream_t s);
 int rowgroups_fill(const Csr& m, const RowGroups& g, const float* dinv, int mode, float eps,
                    int swapped, bool transposed, float* val, uint2* cv, hipStream_t s);

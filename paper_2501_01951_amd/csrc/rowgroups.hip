@@ -80,6 +80,11 @@ __device__ inline int row_class(int64_t len, int64_t piece, int short_row)
 
 constexpr int kBandColumns = 26000;  // columns of a band: 4/5 of the lines of an XCD's L2
 constexpr int kMostBands = 16;
+// Least entries of a row per band on average: with fewer the sums lose precision (see the top).
+constexpr int kBandRow = 12;
+// Largest matrix that may have bands.  Above it the two forms together (24 bytes per entry) would not
+// leave room for the features.
+constexpr int64_t kMostEntries = 1ll << 31;
 // Popularity bins, most popular first: exact up to 64 entries, 16 bins per factor of two above.
 constexpr int kBins = 256;
 
@@ -204,8 +209,7 @@ int plan_bands(const unsigned long long* rows, const unsigned long long* entries
                RowGroups* out)
 {
     constexpr double kInBand = 0.03, kRow = 5;
-    // at least 12 entries of a row per band on average: with fewer the sums lose precision (see the top)
-    const int most = nnz / n / 12 < kMostBands ? (int)(nnz / n / 12) : kMostBands;
+    const int most = nnz / n / kBandRow < kMostBands ? (int)(nnz / n / kBandRow) : kMostBands;
     int best = 1;
     double best_cost = 0;
     for (int k = 1; k <= most && (k - 1) * (double)kBandColumns < n; ++k) {
@@ -785,11 +789,21 @@ void rowgroups_free(RowGroups* g)
     *g = RowGroups();
 }
 
+// Streams for the values of the transpose, all or none: without memory for them its aggregations take
+// the entry-balanced kernel.
 int rowgroups_alloc_transpose(RowGroups* g, hipStream_t s)
 {
+    if (g->bands.empty() || g->bands.back().ent_t) return MIXGCN_OK;
+    int rc = MIXGCN_OK;
     for (Band& b : g->bands)
-        if (!b.ent_t) MIXGCN_TRY(dmalloc(&b.ent_t, (size_t)b.n_batches * kGroupRows + kStreamPad, s));
-    return MIXGCN_OK;
+        if (rc == MIXGCN_OK) rc = dmalloc(&b.ent_t, (size_t)b.n_batches * kGroupRows + kStreamPad, s);
+    if (rc == MIXGCN_OK) return rc;
+    for (Band& b : g->bands) {
+        pool_free_on(b.ent_t, s);  // nothing has used them
+        b.ent_t = nullptr;
+    }
+    if (rc == MIXGCN_ENOMEM) (void)hipGetLastError();
+    return rc == MIXGCN_ENOMEM ? MIXGCN_OK : rc;
 }
 
 namespace {
@@ -842,23 +856,19 @@ int build_band(const int64_t* rowptr, uint32_t n, int64_t nnz, const uint32_t* b
     return MIXGCN_OK;
 }
 
-int build_bands(const Csr& m, uint32_t n, bool symmetric, RowGroups* out, hipStream_t s)
+int build_bands(const Csr& m, uint32_t n, RowGroups* out, hipStream_t s)
 {
-    int n_bands = 1;
     Tmp t(s);
     uint64_t* sorted = nullptr;
-    // Row lengths are column popularities only where the pattern is symmetric.
-    if (symmetric && n > (uint32_t)kBandColumns) {
-        MIXGCN_TRY(dmalloc(&t.keys, n, s));
-        MIXGCN_TRY(dmalloc(&t.hist, 2 * kBins, s));
-        MIXGCN_HIP_TRY(hipMemsetAsync(t.hist, 0, 2 * kBins * sizeof(unsigned long long), s));
-        hipLaunchKernelGGL(popularity_kernel, dim3(blocks(n) < 512u ? blocks(n) : 512u), dim3(kBlock), 0, s,
-                           m.rowptr, n, t.keys, t.hist, t.hist + kBins);
-        unsigned long long h[2 * kBins];
-        MIXGCN_HIP_TRY(hipMemcpyAsync(h, t.hist, sizeof(h), hipMemcpyDeviceToHost, s));
-        MIXGCN_HIP_TRY(hipStreamSynchronize(s));
-        n_bands = plan_bands(h, h + kBins, (double)n, (double)m.nnz, out);
-    }
+    MIXGCN_TRY(dmalloc(&t.keys, n, s));
+    MIXGCN_TRY(dmalloc(&t.hist, 2 * kBins, s));
+    MIXGCN_HIP_TRY(hipMemsetAsync(t.hist, 0, 2 * kBins * sizeof(unsigned long long), s));
+    hipLaunchKernelGGL(popularity_kernel, dim3(blocks(n) < 512u ? blocks(n) : 512u), dim3(kBlock), 0, s,
+                       m.rowptr, n, t.keys, t.hist, t.hist + kBins);
+    unsigned long long h[2 * kBins];
+    MIXGCN_HIP_TRY(hipMemcpyAsync(h, t.hist, sizeof(h), hipMemcpyDeviceToHost, s));
+    MIXGCN_HIP_TRY(hipStreamSynchronize(s));
+    const int n_bands = plan_bands(h, h + kBins, (double)n, (double)m.nnz, out);
     if (n_bands == 1) return MIXGCN_OK;
     out->bands.resize((size_t)n_bands);
 
@@ -901,16 +911,21 @@ int build_bands(const Csr& m, uint32_t n, bool symmetric, RowGroups* out, hipStr
 
 }  // namespace
 
-// The bands and groups of a matrix (none: its columns stay in one band): everything that depends on
-// its pattern only.
-int rowgroups_build(const Csr& m, uint32_t n, bool symmetric, RowGroups* out, hipStream_t s)
+// The bands and groups of a matrix with a symmetric pattern (row lengths are then the popularities of
+// the columns): everything that depends on the pattern only.  None where they cannot pay, and where
+// there is no memory for them.  Waits for the stream.
+int rowgroups_build(const Csr& m, uint32_t n, RowGroups* out, hipStream_t s)
 {
+    if (n <= (uint32_t)kBandColumns || n >= kRowMask || m.nnz < 2 * kBandRow * (int64_t)n || m.nnz > kMostEntries)
+        return MIXGCN_OK;
     RowGroups g;
-    const int rc = build_bands(m, n, symmetric, &g, s);
+    int rc = build_bands(m, n, &g, s);
+    if (rc == MIXGCN_OK && hipStreamSynchronize(s) != hipSuccess) rc = fail(MIXGCN_EHIP, "bands of the columns");
     if (rc != MIXGCN_OK) {
         (void)hipStreamSynchronize(s);  // the arrays may have work queued on them
         rowgroups_free(&g);
-        return rc;
+        if (rc == MIXGCN_ENOMEM) (void)hipGetLastError();
+        return rc == MIXGCN_ENOMEM ? MIXGCN_OK : rc;
     }
     *out = std::move(g);
     return MIXGCN_OK;

@@ -99,3 +99,42 @@ def test_which_passes_take_the_bands(mg):
     assert bands(mg, directed, 128) == 0 and bands(mg, directed, 128, transpose=1) == 0
     for x in (g, sparse, directed):
         x.free()
+
+
+@pytest.mark.parametrize("n,degree,mean", [(4096, 10, False), (80_000, 300, False), (80_000, 300, True)])
+def test_first_normalisation_does_not_wait_for_its_stream(mg, n, degree, mean):
+    src, dst = edges(n, degree, 10)
+    g = mg.build_csr(dev(src.view(np.int32)), dev(dst.view(np.int32)), n,
+                     mg.SYMMETRIZE | (0 if mean else mg.ADD_SELF_LOOPS))
+    stream, done = torch.cuda.Stream(), torch.cuda.Event()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        torch.cuda._sleep(1_000_000_000)  # half a second or more of the stream's time
+        mg.normalize(g, mg.NORM_MEAN if mean else mg.NORM_SYM, stream=stream)
+        done.record()
+    assert not done.query()
+    done.synchronize()
+    want = oracle.build_csr(src, dst, n, True, not mean)
+    want = (oracle.normalize_mean if mean else oracle.normalize)(want)
+    # three fp32 roundings at most
+    np.testing.assert_allclose(g.arrays()["val"].cpu().numpy(), want.val, rtol=2e-7, atol=0)
+    g.free()
+
+
+def test_no_second_layout_where_it_cannot_be_used(mg):
+    """Row pointers apart, a graph without bands takes 16 bytes per entry: columns, values, and both
+    together.  Blocks are at most an eighth larger than what is in them."""
+    n, degree = 300_000, 100
+    src, dst = (dev(e.view(np.int32)) for e in edges(n, degree, 11))
+    mg.release_memory()
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    g = mg.build_csr(src, dst, n)
+    mg.normalize(g)
+    torch.cuda.synchronize()
+    mg.release_memory()
+    taken = before - torch.cuda.mem_get_info()[0]
+    assert bands(mg, g, 256) == 0
+    scratch = mg.load_library().mixgcn_aggregate_scratch_bytes(g.nnz)
+    assert taken < 1.125 * (16 * g.nnz + scratch) + 64 * n, (taken, g.nnz, scratch)
+    g.free()
