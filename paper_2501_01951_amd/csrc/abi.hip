@@ -235,12 +235,6 @@ int mixgcn_build_csr(const uint32_t* src, const uint32_t* dst, uint64_t n_edges,
 int mixgcn_graph_free(mixgcn_graph* g)
 {
     if (!g) return MIXGCN_OK;
-    // work on the arrays may be queued on any stream of the graph's device
-    int dev = g->device;
-    (void)hipGetDevice(&dev);
-    if (dev != g->device) (void)hipSetDevice(g->device);
-    (void)hipDeviceSynchronize();
-    if (dev != g->device) (void)hipSetDevice(dev);
     csr_free(&g->fwd);
     csr_free(&g->tr);
     pool_free(g->deg);

@@ -221,6 +221,12 @@ int dmalloc(T** p, size_t count, hipStream_t s)
     return pool_alloc((void**)p, (count ? count : 1) * sizeof(T), s);
 }
 
+template <typename T>
+int dmalloc_async(T** p, size_t count, hipStream_t s)
+{
+    return pool_alloc_async((void**)p, (count ? count : 1) * sizeof(T), s);
+}
+
 // Work arrays of a build, released on its stream.
 struct TmpBufs {
     explicit TmpBufs(hipStream_t stream) : s(stream) {}
@@ -367,23 +373,23 @@ int fill_values(const Csr& c, uint32_t n, const float* dinv, int mode, float eps
 int normalize_graph(mixgcn_graph* g, int mode, float eps, hipStream_t s)
 {
     const uint32_t n = g->n;
-    if (!g->deg) MIXGCN_TRY(dmalloc(&g->deg, n, s));
-    if (!g->dinv) MIXGCN_TRY(dmalloc(&g->dinv, n, s));
+    if (!g->deg) MIXGCN_TRY(dmalloc_async(&g->deg, n, s));
+    if (!g->dinv) MIXGCN_TRY(dmalloc_async(&g->dinv, n, s));
     if (n > 0)
         hipLaunchKernelGGL(degree_kernel, dim3((unsigned)ceil_div(n, kBlock)), dim3(kBlock), 0, s,
                            g->fwd.rowptr, n, mode, g->deg, g->dinv);
     Csr* mats[2] = {&g->fwd, g->has_transpose ? &g->tr : nullptr};
     for (Csr* c : mats) {
         if (!c) continue;
-        if (!c->val) MIXGCN_TRY(dmalloc(&c->val, (size_t)c->nnz, s));
+        if (!c->val) MIXGCN_TRY(dmalloc_async(&c->val, (size_t)c->nnz, s));
         MIXGCN_TRY(fill_values(*c, n, g->dinv, mode, eps, c == &g->tr ? 1 : 0, false, c->val, c->cv, s));
     }
     // A symmetrised graph stores one pattern for the matrix and its transpose.  The mean
     // weights are not symmetric, so the transpose gets value arrays of its own on that pattern.
     Csr& f = g->fwd;
     if (mode == MIXGCN_NORM_MEAN && (g->flags & MIXGCN_SYMMETRIZE)) {
-        if (!f.val_t) MIXGCN_TRY(dmalloc(&f.val_t, (size_t)f.nnz, s));
-        if (!f.cv_t) MIXGCN_TRY(dmalloc(&f.cv_t, (size_t)f.nnz_padded, s));
+        if (!f.val_t) MIXGCN_TRY(dmalloc_async(&f.val_t, (size_t)f.nnz, s));
+        if (!f.cv_t) MIXGCN_TRY(dmalloc_async(&f.cv_t, (size_t)f.nnz_padded, s));
         MIXGCN_TRY(rowgroups_alloc_transpose(&f.groups, s));
         hipLaunchKernelGGL(copy_entries_kernel, dim3((unsigned)ceil_div(f.nnz_padded, kBlock)),
                            dim3(kBlock), 0, s, f.cv, f.cv_t, f.nnz_padded);

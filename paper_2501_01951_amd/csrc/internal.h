@@ -184,10 +184,12 @@ int radix_sort_u64(uint64_t* keys, uint64_t* alt, int64_t n, int n_bits, uint64_
                    void* tmp, hipStream_t s);
 
 // ---- memory for the library's own arrays (pool.hip) ------------------------------------------
-// pool_alloc: work that the caller queues on `s` may use the block at once.  pool_alloc_unordered:
-// any stream may (no stream is made to wait, so it can be called while one is being recorded).
-// pool_free: no work on the block is queued any more; pool_free_on: only work on `s` may be.
+// pool_alloc: work that the caller queues on `s` may use the block at once; may wait for the device.
+// pool_alloc_async: the same without that wait.  pool_alloc_unordered: any stream may use the block (no
+// stream is made to wait, so it can be called while one is being recorded).
+// pool_free: work on the block may be queued on any stream; pool_free_on: only work on `s` may be.
 int pool_alloc(void** p, size_t bytes, hipStream_t s);
+int pool_alloc_async(void** p, size_t bytes, hipStream_t s);
 int pool_alloc_unordered(void** p, size_t bytes);
 int pool_alloc_pinned(void** p, size_t bytes);
 void pool_free(void* p);

@@ -9,8 +9,11 @@
 //  - Bounded: at most kMaxCachedDevice bytes per device and kMaxCachedPinned of pinned memory stay
 //    cached; the oldest blocks go back to the driver first, blocks larger than half the bound at
 //    once, and all of them when an allocation fails or when mixgcn_release_memory is called.
-//  - A block is released either on a stream that may still have work on it queued (the next owner's
-//    stream waits for an event recorded there), or after the device has been synchronised.
+//  - A block is released either on the one stream that may still have work on it queued (the next
+//    owner's stream waits for an event recorded there), or with work queued on any stream: the arrays of
+//    a graph.  Such a block is handed on after a wait for its device that has succeeded since, which
+//    only calls that may wait make.  The runtime refuses it while any stream of the process is being
+//    captured; the request then goes to the driver.
 //  - Thread safe: one mutex.
 #include <list>
 #include <mutex>
@@ -30,7 +33,8 @@ struct Block {
     void* p = nullptr;
     size_t bytes = 0;
     int device = 0;
-    hipEvent_t ev = nullptr;  // recorded at the release, if work could still be queued then
+    hipEvent_t ev = nullptr;  // recorded at the release, if work on one stream could still be queued then
+    bool any_stream = false;  // work could be queued on any, and the device has not been waited for since
 };
 
 struct Pool {
@@ -80,9 +84,14 @@ void trim(Pool& P, int device, size_t keep)
     }
 }
 
-// ordered = false: the caller cannot make a stream wait (it may be recording one), so only blocks
-// without pending work are taken from the cache.
-int take(void** out, size_t bytes, int device, bool ordered, hipStream_t s)
+// What a request may do before it takes a block with work queued on it.
+enum class Wait {
+    kNone,    // nothing: its stream may be being recorded
+    kStream,  // make its stream wait
+    kHost,    // and wait for the device
+};
+
+int take(void** out, size_t bytes, int device, Wait wait, hipStream_t s)
 {
     *out = nullptr;
     Pool& P = pool();
@@ -90,10 +99,20 @@ int take(void** out, size_t bytes, int device, bool ordered, hipStream_t s)
     std::lock_guard<std::mutex> lock(P.mu);
     // the smallest block that fits and is not more than a quarter larger; the newest of equals
     auto best = P.cached.end();
-    for (auto it = P.cached.begin(); it != P.cached.end(); ++it) {
-        if (it->device != device || it->bytes < want || it->bytes > want + want / 4) continue;
-        if (it->ev && !ordered) continue;
-        if (best == P.cached.end() || it->bytes <= best->bytes) best = it;
+    for (;;) {
+        bool waiting = false;
+        for (auto it = P.cached.begin(); it != P.cached.end(); ++it) {
+            if (it->device != device || it->bytes < want || it->bytes > want + want / 4) continue;
+            if (it->any_stream) waiting = true;
+            else if ((!it->ev || wait != Wait::kNone) && (best == P.cached.end() || it->bytes <= best->bytes)) best = it;
+        }
+        if (best != P.cached.end() || !waiting || wait != Wait::kHost) break;
+        if (hipDeviceSynchronize() != hipSuccess) {
+            (void)hipGetLastError();
+            break;
+        }
+        for (Block& b : P.cached)
+            if (b.device == device) b.any_stream = false;
     }
     Block b;
     if (best != P.cached.end()) {
@@ -130,7 +149,8 @@ int device_of_caller(int* dev)
     return MIXGCN_OK;
 }
 
-void put_back(void* p, bool queued, hipStream_t s)
+// stream: work on the block may be queued on s only; otherwise on any stream of its device.
+void put_back(void* p, bool stream, hipStream_t s)
 {
     if (!p) return;
     Pool& P = pool();
@@ -140,7 +160,8 @@ void put_back(void* p, bool queued, hipStream_t s)
     Block b = it->second;
     P.in_use.erase(it);
     const size_t most = b.device == kPinned ? kMaxCachedPinned : kMaxCachedDevice;
-    if (queued) {
+    b.any_stream = !stream;
+    if (stream) {
         std::vector<hipEvent_t>& spare = P.events[b.device];
         if (!spare.empty()) {
             b.ev = spare.back();
@@ -149,10 +170,11 @@ void put_back(void* p, bool queued, hipStream_t s)
             b.ev = nullptr;
         }
         if (!b.ev || hipEventRecord(b.ev, s) != hipSuccess) {
-            // nothing to order a reuse by: finish the work instead
-            (void)hipStreamSynchronize(s);
+            // nothing to order a reuse by
+            (void)hipGetLastError();
             if (b.ev) (void)hipEventDestroy(b.ev);
             b.ev = nullptr;
+            b.any_stream = true;
         }
     }
     if (b.bytes > most / 2) {
@@ -169,17 +191,24 @@ int pool_alloc(void** p, size_t bytes, hipStream_t s)
 {
     int dev = 0;
     MIXGCN_TRY(device_of_caller(&dev));
-    return take(p, bytes, dev, true, s);
+    return take(p, bytes, dev, Wait::kHost, s);
+}
+
+int pool_alloc_async(void** p, size_t bytes, hipStream_t s)
+{
+    int dev = 0;
+    MIXGCN_TRY(device_of_caller(&dev));
+    return take(p, bytes, dev, Wait::kStream, s);
 }
 
 int pool_alloc_unordered(void** p, size_t bytes)
 {
     int dev = 0;
     MIXGCN_TRY(device_of_caller(&dev));
-    return take(p, bytes, dev, false, nullptr);
+    return take(p, bytes, dev, Wait::kNone, nullptr);
 }
 
-int pool_alloc_pinned(void** p, size_t bytes) { return take(p, bytes, kPinned, false, nullptr); }
+int pool_alloc_pinned(void** p, size_t bytes) { return take(p, bytes, kPinned, Wait::kNone, nullptr); }
 
 void pool_free(void* p) { put_back(p, false, nullptr); }
 void pool_free_on(void* p, hipStream_t s) { put_back(p, true, s); }

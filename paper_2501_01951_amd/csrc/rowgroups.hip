@@ -796,7 +796,8 @@ int rowgroups_alloc_transpose(RowGroups* g, hipStream_t s)
     if (g->bands.empty() || g->bands.back().ent_t) return MIXGCN_OK;
     int rc = MIXGCN_OK;
     for (Band& b : g->bands)
-        if (rc == MIXGCN_OK) rc = dmalloc(&b.ent_t, (size_t)b.n_batches * kGroupRows + kStreamPad, s);
+        if (rc == MIXGCN_OK)
+            rc = pool_alloc_async((void**)&b.ent_t, ((size_t)b.n_batches * kGroupRows + kStreamPad) * sizeof(uint2), s);
     if (rc == MIXGCN_OK) return rc;
     for (Band& b : g->bands) {
         pool_free_on(b.ent_t, s);  // nothing has used them

@@ -57,3 +57,58 @@ def test_builds_in_reused_memory(n_threads):
     for t in threads:
         t.join()
     assert not errors, errors
+
+
+def _small_graph(mg, seed):
+    src, dst = (np.random.default_rng(seed + i).integers(0, 5000, 40_000).astype(np.uint32) for i in (0, 1))
+    return torch.from_numpy(src.view(np.int32)).cuda(), torch.from_numpy(dst.view(np.int32)).cuda()
+
+
+@pytest.mark.parametrize("capturing", [False, True])
+def test_arrays_of_a_freed_graph_wait_for_work_on_any_stream(capturing):
+    """A graph is dropped with aggregations of it queued on a stream, and another one is built on a
+    second stream at once: it must not get the arrays of the first before they are read.  While a
+    stream is being captured the device cannot be waited for."""
+    import paper_2501_01951_amd as mg
+
+    n = 5000
+    ends, other = _small_graph(mg, 1), _small_graph(mg, 3)
+    h, z = torch.randn(n, 64, device="cuda"), torch.zeros(n, 64, device="cuda")
+    x = torch.zeros(8, device="cuda")
+    reader, builder, captured = (torch.cuda.Stream() for _ in range(3))
+    g = mg.build_csr(*ends, n)
+    mg.normalize(g)
+    want = torch.zeros_like(z)
+    mg.aggregate(g, h, want)
+    torch.cuda.synchronize()
+
+    def drop_and_build(g):
+        with torch.cuda.stream(reader):
+            torch.cuda._sleep(200_000_000)
+            mg.aggregate(g, h, z, stream=reader)
+        g.free()
+        with torch.cuda.stream(builder):
+            second = mg.build_csr(*other, n, stream=builder)
+            mg.normalize(second, stream=builder)
+        return second
+
+    if capturing:
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=captured, capture_error_mode="relaxed"):
+            x.add_(1)
+            second = drop_and_build(g)
+        graph.replay()
+    else:
+        second = drop_and_build(g)
+    torch.cuda.synchronize()
+    assert torch.equal(z, want)
+    fresh = mg.build_csr(*other, n)
+    mg.normalize(fresh)
+    a, b = second.arrays(), fresh.arrays()
+    for name in ("rowptr", "col", "val", "deg", "dinv"):
+        assert torch.equal(a[name], b[name]), name
+    mg.aggregate(second, h, z)
+    mg.aggregate(fresh, h, want)
+    assert torch.equal(z, want)
+    second.free()
+    fresh.free()
