@@ -394,9 +394,10 @@ int mixgcn_softmax_xent(int dtype, const void* logits, int64_t ldl, const int32_
 int mixgcn_graph_info(const mixgcn_graph* g, mixgcn_graph_view* out);
 int mixgcn_graph_free(mixgcn_graph* g);
 /*
- * Device and pinned host memory of freed graphs and of the work arrays of mixgcn_build_csr and
- * mixgcn_reorder_rcm stays cached for the next such call, up to 4 GiB per device (256 MiB pinned).
- * mixgcn_release_memory gives all of it back to the driver.  Thread safe.
+ * Device memory of freed graphs and of the work arrays of mixgcn_build_csr and mixgcn_reorder_rcm stays
+ * cached for the next such call, up to 4 GiB per device.  It goes back to the driver where an allocation
+ * of the library itself finds no memory, and all of it with mixgcn_release_memory, which a program calls
+ * before it allocates the last gigabytes of a device elsewhere.  Thread safe.
  */
 int mixgcn_release_memory(void);
 /*

@@ -58,7 +58,7 @@ int get_scratch(int which, size_t bytes, void** out)
         const size_t floor_bytes = which == 0 ? ((size_t)64 << 20) : ((size_t)1 << 20);
         size_t want = bytes + bytes / 4 + 256;
         if (want < floor_bytes) want = floor_bytes;
-        MIXGCN_HIP_TRY(hipMalloc(&sc.p, want));
+        MIXGCN_TRY(pool_malloc(&sc.p, want));
         sc.bytes = want;
     }
     *out = sc.p;

@@ -188,10 +188,11 @@ int radix_sort_u64(uint64_t* keys, uint64_t* alt, int64_t n, int n_bits, uint64_
 // pool_alloc_async: the same without that wait.  pool_alloc_unordered: any stream may use the block (no
 // stream is made to wait, so it can be called while one is being recorded).
 // pool_free: work on the block may be queued on any stream; pool_free_on: only work on `s` may be.
+// pool_malloc: memory from the driver, not the cache, and back to it with hipFree; the cache makes room.
 int pool_alloc(void** p, size_t bytes, hipStream_t s);
 int pool_alloc_async(void** p, size_t bytes, hipStream_t s);
 int pool_alloc_unordered(void** p, size_t bytes);
-int pool_alloc_pinned(void** p, size_t bytes);
+int pool_malloc(void** p, size_t bytes);
 void pool_free(void* p);
 void pool_free_on(void* p, hipStream_t s);
 void pool_release();

@@ -161,8 +161,8 @@ extern "C" int mixgcn_measure_peaks(double* read_gbs, double* copy_gbs, double* 
     // streaming copy of 4 GiB (read 4 GiB + write 4 GiB), third of three runs
     const int64_t bytes = 4ll << 30, n4 = bytes / 16;
     DevBuf src, dst;
-    MIXGCN_HIP_TRY(hipMalloc(&src.p, (size_t)bytes));
-    MIXGCN_HIP_TRY(hipMalloc(&dst.p, (size_t)bytes));
+    MIXGCN_TRY(pool_malloc(&src.p, (size_t)bytes));
+    MIXGCN_TRY(pool_malloc(&dst.p, (size_t)bytes));
     const unsigned copy_grid = 8192;  // 4 * 8192 * 256 float4 = 128 MiB per trip of the loop
     hipLaunchKernelGGL(copy_kernel, dim3(copy_grid), dim3(kBlock), 0, s, (const float4*)dst.p,
                        (float4*)src.p, n4);  // first touch of both buffers
@@ -176,7 +176,7 @@ extern "C" int mixgcn_measure_peaks(double* read_gbs, double* copy_gbs, double* 
     }
     *copy_gbs = 2.0 * (double)bytes / ((double)ms * 1e-3) / 1e9;
     DevBuf sums;
-    MIXGCN_HIP_TRY(hipMalloc(&sums.p, (size_t)copy_grid * kBlock * sizeof(float)));
+    MIXGCN_TRY(pool_malloc(&sums.p, (size_t)copy_grid * kBlock * sizeof(float)));
     for (int rep = 0; rep < 3; ++rep) {
         MIXGCN_HIP_TRY(hipEventRecord(ev.a, s));
         hipLaunchKernelGGL(read_kernel, dim3(copy_grid), dim3(kBlock), 0, s, (const float4*)src.p,
@@ -196,7 +196,7 @@ extern "C" int mixgcn_measure_peaks(double* read_gbs, double* copy_gbs, double* 
         const uint32_t masks[2] = {(2u << 20) / 128 - 1, (uint32_t)(bytes / 128 - 1)};
         double* outs[2] = {gather_l2_gbs, gather_hbm_gbs};
         DevBuf gout;
-        MIXGCN_HIP_TRY(hipMalloc(&gout.p, (size_t)ggrid * kBlock * sizeof(uint4)));
+        MIXGCN_TRY(pool_malloc(&gout.p, (size_t)ggrid * kBlock * sizeof(uint4)));
         for (int k = 0; k < 2; ++k) {
             for (int rep = 0; rep < 3; ++rep) {
                 MIXGCN_HIP_TRY(hipEventRecord(ev.a, s));

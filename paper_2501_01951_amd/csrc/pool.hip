@@ -1,14 +1,14 @@
-// Device memory and pinned host memory for the library's own arrays (graphs, their scratch, the
-// work arrays of a build or a reordering), kept for reuse after their release.
+// Device memory for the library's own arrays (graphs, their scratch, the work arrays of a build or a
+// reordering), kept for reuse after their release.
 //
 // Building the matrix of a 10^6-node graph takes about 4 ms of kernels and allocates 13 arrays for
 // it.  Allocating and freeing them through the driver costs 2 ms at its best and 45 to 115 ms once
 // a process has cycled a few tens of gigabytes that way (a free of more than 128 MB then takes tens
 // of milliseconds).  A released block therefore stays here and goes to the next request it fits.
 //
-//  - Bounded: at most kMaxCachedDevice bytes per device and kMaxCachedPinned of pinned memory stay
-//    cached; the oldest blocks go back to the driver first, blocks larger than half the bound at
-//    once, and all of them when an allocation fails or when mixgcn_release_memory is called.
+//  - Bounded: at most kMaxCached bytes per device stay cached; the oldest blocks go back to the driver
+//    first, blocks larger than half the bound at once, and all of them when an allocation of the
+//    library fails or when mixgcn_release_memory is called.
 //  - A block is released either on the one stream that may still have work on it queued (the next
 //    owner's stream waits for an event recorded there), or with work queued on any stream: the arrays of
 //    a graph.  Such a block is handed on after a wait for its device that has succeeded since, which
@@ -24,9 +24,7 @@
 namespace mixgcn {
 namespace {
 
-constexpr size_t kMaxCachedDevice = (size_t)4 << 30;
-constexpr size_t kMaxCachedPinned = (size_t)256 << 20;
-constexpr int kPinned = -1;  // in the place of the device of a block: pinned host memory
+constexpr size_t kMaxCached = (size_t)4 << 30;
 constexpr int kPoolDevices = 16;
 
 struct Block {
@@ -63,11 +61,10 @@ void to_driver(Pool& P, Block& b)
         (void)hipEventSynchronize(b.ev);
         P.events[b.device].push_back(b.ev);
     }
-    if (b.device == kPinned) (void)hipHostFree(b.p);
-    else (void)hipFree(b.p);
+    (void)hipFree(b.p);
 }
 
-// Gives cached blocks back, oldest first, until at most `keep` bytes of their kind are left.
+// Gives cached blocks of a device back, oldest first, until at most `keep` bytes are left.
 void trim(Pool& P, int device, size_t keep)
 {
     size_t have = 0;
@@ -82,6 +79,18 @@ void trim(Pool& P, int device, size_t keep)
         to_driver(P, *it);
         it = P.cached.erase(it);
     }
+}
+
+// Memory from the driver; the cache of the device goes back to it where that fails.
+hipError_t malloc_or_trim(Pool& P, int device, void** out, size_t bytes)
+{
+    hipError_t e = hipMalloc(out, bytes);
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();
+    trim(P, device, 0);
+    e = hipMalloc(out, bytes);
+    if (e == hipErrorOutOfMemory) (void)hipGetLastError();
+    return e;
 }
 
 // What a request may do before it takes a block with work queued on it.
@@ -126,16 +135,7 @@ int take(void** out, size_t bytes, int device, Wait wait, hipStream_t s)
     } else {
         b.bytes = want;
         b.device = device;
-        const auto from_driver = [&] {
-            return device == kPinned ? hipHostMalloc(&b.p, want, hipHostMallocDefault) : hipMalloc(&b.p, want);
-        };
-        hipError_t e = from_driver();
-        if (e == hipErrorOutOfMemory) {
-            (void)hipGetLastError();
-            trim(P, device, 0);
-            e = from_driver();
-        }
-        MIXGCN_HIP_TRY(e);
+        MIXGCN_HIP_TRY(malloc_or_trim(P, device, &b.p, want));
     }
     P.in_use[b.p] = b;
     *out = b.p;
@@ -159,7 +159,6 @@ void put_back(void* p, bool stream, hipStream_t s)
     if (it == P.in_use.end()) return;
     Block b = it->second;
     P.in_use.erase(it);
-    const size_t most = b.device == kPinned ? kMaxCachedPinned : kMaxCachedDevice;
     b.any_stream = !stream;
     if (stream) {
         std::vector<hipEvent_t>& spare = P.events[b.device];
@@ -177,12 +176,12 @@ void put_back(void* p, bool stream, hipStream_t s)
             b.any_stream = true;
         }
     }
-    if (b.bytes > most / 2) {
+    if (b.bytes > kMaxCached / 2) {
         to_driver(P, b);
         return;
     }
     P.cached.push_back(b);
-    trim(P, b.device, most);
+    trim(P, b.device, kMaxCached);
 }
 
 }  // namespace
@@ -208,7 +207,14 @@ int pool_alloc_unordered(void** p, size_t bytes)
     return take(p, bytes, dev, Wait::kNone, nullptr);
 }
 
-int pool_alloc_pinned(void** p, size_t bytes) { return take(p, bytes, kPinned, Wait::kNone, nullptr); }
+int pool_malloc(void** p, size_t bytes)
+{
+    int dev = 0;
+    MIXGCN_TRY(device_of_caller(&dev));
+    std::lock_guard<std::mutex> lock(pool().mu);
+    MIXGCN_HIP_TRY(malloc_or_trim(pool(), dev, p, bytes));
+    return MIXGCN_OK;
+}
 
 void pool_free(void* p) { put_back(p, false, nullptr); }
 void pool_free_on(void* p, hipStream_t s) { put_back(p, true, s); }

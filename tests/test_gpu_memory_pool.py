@@ -112,3 +112,29 @@ def test_arrays_of_a_freed_graph_wait_for_work_on_any_stream(capturing):
     assert torch.equal(z, want)
     second.free()
     fresh.free()
+
+
+def test_cached_memory_makes_room_for_other_allocations_of_the_library():
+    """With the device nearly full, a call that allocates past the cache (8 GiB for the peaks) gets what
+    the cache holds."""
+    import paper_2501_01951_amd as mg
+
+    n = 300_000
+    gen = torch.Generator("cuda").manual_seed(1)
+    src, dst = (torch.randint(0, n, (45_000_000,), device="cuda", dtype=torch.int32, generator=gen) for _ in range(2))
+    mg.release_memory()
+    mg.measure_peaks()  # what the runtime itself needs for its kernels is there
+    g = mg.build_csr(src, dst, n)
+    g.free()
+    torch.cuda.empty_cache()
+    torch.cuda.synchronize()
+    gib = 1 << 30
+    hog = []
+    while torch.cuda.mem_get_info()[0] > 8 * gib - (gib >> 1):
+        hog.append(torch.empty(min(32 * gib, torch.cuda.mem_get_info()[0] - 7 * gib), dtype=torch.uint8, device="cuda"))
+    free = torch.cuda.mem_get_info()[0]
+    assert 6 * gib < free < 8 * gib
+    assert mg.measure_peaks()
+    assert torch.cuda.mem_get_info()[0] > free + gib
+    del hog
+    torch.cuda.empty_cache()
