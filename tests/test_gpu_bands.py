@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 import oracle
-from parity import say
+from parity import RTOL_F32, assert_close, say
 
 pytestmark = pytest.mark.gpu
 
@@ -137,4 +137,91 @@ def test_no_second_layout_where_it_cannot_be_used(mg):
     assert bands(mg, g, 256) == 0
     scratch = mg.load_library().mixgcn_aggregate_scratch_bytes(g.nnz)
     assert taken < 1.125 * (16 * g.nnz + scratch) + 64 * n, (taken, g.nnz, scratch)
+    g.free()
+
+
+@pytest.mark.parametrize("mean", [False, True])
+def test_bands_against_the_oracle(mg, mean):
+    """Rows cut into pieces in several bands; column ranges that start and end inside a 16-byte group, with
+    ReLU, accumulating and masked; feature rows so far apart that offsets need 64 bits."""
+    n, f = 80_000, 48
+    src, dst = edges(n, 150, 12, hubs=30)
+    g = graph(mg, src, dst, n, mean)
+    tr = int(mean)
+    assert bands(mg, g, f, transpose=tr) > 1
+    og = oracle.build_csr(src, dst, n, True, not mean)
+    og = oracle.transpose((oracle.normalize_mean if mean else oracle.normalize)(og))
+    gen = torch.Generator("cuda").manual_seed(12)
+    wide = torch.empty(n, 13440, device="cuda")  # 4.3 GB
+    wide[:, :f] = torch.randn(n, f, device="cuda", generator=gen)
+    z0 = torch.randn(n, f, device="cuda", generator=gen)
+    agg = oracle.spmm(og, wide[:, :f].cpu().numpy().astype(np.float64), transposed=bool(tr))
+    old = z0.cpu().numpy().astype(np.float64)
+    near = wide[:, :f].contiguous()
+    for h in (near, wide):
+        for c0, c1 in ((0, f), (3, 45)):
+            for relu, acc in ((False, False), (True, False), (True, True)):
+                say(f"bands mean={mean} pitch={h.stride(0)} columns [{c0},{c1}) relu={relu} accumulate={acc}")
+                z = z0.clone()
+                mg.aggregate(g, h, z, c0, c1, transpose=tr, relu=relu, accumulate=acc)
+                want = agg + old if acc else agg
+                want = np.maximum(want, 0) if relu else want
+                assert_close(z[:, c0:c1].cpu().numpy(), want[:, c0:c1], RTOL_F32, "bands")
+                assert torch.equal(z[:, :c0], z0[:, :c0]) and torch.equal(z[:, c1:], z0[:, c1:])
+    bits = oracle.dropout_bitmap(3, n, f, 0.5)
+    keep = ((bits[:, np.arange(f) // 32] >> (np.arange(f) % 32).astype(np.uint32)) & 1).astype(bool)
+    z = z0.clone()
+    mg.aggregate_masked(g, near, z, dev(bits.view(np.int32)), transpose=tr)
+    assert_close(z.cpu().numpy(), np.where(keep, agg, 0.0), RTOL_F32, "masked")
+    g.free()
+
+
+def test_bands_on_several_streams(mg):
+    """Column slices of one graph on four streams at once give the bits of the same calls in a row."""
+    n, f = 80_000, 128
+    g = graph(mg, *edges(n, 150, 13, hubs=30), n)
+    assert bands(mg, g, f) > 1
+    h = torch.randn(n, 4 * f, device="cuda")
+    want, z = torch.zeros_like(h), torch.zeros_like(h)
+    for i in range(4):
+        mg.aggregate(g, h, want, i * f, (i + 1) * f)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    for _ in range(3):
+        for i, s in enumerate(streams):
+            mg.aggregate(g, h, z, i * f, (i + 1) * f, stream=s)
+        torch.cuda.synchronize()
+        assert torch.equal(z, want)
+        z.zero_()
+        torch.cuda.synchronize()
+    g.free()
+
+
+def test_transpose_without_memory_for_its_bands(mg):
+    """Room for the mean weights of the transpose (16 bytes per entry in all) but not for their streams
+    (8 more): its aggregations take the entry-balanced kernel, those of the matrix the bands."""
+    n, f = 80_000, 40
+    src, dst = edges(n, 300, 14)
+    g = mg.build_csr(dev(src.view(np.int32)), dev(dst.view(np.int32)), n, mg.SYMMETRIZE)
+    mg.release_memory()
+    torch.cuda.empty_cache()
+    torch.cuda.synchronize()
+    # blocks are at most a sixteenth larger than what is in them
+    need = int(17 * g.nnz) + 2 * mg.load_library().mixgcn_aggregate_scratch_bytes(g.nnz) + (32 << 20)
+    hog = []
+    while torch.cuda.mem_get_info()[0] > need + (64 << 20):
+        hog.append(torch.empty(min(32 << 30, torch.cuda.mem_get_info()[0] - need), dtype=torch.uint8, device="cuda"))
+    assert need - (8 << 20) <= torch.cuda.mem_get_info()[0] < need + (64 << 20)
+    mg.normalize(g, mg.NORM_MEAN)
+    torch.cuda.synchronize()
+    del hog
+    torch.cuda.empty_cache()
+    assert bands(mg, g, f) > 1 and bands(mg, g, f, transpose=1) == 0
+    og = oracle.transpose(oracle.normalize_mean(oracle.build_csr(src, dst, n, True, False)))
+    h = torch.randn(n, f, device="cuda")
+    for tr in (0, 1):
+        z = torch.empty_like(h)
+        mg.aggregate(g, h, z, transpose=tr)
+        assert_close(z.cpu().numpy(), oracle.spmm(og, h.cpu().numpy().astype(np.float64), transposed=bool(tr)),
+                     RTOL_F32, f"transpose={tr}")
     g.free()

@@ -18,11 +18,19 @@ def _check(mg, case, stream):
     with torch.cuda.stream(stream):
         g = mg.build_csr(src, dst, n, stream=stream)
         mg.normalize(g, stream=stream)
+        h = torch.ones(n, 40, device="cuda")
+        z = torch.empty_like(h)
+        mg.aggregate(g, h, z, stream=stream)
         stream.synchronize()
         a = g.arrays()
     assert np.array_equal(a["rowptr"].cpu().numpy(), want.rowptr)
     assert np.array_equal(a["col"].cpu().numpy().view(np.uint32), want.col)
     assert np.array_equal(a["deg"].cpu().numpy().view(np.uint32), np.diff(want.rowptr))
+    np.testing.assert_allclose(a["val"].cpu().numpy(), want.val, rtol=2e-7)  # three fp32 roundings
+    # positive sums of fewer than 2^12 values, in eight chains
+    sums = np.add.reduceat(want.val, want.rowptr[:-1])
+    np.testing.assert_allclose(z[:, 0].cpu().numpy(), sums, rtol=512 * 6e-8)
+    assert torch.equal(z, z[:, :1].expand_as(z))
     g.free()
 
 
@@ -33,11 +41,13 @@ def test_builds_in_reused_memory(n_threads):
     import paper_2501_01951_amd as mg
 
     mg.load_library()
+    graphs = [gg.config_graph("c2", scale_override=scale) for scale in (6, 9, 12, 13)]
+    rng = np.random.default_rng(4)  # and one whose columns form bands
+    graphs.append((*(rng.integers(0, 60_000, 1_830_000).astype(np.uint32) for _ in range(2)), 60_000))
     cases = []
-    for scale in (6, 9, 12, 13):
-        src, dst, n = gg.config_graph("c2", scale_override=scale)
-        cases.append((torch.from_numpy(src.view(np.int32)).cuda(),
-                      torch.from_numpy(dst.view(np.int32)).cuda(), n, oracle.build_csr(src, dst, n)))
+    for src, dst, n in graphs:
+        cases.append((torch.from_numpy(src.view(np.int32)).cuda(), torch.from_numpy(dst.view(np.int32)).cuda(),
+                      n, oracle.normalize(oracle.build_csr(src, dst, n))))
     torch.cuda.synchronize()
     errors = []
 
