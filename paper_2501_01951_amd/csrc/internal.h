@@ -273,7 +273,8 @@ int launch_update_split(int op, const float* A, int64_t lda, const float* W, int
 // Row slabs of a weight gradient of `tiles` output tiles over n rows: slabs of at most `most_rows`
 // rows (1024 workgroups at most), and on small inputs shorter ones until every compute unit has a
 // workgroup, but never below 128 rows: a slab costs its partial tile once more in the reduction, and
-// a workgroup its start.  (64 x 32 over 4096 rows: 4 slabs of 1024 rows took 49 us.)
+// a workgroup its start.  (64 x 32 over 4096 rows: 4 slabs of 1024 rows took 49 us, 32 of 128 take 9.8.)
+// Shorter slabs are also more exact, the reduction adds them in fp64: 0.37 of the error there.
 inline int64_t wgrad_slabs(int64_t n, int64_t tiles, int64_t most_rows)
 {
     int64_t slabs = ceil_div(n, most_rows);

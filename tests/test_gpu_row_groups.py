@@ -1,7 +1,7 @@
-"""Aggregation over whole matrices (rows grouped by length, columns in bands) at the sizes where the
-layout can go wrong: rows around the longest that shares a group (32 or 64 entries, by the size of the
-matrix) and around a piece (256 or 1024), windows of 4096 rows, both gather widths, and a dense graph
-whose columns are dealt to bands."""
+"""Aggregation over whole matrices against the oracle: row lengths around the limits of the row groups
+that the bands of dense graphs use (32, 64, 256, 1024 entries, windows of 4096 rows) in matrices without
+bands, both gather widths, and dense graphs on both sides of the rule for bands, the kernel that takes a
+call asserted."""
 import numpy as np
 import pytest
 import torch
@@ -79,14 +79,16 @@ def test_dense_graph_whose_columns_form_bands(mg, mean):
     og = oracle.build_csr(src, dst, n, True, not mean)
     og = oracle.transpose((oracle.normalize_mean if mean else oracle.normalize)(og))
     for f, bf in ((16, False), (40, False), (72, True)):
+        in_bands = mg.load_library().mixgcn_aggregate_bands(g._h, int(mean), mg.BF16 if bf else mg.F32, f) > 1
+        assert in_bands == (f == 40)
         check(mg, g, og, f, bf, mean, f"bands n={n} nnz={og.nnz}")
     g.free()
 
 
 @pytest.mark.parametrize("mean_len", [85, 105, 160, 200])
 def test_both_sides_of_the_dispatch(mg, mean_len):
-    """28 k columns fit an L2, so the groups pay up to about 93 (fp32), 140 (narrow passes) and 188 (bf16)
-    entries per row; all of these have more than 4 M entries or come close, and rows in pieces."""
+    """A directed graph of 28 k columns, which never has bands: short rows and rows of 5000 entries, which
+    cross many spans."""
     n = 28_000
     lens = np.full(n, 3, dtype=np.int64)
     long_rows = np.random.default_rng(mean_len).permutation(n)[:n * (mean_len - 3) // 5000]
@@ -103,7 +105,7 @@ def test_both_sides_of_the_dispatch(mg, mean_len):
 
 
 def test_bands_of_narrow_and_bf16_passes(mg):
-    """Dense enough that bands pay for bf16 rows, which wait in fp32 between them, and for half lines."""
+    """A graph with bands whose narrow and bf16 passes do not take them."""
     n, degree = 80_000, 300
     rng = np.random.default_rng(6)
     src, dst = (rng.integers(0, n, n * degree // 2).astype(np.uint32) for _ in range(2))
@@ -111,5 +113,6 @@ def test_bands_of_narrow_and_bf16_passes(mg):
     mg.normalize(g)
     og = oracle.normalize(oracle.build_csr(src, dst, n, True, True))
     for f, bf in ((16, False), (72, True)):
+        assert mg.load_library().mixgcn_aggregate_bands(g._h, 0, mg.BF16 if bf else mg.F32, f) == 0
         check(mg, g, og, f, bf, False, f"bands n={n} nnz={og.nnz}")
     g.free()
