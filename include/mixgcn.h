@@ -172,8 +172,9 @@ int mixgcn_normalize_mode(mixgcn_graph* g, int mode, float eps, void* stream);
  * in stream order, calls on different streams use different buffers, so the column slices of one
  * graph may be aggregated on several streams at once.  The buffer of the first stream is
  * allocated by mixgcn_normalize; each further stream that aggregates the graph gets its own on
- * its first call (one hipMalloc of mixgcn_aggregate_scratch_bytes(nnz), no synchronisation), or
- * ahead of time through mixgcn_graph_reserve_streams.  Up to 16 streams per graph are served
+ * its first call (at most one hipMalloc, of mixgcn_aggregate_scratch_bytes(nnz) and up to a sixteenth
+ * more; no synchronisation unless the device is out of memory), or ahead of time through
+ * mixgcn_graph_reserve_streams.  Up to 16 streams per graph are served
  * this way; a 17th takes over the least recently used buffer after a device synchronisation.
  * Otherwise the call allocates nothing and does not synchronise.
  */

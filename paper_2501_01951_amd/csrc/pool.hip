@@ -197,7 +197,12 @@ int pool_alloc_async(void** p, size_t bytes, hipStream_t s)
 {
     int dev = 0;
     MIXGCN_TRY(device_of_caller(&dev));
-    return take(p, bytes, dev, Wait::kStream, s);
+    // a stream that is being captured cannot wait for events from outside (nor can the status of the null
+    // stream be had while another one is)
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const bool free_stream = hipStreamIsCapturing(s, &status) == hipSuccess && status == hipStreamCaptureStatusNone;
+    if (!free_stream) (void)hipGetLastError();
+    return take(p, bytes, dev, free_stream ? Wait::kStream : Wait::kNone, s);
 }
 
 int pool_alloc_unordered(void** p, size_t bytes)

@@ -148,3 +148,34 @@ def test_cached_memory_makes_room_for_other_allocations_of_the_library():
     assert torch.cuda.mem_get_info()[0] > free + gib
     del hog
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("n,degree,mean", [(5000, 16, False), (60_000, 61, True)])
+def test_first_normalisation_can_be_captured(n, degree, mean):
+    """Its arrays come from the driver or from blocks without pending work: a stream being captured
+    cannot wait for events of others.  Replays give the values of an eager call."""
+    import paper_2501_01951_amd as mg
+
+    rng = np.random.default_rng(5)
+    src, dst = (torch.from_numpy(rng.integers(0, n, n * degree // 2).astype(np.int32)).cuda() for _ in range(2))
+    flags = mg.SYMMETRIZE | (0 if mean else mg.ADD_SELF_LOOPS)
+    kind = mg.NORM_MEAN if mean else mg.NORM_SYM
+    g, want = (mg.build_csr(src, dst, n, flags) for _ in range(2))
+    mg.build_csr(src, dst, n, flags).free()  # blocks of its work arrays wait in the cache
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side, capture_error_mode="relaxed"):
+        mg.normalize(g, kind, stream=side)
+    mg.normalize(want, kind)
+    h = torch.randn(n, 40, device="cuda")
+    z, z_want = torch.empty_like(h), torch.empty_like(h)
+    mg.aggregate(want, h, z_want, transpose=mean)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(g.arrays()["val"], want.arrays()["val"])
+        mg.aggregate(g, h, z, transpose=mean)
+        assert torch.equal(z, z_want)
+        z.zero_()
+    g.free()
+    want.free()
