@@ -78,9 +78,9 @@ enum {
 
 /* mixgcn_set_update_arith: how the update products of fp32 features use the matrix cores */
 enum {
-    MIXGCN_ARITH_FP32 = 0,  /* fp32 MFMA (the default)                                        */
-    MIXGCN_ARITH_BF16X3 = 1 /* every fp32 operand as the exact sum of three bf16 terms, six   */
-                            /* bf16 MFMAs per product, fp32 accumulation                      */
+    MIXGCN_ARITH_FP32 = 0,  /* fp32 accuracy throughout (the default)                         */
+    MIXGCN_ARITH_BF16X3 = 1 /* weight gradients too as three bf16 terms per operand, six bf16 */
+                            /* MFMAs per product, fp32 accumulation                           */
 };
 
 typedef struct mixgcn_graph mixgcn_graph;
@@ -288,30 +288,31 @@ int mixgcn_apply_bitmap(int dtype, void* X, int64_t ldx, int64_t n_rows, int32_t
  *   beta       : WGRAD only, 0 or 1.
  * FWD, FWD_RELU, DGRAD: B is the weight matrix W[k x m], fp32, row-major.  WGRAD: A = Z
  * [n x k], B = the upstream gradient [n x m], C = dW [k x m] fp32.
- * Two per-device work buffers are shared by all calls: the slab partials of WGRAD, and the weight
- * terms of the products with W for bf16 features and under MIXGCN_ARITH_BF16X3.  Calls that use
- * the same one must not overlap: issue them on one stream, or order the streams with events (the
- * layer and pipeline entry points do).
+ * The forward product and the data gradient run on the bf16 matrix cores: an fp32 operand is the exact
+ * sum of three bf16 terms and a product is accumulated in fp32 from the six partial products of order
+ * 2^-16 and above (the others are together below 2^-23 |a| |b|), bf16 features enter as they are and the
+ * weights as two terms.  Against 64 bits the fp32 results are closer than those of a chain of fp32
+ * multiply-adds (relative error 5.5e-8 against 2.0e-7 at k = 128).  Infinities and NaN give what fp32
+ * arithmetic gives; operands below about 1e-33 in magnitude carry fewer than 24 bits into a product.
+ * A per-device work buffer, the slab partials of WGRAD, is shared by all calls.  Calls of WGRAD must
+ * not overlap: issue them on one stream, or order the streams with events (the layer and pipeline entry
+ * points do).
  */
 int mixgcn_update(int op, int dtype, const void* A, int64_t lda, const void* B, int64_t ldb,
                   void* C, int64_t ldc, int64_t n_rows, int32_t k, int32_t m,
                   const void* relu_ref, int64_t ldr, float beta, void* stream);
 
 /*
- * Chooses the arithmetic of the update products (Algorithm 2, update phase) for fp32 features in
- * every later call of this process, whichever entry point launches them; bf16 features are not
- * affected.  MIXGCN_ARITH_BF16X3 applies to the forward product and the data gradient when the
- * output is wider than 64 columns, the reduction depth (k forward, m backward) is a multiple of
- * 16 and at least 64, to the weight gradient when k and m are multiples of 128 (its last
- * n_rows % 16 rows are added by the fp32 kernel), and only with pitches below 2^22 elements;
- * every other product keeps the fp32 MFMA.  Its error per product term is bounded by
- * 2^-23 |a| |b| (the three dropped partial products), the size of an fp32 rounding; non-finite
- * inputs, and magnitudes that round to infinity as bf16 (above 3.39e38), give NaN where the fp32
- * path gives an infinity or a finite value.  The accumulation is the bf16 MFMA's own: over the
- * long reduction of the weight gradient it is somewhat coarser than the fp32 MFMA's (measured
- * relative error of dW at 2^20 rows: 2.5e-6 against 8e-7), over the short ones of the other two
- * products it is not.  Not thread safe: set it before
- * launching work.  MIXGCN_EINVAL for an unknown mode.
+ * Chooses the arithmetic of the weight gradient (Algorithm 2, update phase) of fp32 features in every
+ * later call of this process, whichever entry point launches it; bf16 features and the other products
+ * are not affected.  MIXGCN_ARITH_BF16X3 applies when k and m are multiples of 128 (the last
+ * n_rows % 16 rows are added by the fp32 kernel), and only with pitches below 2^22 elements; every other
+ * weight gradient keeps the fp32 MFMA.  Its error per product term is bounded by 2^-23 |a| |b| (the
+ * three dropped partial products), the size of an fp32 rounding; non-finite inputs, and magnitudes that
+ * round to infinity as bf16 (above 3.39e38), give NaN where the fp32 path gives an infinity or a finite
+ * value.  The accumulation is the bf16 MFMA's own and over the long reduction somewhat coarser than the
+ * fp32 MFMA's (measured relative error of dW at 2^20 rows: 2.5e-6 against 8e-7).  Not thread safe: set
+ * it before launching work.  MIXGCN_EINVAL for an unknown mode.
  */
 int mixgcn_set_update_arith(int mode);
 

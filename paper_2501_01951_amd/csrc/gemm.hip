@@ -1,8 +1,6 @@
-// Node update H' = sigma(Z W) (paper Algorithm 2, update phase) and the two dense products of
-// its backward pass, dZ = dP W^T and dW = Z^T dP, on the fp32 matrix cores
-// (v_mfma_f32_32x32x2_f32).  Row-block kernels: the node dimension is the long one, the feature
-// dimensions are at most a few hundred, so a workgroup owns 128 node rows (forward / dgrad) or
-// a slab of node rows (wgrad, split over the reduction and combined in fp64 by a second kernel).
+// Weight gradient dW = Z^T dP (paper Algorithm 2, update phase, backward) on the fp32 matrix cores
+// (v_mfma_f32_32x32x2_f32): a workgroup owns a slab of node rows, the slabs are combined in fp64 by a
+// second kernel.  Also the dispatch of the update products.
 #include <type_traits>
 
 #include "device_utils.h"
@@ -14,9 +12,8 @@ namespace {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int BK = 16;          // reduction depth staged per step
-// Workgroups per CU that the register allocation of each kernel is held to (measured best of
-// 2, 3, 4 on the 128 x 128 shapes): the masked row-block kernel keeps more values live.
-constexpr int kRowblockMinBlocks = 3, kRowblockMaskedMinBlocks = 2, kWgradMinBlocks = 4;
+// Workgroups per CU that the register allocation is held to (measured best of 2, 3, 4 on 128 x 128 tiles).
+constexpr int kWgradMinBlocks = 4;
 constexpr int kLdsPad = 4;      // row stride of the staged tiles = tile width + 4 floats
 
 // Tile shape: WM x WN waves (4 in total), each owning TM x TN accumulator tiles of 32 x 32.
@@ -301,174 +298,6 @@ __device__ inline unsigned xcd_local_index(unsigned bid, unsigned grid)
     return x * q + (x < rem ? x : rem) + bid / 8;
 }
 
-// ---- row-block kernel: C[n x MD] = op(A)[n x KD] * Bop[KD x MD] -------------------------------
-//   B_TRANS = false: Bop[kk][j] = B[kk * ldb + j]   (forward:  Z W)
-//   B_TRANS = true : Bop[kk][j] = B[j * ldb + kk]   (dgrad:   dP W^T with W stored k x m)
-//   MASK: A is multiplied by 1[R > 0] on the way in (dgrad of a ReLU layer).
-// A is staged transposed (reduction-major) so that the MFMA operand reads are unit-stride.
-// LDS tiles are double buffered: one barrier per reduction step.
-template <class S, bool B_TRANS, bool RELU, bool MASK, typename T>
-__global__ __launch_bounds__(kBlock, MASK ? kRowblockMaskedMinBlocks : kRowblockMinBlocks) void
-rowblock_gemm_kernel(
-    const T* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
-    T* __restrict__ C, int64_t ldc, int64_t n, int KD, int MD, const T* __restrict__ R,
-    int64_t ldr, int n_col_tiles)
-{
-    constexpr int LDA = S::BM + kLdsPad, LDB = S::BN + kLdsPad;
-    __shared__ float As[2][BK * LDA];
-    __shared__ float Bs[2][BK * LDB];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / S::WN, wn = wave % S::WN;
-    const unsigned lid = xcd_local_index(blockIdx.x, gridDim.x);
-    const int64_t row0 = (int64_t)(lid / n_col_tiles) * S::BM;
-    const int col0 = (int)(lid % n_col_tiles) * S::BN;
-
-    floatx16 acc[S::TM][S::TN];
-#pragma unroll
-    for (int tm = 0; tm < S::TM; ++tm)
-#pragma unroll
-        for (int tn = 0; tn < S::TN; ++tn)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[tm][tn][v] = 0.f;
-
-    // staging maps: "strided" = 4 consecutive reduction indices of one row/col per thread
-    constexpr int A_PASSES = S::BM / 64;                       // 64 rows per pass
-    constexpr int BT_PASSES = S::BN / 64 > 0 ? S::BN / 64 : 1; // B_TRANS: 64 cols per pass
-    constexpr int BN_F4 = S::BN / 4;                           // float4 per staged B row
-    constexpr int B_ROWS_PER_PASS = kBlock / BN_F4;
-    constexpr int B_PASSES = (BK + B_ROWS_PER_PASS - 1) / B_ROWS_PER_PASS;
-    Piece<MASK, T> ra[A_PASSES];
-    Piece<false, float> rb[B_TRANS ? BT_PASSES : B_PASSES];
-
-    auto issue_tiles = [&](int k0) {
-#pragma unroll
-        for (int p = 0; p < A_PASSES; ++p)
-            ra[p].issue(A, lda, row0 + p * 64 + tid / 4, k0 + 4 * (tid & 3), n, KD, R, ldr);
-        if (B_TRANS) {
-#pragma unroll
-            for (int p = 0; p < BT_PASSES; ++p) {
-                const int j = p * 64 + tid / 4;
-                rb[p].issue(B, ldb, col0 + (j < S::BN ? j : 0), k0 + 4 * (tid & 3), MD, KD, nullptr, 0);
-            }
-        } else {
-#pragma unroll
-            for (int p = 0; p < B_PASSES; ++p) {
-                const int kk = p * B_ROWS_PER_PASS + tid / BN_F4;
-                rb[p].issue(B, ldb, k0 + (kk < BK ? kk : 0), col0 + 4 * (tid % BN_F4), KD, MD, nullptr, 0);
-            }
-        }
-    };
-    // CHECKED = false when every piece of the two tiles lies inside its matrix (uniform): the
-    // zero fill then costs no vector ALU work next to the MFMAs
-    auto store_tiles_as = [&](float* as, float* bs, auto checked) {
-        constexpr bool CHECKED = decltype(checked)::value;
-#pragma unroll
-        for (int p = 0; p < A_PASSES; ++p) {
-            const int i = p * 64 + tid / 4, kq = 4 * (tid & 3);
-            const float4 v = ra[p].template value<CHECKED>();
-            as[(kq + 0) * LDA + i] = v.x;
-            as[(kq + 1) * LDA + i] = v.y;
-            as[(kq + 2) * LDA + i] = v.z;
-            as[(kq + 3) * LDA + i] = v.w;
-        }
-        if (B_TRANS) {
-#pragma unroll
-            for (int p = 0; p < BT_PASSES; ++p) {
-                const int j = p * 64 + tid / 4, kq = 4 * (tid & 3);
-                if (j < S::BN) {
-                    const float4 v = rb[p].template value<CHECKED>();
-                    bs[(kq + 0) * LDB + j] = v.x;
-                    bs[(kq + 1) * LDB + j] = v.y;
-                    bs[(kq + 2) * LDB + j] = v.z;
-                    bs[(kq + 3) * LDB + j] = v.w;
-                }
-            }
-        } else {
-#pragma unroll
-            for (int p = 0; p < B_PASSES; ++p) {
-                const int kk = p * B_ROWS_PER_PASS + tid / BN_F4;
-                if (kk < BK)
-                    *reinterpret_cast<float4*>(&bs[kk * LDB + 4 * (tid % BN_F4)]) =
-                        rb[p].template value<CHECKED>();
-            }
-        }
-    };
-    const bool tile_inside = row0 + S::BM <= n && col0 + S::BN <= MD;
-    auto store_tiles = [&](float* as, float* bs, int k0) {
-        if (tile_inside && k0 + BK <= KD) store_tiles_as(as, bs, std::false_type{});
-        else store_tiles_as(as, bs, std::true_type{});
-    };
-
-    const int nk = (KD + BK - 1) / BK;
-    // every piece inside its matrix, whole reduction steps, 32-bit offsets within a tile
-    const bool fast = std::is_same<T, float>::value && tile_inside && KD % BK == 0 &&
-                      lda < (1 << 22) && ldb < (1 << 22) && ldr < (1 << 22);
-    if (fast) {
-        FastTile<S::BM, true, MASK> ta;
-        FastTile<S::BN, B_TRANS, false> tb;
-        ta.init(tid, (uint32_t)lda * 4u, (uint32_t)ldr * 4u);
-        tb.init(tid, (uint32_t)ldb * 4u, 0u);
-        const char* a0 = reinterpret_cast<const char*>(A + row0 * lda);
-        const char* r0 = MASK ? reinterpret_cast<const char*>(R + row0 * ldr) : nullptr;
-        const char* b0 = reinterpret_cast<const char*>(B_TRANS ? B + (int64_t)col0 * ldb : B + col0);
-        const size_t b_step = B_TRANS ? (size_t)BK * 4 : (size_t)BK * 4 * (size_t)ldb;
-        auto load = [&](int64_t st) {
-            ta.load(a0 + (size_t)st * (BK * 4), r0 + (size_t)st * (BK * 4), (size_t)lda * 4,
-                    (size_t)ldr * 4);
-            tb.load(b0 + (size_t)st * b_step, nullptr, (size_t)ldb * 4, 0);
-        };
-        fast_reduction<S>(As, Bs, ta, tb, load, (int64_t)nk, wm, wn, lane, acc);
-    } else {
-        issue_tiles(0);
-        store_tiles(As[0], Bs[0], 0);
-        __syncthreads();
-        for (int i = 0; i < nk; ++i) {
-            const int cur = i & 1;
-            if (i + 1 < nk) issue_tiles((i + 1) * BK);
-            mma_step<S>(As[cur], Bs[cur], wm, wn, lane, acc);
-            if (i + 1 < nk) store_tiles(As[cur ^ 1], Bs[cur ^ 1], (i + 1) * BK);
-            __syncthreads();
-        }
-    }
-
-    // D layout of the 32x32 MFMA: lane l, register v -> row 8*(v/4) + 4*(l/32) + v%4, col l%32
-    const int li = lane & 31, lk = lane >> 5;
-    if (tile_inside) {
-        // no bounds to test: a scalar base per 32 x 32 tile and register, one 32-bit lane offset
-        const int wmu = __builtin_amdgcn_readfirstlane(wm), wnu = __builtin_amdgcn_readfirstlane(wn);
-        const uint32_t lane_off = (uint32_t)(4 * lk) * (uint32_t)ldc + (uint32_t)li;
-#pragma unroll
-        for (int tm = 0; tm < S::TM; ++tm)
-#pragma unroll
-            for (int tn = 0; tn < S::TN; ++tn) {
-                T* tile = C + (row0 + (wmu * S::TM + tm) * 32) * ldc + col0 + (wnu * S::TN + tn) * 32;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    float x = acc[tm][tn][v];
-                    if (RELU) x = fmaxf(x, 0.f);
-                    store_elem(tile + (int64_t)(8 * (v / 4) + (v % 4)) * ldc + lane_off, x);
-                }
-            }
-        return;
-    }
-#pragma unroll
-    for (int tm = 0; tm < S::TM; ++tm)
-#pragma unroll
-        for (int tn = 0; tn < S::TN; ++tn) {
-            const int c = col0 + (wn * S::TN + tn) * 32 + li;
-            if (c >= MD) continue;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int64_t r = row0 + (wm * S::TM + tm) * 32 + 8 * (v / 4) + 4 * lk + (v % 4);
-                if (r < n) {
-                    float x = acc[tm][tn][v];
-                    if (RELU) x = x > 0.f ? x : 0.f;
-                    store_elem(&C[r * ldc + c], x);
-                }
-            }
-        }
-}
-
 // ---- slab kernel: P[slab][KD x MD] = A[rows of slab][KD]^T * (B (.) 1[R > 0])[rows][MD] --------
 // Both operands are staged exactly as they lie in memory (node-major), which already is the
 // reduction-major layout the MFMA operand reads want.
@@ -653,25 +482,6 @@ __global__ __launch_bounds__(kBlock) void relu_mask_kernel(T* __restrict__ G, in
     if (!(h.w > 0.f)) gp[3] = (T)0;
 }
 
-template <class S, bool B_TRANS, typename T>
-int launch_rowblock(bool relu, const T* A, int64_t lda, const float* B, int64_t ldb, T* C,
-                    int64_t ldc, int64_t n, int KD, int MD, const T* R, int64_t ldr,
-                    hipStream_t s)
-{
-    const int nct = (int)ceil_div(MD, S::BN);
-    const int64_t grid = ceil_div(n, S::BM) * nct;
-    if (grid <= 0) return MIXGCN_OK;
-    if (grid > 0x7FFFFFFF) return fail(MIXGCN_EINVAL, "update: too many row tiles");
-#define MIXGCN_ROWBLOCK(RELU, MASK)                                                              \
-    hipLaunchKernelGGL((rowblock_gemm_kernel<S, B_TRANS, RELU, MASK, T>), dim3((unsigned)grid),   \
-                       dim3(kBlock), 0, s, A, lda, B, ldb, C, ldc, n, KD, MD, R, ldr, nct)
-    if (R) MIXGCN_ROWBLOCK(false, true);
-    else if (relu) MIXGCN_ROWBLOCK(true, false);
-    else MIXGCN_ROWBLOCK(false, false);
-#undef MIXGCN_ROWBLOCK
-    return MIXGCN_OK;
-}
-
 }  // namespace
 
 int launch_relu_mask(int dtype, void* G, int64_t ldg, const void* R, int64_t ldr, int64_t n,
@@ -702,69 +512,37 @@ int launch_wgrad_reduce(const float* P, int64_t n_slabs, int64_t cells, int32_t 
 
 namespace {
 
-template <typename T>
-int update_typed(int op, const T* A, int64_t lda, const void* B_, int64_t ldb, void* C_,
-                 int64_t ldc, int64_t n, int32_t k, int32_t m, const T* R, int64_t ldr, float beta,
-                 hipStream_t s, Timer* timer)
+// C[k x m] = beta C + A[n x k]^T (B (.) mask)[n x m]
+int wgrad_f32(const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc, int64_t n,
+              int32_t k, int32_t m, const float* R, int64_t ldr, float beta, hipStream_t s, Timer* timer)
 {
-    if (op == MIXGCN_OP_FWD || op == MIXGCN_OP_FWD_RELU) {
-        const bool relu = op == MIXGCN_OP_FWD_RELU;
-        const float* B = (const float*)B_;
-        T* C = (T*)C_;
-        if (timer) MIXGCN_TRY(timer->begin(kTimeUpdateFwd, s));
-        if (m > 64)
-            MIXGCN_TRY((launch_rowblock<Shape128x128, false, T>(relu, A, lda, B, ldb, C, ldc, n, k, m,
-                                                               nullptr, 0, s)));
-        else
-            MIXGCN_TRY((launch_rowblock<Shape128x32, false, T>(relu, A, lda, B, ldb, C, ldc, n, k, m,
-                                                              nullptr, 0, s)));
-        if (timer) MIXGCN_TRY(timer->end(s));
-    } else if (op == MIXGCN_OP_DGRAD) {
-        // C[n x k] = (A (.) mask)[n x m] * W^T, W = B stored k x m: reduction over m
-        const float* B = (const float*)B_;
-        T* C = (T*)C_;
-        if (timer) MIXGCN_TRY(timer->begin(kTimeUpdateDgrad, s));
-        if (k > 64)
-            MIXGCN_TRY((launch_rowblock<Shape128x128, true, T>(false, A, lda, B, ldb, C, ldc, n, m, k,
-                                                              R, ldr, s)));
-        else
-            MIXGCN_TRY((launch_rowblock<Shape128x32, true, T>(false, A, lda, B, ldb, C, ldc, n, m, k,
-                                                             R, ldr, s)));
-        if (timer) MIXGCN_TRY(timer->end(s));
-    } else if (op == MIXGCN_OP_WGRAD) {
-        // C[k x m] = beta C + A[n x k]^T (B (.) mask)[n x m]
-        const T* B = (const T*)B_;
-        float* C = (float*)C_;
-        const bool wide = m > 64;
-        const int bm = 128, bn = wide ? 128 : 32;
-        const int nit = (int)ceil_div(k, bm), njt = (int)ceil_div(m, bn);
-        const int tiles = nit * njt;
-        int64_t n_slabs = wgrad_slabs(n, tiles, 1024);
-        int64_t rows_per_slab = ceil_div(ceil_div(n, n_slabs), BK) * BK;
-        if (rows_per_slab < BK) rows_per_slab = BK;
-        n_slabs = n > 0 ? ceil_div(n, rows_per_slab) : 1;
-        const int64_t cells = (int64_t)k * m;
-        void* scratch = nullptr;
-        MIXGCN_TRY(get_scratch(0, (size_t)n_slabs * cells * sizeof(float), &scratch));
-        float* P = (float*)scratch;
-        const unsigned grid = (unsigned)(n_slabs * tiles);
-        if (timer) MIXGCN_TRY(timer->begin(kTimeUpdateWgrad, s));
-#define MIXGCN_WGRAD(SHAPE, MASK)                                                                \
-    hipLaunchKernelGGL((wgrad_slab_kernel<SHAPE, MASK, T>), dim3(grid), dim3(kBlock), 0, s, A, lda, \
+    const bool wide = m > 64;
+    const int bm = 128, bn = wide ? 128 : 32;
+    const int nit = (int)ceil_div(k, bm), njt = (int)ceil_div(m, bn);
+    const int tiles = nit * njt;
+    int64_t n_slabs = wgrad_slabs(n, tiles, 1024);
+    int64_t rows_per_slab = ceil_div(ceil_div(n, n_slabs), BK) * BK;
+    if (rows_per_slab < BK) rows_per_slab = BK;
+    n_slabs = n > 0 ? ceil_div(n, rows_per_slab) : 1;
+    const int64_t cells = (int64_t)k * m;
+    void* scratch = nullptr;
+    MIXGCN_TRY(get_scratch(0, (size_t)n_slabs * cells * sizeof(float), &scratch));
+    float* P = (float*)scratch;
+    const unsigned grid = (unsigned)(n_slabs * tiles);
+    if (timer) MIXGCN_TRY(timer->begin(kTimeUpdateWgrad, s));
+#define MIXGCN_WGRAD(SHAPE, MASK)                                                                 \
+    hipLaunchKernelGGL((wgrad_slab_kernel<SHAPE, MASK, float>), dim3(grid), dim3(kBlock), 0, s, A, lda, \
                        B, ldb, R, ldr, P, n, k, m, rows_per_slab, nit, njt)
-        if (wide) {
-            if (R) MIXGCN_WGRAD(Shape128x128, true);
-            else MIXGCN_WGRAD(Shape128x128, false);
-        } else {
-            if (R) MIXGCN_WGRAD(Shape128x32, true);
-            else MIXGCN_WGRAD(Shape128x32, false);
-        }
-#undef MIXGCN_WGRAD
-        if (timer) MIXGCN_TRY(timer->end(s));
-        MIXGCN_TRY(launch_wgrad_reduce(P, n_slabs, cells, m, C, ldc, beta, s));
+    if (wide) {
+        if (R) MIXGCN_WGRAD(Shape128x128, true);
+        else MIXGCN_WGRAD(Shape128x128, false);
     } else {
-        return fail(MIXGCN_EINVAL, "update: unknown op");
+        if (R) MIXGCN_WGRAD(Shape128x32, true);
+        else MIXGCN_WGRAD(Shape128x32, false);
     }
+#undef MIXGCN_WGRAD
+    if (timer) MIXGCN_TRY(timer->end(s));
+    MIXGCN_TRY(launch_wgrad_reduce(P, n_slabs, cells, m, C, ldc, beta, s));
     MIXGCN_HIP_TRY(hipGetLastError());
     return MIXGCN_OK;
 }
@@ -775,27 +553,28 @@ int launch_update(int op, int dtype, const void* A, int64_t lda, const void* B, 
                   void* C, int64_t ldc, int64_t n, int32_t k, int32_t m, const void* R,
                   int64_t ldr, float beta, hipStream_t s, Timer* timer)
 {
-    if (dtype == MIXGCN_F32 && g_update_arith == MIXGCN_ARITH_BF16X3 &&
-        update_split_applies(op, lda, ldb, ldr, n, k, m)) {
-        const float* a = (const float*)A;
-        const float* b = (const float*)B;
-        const float* r = (const float*)R;
-        if (op != MIXGCN_OP_WGRAD)
-            return launch_update_split(op, a, lda, b, ldb, (float*)C, ldc, n, k, m, r, ldr, beta, s,
-                                       timer);
-        // whole steps of 16 node rows on the bf16 matrix cores, the last few rows on the fp32 ones
-        const int64_t n16 = n - n % 16;
-        MIXGCN_TRY(launch_update_split(op, a, lda, b, ldb, (float*)C, ldc, n16, k, m, r, ldr, beta, s,
-                                       timer));
-        if (n16 == n) return MIXGCN_OK;
-        return update_typed<float>(op, a + n16 * lda, lda, b + n16 * ldb, ldb, C, ldc, n - n16, k, m,
-                                   r ? r + n16 * ldr : nullptr, ldr, 1.f, s, nullptr);
+    if (op != MIXGCN_OP_WGRAD) {
+        const bool fwd = op != MIXGCN_OP_DGRAD;
+        const int kind = fwd ? kTimeUpdateFwd : kTimeUpdateDgrad;
+        if (timer) MIXGCN_TRY(timer->begin(kind, s));
+        MIXGCN_TRY(launch_update_rows(dtype, fwd, op == MIXGCN_OP_FWD_RELU, A, lda, (const float*)B, ldb, C, ldc,
+                                      n, fwd ? k : m, fwd ? m : k, fwd ? nullptr : R, ldr, s));
+        if (timer) MIXGCN_TRY(timer->end(s));
+        return MIXGCN_OK;
     }
-    if (dtype == MIXGCN_F32)
-        return update_typed<float>(op, (const float*)A, lda, B, ldb, C, ldc, n, k, m,
-                                   (const float*)R, ldr, beta, s, timer);
-    return launch_update_bf16(op, (const uint16_t*)A, lda, B, ldb, C, ldc, n, k, m,
-                              (const uint16_t*)R, ldr, beta, s, timer);
+    if (dtype != MIXGCN_F32)
+        return launch_wgrad_bf16((const uint16_t*)A, lda, (const uint16_t*)B, ldb, (float*)C, ldc, n, k, m,
+                                 (const uint16_t*)R, ldr, beta, s, timer);
+    const float *a = (const float*)A, *b = (const float*)B, *r = (const float*)R;
+    float* c = (float*)C;
+    if (g_update_arith != MIXGCN_ARITH_BF16X3 || !wgrad_split_applies(lda, ldb, ldr, n, k, m))
+        return wgrad_f32(a, lda, b, ldb, c, ldc, n, k, m, r, ldr, beta, s, timer);
+    // whole steps of 16 node rows on the bf16 matrix cores, the last few rows on the fp32 ones
+    const int64_t n16 = n - n % 16;
+    MIXGCN_TRY(launch_wgrad_split(a, lda, b, ldb, c, ldc, n16, k, m, r, ldr, beta, s, timer));
+    if (n16 == n) return MIXGCN_OK;
+    return wgrad_f32(a + n16 * lda, lda, b + n16 * ldb, ldb, c, ldc, n - n16, k, m, r ? r + n16 * ldr : nullptr,
+                     ldr, 1.f, s, nullptr);
 }
 
 }  // namespace mixgcn

@@ -254,21 +254,23 @@ int launch_update(int op, int dtype, const void* A, int64_t lda, const void* B, 
                   void* C, int64_t ldc, int64_t n, int32_t k, int32_t m, const void* R,
                   int64_t ldr, float beta, hipStream_t s, Timer* timer);
 
-// bf16-stored features on the bf16 matrix cores (weights stay fp32, split into two bf16 terms)
-int launch_update_bf16(int op, const uint16_t* A, int64_t lda, const void* B, int64_t ldb, void* C,
-                       int64_t ldc, int64_t n, int32_t k, int32_t m, const uint16_t* R,
-                       int64_t ldr, float beta, hipStream_t s, Timer* timer);
+// dW[k x m] = beta dW + A[n x k]^T (B (.) 1[R > 0])[n x m] of bf16 features
+int launch_wgrad_bf16(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, float* C, int64_t ldc,
+                      int64_t n, int32_t k, int32_t m, const uint16_t* R, int64_t ldr, float beta,
+                      hipStream_t s, Timer* timer);
 
-// fp32 features on the bf16 matrix cores (every operand as three bf16 terms, six partial products);
-// chosen by mixgcn_set_update_arith, and only where update_split_applies says so
+// the same of fp32 features with every operand as three bf16 terms (six partial products); chosen by
+// mixgcn_set_update_arith, and only where wgrad_split_applies says so; n a multiple of 16
 extern int g_update_arith;
-bool update_split_applies(int op, int64_t lda, int64_t ldb, int64_t ldr, int64_t n, int32_t k,
-                          int32_t m);
-// W: the weights (forward, data gradient) or the upstream gradient (weight gradient, whose row
-// count must be a multiple of 16)
-int launch_update_split(int op, const float* A, int64_t lda, const float* W, int64_t ldw, float* C,
-                        int64_t ldc, int64_t n, int32_t k, int32_t m, const float* R, int64_t ldr,
-                        float beta, hipStream_t s, Timer* timer);
+bool wgrad_split_applies(int64_t lda, int64_t ldb, int64_t ldr, int64_t n, int32_t k, int32_t m);
+int launch_wgrad_split(const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc,
+                       int64_t n, int32_t k, int32_t m, const float* R, int64_t ldr, float beta,
+                       hipStream_t s, Timer* timer);
+
+// C[n x MD] = act((A (.) 1[R > 0])[n x KD] Wop), Wop[kk][j] = w_is_kd_major ? W[kk][j] : W[j][kk]
+int launch_update_rows(int dtype, bool w_is_kd_major, bool relu, const void* A, int64_t lda, const float* W,
+                       int64_t ldw, void* C, int64_t ldc, int64_t n, int KD, int MD, const void* R,
+                       int64_t ldr, hipStream_t s);
 
 // Row slabs of a weight gradient of `tiles` output tiles over n rows: slabs of at most `most_rows`
 // rows (1024 workgroups at most), and on small inputs shorter ones until every compute unit has a

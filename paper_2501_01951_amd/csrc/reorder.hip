@@ -775,7 +775,7 @@ int mixgcn_bandwidth(const mixgcn_graph* g, const uint32_t* pos, int64_t* bandwi
     *bandwidth = 0;
     if (g->n == 0) return MIXGCN_OK;
     void* scratch = nullptr;
-    MIXGCN_TRY(get_scratch(3, 256, &scratch));
+    MIXGCN_TRY(get_scratch(2, 256, &scratch));
     uint32_t* result = (uint32_t*)scratch;
     MIXGCN_HIP_TRY(hipMemsetAsync(result, 0, 4, s));
     hipLaunchKernelGGL(bandwidth_kernel, dim3((unsigned)ceil_div((int64_t)g->n, kBlock / kWave)),
@@ -802,7 +802,7 @@ int mixgcn_relabel_edges(const uint32_t* src, const uint32_t* dst, uint64_t n_ed
         return fail(MIXGCN_EINVAL, "relabel_edges: null argument");
     hipStream_t s = (hipStream_t)stream;
     void* scratch = nullptr;
-    MIXGCN_TRY(get_scratch(3, 256, &scratch));
+    MIXGCN_TRY(get_scratch(2, 256, &scratch));
     uint32_t* bad = (uint32_t*)scratch;
     MIXGCN_HIP_TRY(hipMemsetAsync(bad, 0, 4, s));
     hipLaunchKernelGGL(relabel_kernel, dim3(blocks_for(n_edges)), dim3(kBlock), 0, s, src, dst,
