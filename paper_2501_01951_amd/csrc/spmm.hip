@@ -10,12 +10,22 @@
 // distribution: a hub is spread over many spans, a run of short rows shares one.  Control flow
 // is uniform across the wavefront: the end-of-row marks (bit 31 of an entry's column word) of a
 // batch are collected with one ballot, and only when a row ends inside the batch the sub-group
-// sums are combined with lane shuffles and the row is written.
+// sums are combined and the row is put into LDS, where finished rows wait until there is one for
+// every sub-group; then all lanes apply the epilogue and write them, 16 bytes each.
+//
+// Why rows wait: on graphs that the L2s hold, the ends of rows are what the kernel spends its time on.
+// Written one by one, a row cost three rounds of lane exchanges through LDS and a store by an eighth of
+// the lanes, and every store lies between the gathers in the one counter that a wavefront waits on, so
+// that the gathers in flight got fewer by the stores in flight.  us per launch, one by one -> waiting:
+// 20 k nodes of 16 neighbors, bf16, 47 / 100 / 256 columns: 44.6 / 45.4 / 50.1 -> 22.9 / 24.5 / 29.7;
+// 100 k nodes of 24, bf16, 128: 113 -> 71;  262 k of 32, fp32, 256: 692 -> 638;  1 M of 32, fp32, 16:
+// 360 -> 336;  4096 of 10, fp32, 8 / 64: 14.3 / 15.6 -> 10.9 / 13.1.  Bound by L2 misses, unchanged:
+// 1 M of 32, fp32, 256: 3125 -> 3110.
 //
 // Rows that cross a span boundary are finished by a second, tiny kernel: a wavefront stores the
 // piece that completes a row begun in an earlier span in its "head" slot and the piece of a row
 // it cannot complete in its "tail" slot; the fix-up kernel adds the pieces of each such row in
-// span order.  No atomics: the result is deterministic.
+// span order (eight loads in flight: a hub has hundreds; 1 M nodes, 256 columns 22.0 -> 14.7 us).  No atomics: the result is deterministic.
 //
 // XCD mapping.  The slice index is taken from the low bits of the workgroup index.  Workgroups
 // are dealt round-robin to the 8 XCDs, so every slice is pinned to a fixed subset of the XCDs
@@ -84,6 +94,40 @@ __global__ __launch_bounds__(kBlock) void aggregate_kernel(
     const int64_t coff = (int64_t)c0 + (int64_t)lj * VEC;
     const int64_t coff_load = active ? coff : (int64_t)c0;  // idle lanes re-read column c0
     float* const part = partials + (size_t)sk * 2 * part_stride + (size_t)slice * PW + (size_t)lj * VEC;
+
+    // finished rows waiting to be written, one per sub-group, and the row of this lane's slot
+    __shared__ __attribute__((aligned(16))) float waiting[kBlock / kWave][kWave * VEC];
+    float* const rows = waiting[threadIdx.x >> 6];
+    int filled = 0;  // uniform
+    uint32_t my_row = 0;
+    auto write_rows = [&]() {
+        // what other lanes of the wavefront wrote to LDS is read: LDS operations of a wavefront are done
+        // in order, the fences keep the compiler to it
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        float v[VEC];
+#pragma unroll
+        for (int i = 0; i < VEC; i += 4) {
+            const float4 q = *reinterpret_cast<const float4*>(rows + lane * VEC + i);
+            v[i] = q.x;
+            v[i + 1] = q.y;
+            v[i + 2] = q.z;
+            v[i + 3] = q.w;
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (active && sub < filled) {
+            const int64_t z_row = (int64_t)my_row * ldz;
+            if (relu & kEpiAccumulate) add_stored<DT>(v, Z, z_row + coff);
+            if (relu & kEpiRelu) {
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) v[i] = fmaxf(v[i], 0.f);
+            }
+            if (mask) apply_mask<VEC>(v, mask, ldm, my_row, coff);
+            store_in_range<DT>(Z, z_row, coff, v, c_lo, c_hi);
+        }
+        filled = 0;
+    };
 
     float acc[VEC];
 #pragma unroll
@@ -159,9 +203,10 @@ __global__ __launch_bounds__(kBlock) void aggregate_kernel(
             } else {
                 // Rows end in this batch.  t carries the open row's sum so far; each marked
                 // sub-group closes one row: the lanes up to and including it add their products,
-                // the sub-group sums are combined and the row (or its piece) is written.  acc is
-                // only read here and restarts from zero, so the common multiply-add below is
-                // the one place that writes it.
+                // the sub-group sums are combined and the row (or its piece) is put where it waits
+                // to be written.  acc is only read here and restarts from zero, so the common
+                // multiply-add below is the one place that writes it (adding in place, here and
+                // there, costs nine register copies in every batch).
                 float t[VEC];
 #pragma unroll
                 for (int i = 0; i < VEC; ++i) t[i] = acc[i];
@@ -173,20 +218,13 @@ __global__ __launch_bounds__(kBlock) void aggregate_kernel(
 #pragma unroll
                         for (int i = 0; i < VEC; ++i) t[i] = fmaf(au, x[i], t[i]);
                     }
-                    reduce_subgroups<LPR, VEC>(t);
-                    if (sub == 0 && active) {
-                        if (head) {
-#pragma unroll
-                            for (int i = 0; i < VEC; ++i) part[i] = t[i];
-                        } else {
-                            if (relu & kEpiAccumulate) add_stored<DT>(t, Z, r * ldz + coff);
-                            if (relu & kEpiRelu) {
-#pragma unroll
-                                for (int i = 0; i < VEC; ++i) t[i] = fmaxf(t[i], 0.f);
-                            }
-                            if (mask) apply_mask<VEC>(t, mask, ldm, r, coff);
-                            store_in_range<DT>(Z, r * ldz, coff, t, c_lo, c_hi);
-                        }
+                    if (head) {
+                        combine_subgroups<LPR, VEC>(t, lane, active ? part : nullptr);
+                    } else {
+                        if (filled == EPB) write_rows();
+                        combine_subgroups<LPR, VEC>(t, lane, rows + filled * PW + lj * VEC);
+                        if (sub == filled) my_row = (uint32_t)r;
+                        ++filled;
                     }
                     head = false;
 #pragma unroll
@@ -223,13 +261,8 @@ __global__ __launch_bounds__(kBlock) void aggregate_kernel(
         eb2 = rcv[(int64_t)(b + 3 * D) * EPB];
         round(b + D, ea);
     }
-    if (pending) {
-        reduce_subgroups<LPR, VEC>(acc);
-        if (sub == 0 && active) {
-#pragma unroll
-            for (int i = 0; i < VEC; ++i) part[part_stride + i] = acc[i];
-        }
-    }
+    if (filled) write_rows();
+    if (pending) combine_subgroups<LPR, VEC>(acc, lane, active ? part + part_stride : nullptr);
 }
 
 // One lane group per span boundary; the group whose boundary is the first one crossed by a row
@@ -260,12 +293,32 @@ __global__ __launch_bounds__(kBlock) void aggregate_fixup_kernel(
     const float* p = partials + (size_t)(sk - 1) * 2 * PS + PS + (size_t)lg * VEC;  // tail
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc[i] = p[i];
+    // spans that lie wholly inside the row, up to the one where it ends: eight pieces on their way at a
+    // time, added in span order
+    const int64_t last = (re - 1) / span - span_first;
     int64_t kk = sk;
-    while ((span_first + kk + 1) * span < re) {  // spans that lie wholly inside the row
+    for (; kk + 8 <= last; kk += 8) {
+        float4 q[8][VEC / 4];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int i = 0; i < VEC; i += 4)
+                q[u][i / 4] = *reinterpret_cast<const float4*>(partials + (size_t)(kk + u) * 2 * PS + PS +
+                                                               (size_t)lg * VEC + i);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int i = 0; i < VEC; i += 4) {
+                acc[i] += q[u][i / 4].x;
+                acc[i + 1] += q[u][i / 4].y;
+                acc[i + 2] += q[u][i / 4].z;
+                acc[i + 3] += q[u][i / 4].w;
+            }
+    }
+    for (; kk < last; ++kk) {
         p = partials + (size_t)kk * 2 * PS + PS + (size_t)lg * VEC;
 #pragma unroll
         for (int i = 0; i < VEC; ++i) acc[i] += p[i];
-        ++kk;
     }
     p = partials + (size_t)kk * 2 * PS + (size_t)lg * VEC;  // head of the span where it ends
 #pragma unroll
