@@ -1,6 +1,7 @@
-// Weight gradient dW = Z^T dP (paper Algorithm 2, update phase, backward) on the fp32 matrix cores
-// (v_mfma_f32_32x32x2_f32): a workgroup owns a slab of node rows, the slabs are combined in fp64 by a
-// second kernel.  Also the dispatch of the update products.
+// Dispatch of the update products (paper Algorithm 2, update phase), the reduction of the slabs of a weight
+// gradient, and the weight gradient dW = Z^T dP of fp32 matrices with pitches of 2^22 elements and more on the
+// fp32 matrix cores (v_mfma_f32_32x32x2_f32), with 64-bit offsets throughout; every other one runs on the bf16
+// matrix cores (1.15 to 1.6 times as fast, and closer to 64 bits).
 #include <type_traits>
 
 #include "device_utils.h"
@@ -12,8 +13,7 @@ namespace {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int BK = 16;          // reduction depth staged per step
-// Workgroups per CU that the register allocation is held to (measured best of 2, 3, 4 on 128 x 128 tiles).
-constexpr int kWgradMinBlocks = 4;
+constexpr int kWgradMinBlocks = 4;  // workgroups per CU that the register allocation is held to
 constexpr int kLdsPad = 4;      // row stride of the staged tiles = tile width + 4 floats
 
 // Tile shape: WM x WN waves (4 in total), each owning TM x TN accumulator tiles of 32 x 32.
@@ -24,7 +24,6 @@ struct Shape {
     static constexpr int BN = WN * TN * 32;  // extent along the B-operand free dimension
     static_assert(WM * WN == 4, "four waves per block");
 };
-using Shape128x128 = Shape<2, 2, 2, 2>;
 using Shape128x32 = Shape<4, 1, 1, 1>;
 
 // acc += As[kk][a-rows] (x) Bs[kk][b-cols] over the BK staged reduction steps.  The operand
@@ -135,160 +134,6 @@ struct Piece {
     }
 };
 
-// ---- fast path: tiles that lie wholly inside their matrices, fp32 -------------------------------
-// A vector instruction costs the SIMD four cycles during which its matrix core idles (measured:
-// MFMA and vector work of a SIMD do not overlap on this part), so the inner loop of a tile with
-// nothing to clip is written to need almost none: every global address is a scalar base (stepped
-// with scalar arithmetic) plus a per-thread 32-bit offset that never changes, and every LDS
-// address is a per-thread base plus an immediate.  LDS accesses go through volatile pointers so
-// that the compiler keeps them as single instructions with 16-bit immediates: fused into
-// two-address forms (8-bit offsets) they would need a vector add per pair to rebase.
-typedef __attribute__((address_space(3))) float lds_float;
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) floatx4 lds_floatx4;
-
-// One operand tile of a step: E free indices x BK reduction indices, staged to LDS as [k][e].
-//   TRANSPOSED: memory is [e][k]; an item is 4 consecutive k of one e (4 single-word writes)
-//   DIRECT:     memory is [k][e]; an item is 4 consecutive e of one k (one 16-byte write)
-// Item `tid` of pass p lies a whole number of rows (of memory) after item `tid` of pass 0, so one
-// 32-bit offset per thread serves every pass: the pass only moves the uniform base.
-template <int E, bool TRANSPOSED, bool MASK>
-struct FastTile {
-    static constexpr int LD = E + kLdsPad;
-    static constexpr int ITEMS = TRANSPOSED ? E * (BK / 4) : BK * (E / 4);
-    static constexpr int PASSES = (ITEMS + kBlock - 1) / kBlock;
-    // rows of memory between passes, and floats of LDS between passes
-    static constexpr int PASS_ROWS = TRANSPOSED ? kBlock / (BK / 4) : kBlock / (E / 4);
-    static constexpr int PASS_LDS = TRANSPOSED ? PASS_ROWS : PASS_ROWS * LD;
-    static_assert(PASSES == 1 || ITEMS % kBlock == 0, "whole passes");
-    uint32_t goff, moff;  // byte offset of the thread's item in the operand / the mask reference
-    int lpos;             // float index of the item in the LDS tile
-    bool on;              // the thread has an item (tiles smaller than one pass)
-    float4 v[PASSES], m[PASSES];
-
-    __device__ inline void init(int tid, uint32_t pitch, uint32_t pitch_r)
-    {
-        on = (ITEMS % kBlock == 0) || tid < ITEMS;
-        const int it = on ? tid : 0;
-        if (TRANSPOSED) {
-            const int e = it / (BK / 4), kq = 4 * (it % (BK / 4));
-            goff = (uint32_t)e * pitch + 4u * kq;
-            moff = (uint32_t)e * pitch_r + 4u * kq;
-            lpos = kq * LD + e;
-        } else {
-            const int kk = it / (E / 4), e = 4 * (it % (E / 4));
-            goff = (uint32_t)kk * pitch + 4u * e;
-            moff = (uint32_t)kk * pitch_r + 4u * e;
-            lpos = kk * LD + e;
-        }
-    }
-    // base, base_r: uniform addresses of the step's tile; pitch in bytes
-    __device__ inline void load(const char* base, const char* base_r, size_t pitch, size_t pitch_r)
-    {
-        if (on) {
-#pragma unroll
-            for (int p = 0; p < PASSES; ++p) {
-                v[p] = *reinterpret_cast<const float4*>(base + p * PASS_ROWS * pitch + goff);
-                if (MASK)
-                    m[p] = *reinterpret_cast<const float4*>(base_r + p * PASS_ROWS * pitch_r + moff);
-            }
-        }
-    }
-    __device__ static inline float keep(float x, float r) { return MASK ? (r > 0.f ? x : 0.f) : x; }
-    __device__ inline void store(float* tile) const
-    {
-        if (on) {
-#pragma unroll
-            for (int p = 0; p < PASSES; ++p) {
-                const float x0 = keep(v[p].x, m[p].x), x1 = keep(v[p].y, m[p].y);
-                const float x2 = keep(v[p].z, m[p].z), x3 = keep(v[p].w, m[p].w);
-                if (TRANSPOSED) {
-                    volatile lds_float* o = (volatile lds_float*)(tile + lpos + p * PASS_LDS);
-                    o[0 * LD] = x0;
-                    o[1 * LD] = x1;
-                    o[2 * LD] = x2;
-                    o[3 * LD] = x3;
-                } else {
-                    const floatx4 q = {x0, x1, x2, x3};
-                    *(lds_floatx4*)(tile + lpos + p * PASS_LDS) = q;
-                }
-            }
-        }
-    }
-};
-
-// mma_step with single-word LDS reads at immediate offsets.
-template <class S>
-__device__ inline void mma_step_fast(const float* As, const float* Bs, int wm, int wn, int lane,
-                                     floatx16 (&acc)[S::TM][S::TN])
-{
-    constexpr int LDA = S::BM + kLdsPad, LDB = S::BN + kLdsPad;
-    const int li = lane & 31, lk = lane >> 5;
-    const volatile lds_float* ap = (const volatile lds_float*)(As + lk * LDA + wm * S::TM * 32 + li);
-    const volatile lds_float* bp = (const volatile lds_float*)(Bs + lk * LDB + wn * S::TN * 32 + li);
-    float a[2][S::TM], b[2][S::TN];
-#pragma unroll
-    for (int tm = 0; tm < S::TM; ++tm) a[0][tm] = ap[tm * 32];
-#pragma unroll
-    for (int tn = 0; tn < S::TN; ++tn) b[0][tn] = bp[tn * 32];
-#pragma unroll
-    for (int k2 = 0; k2 < BK; k2 += 2) {
-        const int cur = (k2 >> 1) & 1, nxt = cur ^ 1;
-        if (k2 + 2 < BK) {
-#pragma unroll
-            for (int tm = 0; tm < S::TM; ++tm) a[nxt][tm] = ap[(k2 + 2) * LDA + tm * 32];
-#pragma unroll
-            for (int tn = 0; tn < S::TN; ++tn) b[nxt][tn] = bp[(k2 + 2) * LDB + tn * 32];
-        }
-#pragma unroll
-        for (int tm = 0; tm < S::TM; ++tm)
-#pragma unroll
-            for (int tn = 0; tn < S::TN; ++tn)
-                acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[cur][tm], b[cur][tn],
-                                                                   acc[tm][tn], 0, 0, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, S::TM + S::TN, 0);  // DS reads of step k2 + 2
-        __builtin_amdgcn_sched_group_barrier(0x008, S::TM * S::TN, 0);  // MFMAs of step k2
-    }
-}
-
-// The reduction loop of the fast path: nk full steps, LDS double buffered with compile-time
-// buffer indices (two steps per trip) so that buffer offsets fold into the immediates.
-template <class S, class TA, class TB, class LoadFn>
-__device__ inline void fast_reduction(float (&As)[2][BK * (S::BM + kLdsPad)],
-                                      float (&Bs)[2][BK * (S::BN + kLdsPad)], TA& ta, TB& tb,
-                                      LoadFn load, int64_t nk, int wm, int wn, int lane,
-                                      floatx16 (&acc)[S::TM][S::TN])
-{
-    load((int64_t)0);
-    ta.store(As[0]);
-    tb.store(Bs[0]);
-    __syncthreads();
-    int64_t s = 0;
-    while (s + 2 < nk) {
-        load(s + 1);
-        mma_step_fast<S>(As[0], Bs[0], wm, wn, lane, acc);
-        ta.store(As[1]);
-        tb.store(Bs[1]);
-        __syncthreads();
-        load(s + 2);
-        mma_step_fast<S>(As[1], Bs[1], wm, wn, lane, acc);
-        ta.store(As[0]);
-        tb.store(Bs[0]);
-        __syncthreads();
-        s += 2;
-    }
-    if (s + 1 < nk) {
-        load(s + 1);
-        mma_step_fast<S>(As[0], Bs[0], wm, wn, lane, acc);
-        ta.store(As[1]);
-        tb.store(Bs[1]);
-        __syncthreads();
-        mma_step_fast<S>(As[1], Bs[1], wm, wn, lane, acc);
-    } else {
-        mma_step_fast<S>(As[0], Bs[0], wm, wn, lane, acc);
-    }
-}
-
 // Workgroups are dealt round-robin to the 8 XCDs.  This maps the hardware block index to a
 // logical one such that consecutive logical indices run on the same XCD, so tiles that share
 // an operand (the column tiles of one row block) find it in that XCD's L2.
@@ -369,24 +214,7 @@ __global__ __launch_bounds__(kBlock, kWgradMinBlocks) void wgrad_slab_kernel(
         else store_tiles_as(as, bs, std::true_type{});
     };
 
-    const bool fast = std::is_same<T, float>::value && tile_inside && r_begin < r_end &&
-                      (r_end - r_begin) % BK == 0 && lda < (1 << 22) && ldb < (1 << 22) &&
-                      ldr < (1 << 22);
-    if (fast) {
-        FastTile<S::BM, false, false> ta;
-        FastTile<S::BN, false, MASK> tb;
-        ta.init(tid, (uint32_t)lda * 4u, 0u);
-        tb.init(tid, (uint32_t)ldb * 4u, (uint32_t)ldr * 4u);
-        const char* a0 = reinterpret_cast<const char*>(A + r_begin * lda + i0);
-        const char* b0 = reinterpret_cast<const char*>(B + r_begin * ldb + j0);
-        const char* m0 = MASK ? reinterpret_cast<const char*>(R + r_begin * ldr + j0) : nullptr;
-        auto load = [&](int64_t st) {
-            ta.load(a0 + (size_t)st * BK * 4 * (size_t)lda, nullptr, (size_t)lda * 4, 0);
-            tb.load(b0 + (size_t)st * BK * 4 * (size_t)ldb, m0 + (size_t)st * BK * 4 * (size_t)ldr,
-                    (size_t)ldb * 4, (size_t)ldr * 4);
-        };
-        fast_reduction<S>(As, Bs, ta, tb, load, (r_end - r_begin) / BK, wm, wn, lane, acc);
-    } else if (r_begin < r_end) {
+    if (r_begin < r_end) {
         const int64_t nk = (r_end - r_begin + BK - 1) / BK;
         issue_tiles(r_begin);
         store_tiles(As[0], Bs[0], r_begin);
@@ -401,21 +229,6 @@ __global__ __launch_bounds__(kBlock, kWgradMinBlocks) void wgrad_slab_kernel(
     }
     float* out = P + (size_t)slab * KD * MD;
     const int li = lane & 31, lk = lane >> 5;
-    if (tile_inside) {
-        const int wmu = __builtin_amdgcn_readfirstlane(wm), wnu = __builtin_amdgcn_readfirstlane(wn);
-        const uint32_t lane_off = (uint32_t)(4 * lk) * (uint32_t)MD + (uint32_t)li;
-#pragma unroll
-        for (int tm = 0; tm < S::TM; ++tm)
-#pragma unroll
-            for (int tn = 0; tn < S::TN; ++tn) {
-                float* tile = out + (size_t)(i0 + (wmu * S::TM + tm) * 32) * MD + j0 +
-                              (wnu * S::TN + tn) * 32;
-#pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    tile[(size_t)(8 * (v / 4) + (v % 4)) * MD + lane_off] = acc[tm][tn][v];
-            }
-        return;
-    }
 #pragma unroll
     for (int tm = 0; tm < S::TM; ++tm)
 #pragma unroll
@@ -516,9 +329,7 @@ namespace {
 int wgrad_f32(const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc, int64_t n,
               int32_t k, int32_t m, const float* R, int64_t ldr, float beta, hipStream_t s, Timer* timer)
 {
-    const bool wide = m > 64;
-    const int bm = 128, bn = wide ? 128 : 32;
-    const int nit = (int)ceil_div(k, bm), njt = (int)ceil_div(m, bn);
+    const int nit = (int)ceil_div(k, Shape128x32::BM), njt = (int)ceil_div(m, Shape128x32::BN);
     const int tiles = nit * njt;
     int64_t n_slabs = wgrad_slabs(n, tiles, 1024);
     int64_t rows_per_slab = ceil_div(ceil_div(n, n_slabs), BK) * BK;
@@ -530,16 +341,11 @@ int wgrad_f32(const float* A, int64_t lda, const float* B, int64_t ldb, float* C
     float* P = (float*)scratch;
     const unsigned grid = (unsigned)(n_slabs * tiles);
     if (timer) MIXGCN_TRY(timer->begin(kTimeUpdateWgrad, s));
-#define MIXGCN_WGRAD(SHAPE, MASK)                                                                 \
-    hipLaunchKernelGGL((wgrad_slab_kernel<SHAPE, MASK, float>), dim3(grid), dim3(kBlock), 0, s, A, lda, \
+#define MIXGCN_WGRAD(MASK)                                                                                  \
+    hipLaunchKernelGGL((wgrad_slab_kernel<Shape128x32, MASK, float>), dim3(grid), dim3(kBlock), 0, s, A, lda, \
                        B, ldb, R, ldr, P, n, k, m, rows_per_slab, nit, njt)
-    if (wide) {
-        if (R) MIXGCN_WGRAD(Shape128x128, true);
-        else MIXGCN_WGRAD(Shape128x128, false);
-    } else {
-        if (R) MIXGCN_WGRAD(Shape128x32, true);
-        else MIXGCN_WGRAD(Shape128x32, false);
-    }
+    if (R) MIXGCN_WGRAD(true);
+    else MIXGCN_WGRAD(false);
 #undef MIXGCN_WGRAD
     if (timer) MIXGCN_TRY(timer->end(s));
     MIXGCN_TRY(launch_wgrad_reduce(P, n_slabs, cells, m, C, ldc, beta, s));
@@ -567,14 +373,9 @@ int launch_update(int op, int dtype, const void* A, int64_t lda, const void* B, 
                                  (const uint16_t*)R, ldr, beta, s, timer);
     const float *a = (const float*)A, *b = (const float*)B, *r = (const float*)R;
     float* c = (float*)C;
-    if (g_update_arith != MIXGCN_ARITH_BF16X3 || !wgrad_split_applies(lda, ldb, ldr, n, k, m))
-        return wgrad_f32(a, lda, b, ldb, c, ldc, n, k, m, r, ldr, beta, s, timer);
-    // whole steps of 16 node rows on the bf16 matrix cores, the last few rows on the fp32 ones
-    const int64_t n16 = n - n % 16;
-    MIXGCN_TRY(launch_wgrad_split(a, lda, b, ldb, c, ldc, n16, k, m, r, ldr, beta, s, timer));
-    if (n16 == n) return MIXGCN_OK;
-    return wgrad_f32(a + n16 * lda, lda, b + n16 * ldb, ldb, c, ldc, n - n16, k, m, r ? r + n16 * ldr : nullptr,
-                     ldr, 1.f, s, nullptr);
+    if (wgrad_split_applies(lda, ldb, ldr, n))
+        return launch_wgrad_split(a, lda, b, ldb, c, ldc, n, k, m, r, ldr, beta, s, timer);
+    return wgrad_f32(a, lda, b, ldb, c, ldc, n, k, m, r, ldr, beta, s, timer);
 }
 
 }  // namespace mixgcn

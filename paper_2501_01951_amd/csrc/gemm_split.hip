@@ -1,16 +1,28 @@
-// Weight gradient of fp32 features (paper Algorithm 2, update phase) on the bf16 matrix cores; opt-in
-// (mixgcn_set_update_arith), whole 128 x 128 tiles only.  Every fp32 operand is written as the exact sum
-// of three bf16 terms (round to nearest at each stage),
+// Weight gradient of fp32 features (paper Algorithm 2, update phase) on the bf16 matrix cores.  Every
+// fp32 operand is written as the exact sum of three bf16 terms (round to nearest at each stage),
 //     x = x0 + x1 + x2,   |x1| <= 2^-8 |x|,   |x2| <= 2^-16 |x|,
 // and a product a b is accumulated in fp32 from the six partial products of order 2^-16 and
 // above: a2 b0, a0 b2, a1 b1, a1 b0, a0 b1, a0 b0, smallest first.  The three dropped ones are
-// together below 2^-23 |a| |b|, the size of one fp32 rounding.  Non-finite inputs give NaN.
+// together below 2^-23 |a| |b|, the size of one fp32 rounding.
 //
-// Pipeline of a tile: global loads run two steps ahead in two register sets; LDS is double
-// buffered; the MFMA operands are themselves double buffered in registers, read from LDS one
-// step before their MFMAs, so the only thing between a barrier and the next MFMA is the issue of
-// those reads.  The main loop has no conditional load or store, which lets every wait on a load
-// leave the other register set's loads in flight.
+// Sums.  The matrix cores do not round to nearest: their sums are too low by 9e-9 of a step's partial sum on
+// average, whatever the sign, and over 2^20 rows that adds up to three times the error of fp32 MFMAs.  So the
+// partial products of a step of 16 rows are added up from zero, added to the running sum by the vector units,
+// and odd steps are computed of the negated features and subtracted: what is lost cancels.  Relative error of
+// dW against 64 bits, normal inputs, 2^20 rows 128 x 256: 2.1e-7 (without the negation 2.3e-6, fp32 MFMAs
+// 5.8e-7); 11.1 M rows 128 x 128: 4.7e-7 (7.1e-6, 1.9e-6); 4096 rows 64 x 32: 0.7e-7 (fp32 MFMAs 2.1e-7).
+//
+// Pipeline of a tile: global loads run two steps ahead in two register sets, LDS is double buffered, one
+// barrier per step; the split of the next step's tile and the products of this one are independent of each
+// other.  Rows past a slab's end are read as zeros, so that the loop has no conditional load or store.
+//
+// What bounds it: memory on the wide layers (2^21 rows 128 x 1024 reads and masks 18.2 GB at 4.7 TB/s, a
+// streaming read reaches 5.7), vector work of the splits and the sums (175 instructions beside 24 MFMAs) where
+// a tile has both operands to itself.  us, fp32 MFMAs -> now: 2^20 rows 128 x 256 761 -> 619, 256 x 256
+// 1280 -> 1020, 256 x 47 574 -> 365, 256 x 16 315 -> 282; 2^21 rows 128 x 1024 5100 -> 3900; 11.1 M rows
+// 128 x 128 3170 -> 2520; 232965 rows 602 x 128 458 -> 331; 4096 rows 64 x 100 19.7 -> 15.2.
+#include <type_traits>
+
 #include "device_utils.h"
 #include "internal.h"
 
@@ -22,9 +34,10 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) uintx2 lds_uintx2;
 
-constexpr int BKS = 16;       // reduction depth per step = one MFMA
+constexpr int BKS = 16;       // node rows per step = the reduction depth of one MFMA
 constexpr int kPlanes = 3;
 
 __device__ inline unsigned xcd_local_index(unsigned bid, unsigned grid)
@@ -45,8 +58,8 @@ __device__ inline uint32_t pack_bf16(float a, float b)
 __device__ inline float low_half(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ inline float high_half(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
 
-// Four fp32 of a row on their way to LDS: the three bf16 planes of the (masked) values.
-template <bool MASK>
+// Four fp32 of a row on their way to LDS: the three bf16 planes of the (masked, negated) values.
+template <bool MASK, bool NEGATE>
 __device__ inline void split_store(const float4& a, const float4& r, uint16_t* p0, uint16_t* p1,
                                    uint16_t* p2)
 {
@@ -57,6 +70,7 @@ __device__ inline void split_store(const float4& a, const float4& r, uint16_t* p
         x.z = r.z > 0.f ? x.z : 0.f;
         x.w = r.w > 0.f ? x.w : 0.f;
     }
+    if (NEGATE) x = make_float4(-x.x, -x.y, -x.z, -x.w);
     const uintx2 t0 = {pack_bf16(x.x, x.y), pack_bf16(x.z, x.w)};
     x.x -= low_half(t0.x);
     x.y -= high_half(t0.x);
@@ -100,174 +114,246 @@ __device__ inline bf16x8 read_transposed(const uint16_t* p)
     return o;
 }
 
-template <bool MASK>
+// Sixteen bytes at a byte offset of a step's rows; zeros where the step has no such row.
+__device__ inline float4 load16(__amdgpu_buffer_rsrc_t rows, uint32_t offset)
+{
+    const uintx4 v = __builtin_amdgcn_raw_buffer_load_b128(rows, (int)offset, 0, 0);
+    return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
+}
+__device__ inline float load4(__amdgpu_buffer_rsrc_t rows, uint32_t offset)
+{
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows, (int)offset, 0, 0));
+}
+
+// The rows of a step, `bytes` of them from `first` on, as a buffer: what lies past the slab's end is read as
+// zeros, a step past the end reads nothing, and no load is conditional.
+__device__ inline __amdgpu_buffer_rsrc_t rows_at(const char* first, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(first), 0, bytes, 0x00020000);
+}
+
+template <int BN, bool MASK>
 __global__ __launch_bounds__(kBlock, 2) void wgrad_split_kernel(
     const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
     const float* __restrict__ R, int64_t ldr, float* __restrict__ P, int KD, int MD,
     int64_t rows_per_slab, int64_t n_rows, int n_i_tiles, int n_j_tiles)
 {
-    constexpr int TM = 2, TN = 2;
+    // tile of 128 x BN: 2 x 2 wavefronts of 64 x BN / 2, or (32 columns) four of 32 x 32
+    constexpr int WN = BN > 32 ? 2 : 1, TM = BN > 32 ? 2 : 1, TN = BN / WN / 32;
+    constexpr int PB = BN == 128 ? 2 : 1;  // pieces of B per thread and step
     __shared__ __attribute__((aligned(16))) uint16_t As[2][kPlanes * kWPlane];
     __shared__ __attribute__((aligned(16))) uint16_t Bs[2][kPlanes * kWPlane];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
     const int tiles = n_i_tiles * n_j_tiles;
     const unsigned lid = xcd_local_index(blockIdx.x, gridDim.x);
-    const int64_t slab = lid / tiles;
-    const int t = (int)(lid % tiles);
-    const int i0 = (t / n_j_tiles) * 128, j0 = (t % n_j_tiles) * 128;
+    // (scalar: the division is done in vector registers, and a buffer in those is loaded from in a loop)
+    const int slab = __builtin_amdgcn_readfirstlane((int)(lid / (unsigned)tiles));
+    const int t = __builtin_amdgcn_readfirstlane((int)(lid % (unsigned)tiles));
+    const int i0 = (t / n_j_tiles) * 128, j0 = (t % n_j_tiles) * BN;
     const int64_t r_begin = slab * rows_per_slab;
     const int64_t r_end = (r_begin + rows_per_slab) < n_rows ? (r_begin + rows_per_slab) : n_rows;
-    const int nk = (int)((r_end - r_begin) / BKS);  // whole steps: the caller sees to it
+    int left = __builtin_amdgcn_readfirstlane((int)(r_end - r_begin));  // rows from the load cursor on
+    const int nk = (left + BKS - 1) / BKS;
 
     floatx16 acc[TM][TN];
+    auto clear = [&]() {
 #pragma unroll
-    for (int tm = 0; tm < TM; ++tm)
+        for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn)
+            for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[tm][tn][v] = 0.f;
+                for (int v = 0; v < 16; ++v) acc[tm][tn][v] = 0.f;
+    };
+    clear();
 
-    // staging: thread -> rows tid / 32 and tid / 32 + 8 of the step, features 4 (tid % 32) .. + 3
+    // staging: thread -> rows tid / 32 and tid / 32 + 8 of the step, features 4 (tid % 32) .. + 3 (fewer
+    // columns of B: a row each; of 32 columns the second half of the threads repeats the first).  Features
+    // past the matrix reach only cells of the product that are not stored: any column of the row will do.
     const int srow = tid >> 5, scol = 4 * (tid & 31);
-    uint32_t aoff[2], boff[2], roff[2];
+    const int trow = tid / (BN / 4) % BKS, tcol = 4 * (tid % (BN / 4));
+    const uint32_t acol = 4u * (i0 + (i0 + scol < KD ? scol : 0)), bcol = 4u * (j0 + (j0 + tcol < MD ? tcol : 0));
+    uint32_t aoff[2], boff[PB], roff[PB];
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
-        aoff[p] = (uint32_t)(srow + 8 * p) * (uint32_t)lda * 4u + 4u * scol;
-        boff[p] = (uint32_t)(srow + 8 * p) * (uint32_t)ldb * 4u + 4u * scol;
-        roff[p] = MASK ? (uint32_t)(srow + 8 * p) * (uint32_t)ldr * 4u + 4u * scol : 0u;
+    for (int p = 0; p < 2; ++p) aoff[p] = (uint32_t)(srow + 8 * p) * (uint32_t)lda * 4u + acol;
+#pragma unroll
+    for (int p = 0; p < PB; ++p) {
+        boff[p] = (uint32_t)(trow + 8 * p) * (uint32_t)ldb * 4u + bcol;
+        roff[p] = MASK ? (uint32_t)(trow + 8 * p) * (uint32_t)ldr * 4u + bcol : 0u;
     }
-    const int spos = srow * LDW + scol;
-    const char* a0 = reinterpret_cast<const char*>(A + r_begin * lda + i0);
-    const char* b0 = reinterpret_cast<const char*>(B + r_begin * ldb + j0);
-    const char* m0 = MASK ? reinterpret_cast<const char*>(R + r_begin * ldr + j0) : nullptr;
-    const size_t step_a = (size_t)BKS * 4 * (size_t)lda, step_b = (size_t)BKS * 4 * (size_t)ldb,
-                 step_r = (size_t)BKS * 4 * (size_t)ldr;
+    const int spos = srow * LDW + scol, tpos = trow * LDW + tcol;
 
     struct Regs {
-        float4 a[2], b[2], r[2];
+        float4 a[2], b[PB], r[MASK ? PB : 1];
     };
-    // a step beyond the last one loads the last one again (never stored): no branch around loads
-    auto load = [&](Regs& g, int step) {
-        const size_t sc = (size_t)(step < nk ? step : nk - 1);
+    const char* ap = reinterpret_cast<const char*>(A + r_begin * lda);
+    const char* bp = reinterpret_cast<const char*>(B + r_begin * ldb);
+    const char* rp = MASK ? reinterpret_cast<const char*>(R + r_begin * ldr) : nullptr;
+    const int pa = (int)lda * 4, pb = (int)ldb * 4, pr = (int)ldr * 4;
+    auto load = [&](Regs& g) {
+        const int rows = __builtin_amdgcn_readfirstlane(left >= BKS ? BKS : left > 0 ? left : 0);
+        const auto ra = rows_at(ap, rows * pa), rb = rows_at(bp, rows * pb);
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            g.a[p] = *reinterpret_cast<const float4*>(a0 + sc * step_a + aoff[p]);
-            g.b[p] = *reinterpret_cast<const float4*>(b0 + sc * step_b + boff[p]);
-            if (MASK) g.r[p] = *reinterpret_cast<const float4*>(m0 + sc * step_r + roff[p]);
+        for (int p = 0; p < 2; ++p) g.a[p] = load16(ra, aoff[p]);
+#pragma unroll
+        for (int p = 0; p < PB; ++p) g.b[p] = load16(rb, boff[p]);
+        if (MASK) {
+            const auto rr = rows_at(rp, rows * pr);
+#pragma unroll
+            for (int p = 0; p < PB; ++p) g.r[MASK ? p : 0] = load16(rr, roff[p]);
+            rp += (int64_t)BKS * pr;
         }
+        ap += (int64_t)BKS * pa;
+        bp += (int64_t)BKS * pb;
+        left -= BKS;
     };
-    auto store = [&](const Regs& g, uint16_t* as, uint16_t* bs) {
+    auto store = [&](const Regs& g, uint16_t* as, uint16_t* bs, auto odd) {
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             uint16_t* qa = as + spos + p * 8 * LDW;
-            split_store<false>(g.a[p], g.a[p], qa, qa + kWPlane, qa + 2 * kWPlane);
-            uint16_t* qb = bs + spos + p * 8 * LDW;
-            split_store<MASK>(g.b[p], g.r[p], qb, qb + kWPlane, qb + 2 * kWPlane);
+            split_store<false, decltype(odd)::value>(g.a[p], g.a[p], qa, qa + kWPlane, qa + 2 * kWPlane);
+        }
+#pragma unroll
+        for (int p = 0; p < PB; ++p) {
+            uint16_t* qb = bs + tpos + p * 8 * LDW;
+            split_store<MASK, false>(g.b[p], g.r[MASK ? p : 0], qb, qb + kWPlane, qb + 2 * kWPlane);
         }
     };
     // operand reads: lane -> 16-lane group (feature block, reduction half), place in the group
     const int grp = lane >> 4, gs = lane & 15;
     const int rpos = (8 * (grp >> 1) + (gs >> 2)) * LDW + 16 * (grp & 1) + 4 * (gs & 3);
-    struct Operands {
-        bf16x8 a[kPlanes][TM], b[kPlanes][TN];
-    };
-    auto read_operands = [&](Operands& o, const uint16_t* as, const uint16_t* bs) {
+    // The partial products of a step are added up from zero and then to the running sum, once per step.
+    auto mma = [&](const uint16_t* as, const uint16_t* bs, auto odd) {
+        constexpr int qa[6] = {2, 0, 1, 1, 0, 0};
+        constexpr int qb[6] = {0, 2, 1, 0, 1, 0};
+        bf16x8 a[TM][kPlanes], b[TN][kPlanes];
 #pragma unroll
         for (int p = 0; p < kPlanes; ++p) {
 #pragma unroll
+            for (int tn = 0; tn < TN; ++tn)
+                b[tn][p] = read_transposed(bs + p * kWPlane + rpos + (wn * TN + tn) * 32);
+#pragma unroll
             for (int tm = 0; tm < TM; ++tm)
-                o.a[p][tm] = read_transposed(as + p * kWPlane + rpos + (wm * TM + tm) * 32);
+                a[tm][p] = read_transposed(as + p * kWPlane + rpos + (wm * TM + tm) * 32);
+        }
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) {
+            floatx16 part[TN];
+#pragma unroll
+            for (int q = 0; q < 6; ++q)
+#pragma unroll
+                for (int tn = 0; tn < TN; ++tn) {
+                    const floatx16 zero = {};
+                    part[tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[tm][qa[q]], b[tn][qb[q]],
+                                                                       q == 0 ? zero : part[tn], 0, 0, 0);
+                }
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn)
-                o.b[p][tn] = read_transposed(bs + p * kWPlane + rpos + (wn * TN + tn) * 32);
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[tm][tn][v] += decltype(odd)::value ? -part[tn][v] : part[tn][v];
         }
-    };
-    auto mma = [&](const Operands& o) {
-        constexpr int pa[6] = {2, 0, 1, 1, 0, 0};
-        constexpr int pb[6] = {0, 2, 1, 0, 1, 0};
-#pragma unroll
-        for (int q = 0; q < 6; ++q)
-#pragma unroll
-            for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-                for (int tn = 0; tn < TN; ++tn)
-                    acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        o.a[pa[q]][tm], o.b[pb[q]][tn], acc[tm][tn], 0, 0, 0);
     };
 
     if (nk > 0) {
-        // the pipeline of the row-block kernel: MFMAs of step i on operands read during step
-        // i - 1, operands of step i + 1 read, tiles of step i + 2 split and written, loads two
-        // more steps ahead
+        constexpr std::false_type even{};
+        constexpr std::true_type odd{};
         Regs g0, g1;
-        Operands o0, o1;
-        load(g0, 0);
-        load(g1, 1);
-        store(g0, As[0], Bs[0]);
-        load(g0, 2);
-        if (nk > 1) store(g1, As[1], Bs[1]);
-        load(g1, 3);
+        load(g0);
+        load(g1);
+        store(g0, As[0], Bs[0], even);
+        load(g0);
         __syncthreads();
-        read_operands(o0, As[0], Bs[0]);
-        __syncthreads();
-        int i = 0;
-        for (; i + 3 < nk; i += 2) {
-            read_operands(o1, As[1], Bs[1]);
-            mma(o0);
-            store(g0, As[0], Bs[0]);
-            load(g0, i + 4);
+        for (int i = 0; i + 1 < nk; i += 2) {
+            store(g1, As[1], Bs[1], odd);
+            load(g1);
+            mma(As[0], Bs[0], even);
             __syncthreads();
-            read_operands(o0, As[0], Bs[0]);
-            mma(o1);
-            store(g1, As[1], Bs[1]);
-            load(g1, i + 5);
+            store(g0, As[0], Bs[0], even);
+            load(g0);
+            mma(As[1], Bs[1], odd);
             __syncthreads();
         }
-        const int rem = nk - i;
-        if (rem >= 2) read_operands(o1, As[1], Bs[1]);
-        mma(o0);
-        if (rem >= 3) store(g0, As[0], Bs[0]);
-        if (rem >= 2) {
-            __syncthreads();
-            if (rem >= 3) read_operands(o0, As[0], Bs[0]);
-            mma(o1);
-            if (rem >= 3) mma(o0);
-        }
+        if (nk & 1) mma(As[0], Bs[0], even);
     }
 
     // D layout: lane l, register v -> row 8 (v / 4) + 4 (l / 32) + v % 4, col l % 32
     const int li = lane & 31, lk = lane >> 5;
+    const int iw = i0 + wm * TM * 32, jw = j0 + wn * TN * 32;
+    float z = 0.f;
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const bool in = iw + tm * 32 + 8 * (v / 4) + 4 * lk + (v % 4) < KD && jw + tn * 32 + li < MD;
+                z = fmaf(in ? acc[tm][tn][v] : 0.f, 0.f, z);
+            }
+    if (__builtin_expect(__any(!(z == 0.f)), 0)) {
+        // A sum that is not finite (a term of an infinity is NaN, a value next to the largest float rounds
+        // up to an infinity): the wavefront's tile again on the fp32 matrix cores, straight from memory.
+        // 32x32x2: lane l supplies column l % 32 of reduction index l / 32.
+        clear();
+        uint32_t ca[TM], cb[TN];
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) ca[tm] = 4u * (iw + tm * 32 + li < KD ? iw + tm * 32 + li : i0);
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) cb[tn] = 4u * (jw + tn * 32 + li < MD ? jw + tn * 32 + li : j0);
+        for (int64_t r = r_begin; r < r_end; r += BKS) {
+            const int rows = r_end - r < BKS ? (int)(r_end - r) : BKS;
+            const auto ra = rows_at(reinterpret_cast<const char*>(A + r * lda), rows * pa);
+            const auto rb = rows_at(reinterpret_cast<const char*>(B + r * ldb), rows * pb);
+            const auto rr = MASK ? rows_at(reinterpret_cast<const char*>(R + r * ldr), rows * pr) : rb;
+#pragma unroll 2
+            for (int k2 = 0; k2 < BKS; k2 += 2) {
+                float a[TM], b[TN];
+#pragma unroll
+                for (int tm = 0; tm < TM; ++tm) a[tm] = load4(ra, (uint32_t)((k2 + lk) * pa) + ca[tm]);
+#pragma unroll
+                for (int tn = 0; tn < TN; ++tn) {
+                    b[tn] = load4(rb, (uint32_t)((k2 + lk) * pb) + cb[tn]);
+                    if (MASK)
+                        b[tn] = load4(rr, (uint32_t)((k2 + lk) * pr) + cb[tn]) > 0.f ? b[tn] : 0.f;
+                }
+#pragma unroll
+                for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                    for (int tn = 0; tn < TN; ++tn)
+                        acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[tm], b[tn], acc[tm][tn], 0, 0, 0);
+            }
+        }
+    }
+
     float* out = P + (size_t)slab * KD * MD;
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn) {
-            const int j = j0 + (wn * TN + tn) * 32 + li;
+            const int j = jw + tn * 32 + li;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int i = i0 + (wm * TM + tm) * 32 + 8 * (v / 4) + 4 * lk + (v % 4);
-                out[(size_t)i * MD + j] = acc[tm][tn][v];
+                const int i = iw + tm * 32 + 8 * (v / 4) + 4 * lk + (v % 4);
+                if (i < KD && j < MD) out[(size_t)i * MD + j] = acc[tm][tn][v];
             }
         }
 }
 
 }  // namespace
 
-bool wgrad_split_applies(int64_t lda, int64_t ldb, int64_t ldr, int64_t n, int32_t k, int32_t m)
+bool wgrad_split_applies(int64_t lda, int64_t ldb, int64_t ldr, int64_t n)
 {
-    // 32-bit offsets inside a tile; whole 128 x 128 tiles and at least one whole step of rows
-    if (lda >= (1 << 22) || ldb >= (1 << 22) || ldr >= (1 << 22)) return false;
-    return k % 128 == 0 && m % 128 == 0 && n >= BKS;
+    // a step of 16 rows as one buffer with 32-bit offsets
+    return n > 0 && lda < (1 << 22) && ldb < (1 << 22) && ldr < (1 << 22);
 }
 
-// dW[k x m] = beta dW + A[n x k]^T (B (.) mask)[n x m] for whole 128 x 128 tiles and a row count of
-// whole steps
-int launch_wgrad_split(const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
-                              int64_t ldc, int64_t n, int32_t k, int32_t m, const float* R,
-                              int64_t ldr, float beta, hipStream_t s, Timer* timer)
+// dW[k x m] = beta dW + A[n x k]^T (B (.) mask)[n x m]
+int launch_wgrad_split(const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc, int64_t n,
+                       int32_t k, int32_t m, const float* R, int64_t ldr, float beta, hipStream_t s, Timer* timer)
 {
-    const int nit = k / 128, njt = m / 128, tiles = nit * njt;
+    // The narrowest tile that holds the columns (2^20 rows 256 x 47: 508 us with 128 columns, 360 with 64;
+    // 256 x 16: 333 with 64, 282 with 32).
+    const int bn = m > 64 ? 128 : m > 32 ? 64 : 32;
+    const int nit = (int)ceil_div(k, 128), njt = (int)ceil_div(m, bn), tiles = nit * njt;
     int64_t n_slabs = wgrad_slabs(n, tiles, 1024);
     const int64_t rows_per_slab = ceil_div(ceil_div(n, n_slabs), BKS) * BKS;
     n_slabs = ceil_div(n, rows_per_slab);
@@ -277,12 +363,19 @@ int launch_wgrad_split(const float* A, int64_t lda, const float* B, int64_t ldb,
     float* P = (float*)scratch;
     const unsigned grid = (unsigned)(n_slabs * tiles);
     if (timer) MIXGCN_TRY(timer->begin(kTimeUpdateWgrad, s));
-    if (R)
-        hipLaunchKernelGGL((wgrad_split_kernel<true>), dim3(grid), dim3(kBlock), 0, s, A, lda, B, ldb, R,
-                           ldr, P, k, m, rows_per_slab, n, nit, njt);
-    else
-        hipLaunchKernelGGL((wgrad_split_kernel<false>), dim3(grid), dim3(kBlock), 0, s, A, lda, B, ldb,
-                           R, ldr, P, k, m, rows_per_slab, n, nit, njt);
+#define MIXGCN_WGRAD(BN)                                                                                       \
+    do {                                                                                                       \
+        if (R)                                                                                                 \
+            hipLaunchKernelGGL((wgrad_split_kernel<BN, true>), dim3(grid), dim3(kBlock), 0, s, A, lda, B, ldb, \
+                               R, ldr, P, k, m, rows_per_slab, n, nit, njt);                                   \
+        else                                                                                                   \
+            hipLaunchKernelGGL((wgrad_split_kernel<BN, false>), dim3(grid), dim3(kBlock), 0, s, A, lda, B,     \
+                               ldb, R, ldr, P, k, m, rows_per_slab, n, nit, njt);                              \
+    } while (0)
+    if (bn == 128) MIXGCN_WGRAD(128);
+    else if (bn == 64) MIXGCN_WGRAD(64);
+    else MIXGCN_WGRAD(32);
+#undef MIXGCN_WGRAD
     if (timer) MIXGCN_TRY(timer->end(s));
     MIXGCN_TRY(launch_wgrad_reduce(P, n_slabs, cells, m, C, ldc, beta, s));
     MIXGCN_HIP_TRY(hipGetLastError());

@@ -1,4 +1,4 @@
-"""The row products (forward and data gradient) at the edges of their kernel: 32-row tiles, reduction steps
+"""The update products of rows (forward, data gradient, fp32 weight gradient) at the edges of their kernels: 32-row tiles, reduction steps
 of 128 bytes of a row, weights that stay in LDS and weights that stream through it, output tiles of 16, 32,
 64 and 128 columns; what rows hold past their columns, infinities and NaN."""
 import pytest
@@ -89,3 +89,72 @@ def test_fp32_values_that_are_not_finite(mg, k, m):
     z = torch.rand(n, k, device="cuda", generator=gen) + 0.5
     mg.update(mg.OP_FWD, z, w, out, n, k, m)
     assert out[:, 0].isposinf().all() and not out[:, 1:].isinf().any() and not out.isnan().any()
+
+
+# rows: one, around a step of 16 and around slabs; columns of both operands around the tiles of 32, 64 and 128
+WGRAD_SHAPES = [(1, 1, 1), (15, 3, 32), (16, 33, 33), (17, 127, 64), (130, 129, 65), (1000, 100, 127),
+                (2063, 128, 128), (4096, 64, 32), (3001, 602, 41), (777, 257, 130), (40000, 16, 300)]
+
+
+@pytest.mark.parametrize("n,k,m", WGRAD_SHAPES)
+def test_fp32_weight_gradient_element_by_element(mg, n, k, m):
+    """A dropped term and six roundings of a step's partial sum per product (as above, MFMAs that truncate
+    counted twice), one rounding of the running sum per step of a slab, slabs added in 64 bits, and the
+    rounding of the result."""
+    gen = torch.Generator(device="cuda").manual_seed(n + k + m)
+    z, g, h = (padded(n, c, torch.float32, gen) for c in (k, m, m))
+    for ref in (None, h[:, :m]):
+        for beta in (0.0, 1.0):
+            dw = torch.full((k, (m + 3) // 4 * 4 + 4), 3.0, device="cuda")
+            mg.update(mg.OP_WGRAD, z[:, :k], g[:, :m], dw[:, :m], n, k, m, relu_ref=ref, beta=beta)
+            dp = g[:, :m] if ref is None else torch.where(ref > 0, g[:, :m], torch.zeros_like(g[:, :m]))
+            want = z[:, :k].double().t() @ dp.double() + 3.0 * beta
+            mag = z[:, :k].double().abs().t() @ dp.double().abs()
+            steps = -(-min(n, 1024) // 16)
+            bad = (dw[:, :m].double() - want).abs() > (mag + 3.0) * (26 + steps) * 2.0 ** -24
+            assert not bad.any() and (dw[:, m:] == 3.0).all(), (int(bad.sum()), beta)
+
+
+def test_fp32_weight_gradient_keeps_its_accuracy_over_many_rows(mg):
+    """What the matrix cores lose by truncation does not add up over the rows: normal inputs, relative error
+    below 64 roundings of 2^-25 added as a random walk (64 steps in a slab) with room for the partial sums;
+    a drift of the truncation would give 2e-6 here."""
+    n, k, m = 1 << 19, 128, 128
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    z, g = (torch.randn(n, c, device="cuda", generator=gen) for c in (k, m))
+    dw = torch.empty(k, m, device="cuda")
+    mg.update(mg.OP_WGRAD, z, g, dw, n, k, m)
+    ref = z.double().t() @ g.double()
+    assert (dw.double() - ref).norm() <= 8 * 2.0 ** -24 * ref.norm()
+
+
+@pytest.mark.parametrize("m", [128, 40, 16])
+def test_fp32_weight_gradient_of_values_that_are_not_finite(mg, m):
+    n, k = 1100, 200
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    z = torch.rand(n, k, device="cuda", generator=gen) + 0.5
+    g = torch.rand(n, m, device="cuda", generator=gen) * 0.25 + 0.25
+    z[3, 5], z[40, 20], z[70, 140], z[1099, 150] = float("inf"), float("nan"), 3.4e38, -float("inf")
+    dw = torch.empty(k, m, device="cuda")
+    mg.update(mg.OP_WGRAD, z, g, dw, n, k, m)
+    ref = (z.double().t() @ g.double()).float()
+    assert torch.equal(dw.isnan(), ref.isnan()) and torch.equal(dw.isposinf(), ref.isposinf())
+    assert torch.equal(dw.isneginf(), ref.isneginf())
+    fin = ref.isfinite()
+    assert ((dw - ref)[fin].abs() <= 1e-5 * ref[fin].abs()).all()
+    # the ReLU derivative takes an infinity of the gradient out
+    h = torch.ones(n, m, device="cuda")
+    h[7], g[7] = -1.0, float("inf")
+    mg.update(mg.OP_WGRAD, z[:, :4], g, dw[:4], n, 4, m, relu_ref=h)
+    assert dw[:4].isfinite().all()
+
+
+def test_fp32_weight_gradient_of_a_pitch_past_32_bit_offsets(mg):
+    n, k, m, pitch = 19, 70, 40, 1 << 22
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    z = torch.empty(n * pitch, device="cuda").view(n, pitch)[:, :k]
+    z.copy_(torch.randn(n, k, device="cuda", generator=gen))
+    g, h = (torch.randn(n, m, device="cuda", generator=gen) for _ in range(2))
+    dw = torch.empty(k, m, device="cuda")
+    mg.update(mg.OP_WGRAD, z, g, dw, n, k, m, relu_ref=h)
+    check(dw, z.t(), torch.where(h > 0, g, torch.zeros_like(g)), torch.float32, n, "weight gradient")
