@@ -293,9 +293,10 @@ int mixgcn_apply_bitmap(int dtype, void* X, int64_t ldx, int64_t n_rows, int32_t
  * weights as two terms.  Against 64 bits the fp32 results are closer than those of a chain of fp32
  * multiply-adds (relative error 5.5e-8 against 2.0e-7 at k = 128).  Infinities and NaN give what fp32
  * arithmetic gives; operands below about 1e-33 in magnitude carry fewer than 24 bits into a product.
- * A per-device work buffer, the slab partials of WGRAD, is shared by all calls.  Calls of WGRAD must
- * not overlap: issue them on one stream, or order the streams with events (the layer and pipeline entry
- * points do).
+ * Two per-device work buffers are shared by all calls: the slab partials of WGRAD, and the weight terms of
+ * bf16 products whose weights do not fit LDS (more than 256 reduction indices).  Calls that use the same one
+ * must not overlap: issue them on one stream, or order the streams with events (the layer and pipeline
+ * entry points do).
  */
 int mixgcn_update(int op, int dtype, const void* A, int64_t lda, const void* B, int64_t ldb,
                   void* C, int64_t ldc, int64_t n_rows, int32_t k, int32_t m,

@@ -30,7 +30,7 @@ struct Scratch {
     size_t bytes = 0;
 };
 constexpr int kMaxDevices = 16;
-constexpr int kScratchKinds = 3;  // wgrad slabs, loss partials, small results
+constexpr int kScratchKinds = 4;  // wgrad slabs, loss partials, small results, split weights
 Scratch g_scratch[kMaxDevices][kScratchKinds];
 std::mutex g_scratch_mu;
 }  // namespace

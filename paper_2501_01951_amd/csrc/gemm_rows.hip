@@ -13,8 +13,8 @@
 // 120 to 128 KB); its eight wavefronts then walk 32-row tiles of their own without a barrier, each with
 // the rows of the next two steps in flight from global memory straight to registers (16 rows of 64 bytes
 // per load: such a read runs at the streaming rate, 6.1 TB/s).  No other wavefront needs a row, so
-// nothing is gained from LDS, and a term split happens once.  Deeper products stream the weights through
-// two LDS buffers, split on the way, one barrier per step.
+// nothing is gained from LDS, and a term split happens once.  Deeper fp32 products stream the weights
+// through two LDS buffers, split on the way, one barrier per step; deeper bf16 ones have a kernel of their own.
 //
 // What bounds it: memory (a copy in the same pattern reaches 5.2 TB/s) up to 128 x 128, from there on
 // about evenly the matrix cores and the vector work of the splits.  Six bf16 MFMAs take 3/8 of the time
@@ -623,6 +623,9 @@ int launch_rows_tn(bool relu, const RowsArgs& args, hipStream_t s)
     constexpr int kChunkBytes = TN * Terms<DT>::NB * Terms<DT>::PB * 1024;
     const int nch = (a.KD + KC - 1) / KC;
     const bool resident = nch * kChunkBytes <= kRowsLds;
+    if (DT == MIXGCN_BF16 && !resident)
+        return launch_update_bf16_deep(WT, relu, (const uint16_t*)a.A, a.lda, a.W, a.ldw, (uint16_t*)a.C, a.ldc,
+                                       a.n, a.KD, a.MD, (const uint16_t*)a.R, a.ldr, s);
     a.n_col_tiles = (int)ceil_div(a.MD, TN * 16);
     const int64_t tiles = ceil_div(a.n, kWaveRows);
     // One workgroup per compute unit.  Where there are fewer tiles than wavefronts the workgroups get
@@ -639,12 +642,12 @@ int launch_rows_tn(bool relu, const RowsArgs& args, hipStream_t s)
     const unsigned lds = (unsigned)((resident ? nch : 2) * kChunkBytes);
 #define MIXGCN_ROWS(RELU, MASK)                                                                       \
     do {                                                                                              \
-        if (resident)                                                                                 \
+        if (DT == MIXGCN_BF16 || resident)                                                            \
             hipLaunchKernelGGL((update_rows_kernel<DT, TN, WT, RELU, MASK, true>), dim3(grid),        \
                                dim3(kRowsBlock), lds, s, a);                                          \
         else                                                                                          \
-            hipLaunchKernelGGL((update_rows_kernel<DT, TN, WT, RELU, MASK, false>), dim3(grid),       \
-                               dim3(kRowsBlock), lds, s, a);                                          \
+            hipLaunchKernelGGL((update_rows_kernel<DT, TN, WT, RELU, MASK, DT == MIXGCN_BF16>),       \
+                               dim3(grid), dim3(kRowsBlock), lds, s, a);                              \
     } while (0)
     if constexpr (WT) {
         if (relu) MIXGCN_ROWS(true, false);

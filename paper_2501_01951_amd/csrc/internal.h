@@ -265,6 +265,11 @@ int launch_wgrad_split(const float* A, int64_t lda, const float* B, int64_t ldb,
                        int64_t n, int32_t k, int32_t m, const float* R, int64_t ldr, float beta,
                        hipStream_t s, Timer* timer);
 
+// bf16 features and weights that do not fit LDS; launch_update_rows chooses it
+int launch_update_bf16_deep(bool w_is_kd_major, bool relu, const uint16_t* A, int64_t lda, const float* W,
+                            int64_t ldw, uint16_t* C, int64_t ldc, int64_t n, int KD, int MD,
+                            const uint16_t* R, int64_t ldr, hipStream_t s);
+
 // C[n x MD] = act((A (.) 1[R > 0])[n x KD] Wop), Wop[kk][j] = w_is_kd_major ? W[kk][j] : W[j][kk]
 int launch_update_rows(int dtype, bool w_is_kd_major, bool relu, const void* A, int64_t lda, const float* W,
                        int64_t ldw, void* C, int64_t ldc, int64_t n, int KD, int MD, const void* R,
