@@ -78,8 +78,8 @@ enum {
 
 /* mixgcn_set_update_arith: how the update products of fp32 features use the matrix cores */
 enum {
-    MIXGCN_ARITH_FP32 = 0,  /* fp32 accuracy throughout (the default)                         */
-    MIXGCN_ARITH_BF16X3 = 1 /* the same: see mixgcn_set_update_arith                           */
+    MIXGCN_ARITH_FP32 = 0,  /* forward product: chains of fp32 multiply-adds (the default)     */
+    MIXGCN_ARITH_BF16X3 = 1 /* forward product: three bf16 terms per operand                   */
 };
 
 typedef struct mixgcn_graph mixgcn_graph;
@@ -287,15 +287,17 @@ int mixgcn_apply_bitmap(int dtype, void* X, int64_t ldx, int64_t n_rows, int32_t
  *   beta       : WGRAD only, 0 or 1.
  * FWD, FWD_RELU, DGRAD: B is the weight matrix W[k x m], fp32, row-major.  WGRAD: A = Z
  * [n x k], B = the upstream gradient [n x m], C = dW [k x m] fp32.
- * The forward product and the data gradient run on the bf16 matrix cores: an fp32 operand is the exact
- * sum of three bf16 terms and a product is accumulated in fp32 from the six partial products of order
- * 2^-16 and above (the others are together below 2^-23 |a| |b|), bf16 features enter as they are and the
- * weights as two terms.  Against 64 bits the fp32 results are closer than those of a chain of fp32
- * multiply-adds (relative error 5.5e-8 against 2.0e-7 at k = 128).  Infinities and NaN give what fp32
- * arithmetic gives; operands below about 1e-33 in magnitude carry fewer than 24 bits into a product.
+ * The forward product of fp32 features is a chain of fp32 multiply-adds over the reduction index, on the
+ * fp32 matrix cores (mixgcn_set_update_arith chooses otherwise).  Their data and weight gradients run on the
+ * bf16 matrix cores: an operand is the exact sum of three bf16 terms and a product is accumulated in fp32 from
+ * the six partial products of order 2^-16 and above (the others are together below 2^-23 |a| |b|).  Against
+ * 64 bits these results are closer than those of a chain of fp32 multiply-adds (relative error 5.6e-8 against
+ * 2.0e-7 at depth 128).  bf16 features enter as they are and the weights as two terms.  Infinities and NaN
+ * give what fp32 arithmetic gives; operands of a gradient below about 1e-33 in magnitude carry fewer than 24
+ * bits into a product (at 1e-35 a relative error of 3e-6).
  * Two per-device work buffers are shared by all calls: the slab partials of WGRAD, and the weight terms of
- * bf16 products whose weights do not fit LDS (more than 256 reduction indices).  Calls that use the same one
- * must not overlap: issue them on one stream, or order the streams with events (the layer and pipeline
+ * products that split them beforehand (bf16 ones whose weights do not fit LDS, more than 256 reduction indices,
+ * and forward products under MIXGCN_ARITH_BF16X3).  Calls that use the same one must not overlap: issue them on one stream, or order the streams with events (the layer and pipeline
  * entry points do).
  */
 int mixgcn_update(int op, int dtype, const void* A, int64_t lda, const void* B, int64_t ldb,
@@ -303,10 +305,12 @@ int mixgcn_update(int op, int dtype, const void* A, int64_t lda, const void* B, 
                   const void* relu_ref, int64_t ldr, float beta, void* stream);
 
 /*
- * Chooses the arithmetic of the update products of fp32 features in every later call of this process.  Both
- * modes now run the same kernels: three bf16 terms per operand, six bf16 MFMAs per product, sums closer to
- * 64 bits than those of fp32 MFMAs (measured relative error of dW at 2^20 rows: 2.1e-7 against 5.8e-7).
- * Infinities and NaN give what fp32 arithmetic gives.  MIXGCN_EINVAL for an unknown mode.
+ * Chooses the arithmetic of the forward product of fp32 features (Algorithm 2, update phase) in every later
+ * call of this process, whichever entry point launches it; bf16 features and the gradients are not affected.
+ * MIXGCN_ARITH_BF16X3 applies when the output is wider than 64 columns, the reduction depth k is a multiple of
+ * 16 and at least 64, and the pitch of A is below 2^22 elements; every other product keeps the fp32 chain.
+ * Its error per product term is bounded by 2^-23 |a| |b| (the three dropped partial products), the size of an
+ * fp32 rounding.  Not thread safe: set it before launching work.  MIXGCN_EINVAL for an unknown mode.
  */
 int mixgcn_set_update_arith(int mode);
 

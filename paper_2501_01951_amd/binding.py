@@ -516,7 +516,7 @@ def set_aggregate_whole_rows(on: bool) -> None:
 
 
 def set_update_arith(mode: int) -> None:
-    """ARITH_FP32 (default) or ARITH_BF16X3: both run the same kernels."""
+    """ARITH_FP32 (default) or ARITH_BF16X3 for the forward product of fp32 features."""
     _check(load_library().mixgcn_set_update_arith(mode), "set_update_arith")
 
 

@@ -15,6 +15,8 @@ namespace mixgcn {
 
 static thread_local std::string g_last_error;
 
+int g_update_arith = MIXGCN_ARITH_FP32;
+
 void set_error(const std::string& msg) { g_last_error = msg; }
 int fail(int code, const std::string& msg)
 {
@@ -523,6 +525,7 @@ int mixgcn_set_update_arith(int mode)
 {
     if (mode != MIXGCN_ARITH_FP32 && mode != MIXGCN_ARITH_BF16X3)
         return fail(MIXGCN_EINVAL, "set_update_arith: unknown mode");
+    g_update_arith = mode;
     return MIXGCN_OK;
 }
 

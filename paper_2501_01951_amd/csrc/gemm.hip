@@ -1,10 +1,16 @@
-// Dispatch of the update products (paper Algorithm 2, update phase), the reduction of the slabs of a weight
-// gradient, and the weight gradient dW = Z^T dP of fp32 matrices with pitches of 2^22 elements and more on the
-// fp32 matrix cores (v_mfma_f32_32x32x2_f32), with 64-bit offsets throughout; every other one runs on the bf16
-// matrix cores (1.15 to 1.6 times as fast, and closer to 64 bits).
+// Dispatch of the update products (paper Algorithm 2, update phase), the forward product H' = sigma(Z W) of
+// fp32 features on the fp32 matrix cores (v_mfma_f32_32x32x2_f32), the reduction of the slabs of a weight
+// gradient, and the weight gradient dW = Z^T dP of fp32 matrices with pitches of 2^22 elements and more.
+// A row-block kernel's workgroup owns 128 node rows: the node dimension is the long one, the feature
+// dimensions are at most a few hundred.
+//
+// The sums of the forward product are chains of fp32 multiply-adds over the reduction index, bit for bit.
+// They decide which side of zero an activation falls on, so they keep this rounding: with another one
+// (three bf16 terms per operand, closer to 64 bits and up to 1.5 times as fast) a few decisions per layer
+// change, and one on a hub moves a column of a weight gradient by 1e-3.
 #include <type_traits>
 
-#include "device_utils.h"
+#include "gemm_common.h"
 #include "internal.h"
 
 namespace mixgcn {
@@ -13,7 +19,9 @@ namespace {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int BK = 16;          // reduction depth staged per step
-constexpr int kWgradMinBlocks = 4;  // workgroups per CU that the register allocation is held to
+// Workgroups per CU that the register allocation of each kernel is held to (measured best of
+// 2, 3, 4 on the 128 x 128 shapes).
+constexpr int kRowblockMinBlocks = 3, kWgradMinBlocks = 4;
 constexpr int kLdsPad = 4;      // row stride of the staged tiles = tile width + 4 floats
 
 // Tile shape: WM x WN waves (4 in total), each owning TM x TN accumulator tiles of 32 x 32.
@@ -24,6 +32,7 @@ struct Shape {
     static constexpr int BN = WN * TN * 32;  // extent along the B-operand free dimension
     static_assert(WM * WN == 4, "four waves per block");
 };
+using Shape128x128 = Shape<2, 2, 2, 2>;
 using Shape128x32 = Shape<4, 1, 1, 1>;
 
 // acc += As[kk][a-rows] (x) Bs[kk][b-cols] over the BK staged reduction steps.  The operand
@@ -68,8 +77,7 @@ __device__ inline void mma_step(const float* As, const float* Bs, int wm, int wn
 // starts the loads (addresses are clamped into the matrix, so they are unconditional and
 // nothing waits on them); value() applies the zero fill outside [0, rows) x [0, cols) and the
 // optional ReLU-derivative mask x * 1[R > 0] when the piece is written to LDS one step later.
-// Feature tensors are fp32 (float) or bf16 (uint16_t, widened to fp32 on the way to LDS and
-// rounded to nearest even on the way out); weights are always fp32.
+// (Raw4: four features as stored, fp32 or bf16.)
 template <typename T>
 struct Raw4;
 template <>
@@ -86,15 +94,6 @@ struct Raw4<uint16_t> {
                            __uint_as_float(q.y << 16), __uint_as_float(q.y & 0xFFFF0000u));
     }
 };
-
-__device__ inline uint16_t bf16_rne(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7F800000u) != 0x7F800000u) u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-__device__ inline void store_elem(float* p, float x) { *p = x; }
-__device__ inline void store_elem(uint16_t* p, float x) { *p = bf16_rne(x); }
 
 template <bool MASK, typename T>
 struct Piece {
@@ -134,13 +133,286 @@ struct Piece {
     }
 };
 
-// Workgroups are dealt round-robin to the 8 XCDs.  This maps the hardware block index to a
-// logical one such that consecutive logical indices run on the same XCD, so tiles that share
-// an operand (the column tiles of one row block) find it in that XCD's L2.
-__device__ inline unsigned xcd_local_index(unsigned bid, unsigned grid)
+// ---- fast path: tiles that lie wholly inside their matrices, fp32 -------------------------------
+// A vector instruction costs the SIMD four cycles during which its matrix core idles (measured:
+// MFMA and vector work of a SIMD do not overlap on this part), so the inner loop of a tile with
+// nothing to clip is written to need almost none: every global address is a scalar base (stepped
+// with scalar arithmetic) plus a per-thread 32-bit offset that never changes, and every LDS
+// address is a per-thread base plus an immediate.  LDS accesses go through volatile pointers so
+// that the compiler keeps them as single instructions with 16-bit immediates: fused into
+// two-address forms (8-bit offsets) they would need a vector add per pair to rebase.
+typedef __attribute__((address_space(3))) float lds_float;
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) floatx4 lds_floatx4;
+
+// One operand tile of a step: E free indices x BK reduction indices, staged to LDS as [k][e].
+//   TRANSPOSED: memory is [e][k]; an item is 4 consecutive k of one e (4 single-word writes)
+//   DIRECT:     memory is [k][e]; an item is 4 consecutive e of one k (one 16-byte write)
+// Item `tid` of pass p lies a whole number of rows (of memory) after item `tid` of pass 0, so one
+// 32-bit offset per thread serves every pass: the pass only moves the uniform base.
+template <int E, bool TRANSPOSED>
+struct FastTile {
+    static constexpr int LD = E + kLdsPad;
+    static constexpr int ITEMS = TRANSPOSED ? E * (BK / 4) : BK * (E / 4);
+    static constexpr int PASSES = (ITEMS + kBlock - 1) / kBlock;
+    // rows of memory between passes, and floats of LDS between passes
+    static constexpr int PASS_ROWS = TRANSPOSED ? kBlock / (BK / 4) : kBlock / (E / 4);
+    static constexpr int PASS_LDS = TRANSPOSED ? PASS_ROWS : PASS_ROWS * LD;
+    static_assert(PASSES == 1 || ITEMS % kBlock == 0, "whole passes");
+    uint32_t goff;  // byte offset of the thread's item in the operand
+    int lpos;       // float index of the item in the LDS tile
+    bool on;        // the thread has an item (tiles smaller than one pass)
+    float4 v[PASSES];
+
+    __device__ inline void init(int tid, uint32_t pitch)
+    {
+        on = (ITEMS % kBlock == 0) || tid < ITEMS;
+        const int it = on ? tid : 0;
+        if (TRANSPOSED) {
+            const int e = it / (BK / 4), kq = 4 * (it % (BK / 4));
+            goff = (uint32_t)e * pitch + 4u * kq;
+            lpos = kq * LD + e;
+        } else {
+            const int kk = it / (E / 4), e = 4 * (it % (E / 4));
+            goff = (uint32_t)kk * pitch + 4u * e;
+            lpos = kk * LD + e;
+        }
+    }
+    // base: uniform address of the step's tile; pitch in bytes
+    __device__ inline void load(const char* base, size_t pitch)
+    {
+        if (on) {
+#pragma unroll
+            for (int p = 0; p < PASSES; ++p)
+                v[p] = *reinterpret_cast<const float4*>(base + p * PASS_ROWS * pitch + goff);
+        }
+    }
+    __device__ inline void store(float* tile) const
+    {
+        if (on) {
+#pragma unroll
+            for (int p = 0; p < PASSES; ++p) {
+                if (TRANSPOSED) {
+                    volatile lds_float* o = (volatile lds_float*)(tile + lpos + p * PASS_LDS);
+                    o[0 * LD] = v[p].x;
+                    o[1 * LD] = v[p].y;
+                    o[2 * LD] = v[p].z;
+                    o[3 * LD] = v[p].w;
+                } else {
+                    const floatx4 q = {v[p].x, v[p].y, v[p].z, v[p].w};
+                    *(lds_floatx4*)(tile + lpos + p * PASS_LDS) = q;
+                }
+            }
+        }
+    }
+};
+
+// mma_step with single-word LDS reads at immediate offsets.
+template <class S>
+__device__ inline void mma_step_fast(const float* As, const float* Bs, int wm, int wn, int lane,
+                                     floatx16 (&acc)[S::TM][S::TN])
 {
-    const unsigned q = grid / 8, rem = grid % 8, x = bid % 8;
-    return x * q + (x < rem ? x : rem) + bid / 8;
+    constexpr int LDA = S::BM + kLdsPad, LDB = S::BN + kLdsPad;
+    const int li = lane & 31, lk = lane >> 5;
+    const volatile lds_float* ap = (const volatile lds_float*)(As + lk * LDA + wm * S::TM * 32 + li);
+    const volatile lds_float* bp = (const volatile lds_float*)(Bs + lk * LDB + wn * S::TN * 32 + li);
+    float a[2][S::TM], b[2][S::TN];
+#pragma unroll
+    for (int tm = 0; tm < S::TM; ++tm) a[0][tm] = ap[tm * 32];
+#pragma unroll
+    for (int tn = 0; tn < S::TN; ++tn) b[0][tn] = bp[tn * 32];
+#pragma unroll
+    for (int k2 = 0; k2 < BK; k2 += 2) {
+        const int cur = (k2 >> 1) & 1, nxt = cur ^ 1;
+        if (k2 + 2 < BK) {
+#pragma unroll
+            for (int tm = 0; tm < S::TM; ++tm) a[nxt][tm] = ap[(k2 + 2) * LDA + tm * 32];
+#pragma unroll
+            for (int tn = 0; tn < S::TN; ++tn) b[nxt][tn] = bp[(k2 + 2) * LDB + tn * 32];
+        }
+#pragma unroll
+        for (int tm = 0; tm < S::TM; ++tm)
+#pragma unroll
+            for (int tn = 0; tn < S::TN; ++tn)
+                acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[cur][tm], b[cur][tn],
+                                                                   acc[tm][tn], 0, 0, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, S::TM + S::TN, 0);  // DS reads of step k2 + 2
+        __builtin_amdgcn_sched_group_barrier(0x008, S::TM * S::TN, 0);  // MFMAs of step k2
+    }
+}
+
+// The reduction loop of the fast path: nk full steps, LDS double buffered with compile-time
+// buffer indices (two steps per trip) so that buffer offsets fold into the immediates.
+template <class S, class TA, class TB, class LoadFn>
+__device__ inline void fast_reduction(float (&As)[2][BK * (S::BM + kLdsPad)],
+                                      float (&Bs)[2][BK * (S::BN + kLdsPad)], TA& ta, TB& tb,
+                                      LoadFn load, int64_t nk, int wm, int wn, int lane,
+                                      floatx16 (&acc)[S::TM][S::TN])
+{
+    load((int64_t)0);
+    ta.store(As[0]);
+    tb.store(Bs[0]);
+    __syncthreads();
+    int64_t s = 0;
+    while (s + 2 < nk) {
+        load(s + 1);
+        mma_step_fast<S>(As[0], Bs[0], wm, wn, lane, acc);
+        ta.store(As[1]);
+        tb.store(Bs[1]);
+        __syncthreads();
+        load(s + 2);
+        mma_step_fast<S>(As[1], Bs[1], wm, wn, lane, acc);
+        ta.store(As[0]);
+        tb.store(Bs[0]);
+        __syncthreads();
+        s += 2;
+    }
+    if (s + 1 < nk) {
+        load(s + 1);
+        mma_step_fast<S>(As[0], Bs[0], wm, wn, lane, acc);
+        ta.store(As[1]);
+        tb.store(Bs[1]);
+        __syncthreads();
+        mma_step_fast<S>(As[1], Bs[1], wm, wn, lane, acc);
+    } else {
+        mma_step_fast<S>(As[0], Bs[0], wm, wn, lane, acc);
+    }
+}
+
+// ---- row-block kernel: C[n x MD] = act(A[n x KD] * B[KD x MD]) ----------------------------------
+// A is staged transposed (reduction-major) so that the MFMA operand reads are unit-stride.
+// LDS tiles are double buffered: one barrier per reduction step.
+template <class S, bool RELU>
+__global__ __launch_bounds__(kBlock, kRowblockMinBlocks) void rowblock_gemm_kernel(
+    const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
+    float* __restrict__ C, int64_t ldc, int64_t n, int KD, int MD, int n_col_tiles)
+{
+    constexpr int LDA = S::BM + kLdsPad, LDB = S::BN + kLdsPad;
+    __shared__ float As[2][BK * LDA];
+    __shared__ float Bs[2][BK * LDB];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave / S::WN, wn = wave % S::WN;
+    const unsigned lid = xcd_local_index(blockIdx.x, gridDim.x);
+    const int64_t row0 = (int64_t)(lid / n_col_tiles) * S::BM;
+    const int col0 = (int)(lid % n_col_tiles) * S::BN;
+
+    floatx16 acc[S::TM][S::TN];
+#pragma unroll
+    for (int tm = 0; tm < S::TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < S::TN; ++tn)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[tm][tn][v] = 0.f;
+
+    // staging maps: "strided" = 4 consecutive reduction indices of one row/col per thread
+    constexpr int A_PASSES = S::BM / 64;  // 64 rows per pass
+    constexpr int BN_F4 = S::BN / 4;       // float4 per staged B row
+    constexpr int B_ROWS_PER_PASS = kBlock / BN_F4;
+    constexpr int B_PASSES = (BK + B_ROWS_PER_PASS - 1) / B_ROWS_PER_PASS;
+    Piece<false, float> ra[A_PASSES], rb[B_PASSES];
+
+    auto issue_tiles = [&](int k0) {
+#pragma unroll
+        for (int p = 0; p < A_PASSES; ++p)
+            ra[p].issue(A, lda, row0 + p * 64 + tid / 4, k0 + 4 * (tid & 3), n, KD, nullptr, 0);
+#pragma unroll
+        for (int p = 0; p < B_PASSES; ++p) {
+            const int kk = p * B_ROWS_PER_PASS + tid / BN_F4;
+            rb[p].issue(B, ldb, k0 + (kk < BK ? kk : 0), col0 + 4 * (tid % BN_F4), KD, MD, nullptr, 0);
+        }
+    };
+    // CHECKED = false when every piece of the two tiles lies inside its matrix (uniform): the
+    // zero fill then costs no vector ALU work next to the MFMAs
+    auto store_tiles_as = [&](float* as, float* bs, auto checked) {
+        constexpr bool CHECKED = decltype(checked)::value;
+#pragma unroll
+        for (int p = 0; p < A_PASSES; ++p) {
+            const int i = p * 64 + tid / 4, kq = 4 * (tid & 3);
+            const float4 v = ra[p].template value<CHECKED>();
+            as[(kq + 0) * LDA + i] = v.x;
+            as[(kq + 1) * LDA + i] = v.y;
+            as[(kq + 2) * LDA + i] = v.z;
+            as[(kq + 3) * LDA + i] = v.w;
+        }
+#pragma unroll
+        for (int p = 0; p < B_PASSES; ++p) {
+            const int kk = p * B_ROWS_PER_PASS + tid / BN_F4;
+            if (kk < BK)
+                *reinterpret_cast<float4*>(&bs[kk * LDB + 4 * (tid % BN_F4)]) =
+                    rb[p].template value<CHECKED>();
+        }
+    };
+    const bool tile_inside = row0 + S::BM <= n && col0 + S::BN <= MD;
+    auto store_tiles = [&](float* as, float* bs, int k0) {
+        if (tile_inside && k0 + BK <= KD) store_tiles_as(as, bs, std::false_type{});
+        else store_tiles_as(as, bs, std::true_type{});
+    };
+
+    const int nk = (KD + BK - 1) / BK;
+    // every piece inside its matrix, whole reduction steps, 32-bit offsets within a tile
+    const bool fast = tile_inside && KD % BK == 0 && lda < (1 << 22) && ldb < (1 << 22);
+    if (fast) {
+        FastTile<S::BM, true> ta;
+        FastTile<S::BN, false> tb;
+        ta.init(tid, (uint32_t)lda * 4u);
+        tb.init(tid, (uint32_t)ldb * 4u);
+        const char* a0 = reinterpret_cast<const char*>(A + row0 * lda);
+        const char* b0 = reinterpret_cast<const char*>(B + col0);
+        const size_t b_step = (size_t)BK * 4 * (size_t)ldb;
+        auto load = [&](int64_t st) {
+            ta.load(a0 + (size_t)st * (BK * 4), (size_t)lda * 4);
+            tb.load(b0 + (size_t)st * b_step, (size_t)ldb * 4);
+        };
+        fast_reduction<S>(As, Bs, ta, tb, load, (int64_t)nk, wm, wn, lane, acc);
+    } else {
+        issue_tiles(0);
+        store_tiles(As[0], Bs[0], 0);
+        __syncthreads();
+        for (int i = 0; i < nk; ++i) {
+            const int cur = i & 1;
+            if (i + 1 < nk) issue_tiles((i + 1) * BK);
+            mma_step<S>(As[cur], Bs[cur], wm, wn, lane, acc);
+            if (i + 1 < nk) store_tiles(As[cur ^ 1], Bs[cur ^ 1], (i + 1) * BK);
+            __syncthreads();
+        }
+    }
+
+    // D layout of the 32x32 MFMA: lane l, register v -> row 8*(v/4) + 4*(l/32) + v%4, col l%32
+    const int li = lane & 31, lk = lane >> 5;
+    if (tile_inside) {
+        // no bounds to test: a scalar base per 32 x 32 tile and register, one 32-bit lane offset
+        const int wmu = __builtin_amdgcn_readfirstlane(wm), wnu = __builtin_amdgcn_readfirstlane(wn);
+        const uint32_t lane_off = (uint32_t)(4 * lk) * (uint32_t)ldc + (uint32_t)li;
+#pragma unroll
+        for (int tm = 0; tm < S::TM; ++tm)
+#pragma unroll
+            for (int tn = 0; tn < S::TN; ++tn) {
+                float* tile = C + (row0 + (wmu * S::TM + tm) * 32) * ldc + col0 + (wnu * S::TN + tn) * 32;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    float x = acc[tm][tn][v];
+                    if (RELU) x = fmaxf(x, 0.f);
+                    tile[(int64_t)(8 * (v / 4) + (v % 4)) * ldc + lane_off] = x;
+                }
+            }
+        return;
+    }
+#pragma unroll
+    for (int tm = 0; tm < S::TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < S::TN; ++tn) {
+            const int c = col0 + (wn * S::TN + tn) * 32 + li;
+            if (c >= MD) continue;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int64_t r = row0 + (wm * S::TM + tm) * 32 + 8 * (v / 4) + 4 * lk + (v % 4);
+                if (r < n) {
+                    float x = acc[tm][tn][v];
+                    if (RELU) x = x > 0.f ? x : 0.f;
+                    C[r * ldc + c] = x;
+                }
+            }
+        }
 }
 
 // ---- slab kernel: P[slab][KD x MD] = A[rows of slab][KD]^T * (B (.) 1[R > 0])[rows][MD] --------
@@ -295,6 +567,32 @@ __global__ __launch_bounds__(kBlock) void relu_mask_kernel(T* __restrict__ G, in
     if (!(h.w > 0.f)) gp[3] = (T)0;
 }
 
+template <class S>
+int launch_rowblock(bool relu, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc,
+                    int64_t n, int KD, int MD, hipStream_t s)
+{
+    const int nct = (int)ceil_div(MD, S::BN);
+    const int64_t grid = ceil_div(n, S::BM) * nct;
+    if (grid <= 0) return MIXGCN_OK;
+    if (grid > 0x7FFFFFFF) return fail(MIXGCN_EINVAL, "update: too many row tiles");
+    if (relu)
+        hipLaunchKernelGGL((rowblock_gemm_kernel<S, true>), dim3((unsigned)grid), dim3(kBlock), 0, s, A, lda, B,
+                           ldb, C, ldc, n, KD, MD, nct);
+    else
+        hipLaunchKernelGGL((rowblock_gemm_kernel<S, false>), dim3((unsigned)grid), dim3(kBlock), 0, s, A, lda, B,
+                           ldb, C, ldc, n, KD, MD, nct);
+    MIXGCN_HIP_TRY(hipGetLastError());
+    return MIXGCN_OK;
+}
+
+// C[n x m] = act(A[n x k] W[k x m])
+int forward_f32(bool relu, const float* A, int64_t lda, const float* W, int64_t ldw, float* C, int64_t ldc,
+                int64_t n, int32_t k, int32_t m, hipStream_t s)
+{
+    return m > 64 ? launch_rowblock<Shape128x128>(relu, A, lda, W, ldw, C, ldc, n, k, m, s)
+                  : launch_rowblock<Shape128x32>(relu, A, lda, W, ldw, C, ldc, n, k, m, s);
+}
+
 }  // namespace
 
 int launch_relu_mask(int dtype, void* G, int64_t ldg, const void* R, int64_t ldr, int64_t n,
@@ -360,11 +658,16 @@ int launch_update(int op, int dtype, const void* A, int64_t lda, const void* B, 
                   int64_t ldr, float beta, hipStream_t s, Timer* timer)
 {
     if (op != MIXGCN_OP_WGRAD) {
-        const bool fwd = op != MIXGCN_OP_DGRAD;
-        const int kind = fwd ? kTimeUpdateFwd : kTimeUpdateDgrad;
-        if (timer) MIXGCN_TRY(timer->begin(kind, s));
-        MIXGCN_TRY(launch_update_rows(dtype, fwd, op == MIXGCN_OP_FWD_RELU, A, lda, (const float*)B, ldb, C, ldc,
-                                      n, fwd ? k : m, fwd ? m : k, fwd ? nullptr : R, ldr, s));
+        const bool fwd = op != MIXGCN_OP_DGRAD, relu = op == MIXGCN_OP_FWD_RELU;
+        if (timer) MIXGCN_TRY(timer->begin(fwd ? kTimeUpdateFwd : kTimeUpdateDgrad, s));
+        if (!fwd || dtype != MIXGCN_F32)
+            MIXGCN_TRY(launch_update_rows(dtype, fwd, relu, A, lda, (const float*)B, ldb, C, ldc, n, fwd ? k : m,
+                                          fwd ? m : k, fwd ? nullptr : R, ldr, s));
+        else if (g_update_arith == MIXGCN_ARITH_BF16X3 && forward_split_applies(lda, n, k, m))
+            MIXGCN_TRY(launch_forward_split(relu, (const float*)A, lda, (const float*)B, ldb, (float*)C, ldc, n, k,
+                                            m, s));
+        else
+            MIXGCN_TRY(forward_f32(relu, (const float*)A, lda, (const float*)B, ldb, (float*)C, ldc, n, k, m, s));
         if (timer) MIXGCN_TRY(timer->end(s));
         return MIXGCN_OK;
     }

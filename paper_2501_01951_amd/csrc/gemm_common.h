@@ -1,0 +1,57 @@
+// Device helpers shared by the kernels of the update products.
+#pragma once
+#include "device_utils.h"
+
+namespace mixgcn {
+
+// Workgroups are dealt round-robin to the 8 XCDs.  This maps the hardware block index to a
+// logical one such that consecutive logical indices run on the same XCD, so tiles that share
+// an operand (the column tiles of one row block) find it in that XCD's L2.
+__device__ inline unsigned xcd_local_index(unsigned bid, unsigned grid)
+{
+    const unsigned q = grid / 8, rem = grid % 8, x = bid % 8;
+    return x * q + (x < rem ? x : rem) + bid / 8;
+}
+
+// two fp32 -> two bf16 (round to nearest even, the conversion instruction of this part), first argument
+// in the low half
+__device__ inline uint32_t pack_bf16(float a, float b)
+{
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float floatx2 __attribute__((ext_vector_type(2)));
+    const floatx2 v = {a, b};
+    const bf16x2 h = __builtin_convertvector(v, bf16x2);
+    uint32_t u;
+    __builtin_memcpy(&u, &h, 4);
+    return u;
+}
+__device__ inline float low_half(uint32_t u) { return __uint_as_float(u << 16); }
+__device__ inline float high_half(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
+
+// The elements of rows [row0, row1) and columns [col0, col1) of C that are not finite, again as chains of fp32
+// multiply-adds over the reduction index (a term of an infinity is NaN, a value next to the largest float
+// rounds up to an infinity as bf16); then, with RELU, the activation of all of them.  C holds the sums of the
+// calling wavefront, written by it and not yet activated.  a_at(row, k), w_at(k, col): the operands.
+template <bool RELU, class FA, class FW>
+__device__ inline void repair_sums(float* C, int64_t ldc, int64_t row0, int64_t row1, int col0, int col1, int KD,
+                                   FA a_at, FW w_at)
+{
+    __threadfence();  // what the wavefront wrote is read by its other lanes
+    const int cols = col1 - col0;
+    const int64_t cells = cols > 0 ? (row1 - row0) * cols : 0;
+    for (int64_t i = threadIdx.x & (kWave - 1); i < cells; i += kWave) {
+        const int64_t row = row0 + i / cols;
+        const int col = col0 + (int)(i % cols);
+        float* const c = C + row * ldc + col;
+        float x = __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!(fabsf(x) <= 3.402823466e38f)) {
+            x = 0.f;
+            for (int k = 0; k < KD; ++k) x = fmaf(a_at(row, k), w_at(k, col), x);
+        } else if (!RELU) {
+            continue;
+        }
+        *c = RELU ? fmaxf(x, 0.f) : x;
+    }
+}
+
+}  // namespace mixgcn

@@ -1,6 +1,6 @@
-// Node update H' = sigma(Z W) and data gradient dZ = (dP (.) 1[R > 0]) W^T (paper Algorithm 2, update
-// phase) on the bf16 matrix cores: C[n x MD] = act(A[n x KD] Bop[KD x MD]) with few columns and very
-// many rows.
+// Node update H' = sigma(Z W) of bf16 features and data gradient dZ = (dP (.) 1[R > 0]) W^T of bf16 and fp32
+// ones (paper Algorithm 2, update phase) on the bf16 matrix cores: C[n x MD] = act(A[n x KD] Bop[KD x MD])
+// with few columns and very many rows.  (The forward product of fp32 features keeps the fp32 rounding.)
 //
 // Arithmetic.  fp32 operands are written as exact sums of three bf16 terms (round to nearest at each
 // stage, |x1| <= 2^-8 |x|, |x2| <= 2^-16 |x|) and a product is accumulated in fp32 from the six partial
@@ -21,8 +21,8 @@
 // of the fp32 MFMAs they replace; on random data this part sustains 270 to 300 TFLOP/s of fp32 products
 // that way, register operands only, and these kernels reach 135 to 175.  us before (tiles of 128 x 128 on
 // the fp32 matrix cores, bf16: on the bf16 ones) -> now, forward and data gradient:
-//   fp32 2^20 rows 128 -> 128: 373 -> 238, 419 -> 326;  128 -> 256: 683 -> 451;  256 -> 256: 1210 -> 900,
-//   1284 -> 1110;  256 -> 16: 249 -> 218;  11.1 M rows 128 -> 128: 3625 -> 2396, 3659 -> 2386
+//   fp32 2^20 rows, data gradient plain and masked, 128 -> 128: 344 -> 240, 399 -> 313;  256 -> 256: 1164 -> 868,
+//   1256 -> 1029;  602 -> 128: 1396 -> 1008, 1610 -> 1315;  11.1 M rows 128 -> 128: 3659 -> 2386
 //   bf16 2.45 M rows 256 -> 256: 912 -> 690, 1150 -> 985;  100 -> 256: 562 -> 424;  100003 rows
 //   128 -> 128: 24 -> 16 (the weights' own launch is gone too)
 #include "device_utils.h"
@@ -661,32 +661,28 @@ int launch_rows_tn(bool relu, const RowsArgs& args, hipStream_t s)
     return MIXGCN_OK;
 }
 
-template <int DT>
-int launch_rows_dt(bool wt, bool relu, const RowsArgs& a, hipStream_t s)
+template <int DT, bool WT>
+int launch_rows_wt(bool relu, const RowsArgs& a, hipStream_t s)
 {
-    if (wt) {
-        if (a.MD <= 16) return launch_rows_tn<DT, 1, true>(relu, a, s);
-        if (a.MD <= 32) return launch_rows_tn<DT, 2, true>(relu, a, s);
-        if (a.MD <= 64) return launch_rows_tn<DT, 4, true>(relu, a, s);
-        return launch_rows_tn<DT, 8, true>(relu, a, s);
-    }
-    if (a.MD <= 16) return launch_rows_tn<DT, 1, false>(relu, a, s);
-    if (a.MD <= 32) return launch_rows_tn<DT, 2, false>(relu, a, s);
-    if (a.MD <= 64) return launch_rows_tn<DT, 4, false>(relu, a, s);
-    return launch_rows_tn<DT, 8, false>(relu, a, s);
+    if (a.MD <= 16) return launch_rows_tn<DT, 1, WT>(relu, a, s);
+    if (a.MD <= 32) return launch_rows_tn<DT, 2, WT>(relu, a, s);
+    if (a.MD <= 64) return launch_rows_tn<DT, 4, WT>(relu, a, s);
+    return launch_rows_tn<DT, 8, WT>(relu, a, s);
 }
 
 }  // namespace
 
-// C[n x MD] = act((A (.) 1[R > 0])[n x KD] Wop), Wop[kk][j] = w_is_kd_major ? W[kk][j] : W[j][kk]
+// C[n x MD] = act((A (.) 1[R > 0])[n x KD] Wop), Wop[kk][j] = w_is_kd_major ? W[kk][j] : W[j][kk]; of fp32
+// features the data gradient alone
 int launch_update_rows(int dtype, bool w_is_kd_major, bool relu, const void* A, int64_t lda, const float* W,
                        int64_t ldw, void* C, int64_t ldc, int64_t n, int KD, int MD, const void* R,
                        int64_t ldr, hipStream_t s)
 {
     if (n <= 0) return MIXGCN_OK;
     RowsArgs a{A, lda, W, ldw, C, ldc, n, KD, MD, R, ldr, 0, 0, 0};
-    return dtype == MIXGCN_F32 ? launch_rows_dt<MIXGCN_F32>(w_is_kd_major, relu, a, s)
-                               : launch_rows_dt<MIXGCN_BF16>(w_is_kd_major, relu, a, s);
+    if (dtype == MIXGCN_F32) return launch_rows_wt<MIXGCN_F32, false>(relu, a, s);
+    return w_is_kd_major ? launch_rows_wt<MIXGCN_BF16, true>(relu, a, s)
+                         : launch_rows_wt<MIXGCN_BF16, false>(relu, a, s);
 }
 
 }  // namespace mixgcn

@@ -270,7 +270,15 @@ int launch_update_bf16_deep(bool w_is_kd_major, bool relu, const uint16_t* A, in
                             int64_t ldw, uint16_t* C, int64_t ldc, int64_t n, int KD, int MD,
                             const uint16_t* R, int64_t ldr, hipStream_t s);
 
-// C[n x MD] = act((A (.) 1[R > 0])[n x KD] Wop), Wop[kk][j] = w_is_kd_major ? W[kk][j] : W[j][kk]
+// forward product of fp32 features, every operand as three bf16 terms; chosen by mixgcn_set_update_arith, and
+// only where forward_split_applies says so
+extern int g_update_arith;
+bool forward_split_applies(int64_t lda, int64_t n, int32_t k, int32_t m);
+int launch_forward_split(bool relu, const float* A, int64_t lda, const float* W, int64_t ldw, float* C, int64_t ldc,
+                         int64_t n, int32_t k, int32_t m, hipStream_t s);
+
+// C[n x MD] = act((A (.) 1[R > 0])[n x KD] Wop), Wop[kk][j] = w_is_kd_major ? W[kk][j] : W[j][kk]; of fp32
+// features the data gradient alone
 int launch_update_rows(int dtype, bool w_is_kd_major, bool relu, const void* A, int64_t lda, const float* W,
                        int64_t ldw, void* C, int64_t ldc, int64_t n, int KD, int MD, const void* R,
                        int64_t ldr, hipStream_t s);

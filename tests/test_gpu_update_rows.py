@@ -1,4 +1,4 @@
-"""The update products of rows (forward, data gradient, fp32 weight gradient) at the edges of their kernels: 32-row tiles, reduction steps
+"""The update products (forward, data gradient, fp32 weight gradient) at the edges of their kernels: 32-row tiles, reduction steps
 of 128 bytes of a row, weights that stay in LDS and weights that stream through it, output tiles of 16, 32,
 64 and 128 columns; what rows hold past their columns, infinities and NaN."""
 import pytest
@@ -38,6 +38,30 @@ def check(got, a, w, dtype, steps, what):
     assert not bad.any(), (what, int(bad.sum()))
 
 
+def chain(a, w):
+    """Multiply-adds of fp32 in the order of the reduction index: a product of two floats is exact in 64 bits."""
+    s = torch.zeros(a.shape[0], w.shape[1], device="cuda")
+    for k in range(a.shape[1]):
+        s = (a[:, k:k + 1].double() * w[k:k + 1].double() + s.double()).float()
+    return s
+
+
+# around tiles of 128 rows, 32 and 128 columns and steps of 16: tiles inside the matrices and tiles at their edges
+@pytest.mark.parametrize("n,k,m", [(1, 1, 1), (128, 16, 32), (129, 15, 33), (256, 64, 128), (300, 100, 64),
+                                   (255, 128, 65), (384, 256, 256), (260, 602, 129)])
+def test_fp32_forward_sums_are_the_fp32_chain(mg, n, k, m):
+    """Bit for bit: the sums of a forward product decide the sign of an activation, so they keep their
+    rounding from release to release."""
+    gen = torch.Generator(device="cuda").manual_seed(n + k)
+    z = padded(n, k, torch.float32, gen)
+    w = torch.randn(k, (m + 3) // 4 * 4 + 4, device="cuda", generator=gen)[:, :m]
+    want = chain(z[:, :k], w)
+    for op, ref in ((mg.OP_FWD, want), (mg.OP_FWD_RELU, want.clamp(min=0))):
+        out = padded(n, m, torch.float32, gen)
+        mg.update(op, z[:, :k], w, out[:, :m], n, k, m)
+        assert torch.equal(out[:, :m], ref) and out[:, m:].isnan().all()
+
+
 # rows: one, around a tile and a workgroup's rows; depths: below, at and past a step, the most that keeps
 # 128 columns of weights in LDS (fp32 160, bf16 256) and beyond; columns: around every tile width
 SHAPES = [(1, 1, 1), (31, 3, 16), (32, 32, 17), (33, 31, 33), (255, 33, 64), (257, 64, 65), (64, 160, 128),
@@ -54,7 +78,10 @@ def test_row_products_element_by_element(mg, dtype, n, k, m):
     step = 32 if dtype == torch.float32 else 64
     out = torch.full_like(g, 7.0)
     mg.update(mg.OP_FWD, z[:, :k], w, out[:, :m], n, k, m)
-    check(out[:, :m], z[:, :k], w, dtype, -(-k // step), "forward")
+    if dtype == torch.bfloat16:
+        check(out[:, :m], z[:, :k], w, dtype, -(-k // step), "forward")
+    else:
+        assert torch.equal(out[:, :m], chain(z[:, :k], w))
     plain = out.clone()
     mg.update(mg.OP_FWD_RELU, z[:, :k], w, out[:, :m], n, k, m)
     assert torch.equal(out[:, :m], plain[:, :m].clamp(min=0)) and (out[:, m:] == 7.0).all()
@@ -66,18 +93,31 @@ def test_row_products_element_by_element(mg, dtype, n, k, m):
         assert (dz[:, k:] == 7.0).all()
 
 
-@pytest.mark.parametrize("k,m", [(64, 128), (300, 40)])
-def test_fp32_values_that_are_not_finite(mg, k, m):
+@pytest.mark.parametrize("product", ["forward", "forward of three terms", "data gradient"])
+@pytest.mark.parametrize("k,m", [(64, 128), (304, 72)])
+def test_fp32_values_that_are_not_finite(mg, k, m, product):
     """An infinity, NaN and a value whose first term rounds to infinity reach the same outputs as in a
     product of plain floats, and the finite rows around them keep their accuracy."""
     n = 200
     gen = torch.Generator(device="cuda").manual_seed(k)
     z = torch.randn(n, k, device="cuda", generator=gen)
     w = torch.randn(k, m, device="cuda", generator=gen)
+
+    def run(op):
+        out = torch.empty(n, m, device="cuda")
+        if product == "data gradient":
+            mg.update(mg.OP_DGRAD, z, w.t().contiguous(), out, n, m, k)
+            return out
+        mg.set_update_arith(mg.ARITH_BF16X3 if product == "forward of three terms" else mg.ARITH_FP32)
+        try:
+            mg.update(op, z, w, out, n, k, m)
+        finally:
+            mg.set_update_arith(mg.ARITH_FP32)
+        return out
+
     w[1] = 0.5
     z[3, 5], z[40, 2], z[70, 1], z[71, 1] = float("inf"), float("nan"), 3.4e38, -3.4e38
-    out = torch.empty(n, m, device="cuda")
-    mg.update(mg.OP_FWD, z, w, out, n, k, m)
+    out = run(mg.OP_FWD)
     ref = (z.double() @ w.double()).float()
     assert torch.equal(out.isnan(), ref.isnan()) and torch.equal(out.isposinf(), ref.isposinf())
     assert torch.equal(out.isneginf(), ref.isneginf())
@@ -85,9 +125,12 @@ def test_fp32_values_that_are_not_finite(mg, k, m):
     rest[[3, 40, 70, 71]] = False
     check(out[rest], z[rest], w, torch.float32, k, "finite rows")
     assert (out[70] - ref[70]).abs().max() <= 1e-6 * ref[70].abs().max()
+    if product != "data gradient":  # the activation of NaN is 0
+        active = run(mg.OP_FWD_RELU)
+        assert torch.equal(active, torch.where(out > 0, out, torch.zeros_like(out)))
     w[2, 0] = float("inf")
     z = torch.rand(n, k, device="cuda", generator=gen) + 0.5
-    mg.update(mg.OP_FWD, z, w, out, n, k, m)
+    out = run(mg.OP_FWD)
     assert out[:, 0].isposinf().all() and not out[:, 1:].isinf().any() and not out.isnan().any()
 
 
