@@ -370,10 +370,10 @@ __global__ __launch_bounds__(kRowsBlock) __attribute__((amdgpu_waves_per_eu(2, 2
             }
         }
     };
-    // acc = keep * acc + o * chunk.  The partial products of a step are added up from zero and then to the
-    // running sum, once per step: rounding the running sum for every partial product costs three times
-    // the error (K = 128: 1.5e-7 against 5.5e-8, fp32 MFMA 2.0e-7).
-    auto mma = [&](const Operand& o, const uint16_t* chunk, float keep) {
+    // acc += o * chunk.  The partial products of a step are added up from zero and then to the running
+    // sum, once per step: rounding the running sum for every partial product costs three times the error
+    // (K = 128: 1.5e-7 against 5.5e-8, fp32 MFMA 2.0e-7).
+    auto mma = [&](const Operand& o, const uint16_t* chunk) {
         const uint16_t* src = chunk + lane * 8;
         constexpr int NW = NB * PB;
         bf16x8 b[2][NW];
@@ -406,15 +406,13 @@ __global__ __launch_bounds__(kRowsBlock) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
                 for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        acc[tm][t - 1][v] = fmaf(acc[tm][t - 1][v], keep, part[(t - 1) & 1][tm][v]);
+                    for (int v = 0; v < 4; ++v) acc[tm][t - 1][v] += part[(t - 1) & 1][tm][v];
             }
         }
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
-                acc[tm][TN - 1][v] = fmaf(acc[tm][TN - 1][v], keep, part[(TN - 1) & 1][tm][v]);
+            for (int v = 0; v < 4; ++v) acc[tm][TN - 1][v] += part[(TN - 1) & 1][tm][v];
         // issue order: the weights of the next tile, the products, the sums of the tile before
         __builtin_amdgcn_sched_group_barrier(0x100, NW, 0);
 #pragma unroll
@@ -455,7 +453,6 @@ __global__ __launch_bounds__(kRowsBlock) __attribute__((amdgpu_waves_per_eu(2, 2
                     for (int v = 0; v < 4; ++v) z = fmaf(acc[tm][t][v], 0.f, z);
             if (__builtin_expect(__any(!(z == 0.f)), 0)) {
                 plain_tile(row0);
-                clear();  // the next tile's sums start from zero times these
                 return;
             }
         }
@@ -598,11 +595,12 @@ __global__ __launch_bounds__(kRowsBlock) __attribute__((amdgpu_waves_per_eu(2, 2
         }
         load(x);
         __builtin_amdgcn_sched_barrier(0);
-        mma(o, RESIDENT ? wlds + c * kChunk : wlds + (int)(s & 1) * kChunk, c == 0 ? 0.f : 1.f);
+        mma(o, RESIDENT ? wlds + c * kChunk : wlds + (int)(s & 1) * kChunk);
         if (++c == nch) {
             c = 0;
             __builtin_amdgcn_sched_barrier(0);
             finish(tile);
+            clear();
             __builtin_amdgcn_sched_barrier(0);
             tile += stride;
         }

@@ -134,6 +134,32 @@ def test_fp32_values_that_are_not_finite(mg, k, m, product):
     assert out[:, 0].isposinf().all() and not out[:, 1:].isinf().any() and not out.isnan().any()
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("k,m", [(64, 128), (128, 40), (256, 128), (330, 130)])
+def test_values_that_are_not_finite_stay_in_their_rows(mg, dtype, k, m):
+    """With more rows than the chip walks at a time: what is not finite in a few of the first rows must not
+    reach a row of another tile, whatever the next tile of the same wavefront is."""
+    n, bad = 200000, [0, 5, 37, 70]
+    gen = torch.Generator(device="cuda").manual_seed(k + m)
+    z, g = (padded(n, c, dtype, gen) for c in (k, m))
+    w = torch.randn(k, (m + 3) // 4 * 4, device="cuda", generator=gen)[:, :m]
+    other = torch.ones(n, dtype=torch.bool, device="cuda")
+    if dtype == torch.float32:
+        other[:96] = False  # fp32: the finite sums of the same 32 rows are computed again, too
+    else:
+        other[bad] = False
+    for op, x, cols in ((mg.OP_FWD, z, m), (mg.OP_FWD_RELU, z, m), (mg.OP_DGRAD, g, k)):
+        runs = []
+        for _ in range(2):
+            out = torch.empty(n, (cols + 7) // 8 * 8, device="cuda", dtype=dtype)[:, :cols]
+            mg.update(op, x[:, :k] if op != mg.OP_DGRAD else x[:, :m], w, out, n, k, m)
+            runs.append(out)
+            x[bad[0], 0], x[bad[1], 1], x[bad[2], 2], x[bad[3], 3] = float("inf"), float("nan"), -float("inf"), 3e38
+            x[bad[3], 4] = 3e38
+        assert torch.equal(runs[0][other], runs[1][other]), op
+        assert op == mg.OP_FWD_RELU or not runs[1][bad[:3]].isfinite().any()
+
+
 # rows: one, around a step of 16 and around slabs; columns of both operands around the tiles of 32, 64 and 128
 WGRAD_SHAPES = [(1, 1, 1), (15, 3, 32), (16, 33, 33), (17, 127, 64), (130, 129, 65), (1000, 100, 127),
                 (2063, 128, 128), (4096, 64, 32), (3001, 602, 41), (777, 257, 130), (40000, 16, 300)]
