@@ -293,7 +293,8 @@ int mixgcn_apply_bitmap(int dtype, void* X, int64_t ldx, int64_t n_rows, int32_t
  * the six partial products of order 2^-16 and above (the others are together below 2^-23 |a| |b|).  Against
  * 64 bits these results are closer than those of a chain of fp32 multiply-adds (relative error 5.6e-8 against
  * 2.0e-7 at depth 128).  bf16 features enter as they are and the weights as two terms.  Infinities and NaN
- * give what fp32 arithmetic gives; operands of a gradient below about 1e-33 in magnitude carry fewer than 24
+ * give what fp32 arithmetic gives (fp32 products on the bf16 matrix cores compute every sum that is not finite
+ * again, one multiply-add at a time: a tensor full of NaN takes many times as long); operands of a gradient below about 1e-33 in magnitude carry fewer than 24
  * bits into a product (at 1e-35 a relative error of 3e-6).
  * Two per-device work buffers are shared by all calls: the slab partials of WGRAD, and the weight terms of
  * products that split them beforehand (bf16 ones whose weights do not fit LDS, more than 256 reduction indices,

@@ -25,15 +25,13 @@
 //   1256 -> 1029;  602 -> 128: 1396 -> 1008, 1610 -> 1315;  11.1 M rows 128 -> 128: 3659 -> 2386
 //   bf16 2.45 M rows 256 -> 256: 912 -> 690, 1150 -> 985;  100 -> 256: 562 -> 424;  100003 rows
 //   128 -> 128: 24 -> 16 (the weights' own launch is gone too)
-#include "device_utils.h"
+#include "gemm_common.h"
 #include "internal.h"
 
 namespace mixgcn {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) uintx4 lds_uintx4;
@@ -89,17 +87,6 @@ __device__ inline int tile_column(int t, int i)
     if (DT == MIXGCN_F32 || TN == 1) return t * 16 + i;
     return (t >> 1) * 32 + (i >> 2) * 8 + (t & 1) * 4 + (i & 3);
 }
-
-__device__ inline uint32_t pack_bf16(float a, float b)
-{
-    const floatx2 v = {a, b};
-    const bf16x2 h = __builtin_convertvector(v, bf16x2);
-    uint32_t u;
-    __builtin_memcpy(&u, &h, 4);
-    return u;
-}
-__device__ inline float low_half(uint32_t u) { return __uint_as_float(u << 16); }
-__device__ inline float high_half(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
 
 // x with the halves zeroed whose reference half (bf16 bits) is not > 0
 __device__ inline uint32_t keep_positive(uint32_t x, uint32_t r)
@@ -423,39 +410,23 @@ __global__ __launch_bounds__(kRowsBlock) __attribute__((amdgpu_waves_per_eu(2, 2
         }
     };
 
-    // fp32: a sum that is not finite (a term of an infinity is NaN, a value next to the largest float
-    // rounds up to an infinity) is computed again in plain fp32
-    auto plain_tile = [&](int64_t row0) {
-        for (int i = fresh(lane); i < kWaveRows * BN; i += kWave) {
-            const int64_t row = row0 + i / BN;
-            const int col = col0 + i % BN;
-            if (row >= p.n || col >= p.MD) continue;
-            const float* a = reinterpret_cast<const float*>(p.A) + row * p.lda;
-            const float* r = reinterpret_cast<const float*>(p.R) + (MASK ? row * p.ldr : 0);
-            float s = 0.f;
-            for (int k = 0; k < p.KD; ++k) {
-                const float w = WT ? p.W[(int64_t)k * p.ldw + col] : p.W[(int64_t)col * p.ldw + k];
-                s = fmaf((!MASK || r[k] > 0.f) ? a[k] : 0.f, w, s);
-            }
-            reinterpret_cast<float*>(p.C)[row * p.ldc + col] = RELU ? fmaxf(s, 0.f) : s;
+    // fp32: sums that are not finite, again in plain fp32
+    auto repair = [&](int64_t row0) {
+        if constexpr (DT == MIXGCN_F32) {
+            const float* const A = reinterpret_cast<const float*>(p.A);
+            const float* const R = reinterpret_cast<const float*>(p.R);
+            const int64_t row1 = row0 + kWaveRows < p.n ? row0 + kWaveRows : p.n;
+            const int col1 = col0 + BN < p.MD ? col0 + BN : p.MD;
+            static_assert(!RELU, "of fp32 features the data gradient alone");
+            repair_sums<false>(
+                reinterpret_cast<float*>(p.C), p.ldc, row0, row1, col0, col1, p.KD,
+                [&](int64_t r, int k) { return !MASK || R[r * p.ldr + k] > 0.f ? A[r * p.lda + k] : 0.f; },
+                [&](int k, int c) { return p.W[WT ? (int64_t)k * p.ldw + c : (int64_t)c * p.ldw + k]; });
         }
     };
-    auto finish = [&](int64_t tile) {
+    auto write = [&](int64_t tile) {
         const int li = fresh(lane) & 15, g = fresh(lane) >> 4;
         const int64_t row0 = tile * kWaveRows;
-        if (DT == MIXGCN_F32) {
-            float z = 0.f;
-#pragma unroll
-            for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-                for (int t = 0; t < TN; ++t)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) z = fmaf(acc[tm][t][v], 0.f, z);
-            if (__builtin_expect(__any(!(z == 0.f)), 0)) {
-                plain_tile(row0);
-                return;
-            }
-        }
         if (RELU) {
 #pragma unroll
             for (int tm = 0; tm < TM; ++tm)
@@ -536,6 +507,22 @@ __global__ __launch_bounds__(kRowsBlock) __attribute__((amdgpu_waves_per_eu(2, 2
                 }
             }
         }
+    };
+
+    auto finish = [&](int64_t tile) {
+        bool bad = false;
+        if (DT == MIXGCN_F32) {
+            float z = 0.f;
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                for (int t = 0; t < TN; ++t)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) z = fmaf(acc[tm][t][v], 0.f, z);
+            bad = __any(!(z == 0.f));
+        }
+        write(tile);
+        if (__builtin_expect(bad, 0)) repair(tile * kWaveRows);
     };
 
     auto pin = [](Operand& o) {
