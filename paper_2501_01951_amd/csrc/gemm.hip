@@ -1,8 +1,7 @@
 // Dispatch of the update products (paper Algorithm 2, update phase), the forward product H' = sigma(Z W) of
-// fp32 features on the fp32 matrix cores (v_mfma_f32_32x32x2_f32), the reduction of the slabs of a weight
-// gradient, and the weight gradient dW = Z^T dP of fp32 matrices with pitches of 2^22 elements and more.
-// A row-block kernel's workgroup owns 128 node rows: the node dimension is the long one, the feature
-// dimensions are at most a few hundred.
+// fp32 features on the fp32 matrix cores (v_mfma_f32_32x32x2_f32), and the reduction of the slabs of a weight
+// gradient.  A row-block kernel's workgroup owns 128 node rows: the node dimension is the long one, the
+// feature dimensions are at most a few hundred.
 //
 // The sums of the forward product are chains of fp32 multiply-adds over the reduction index, bit for bit.
 // They decide which side of zero an activation falls on, so they keep this rounding: with another one
@@ -21,7 +20,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 constexpr int BK = 16;          // reduction depth staged per step
 // Workgroups per CU that the register allocation of each kernel is held to (measured best of
 // 2, 3, 4 on the 128 x 128 shapes).
-constexpr int kRowblockMinBlocks = 3, kWgradMinBlocks = 4;
+constexpr int kRowblockMinBlocks = 3;
 constexpr int kLdsPad = 4;      // row stride of the staged tiles = tile width + 4 floats
 
 // Tile shape: WM x WN waves (4 in total), each owning TM x TN accumulator tiles of 32 x 32.
@@ -74,55 +73,26 @@ __device__ inline void mma_step(const float* As, const float* Bs, int wm, int wn
 }
 
 // One 16-byte piece of an operand tile on its way from global memory to LDS.  issue() only
-// starts the loads (addresses are clamped into the matrix, so they are unconditional and
-// nothing waits on them); value() applies the zero fill outside [0, rows) x [0, cols) and the
-// optional ReLU-derivative mask x * 1[R > 0] when the piece is written to LDS one step later.
-// (Raw4: four features as stored, fp32 or bf16.)
-template <typename T>
-struct Raw4;
-template <>
-struct Raw4<float> {
-    float4 q;
-    __device__ inline float4 widen() const { return q; }
-};
-template <>
-struct Raw4<uint16_t> {
-    uint2 q;
-    __device__ inline float4 widen() const
-    {
-        return make_float4(__uint_as_float(q.x << 16), __uint_as_float(q.x & 0xFFFF0000u),
-                           __uint_as_float(q.y << 16), __uint_as_float(q.y & 0xFFFF0000u));
-    }
-};
-
-template <bool MASK, typename T>
+// starts the load (the address is clamped into the matrix, so it is unconditional and nothing
+// waits on it); value() applies the zero fill outside [0, rows) x [0, cols) when the piece is
+// written to LDS one step later.
 struct Piece {
-    Raw4<T> v;
-    Raw4<T> m;
+    float4 v;
     int nvalid;  // leading components inside the matrix (0..4)
 
-    __device__ inline void issue(const T* __restrict__ M, int64_t ld, int64_t r, int c,
-                                 int64_t rows, int cols, const T* __restrict__ R, int64_t ldr)
+    __device__ inline void issue(const float* __restrict__ M, int64_t ld, int64_t r, int c, int64_t rows, int cols)
     {
         const bool ok = r < rows && c < cols;
         nvalid = ok ? (cols - c < 4 ? cols - c : 4) : 0;
         const int64_t rr = r < rows ? r : rows - 1;
         const int cc = c < cols ? c : 0;
-        v = *reinterpret_cast<const Raw4<T>*>(M + rr * ld + cc);
-        if (MASK) m = *reinterpret_cast<const Raw4<T>*>(R + rr * ldr + cc);
+        v = *reinterpret_cast<const float4*>(M + rr * ld + cc);
     }
     // CHECKED = false: the caller knows the piece lies wholly inside the matrix
-    template <bool CHECKED = true>
+    template <bool CHECKED>
     __device__ inline float4 value() const
     {
-        float4 o = v.widen();
-        if (MASK) {
-            const float4 mm = m.widen();
-            o.x = mm.x > 0.f ? o.x : 0.f;
-            o.y = mm.y > 0.f ? o.y : 0.f;
-            o.z = mm.z > 0.f ? o.z : 0.f;
-            o.w = mm.w > 0.f ? o.w : 0.f;
-        }
+        float4 o = v;
         if (CHECKED && nvalid < 4) {
             if (nvalid < 1) o.x = 0.f;
             if (nvalid < 2) o.y = 0.f;
@@ -309,16 +279,16 @@ __global__ __launch_bounds__(kBlock, kRowblockMinBlocks) void rowblock_gemm_kern
     constexpr int BN_F4 = S::BN / 4;       // float4 per staged B row
     constexpr int B_ROWS_PER_PASS = kBlock / BN_F4;
     constexpr int B_PASSES = (BK + B_ROWS_PER_PASS - 1) / B_ROWS_PER_PASS;
-    Piece<false, float> ra[A_PASSES], rb[B_PASSES];
+    Piece ra[A_PASSES], rb[B_PASSES];
 
     auto issue_tiles = [&](int k0) {
 #pragma unroll
         for (int p = 0; p < A_PASSES; ++p)
-            ra[p].issue(A, lda, row0 + p * 64 + tid / 4, k0 + 4 * (tid & 3), n, KD, nullptr, 0);
+            ra[p].issue(A, lda, row0 + p * 64 + tid / 4, k0 + 4 * (tid & 3), n, KD);
 #pragma unroll
         for (int p = 0; p < B_PASSES; ++p) {
             const int kk = p * B_ROWS_PER_PASS + tid / BN_F4;
-            rb[p].issue(B, ldb, k0 + (kk < BK ? kk : 0), col0 + 4 * (tid % BN_F4), KD, MD, nullptr, 0);
+            rb[p].issue(B, ldb, k0 + (kk < BK ? kk : 0), col0 + 4 * (tid % BN_F4), KD, MD);
         }
     };
     // CHECKED = false when every piece of the two tiles lies inside its matrix (uniform): the
@@ -415,106 +385,6 @@ __global__ __launch_bounds__(kBlock, kRowblockMinBlocks) void rowblock_gemm_kern
         }
 }
 
-// ---- slab kernel: P[slab][KD x MD] = A[rows of slab][KD]^T * (B (.) 1[R > 0])[rows][MD] --------
-// Both operands are staged exactly as they lie in memory (node-major), which already is the
-// reduction-major layout the MFMA operand reads want.
-template <class S, bool MASK, typename T>
-__global__ __launch_bounds__(kBlock, kWgradMinBlocks) void wgrad_slab_kernel(
-    const T* __restrict__ A, int64_t lda, const T* __restrict__ B, int64_t ldb,
-    const T* __restrict__ R, int64_t ldr, float* __restrict__ P, int64_t n, int KD, int MD,
-    int64_t rows_per_slab, int n_i_tiles, int n_j_tiles)
-{
-    constexpr int LDA = S::BM + kLdsPad, LDB = S::BN + kLdsPad;
-    __shared__ float As[2][BK * LDA];
-    __shared__ float Bs[2][BK * LDB];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / S::WN, wn = wave % S::WN;
-    const int tiles = n_i_tiles * n_j_tiles;
-    const unsigned lid = xcd_local_index(blockIdx.x, gridDim.x);
-    const int64_t slab = lid / tiles;
-    const int t = (int)(lid % tiles);
-    const int i0 = (t / n_j_tiles) * S::BM, j0 = (t % n_j_tiles) * S::BN;
-    const int64_t r_begin = slab * rows_per_slab;
-    const int64_t r_end = (r_begin + rows_per_slab) < n ? (r_begin + rows_per_slab) : n;
-
-    floatx16 acc[S::TM][S::TN];
-#pragma unroll
-    for (int tm = 0; tm < S::TM; ++tm)
-#pragma unroll
-        for (int tn = 0; tn < S::TN; ++tn)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[tm][tn][v] = 0.f;
-
-    constexpr int AM_F4 = S::BM / 4, BN_F4 = S::BN / 4;
-    constexpr int A_RPP = kBlock / AM_F4, B_RPP = kBlock / BN_F4;
-    constexpr int A_PASSES = (BK + A_RPP - 1) / A_RPP, B_PASSES = (BK + B_RPP - 1) / B_RPP;
-    Piece<false, T> ra[A_PASSES];
-    Piece<MASK, T> rb[B_PASSES];
-
-    auto issue_tiles = [&](int64_t r0) {
-#pragma unroll
-        for (int p = 0; p < A_PASSES; ++p) {
-            const int kk = p * A_RPP + tid / AM_F4;
-            ra[p].issue(A, lda, r0 + (kk < BK ? kk : 0), i0 + 4 * (tid % AM_F4), r_end, KD, nullptr, 0);
-        }
-#pragma unroll
-        for (int p = 0; p < B_PASSES; ++p) {
-            const int kk = p * B_RPP + tid / BN_F4;
-            rb[p].issue(B, ldb, r0 + (kk < BK ? kk : 0), j0 + 4 * (tid % BN_F4), r_end, MD, R, ldr);
-        }
-    };
-    auto store_tiles_as = [&](float* as, float* bs, auto checked) {
-        constexpr bool CHECKED = decltype(checked)::value;
-#pragma unroll
-        for (int p = 0; p < A_PASSES; ++p) {
-            const int kk = p * A_RPP + tid / AM_F4;
-            if (kk < BK)
-                *reinterpret_cast<float4*>(&as[kk * LDA + 4 * (tid % AM_F4)]) =
-                    ra[p].template value<CHECKED>();
-        }
-#pragma unroll
-        for (int p = 0; p < B_PASSES; ++p) {
-            const int kk = p * B_RPP + tid / BN_F4;
-            if (kk < BK)
-                *reinterpret_cast<float4*>(&bs[kk * LDB + 4 * (tid % BN_F4)]) =
-                    rb[p].template value<CHECKED>();
-        }
-    };
-    const bool tile_inside = i0 + S::BM <= KD && j0 + S::BN <= MD;
-    auto store_tiles = [&](float* as, float* bs, int64_t r0) {
-        if (tile_inside && r0 + BK <= r_end) store_tiles_as(as, bs, std::false_type{});
-        else store_tiles_as(as, bs, std::true_type{});
-    };
-
-    if (r_begin < r_end) {
-        const int64_t nk = (r_end - r_begin + BK - 1) / BK;
-        issue_tiles(r_begin);
-        store_tiles(As[0], Bs[0], r_begin);
-        __syncthreads();
-        for (int64_t i = 0; i < nk; ++i) {
-            const int cur = (int)(i & 1);
-            if (i + 1 < nk) issue_tiles(r_begin + (i + 1) * BK);
-            mma_step<S>(As[cur], Bs[cur], wm, wn, lane, acc);
-            if (i + 1 < nk) store_tiles(As[cur ^ 1], Bs[cur ^ 1], r_begin + (i + 1) * BK);
-            __syncthreads();
-        }
-    }
-    float* out = P + (size_t)slab * KD * MD;
-    const int li = lane & 31, lk = lane >> 5;
-#pragma unroll
-    for (int tm = 0; tm < S::TM; ++tm)
-#pragma unroll
-        for (int tn = 0; tn < S::TN; ++tn) {
-            const int j = j0 + (wn * S::TN + tn) * 32 + li;
-            if (j >= MD) continue;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int i = i0 + (wm * S::TM + tm) * 32 + 8 * (v / 4) + 4 * lk + (v % 4);
-                if (i < KD) out[(size_t)i * MD + j] = acc[tm][tn][v];
-            }
-        }
-}
-
 // dW = beta * dW + sum over slabs.  A block owns 64 consecutive cells; its four waves each add
 // every fourth slab (in slab order, fp64) and the four sums are combined in a fixed order, so
 // the result is deterministic.
@@ -548,6 +418,23 @@ __global__ __launch_bounds__(kBlock) void wgrad_reduce_kernel(const float* __res
         *o = (float)(beta != 0.f ? (double)beta * (double)*o + t : t);
     }
 }
+
+// four features as stored
+template <typename T>
+struct Raw4;
+template <>
+struct Raw4<float> {
+    float4 q;
+    __device__ inline float4 widen() const { return q; }
+};
+template <>
+struct Raw4<uint16_t> {
+    uint2 q;
+    __device__ inline float4 widen() const
+    {
+        return make_float4(low_half(q.x), high_half(q.x), low_half(q.y), high_half(q.y));
+    }
+};
 
 // G <- G (.) 1[R > 0], four elements per thread (bf16: zeroing keeps the bits exact).
 template <typename T>
@@ -621,38 +508,6 @@ int launch_wgrad_reduce(const float* P, int64_t n_slabs, int64_t cells, int32_t 
     return MIXGCN_OK;
 }
 
-namespace {
-
-// C[k x m] = beta C + A[n x k]^T (B (.) mask)[n x m]
-int wgrad_f32(const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc, int64_t n,
-              int32_t k, int32_t m, const float* R, int64_t ldr, float beta, hipStream_t s, Timer* timer)
-{
-    const int nit = (int)ceil_div(k, Shape128x32::BM), njt = (int)ceil_div(m, Shape128x32::BN);
-    const int tiles = nit * njt;
-    int64_t n_slabs = wgrad_slabs(n, tiles, 1024);
-    int64_t rows_per_slab = ceil_div(ceil_div(n, n_slabs), BK) * BK;
-    if (rows_per_slab < BK) rows_per_slab = BK;
-    n_slabs = n > 0 ? ceil_div(n, rows_per_slab) : 1;
-    const int64_t cells = (int64_t)k * m;
-    void* scratch = nullptr;
-    MIXGCN_TRY(get_scratch(0, (size_t)n_slabs * cells * sizeof(float), &scratch));
-    float* P = (float*)scratch;
-    const unsigned grid = (unsigned)(n_slabs * tiles);
-    if (timer) MIXGCN_TRY(timer->begin(kTimeUpdateWgrad, s));
-#define MIXGCN_WGRAD(MASK)                                                                                  \
-    hipLaunchKernelGGL((wgrad_slab_kernel<Shape128x32, MASK, float>), dim3(grid), dim3(kBlock), 0, s, A, lda, \
-                       B, ldb, R, ldr, P, n, k, m, rows_per_slab, nit, njt)
-    if (R) MIXGCN_WGRAD(true);
-    else MIXGCN_WGRAD(false);
-#undef MIXGCN_WGRAD
-    if (timer) MIXGCN_TRY(timer->end(s));
-    MIXGCN_TRY(launch_wgrad_reduce(P, n_slabs, cells, m, C, ldc, beta, s));
-    MIXGCN_HIP_TRY(hipGetLastError());
-    return MIXGCN_OK;
-}
-
-}  // namespace
-
 int launch_update(int op, int dtype, const void* A, int64_t lda, const void* B, int64_t ldb,
                   void* C, int64_t ldc, int64_t n, int32_t k, int32_t m, const void* R,
                   int64_t ldr, float beta, hipStream_t s, Timer* timer)
@@ -674,11 +529,8 @@ int launch_update(int op, int dtype, const void* A, int64_t lda, const void* B, 
     if (dtype != MIXGCN_F32)
         return launch_wgrad_bf16((const uint16_t*)A, lda, (const uint16_t*)B, ldb, (float*)C, ldc, n, k, m,
                                  (const uint16_t*)R, ldr, beta, s, timer);
-    const float *a = (const float*)A, *b = (const float*)B, *r = (const float*)R;
-    float* c = (float*)C;
-    if (wgrad_split_applies(lda, ldb, ldr, n))
-        return launch_wgrad_split(a, lda, b, ldb, c, ldc, n, k, m, r, ldr, beta, s, timer);
-    return wgrad_f32(a, lda, b, ldb, c, ldc, n, k, m, r, ldr, beta, s, timer);
+    return launch_wgrad_split((const float*)A, lda, (const float*)B, ldb, (float*)C, ldc, n, k, m, (const float*)R, ldr,
+                              beta, s, timer);
 }
 
 }  // namespace mixgcn

@@ -23,15 +23,13 @@
 // 128 x 128 3170 -> 2520; 232965 rows 602 x 128 458 -> 331; 4096 rows 64 x 100 19.7 -> 15.2.
 #include <type_traits>
 
-#include "device_utils.h"
+#include "gemm_common.h"
 #include "internal.h"
 
 namespace mixgcn {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
@@ -39,24 +37,6 @@ typedef __attribute__((address_space(3))) uintx2 lds_uintx2;
 
 constexpr int BKS = 16;       // node rows per step = the reduction depth of one MFMA
 constexpr int kPlanes = 3;
-
-__device__ inline unsigned xcd_local_index(unsigned bid, unsigned grid)
-{
-    const unsigned q = grid / 8, rem = grid % 8, x = bid % 8;
-    return x * q + (x < rem ? x : rem) + bid / 8;
-}
-
-// two fp32 -> two bf16 (round to nearest even), first argument in the low half
-__device__ inline uint32_t pack_bf16(float a, float b)
-{
-    const floatx2 v = {a, b};
-    const bf16x2 h = __builtin_convertvector(v, bf16x2);
-    uint32_t u;
-    __builtin_memcpy(&u, &h, 4);
-    return u;
-}
-__device__ inline float low_half(uint32_t u) { return __uint_as_float(u << 16); }
-__device__ inline float high_half(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
 
 // Four fp32 of a row on their way to LDS: the three bf16 planes of the (masked, negated) values.
 template <bool MASK, bool NEGATE>
@@ -120,10 +100,6 @@ __device__ inline float4 load16(__amdgpu_buffer_rsrc_t rows, uint32_t offset)
     const uintx4 v = __builtin_amdgcn_raw_buffer_load_b128(rows, (int)offset, 0, 0);
     return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
 }
-__device__ inline float load4(__amdgpu_buffer_rsrc_t rows, uint32_t offset)
-{
-    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows, (int)offset, 0, 0));
-}
 
 // The rows of a step, `bytes` of them from `first` on, as a buffer: what lies past the slab's end is read as
 // zeros, a step past the end reads nothing, and no load is conditional.
@@ -132,7 +108,9 @@ __device__ inline __amdgpu_buffer_rsrc_t rows_at(const char* first, int bytes)
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(first), 0, bytes, 0x00020000);
 }
 
-template <int BN, bool MASK>
+// FAR: a step of 16 rows does not fit a buffer with 32-bit offsets (pitches of 2^22 elements and more).  The
+// same tiles, slabs and order with 64-bit addresses: the arithmetic does not depend on the pitch.
+template <int BN, bool MASK, bool FAR>
 __global__ __launch_bounds__(kBlock, 2) void wgrad_split_kernel(
     const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
     const float* __restrict__ R, int64_t ldr, float* __restrict__ P, int KD, int MD,
@@ -172,14 +150,14 @@ __global__ __launch_bounds__(kBlock, 2) void wgrad_split_kernel(
     // past the matrix reach only cells of the product that are not stored: any column of the row will do.
     const int srow = tid >> 5, scol = 4 * (tid & 31);
     const int trow = tid / (BN / 4) % BKS, tcol = 4 * (tid % (BN / 4));
-    const uint32_t acol = 4u * (i0 + (i0 + scol < KD ? scol : 0)), bcol = 4u * (j0 + (j0 + tcol < MD ? tcol : 0));
+    const int acol = i0 + (i0 + scol < KD ? scol : 0), bcol = j0 + (j0 + tcol < MD ? tcol : 0);
     uint32_t aoff[2], boff[PB], roff[PB];
 #pragma unroll
-    for (int p = 0; p < 2; ++p) aoff[p] = (uint32_t)(srow + 8 * p) * (uint32_t)lda * 4u + acol;
+    for (int p = 0; p < 2; ++p) aoff[p] = (uint32_t)(srow + 8 * p) * (uint32_t)lda * 4u + 4u * acol;
 #pragma unroll
     for (int p = 0; p < PB; ++p) {
-        boff[p] = (uint32_t)(trow + 8 * p) * (uint32_t)ldb * 4u + bcol;
-        roff[p] = MASK ? (uint32_t)(trow + 8 * p) * (uint32_t)ldr * 4u + bcol : 0u;
+        boff[p] = (uint32_t)(trow + 8 * p) * (uint32_t)ldb * 4u + 4u * bcol;
+        roff[p] = MASK ? (uint32_t)(trow + 8 * p) * (uint32_t)ldr * 4u + 4u * bcol : 0u;
     }
     const int spos = srow * LDW + scol, tpos = trow * LDW + tcol;
 
@@ -190,7 +168,25 @@ __global__ __launch_bounds__(kBlock, 2) void wgrad_split_kernel(
     const char* bp = reinterpret_cast<const char*>(B + r_begin * ldb);
     const char* rp = MASK ? reinterpret_cast<const char*>(R + r_begin * ldr) : nullptr;
     const int pa = (int)lda * 4, pb = (int)ldb * 4, pr = (int)ldr * 4;
+    // Four values of row `row` of the step at the load cursor, zeros past the slab's end (FAR; the slab's first
+    // row exists)
+    auto load_far = [&](const float* M, int64_t ld, int row, int col) {
+        const bool in = row < left;
+        const float4 v = *reinterpret_cast<const float4*>(M + (in ? r_end - left + row : r_begin) * ld + col);
+        return in ? v : make_float4(0.f, 0.f, 0.f, 0.f);
+    };
     auto load = [&](Regs& g) {
+        if (FAR) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p) g.a[p] = load_far(A, lda, srow + 8 * p, acol);
+#pragma unroll
+            for (int p = 0; p < PB; ++p) {
+                g.b[p] = load_far(B, ldb, trow + 8 * p, bcol);
+                if (MASK) g.r[MASK ? p : 0] = load_far(R, ldr, trow + 8 * p, bcol);
+            }
+            left -= BKS;
+            return;
+        }
         const int rows = __builtin_amdgcn_readfirstlane(left >= BKS ? BKS : left > 0 ? left : 0);
         const auto ra = rows_at(ap, rows * pa), rb = rows_at(bp, rows * pb);
 #pragma unroll
@@ -294,33 +290,30 @@ __global__ __launch_bounds__(kBlock, 2) void wgrad_split_kernel(
         // up to an infinity): the wavefront's tile again on the fp32 matrix cores, straight from memory.
         // 32x32x2: lane l supplies column l % 32 of reduction index l / 32.
         clear();
-        uint32_t ca[TM], cb[TN];
+        int ca[TM], cb[TN];
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm) ca[tm] = 4u * (iw + tm * 32 + li < KD ? iw + tm * 32 + li : i0);
+        for (int tm = 0; tm < TM; ++tm) ca[tm] = iw + tm * 32 + li < KD ? iw + tm * 32 + li : i0;
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn) cb[tn] = 4u * (jw + tn * 32 + li < MD ? jw + tn * 32 + li : j0);
-        for (int64_t r = r_begin; r < r_end; r += BKS) {
-            const int rows = r_end - r < BKS ? (int)(r_end - r) : BKS;
-            const auto ra = rows_at(reinterpret_cast<const char*>(A + r * lda), rows * pa);
-            const auto rb = rows_at(reinterpret_cast<const char*>(B + r * ldb), rows * pb);
-            const auto rr = MASK ? rows_at(reinterpret_cast<const char*>(R + r * ldr), rows * pr) : rb;
-#pragma unroll 2
-            for (int k2 = 0; k2 < BKS; k2 += 2) {
-                float a[TM], b[TN];
+        for (int tn = 0; tn < TN; ++tn) cb[tn] = jw + tn * 32 + li < MD ? jw + tn * 32 + li : j0;
+        for (int64_t r = r_begin; r < r_end; r += 2) {
+            const bool in = r + lk < r_end;
+            const int64_t row = in ? r + lk : r;
+            float a[TM], b[TN];
 #pragma unroll
-                for (int tm = 0; tm < TM; ++tm) a[tm] = load4(ra, (uint32_t)((k2 + lk) * pa) + ca[tm]);
-#pragma unroll
-                for (int tn = 0; tn < TN; ++tn) {
-                    b[tn] = load4(rb, (uint32_t)((k2 + lk) * pb) + cb[tn]);
-                    if (MASK)
-                        b[tn] = load4(rr, (uint32_t)((k2 + lk) * pr) + cb[tn]) > 0.f ? b[tn] : 0.f;
-                }
-#pragma unroll
-                for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-                    for (int tn = 0; tn < TN; ++tn)
-                        acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[tm], b[tn], acc[tm][tn], 0, 0, 0);
+            for (int tm = 0; tm < TM; ++tm) {
+                const float x = A[row * lda + ca[tm]];
+                a[tm] = in ? x : 0.f;
             }
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn) {
+                const float x = B[row * ldb + cb[tn]];
+                b[tn] = in && (!MASK || R[row * ldr + cb[tn]] > 0.f) ? x : 0.f;
+            }
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                for (int tn = 0; tn < TN; ++tn)
+                    acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[tm], b[tn], acc[tm][tn], 0, 0, 0);
         }
     }
 
@@ -340,12 +333,6 @@ __global__ __launch_bounds__(kBlock, 2) void wgrad_split_kernel(
 
 }  // namespace
 
-bool wgrad_split_applies(int64_t lda, int64_t ldb, int64_t ldr, int64_t n)
-{
-    // a step of 16 rows as one buffer with 32-bit offsets
-    return n > 0 && lda < (1 << 22) && ldb < (1 << 22) && ldr < (1 << 22);
-}
-
 // dW[k x m] = beta dW + A[n x k]^T (B (.) mask)[n x m]
 int launch_wgrad_split(const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc, int64_t n,
                        int32_t k, int32_t m, const float* R, int64_t ldr, float beta, hipStream_t s, Timer* timer)
@@ -355,26 +342,34 @@ int launch_wgrad_split(const float* A, int64_t lda, const float* B, int64_t ldb,
     const int bn = m > 64 ? 128 : m > 32 ? 64 : 32;
     const int nit = (int)ceil_div(k, 128), njt = (int)ceil_div(m, bn), tiles = nit * njt;
     int64_t n_slabs = wgrad_slabs(n, tiles, 1024);
-    const int64_t rows_per_slab = ceil_div(ceil_div(n, n_slabs), BKS) * BKS;
-    n_slabs = ceil_div(n, rows_per_slab);
+    int64_t rows_per_slab = ceil_div(ceil_div(n, n_slabs), BKS) * BKS;
+    if (rows_per_slab < BKS) rows_per_slab = BKS;
+    n_slabs = n > 0 ? ceil_div(n, rows_per_slab) : 1;  // without rows: one slab of zeros
+    const bool far = lda >= (1 << 22) || ldb >= (1 << 22) || (R && ldr >= (1 << 22));
     const int64_t cells = (int64_t)k * m;
     void* scratch = nullptr;
     MIXGCN_TRY(get_scratch(0, (size_t)n_slabs * cells * sizeof(float), &scratch));
     float* P = (float*)scratch;
     const unsigned grid = (unsigned)(n_slabs * tiles);
     if (timer) MIXGCN_TRY(timer->begin(kTimeUpdateWgrad, s));
-#define MIXGCN_WGRAD(BN)                                                                                       \
-    do {                                                                                                       \
-        if (R)                                                                                                 \
-            hipLaunchKernelGGL((wgrad_split_kernel<BN, true>), dim3(grid), dim3(kBlock), 0, s, A, lda, B, ldb, \
-                               R, ldr, P, k, m, rows_per_slab, n, nit, njt);                                   \
-        else                                                                                                   \
-            hipLaunchKernelGGL((wgrad_split_kernel<BN, false>), dim3(grid), dim3(kBlock), 0, s, A, lda, B,     \
-                               ldb, R, ldr, P, k, m, rows_per_slab, n, nit, njt);                              \
+#define MIXGCN_WGRAD(BN, MASK, FAR)                                                                              \
+    hipLaunchKernelGGL((wgrad_split_kernel<BN, MASK, FAR>), dim3(grid), dim3(kBlock), 0, s, A, lda, B, ldb, R, ldr, \
+                       P, k, m, rows_per_slab, n, nit, njt)
+#define MIXGCN_WGRAD_FAR(BN, MASK)                \
+    do {                                          \
+        if (far) MIXGCN_WGRAD(BN, MASK, true);    \
+        else MIXGCN_WGRAD(BN, MASK, false);       \
     } while (0)
-    if (bn == 128) MIXGCN_WGRAD(128);
-    else if (bn == 64) MIXGCN_WGRAD(64);
-    else MIXGCN_WGRAD(32);
+#define MIXGCN_WGRAD_MASK(BN)                     \
+    do {                                          \
+        if (R) MIXGCN_WGRAD_FAR(BN, true);        \
+        else MIXGCN_WGRAD_FAR(BN, false);         \
+    } while (0)
+    if (bn == 128) MIXGCN_WGRAD_MASK(128);
+    else if (bn == 64) MIXGCN_WGRAD_MASK(64);
+    else MIXGCN_WGRAD_MASK(32);
+#undef MIXGCN_WGRAD_MASK
+#undef MIXGCN_WGRAD_FAR
 #undef MIXGCN_WGRAD
     if (timer) MIXGCN_TRY(timer->end(s));
     MIXGCN_TRY(launch_wgrad_reduce(P, n_slabs, cells, m, C, ldc, beta, s));

@@ -259,8 +259,7 @@ int launch_wgrad_bf16(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t
                       int64_t n, int32_t k, int32_t m, const uint16_t* R, int64_t ldr, float beta,
                       hipStream_t s, Timer* timer);
 
-// the same of fp32 features, every operand as three bf16 terms, where the pitches allow 32-bit offsets
-bool wgrad_split_applies(int64_t lda, int64_t ldb, int64_t ldr, int64_t n);
+// the same of fp32 features, every operand as three bf16 terms
 int launch_wgrad_split(const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc,
                        int64_t n, int32_t k, int32_t m, const float* R, int64_t ldr, float beta,
                        hipStream_t s, Timer* timer);

@@ -78,10 +78,7 @@ def test_row_products_element_by_element(mg, dtype, n, k, m):
     step = 32 if dtype == torch.float32 else 64
     out = torch.full_like(g, 7.0)
     mg.update(mg.OP_FWD, z[:, :k], w, out[:, :m], n, k, m)
-    if dtype == torch.bfloat16:
-        check(out[:, :m], z[:, :k], w, dtype, -(-k // step), "forward")
-    else:
-        assert torch.equal(out[:, :m], chain(z[:, :k], w))
+    check(out[:, :m], z[:, :k], w, dtype, -(-k // step), "forward")
     plain = out.clone()
     mg.update(mg.OP_FWD_RELU, z[:, :k], w, out[:, :m], n, k, m)
     assert torch.equal(out[:, :m], plain[:, :m].clamp(min=0)) and (out[:, m:] == 7.0).all()
@@ -93,11 +90,35 @@ def test_row_products_element_by_element(mg, dtype, n, k, m):
         assert (dz[:, k:] == 7.0).all()
 
 
-@pytest.mark.parametrize("product", ["forward", "forward of three terms", "data gradient"])
-@pytest.mark.parametrize("k,m", [(64, 128), (304, 72)])
-def test_fp32_values_that_are_not_finite(mg, k, m, product):
+@pytest.mark.parametrize("k,m", [(64, 128), (300, 40)])
+def test_fp32_values_that_are_not_finite(mg, k, m):
     """An infinity, NaN and a value whose first term rounds to infinity reach the same outputs as in a
     product of plain floats, and the finite rows around them keep their accuracy."""
+    n = 200
+    gen = torch.Generator(device="cuda").manual_seed(k)
+    z = torch.randn(n, k, device="cuda", generator=gen)
+    w = torch.randn(k, m, device="cuda", generator=gen)
+    w[1] = 0.5
+    z[3, 5], z[40, 2], z[70, 1], z[71, 1] = float("inf"), float("nan"), 3.4e38, -3.4e38
+    out = torch.empty(n, m, device="cuda")
+    mg.update(mg.OP_FWD, z, w, out, n, k, m)
+    ref = (z.double() @ w.double()).float()
+    assert torch.equal(out.isnan(), ref.isnan()) and torch.equal(out.isposinf(), ref.isposinf())
+    assert torch.equal(out.isneginf(), ref.isneginf())
+    rest = torch.ones(n, dtype=torch.bool, device="cuda")
+    rest[[3, 40, 70, 71]] = False
+    check(out[rest], z[rest], w, torch.float32, k, "finite rows")
+    assert (out[70] - ref[70]).abs().max() <= 1e-6 * ref[70].abs().max()
+    w[2, 0] = float("inf")
+    z = torch.rand(n, k, device="cuda", generator=gen) + 0.5
+    mg.update(mg.OP_FWD, z, w, out, n, k, m)
+    assert out[:, 0].isposinf().all() and not out[:, 1:].isinf().any() and not out.isnan().any()
+
+
+@pytest.mark.parametrize("product", ["forward of three terms", "data gradient"])
+@pytest.mark.parametrize("k,m", [(64, 128), (304, 72)])
+def test_fp32_values_that_are_not_finite_in_three_terms(mg, k, m, product):
+    """As above in the products that split their operands, and the activation of what is not finite."""
     n = 200
     gen = torch.Generator(device="cuda").manual_seed(k)
     z = torch.randn(n, k, device="cuda", generator=gen)
@@ -108,7 +129,7 @@ def test_fp32_values_that_are_not_finite(mg, k, m, product):
         if product == "data gradient":
             mg.update(mg.OP_DGRAD, z, w.t().contiguous(), out, n, m, k)
             return out
-        mg.set_update_arith(mg.ARITH_BF16X3 if product == "forward of three terms" else mg.ARITH_FP32)
+        mg.set_update_arith(mg.ARITH_BF16X3)
         try:
             mg.update(op, z, w, out, n, k, m)
         finally:
@@ -224,3 +245,26 @@ def test_fp32_weight_gradient_of_a_pitch_past_32_bit_offsets(mg):
     dw = torch.empty(k, m, device="cuda")
     mg.update(mg.OP_WGRAD, z, g, dw, n, k, m, relu_ref=h)
     check(dw, z.t(), torch.where(h > 0, g, torch.zeros_like(g)), torch.float32, n, "weight gradient")
+
+
+@pytest.mark.parametrize("n,k,m,far", [(19, 70, 40, "zgh"), (33, 130, 20, "z"), (16, 20, 100, "g"), (50, 33, 129, "h"),
+                                       (17, 40, 65, "gh"), (2, 5, 3, "zgh")])
+def test_fp32_weight_gradient_does_not_depend_on_the_pitch(mg, n, k, m, far):
+    """From 2^22 elements on rows are addressed with 64 bits: the same bits for every operand that is so far
+    apart, with what is not finite, and zeros for the rows past the last step."""
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    for bad in (False, True):
+        near, wide = {}, {}
+        for name, cols in (("z", k), ("g", m), ("h", m)):
+            t = padded(n, cols, torch.float32, gen)[:, :cols]
+            if bad and name != "h":
+                t[n // 2, 0] = float("inf")
+            near[name] = wide[name] = t
+            if name in far:
+                wide[name] = torch.empty(n * ((1 << 22) + 4), device="cuda").view(n, -1)[:, :cols]
+                wide[name].copy_(t)
+        for ref in (False, True):
+            dw = [torch.empty(k, (m + 3) // 4 * 4, device="cuda")[:, :m] for _ in range(2)]
+            for d, x in zip(dw, (near, wide)):
+                mg.update(mg.OP_WGRAD, x["z"], x["g"], d, n, k, m, relu_ref=x["h"] if ref else None)
+            assert torch.equal(dw[0].view(torch.int32), dw[1].view(torch.int32)), (bad, ref)
