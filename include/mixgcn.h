@@ -289,13 +289,14 @@ int mixgcn_apply_bitmap(int dtype, void* X, int64_t ldx, int64_t n_rows, int32_t
  * [n x k], B = the upstream gradient [n x m], C = dW [k x m] fp32.
  * The forward product of fp32 features is a chain of fp32 multiply-adds over the reduction index, on the
  * fp32 matrix cores (mixgcn_set_update_arith chooses otherwise).  Their data and weight gradients run on the
- * bf16 matrix cores: an operand is the exact sum of three bf16 terms and a product is accumulated in fp32 from
- * the six partial products of order 2^-16 and above (the others are together below 2^-23 |a| |b|).  Against
- * 64 bits these results are closer than those of a chain of fp32 multiply-adds (relative error 5.6e-8 against
- * 2.0e-7 at depth 128).  bf16 features enter as they are and the weights as two terms.  Infinities and NaN
- * give what fp32 arithmetic gives (fp32 products on the bf16 matrix cores compute every sum that is not finite
- * again, one multiply-add at a time: a tensor full of NaN takes many times as long); operands of a gradient below about 1e-33 in magnitude carry fewer than 24
- * bits into a product (at 1e-35 a relative error of 3e-6).
+ * bf16 matrix cores where the reduction has at least four terms: an operand is the exact sum of three bf16
+ * terms and a product is accumulated in fp32 from the six partial products of order 2^-16 and above (the
+ * others are together below 2^-23 |a| |b|).  Against 64 bits these results are closer than those of a chain of
+ * fp32 multiply-adds (relative error 5.6e-8 against 2.0e-7 at depth 128).  Operands of a gradient below about
+ * 1e-33 in magnitude carry fewer than 24 bits into a product (at 1e-35 a relative error of 3e-6).  bf16
+ * features enter as they are and the weights as two terms.  Infinities and NaN give what fp32 arithmetic gives:
+ * fp32 products on the bf16 matrix cores compute every sum that is not finite again, one multiply-add at a
+ * time (a tensor full of NaN takes many times as long).
  * Two per-device work buffers are shared by all calls: the slab partials of WGRAD, and the weight terms of
  * products that split them beforehand (bf16 ones whose weights do not fit LDS, more than 256 reduction indices,
  * and forward products under MIXGCN_ARITH_BF16X3).  Calls that use the same one must not overlap: issue them on one stream, or order the streams with events (the layer and pipeline

@@ -385,6 +385,59 @@ __global__ __launch_bounds__(kBlock, kRowblockMinBlocks) void rowblock_gemm_kern
         }
 }
 
+// ---- data gradient over fewer than four indices: dZ[n x k] = (G (.) 1[R > 0])[n x m] W[k x m]^T -----
+// At these depths a chain of fp32 multiply-adds is closer to 64 bits than the sums of three bf16 terms
+// (relative error at depth 1 2.5e-8 against 3.4e-8, 2 3.1e-8 : 3.3e-8, 3 half of them zero 3.1e-8 : 3.3e-8;
+// from 4 on it is not: 4.1e-8 : 3.2e-8, 16 7.3e-8 : 3.6e-8).  Bound by writing dZ: the masked rows of G of a
+// workgroup wait in LDS, a thread keeps its four columns of W^T and walks the rows.  us at 2^20 rows 2 -> 256,
+// plain and masked, 207 and 214 (three terms 206, 208), 3 -> 100 89 and 90 (282, 278).
+constexpr int kShallowRows = 1024;  // most rows of a workgroup
+template <bool MASK>
+__global__ __launch_bounds__(kBlock) void shallow_dgrad_kernel(const float* __restrict__ G, int64_t ldg,
+                                                               const float* __restrict__ W, int64_t ldw,
+                                                               float* __restrict__ Z, int64_t ldz, int64_t n, int k,
+                                                               int m, const float* __restrict__ R, int64_t ldr,
+                                                               int quads, int block_rows)
+{
+    __shared__ float4 g[kShallowRows];
+    const int64_t row0 = (int64_t)blockIdx.x * block_rows;
+    const int here = n - row0 < block_rows ? (int)(n - row0) : block_rows;
+    for (int i = threadIdx.x; i < here; i += kBlock) {  // (rows are padded to 16 bytes)
+        float4 x = *reinterpret_cast<const float4*>(G + (row0 + i) * ldg);
+        if (MASK) {
+            const float4 r = *reinterpret_cast<const float4*>(R + (row0 + i) * ldr);
+            x = make_float4(r.x > 0.f ? x.x : 0.f, r.y > 0.f ? x.y : 0.f, r.z > 0.f ? x.z : 0.f, 0.f);
+        }
+        g[i] = x;
+    }
+    __syncthreads();
+    const int rows = kBlock / quads;  // rows per pass; the threads past them have no work
+    const int sub = threadIdx.x / quads;
+    const int c = 4 * ((int)blockIdx.y * quads + (int)(threadIdx.x % quads));
+    if (sub >= rows || c >= k) return;
+    float4 w[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = *reinterpret_cast<const float4*>(W + (int64_t)(c + e < k ? c + e : c) * ldw);
+    float* z = Z + (row0 + sub) * ldz + c;
+    for (int i = sub; i < here; i += rows, z += rows * ldz) {
+        const float4 x = g[i];
+        float o[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            o[e] = fmaf(x.x, w[e].x, 0.f);
+            if (m > 1) o[e] = fmaf(x.y, w[e].y, o[e]);
+            if (m > 2) o[e] = fmaf(x.z, w[e].z, o[e]);
+        }
+        if (c + 4 <= k) {
+            *reinterpret_cast<float4*>(z) = make_float4(o[0], o[1], o[2], o[3]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+                if (c + e < k) z[e] = o[e];
+        }
+    }
+}
+
 // dW = beta * dW + sum over slabs.  A block owns 64 consecutive cells; its four waves each add
 // every fourth slab (in slab order, fp64) and the four sums are combined in a fixed order, so
 // the result is deterministic.
@@ -480,6 +533,28 @@ int forward_f32(bool relu, const float* A, int64_t lda, const float* W, int64_t 
                   : launch_rowblock<Shape128x32>(relu, A, lda, W, ldw, C, ldc, n, k, m, s);
 }
 
+int shallow_dgrad(const float* G, int64_t ldg, const float* W, int64_t ldw, float* Z, int64_t ldz, int64_t n, int32_t k,
+                  int32_t m, const float* R, int64_t ldr, hipStream_t s)
+{
+    if (n <= 0) return MIXGCN_OK;
+    const int all = (int)ceil_div(k, 4), quads = all < kBlock ? all : kBlock, rows = kBlock / quads;
+    // at most 16 passes of rows, as long as eight workgroups per compute unit are left
+    int64_t block_rows = n / 2048 / rows * rows;
+    const int64_t most = 16 * rows < kShallowRows ? 16 * rows : kShallowRows / rows * rows;
+    block_rows = block_rows < rows ? rows : block_rows > most ? most : block_rows;
+    const int64_t grid = ceil_div(n, block_rows);
+    if (grid > 0x7FFFFFFF || ceil_div(all, quads) > 65535) return fail(MIXGCN_EINVAL, "update: too many row tiles");
+    const dim3 blocks((unsigned)grid, (unsigned)ceil_div(all, quads));
+    if (R)
+        hipLaunchKernelGGL(shallow_dgrad_kernel<true>, blocks, dim3(kBlock), 0, s, G, ldg, W, ldw, Z, ldz, n, k, m, R,
+                           ldr, quads, (int)block_rows);
+    else
+        hipLaunchKernelGGL(shallow_dgrad_kernel<false>, blocks, dim3(kBlock), 0, s, G, ldg, W, ldw, Z, ldz, n, k, m, R,
+                           ldr, quads, (int)block_rows);
+    MIXGCN_HIP_TRY(hipGetLastError());
+    return MIXGCN_OK;
+}
+
 }  // namespace
 
 int launch_relu_mask(int dtype, void* G, int64_t ldg, const void* R, int64_t ldr, int64_t n,
@@ -515,7 +590,10 @@ int launch_update(int op, int dtype, const void* A, int64_t lda, const void* B, 
     if (op != MIXGCN_OP_WGRAD) {
         const bool fwd = op != MIXGCN_OP_DGRAD, relu = op == MIXGCN_OP_FWD_RELU;
         if (timer) MIXGCN_TRY(timer->begin(fwd ? kTimeUpdateFwd : kTimeUpdateDgrad, s));
-        if (!fwd || dtype != MIXGCN_F32)
+        if (!fwd && dtype == MIXGCN_F32 && m < 4)
+            MIXGCN_TRY(shallow_dgrad((const float*)A, lda, (const float*)B, ldb, (float*)C, ldc, n, k, m,
+                                     (const float*)R, ldr, s));
+        else if (!fwd || dtype != MIXGCN_F32)
             MIXGCN_TRY(launch_update_rows(dtype, fwd, relu, A, lda, (const float*)B, ldb, C, ldc, n, fwd ? k : m,
                                           fwd ? m : k, fwd ? nullptr : R, ldr, s));
         else if (g_update_arith == MIXGCN_ARITH_BF16X3 && forward_split_applies(lda, n, k, m))

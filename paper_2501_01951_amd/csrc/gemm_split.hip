@@ -285,9 +285,10 @@ __global__ __launch_bounds__(kBlock, 2) void wgrad_split_kernel(
                 const bool in = iw + tm * 32 + 8 * (v / 4) + 4 * lk + (v % 4) < KD && jw + tn * 32 + li < MD;
                 z = fmaf(in ? acc[tm][tn][v] : 0.f, 0.f, z);
             }
-    if (__builtin_expect(__any(!(z == 0.f)), 0)) {
+    if (__builtin_expect(r_end - r_begin < 4 || __any(!(z == 0.f)), 0)) {
         // A sum that is not finite (a term of an infinity is NaN, a value next to the largest float rounds
-        // up to an infinity): the wavefront's tile again on the fp32 matrix cores, straight from memory.
+        // up to an infinity), or fewer than four rows, over which a chain of fp32 multiply-adds is closer to
+        // 64 bits: the wavefront's tile again on the fp32 matrix cores, straight from memory.
         // 32x32x2: lane l supplies column l % 32 of reduction index l / 32.
         clear();
         int ca[TM], cb[TN];

@@ -155,6 +155,53 @@ def test_fp32_values_that_are_not_finite_in_three_terms(mg, k, m, product):
     assert out[:, 0].isposinf().all() and not out[:, 1:].isinf().any() and not out.isnan().any()
 
 
+@pytest.mark.parametrize("values", ["normal", "half zero", "positive"])
+@pytest.mark.parametrize("depth", [1, 2, 3, 4, 8, 16, 32, 128, 1024])
+def test_fp32_gradients_are_no_further_from_64_bits_than_the_chain(mg, depth, values):
+    """2-norm over 4096 x 100 results of the data gradient and 100 x 100 of the weight gradient; the two errors
+    are the same number of roundings at depth 4 with half of the values zero (5 % for the sample)."""
+    gen = torch.Generator(device="cuda").manual_seed(depth)
+    rows, cols = 4096, 100
+    g = torch.randn(rows, depth, device="cuda", generator=gen)
+    w = torch.randn(depth, cols, device="cuda", generator=gen) * 0.1
+    if values == "half zero":
+        g.clamp_(min=0)
+    elif values == "positive":
+        g.abs_(), w.abs_()
+
+    def aligned(t):
+        out = torch.zeros(t.shape[0], (t.shape[1] + 3) // 4 * 4, device="cuda")
+        out[:, :t.shape[1]] = t
+        return out[:, :t.shape[1]]
+
+    def error(x, a, b):
+        ref = a.double() @ b.double()
+        return ((x.double() - ref).norm() / ref.norm()).item()
+
+    dz = torch.empty(rows, cols, device="cuda")
+    mg.update(mg.OP_DGRAD, aligned(g), aligned(w.t()), dz, rows, cols, depth)
+    assert error(dz, g, w) <= 1.05 * error(chain(g, w), g, w)
+    a = g[:cols].contiguous()  # as [cols x depth]: features of `depth` nodes, transposed
+    dw = torch.empty(cols, cols, device="cuda")
+    mg.update(mg.OP_WGRAD, aligned(a.t()), aligned(w), dw, depth, cols, cols)
+    assert error(dw, a, w) <= 1.05 * error(chain(a, w), a, w)
+
+
+@pytest.mark.parametrize("n,k,m", [(1, 1, 1), (1000, 3, 2), (777, 64, 3), (333, 129, 1), (2048, 256, 2), (50, 602, 3),
+                                   (40, 1100, 2), (2200003, 1, 3)])
+def test_fp32_data_gradient_of_few_columns_is_the_fp32_chain(mg, n, k, m):
+    gen = torch.Generator(device="cuda").manual_seed(n + k)
+    g, h = (padded(n, m, torch.float32, gen) for _ in range(2))
+    w = padded(k, m, torch.float32, gen)[:, :m]
+    g[n // 2, 0], h[n // 3, 0] = float("inf"), float("nan")
+    for ref in (None, h[:, :m]):
+        dz = padded(n, k, torch.float32, gen)
+        mg.update(mg.OP_DGRAD, g[:, :m], w, dz[:, :k], n, k, m, relu_ref=ref)
+        dp = g[:, :m] if ref is None else torch.where(ref > 0, g[:, :m], torch.zeros_like(g[:, :m]))
+        want = chain(dp, w.t())
+        assert torch.equal(dz[:, :k].nan_to_num(7.0), want.nan_to_num(7.0)) and dz[:, k:].isnan().all()
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("k,m", [(64, 128), (128, 40), (256, 128), (330, 130)])
 def test_values_that_are_not_finite_stay_in_their_rows(mg, dtype, k, m):
