@@ -67,6 +67,8 @@ def test_fp32_forward_sums_are_the_fp32_chain(mg, n, k, m):
 SHAPES = [(1, 1, 1), (31, 3, 16), (32, 32, 17), (33, 31, 33), (255, 33, 64), (257, 64, 65), (64, 160, 128),
           (100, 161, 129), (300, 256, 127), (290, 257, 100), (520, 320, 47), (45, 602, 41), (8200, 16, 96),
           (129, 1027, 130)]
+# more column tiles than compute units of an XCD: several rounds of workgroups
+SHAPES += [(20000, 32, 4130), (20000, 4130, 32)]
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
