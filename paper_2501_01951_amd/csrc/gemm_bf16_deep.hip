@@ -11,7 +11,7 @@
 //
 // MFMA 32x32x16 operand layout: lane l supplies A[i = l % 32][k = 8 (l / 32) + 0..7] and
 // B[k = 8 (l / 32) + 0..7][j = l % 32] as eight consecutive bf16; D as for the fp32 32x32 MFMA.
-#include "device_utils.h"
+#include "gemm_common.h"
 #include "internal.h"
 
 namespace mixgcn {
@@ -38,12 +38,6 @@ __device__ inline uint16_t bf16_rne(float f)
     uint32_t u = __float_as_uint(f);
     if ((u & 0x7F800000u) != 0x7F800000u) u += 0x7FFFu + ((u >> 16) & 1u);
     return (uint16_t)(u >> 16);
-}
-
-__device__ inline unsigned xcd_local_index(unsigned bid, unsigned grid)
-{
-    const unsigned q = grid / 8, rem = grid % 8, x = bid % 8;
-    return x * q + (x < rem ? x : rem) + bid / 8;
 }
 
 // Operand element (j, kk) = transpose ? W[kk][j] : W[j][kk], zero outside W, as bf16 hi and lo
@@ -124,27 +118,12 @@ __device__ inline bf16x8 lds_operand(const uint16_t* p)
 // scalar base plus a fixed per-thread offset to a fixed LDS position (the split weights are
 // padded to whole tiles with zeros).  What is left per step is the ReLU mask, three packed 16-bit
 // integer instructions and an AND per 32-bit word.
-typedef short short2v __attribute__((ext_vector_type(2)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) uintx4 lds_uintx4;
 __device__ inline void lds_store16(uint16_t* p, const uint4& v)
 {
     const uintx4 q = {v.x, v.y, v.z, v.w};
     *(lds_uintx4*)p = q;
-}
-
-// x with the halves zeroed whose reference half (bf16 bits) is not > 0: as 16-bit integers,
-// max(r, 0) is positive exactly for positive finite values (and +inf), its negation then has
-// the sign bit set, which an arithmetic shift spreads over the half.
-__device__ inline uint32_t keep_positive(uint32_t x, uint32_t r)
-{
-    short2v rr;
-    __builtin_memcpy(&rr, &r, 4);
-    const short2v zero = {0, 0};
-    const short2v keep = (-__builtin_elementwise_max(rr, zero)) >> 15;
-    uint32_t k;
-    __builtin_memcpy(&k, &keep, 4);
-    return x & k;
 }
 
 // two fp32 -> two bf16 (round to nearest even, the conversion instruction of this part), first

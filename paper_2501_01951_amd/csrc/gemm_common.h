@@ -28,6 +28,25 @@ __device__ inline uint32_t pack_bf16(float a, float b)
 __device__ inline float low_half(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ inline float high_half(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
 
+// x with the halves zeroed whose reference half (bf16 bits) is not > 0: 1 .. 0x7F80 are the positive values up
+// to +inf.  r - 1 is then below 0x7F80, and 0x7F80 less that, saturated, positive exactly for them; its negation
+// has the sign bit set, which an arithmetic shift spreads over the half.
+__device__ inline uint32_t keep_positive(uint32_t x, uint32_t r)
+{
+    typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
+    typedef short short2v __attribute__((ext_vector_type(2)));
+    ushort2v rr;
+    __builtin_memcpy(&rr, &r, 4);
+    const ushort2v one = {1, 1}, inf = {0x7F80, 0x7F80};
+    const ushort2v above = __builtin_elementwise_sub_sat(inf, (ushort2v)(rr - one));
+    short2v a;
+    __builtin_memcpy(&a, &above, 4);
+    const short2v keep = (-a) >> 15;
+    uint32_t k;
+    __builtin_memcpy(&k, &keep, 4);
+    return x & k;
+}
+
 // The elements of rows [row0, row1) and columns [col0, col1) of C that are not finite, again as chains of fp32
 // multiply-adds over the reduction index (a term of an infinity is NaN, a value next to the largest float
 // rounds up to an infinity as bf16); then, with RELU, the activation of all of them.  C holds the sums of the

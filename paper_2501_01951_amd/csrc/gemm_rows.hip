@@ -35,7 +35,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) uintx4 lds_uintx4;
-typedef short short2v __attribute__((ext_vector_type(2)));
 
 constexpr int kRowsWaves = 8;                      // most wavefronts per workgroup
 constexpr int kRowsBlock = kRowsWaves * kWave;
@@ -86,18 +85,6 @@ __device__ inline int tile_column(int t, int i)
 {
     if (DT == MIXGCN_F32 || TN == 1) return t * 16 + i;
     return (t >> 1) * 32 + (i >> 2) * 8 + (t & 1) * 4 + (i & 3);
-}
-
-// x with the halves zeroed whose reference half (bf16 bits) is not > 0
-__device__ inline uint32_t keep_positive(uint32_t x, uint32_t r)
-{
-    short2v rr;
-    __builtin_memcpy(&rr, &r, 4);
-    const short2v zero = {0, 0};
-    const short2v keep = (-__builtin_elementwise_max(rr, zero)) >> 15;
-    uint32_t k;
-    __builtin_memcpy(&k, &keep, 4);
-    return x & k;
 }
 
 // P bf16 terms of eight fp32 values, term p in out[4 p ..]: words of two consecutive values.

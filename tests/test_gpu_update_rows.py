@@ -317,3 +317,26 @@ def test_fp32_weight_gradient_does_not_depend_on_the_pitch(mg, n, k, m, far):
             for d, x in zip(dw, (near, wide)):
                 mg.update(mg.OP_WGRAD, x["z"], x["g"], d, n, k, m, relu_ref=x["h"] if ref else None)
             assert torch.equal(dw[0].view(torch.int32), dw[1].view(torch.int32)), (bad, ref)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("n,k,m", [(300, 40, 72), (300, 128, 256), (140, 130, 700), (300, 20, 24)])
+def test_the_relu_derivative_of_nan_is_zero(mg, dtype, n, k, m):
+    """1[R > 0] in every path of a masked product, next to both infinities and both zeros."""
+    gen = torch.Generator(device="cuda").manual_seed(n + k + m)
+    z, g, h = (padded(n, c, dtype, gen) for c in (k, m, m))
+    w = torch.randn(k, m, device="cuda", generator=gen)
+    special = torch.tensor([float("nan"), float("inf"), -float("inf"), 0.0, -0.0, 1e-38], device="cuda", dtype=dtype)
+    at = torch.randint(0, 24, (n, m), device="cuda", generator=gen)
+    h[:, :m] = torch.where(at < 6, special[at.clamp(max=5)], h[:, :m])
+    if dtype == torch.bfloat16:  # a NaN of every sign and payload
+        h[:, :m].view(torch.int16)[at == 6] = 0x7F81
+        h[:, :m].view(torch.int16)[at == 7] = -1
+    plain = torch.where(h > 0, 1.0, -1.0).to(dtype)
+    out = []
+    for ref in (h[:, :m], plain[:, :m]):
+        dz, dw = padded(n, k, dtype, gen), torch.empty(k, m, device="cuda")
+        mg.update(mg.OP_DGRAD, g[:, :m], w, dz[:, :k], n, k, m, relu_ref=ref)
+        mg.update(mg.OP_WGRAD, z[:, :k], g[:, :m], dw, n, k, m, relu_ref=ref)
+        out.append((dz[:, :k], dw))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
