@@ -298,9 +298,11 @@ int mixgcn_apply_bitmap(int dtype, void* X, int64_t ldx, int64_t n_rows, int32_t
  * fp32 products on the bf16 matrix cores compute every sum that is not finite again, one multiply-add at a
  * time (a tensor full of NaN takes many times as long).
  * Two per-device work buffers are shared by all calls: the slab partials of WGRAD, and the weight terms of
- * products that split them beforehand (bf16 ones whose weights do not fit LDS, more than 256 reduction indices,
- * and forward products under MIXGCN_ARITH_BF16X3).  Calls that use the same one must not overlap: issue them on one stream, or order the streams with events (the layer and pipeline
- * entry points do).
+ * products that split them beforehand: bf16 FWD and DGRAD whose weights do not fit LDS (4 bytes for every
+ * reduction index, rounded up to 64, and output column, rounded up to 16, 32, 64 or 128 and 128 at most, are
+ * more than 160 KB: 320 indices of more than 64 columns, 640, 1280 and 2560 of fewer), and FWD under
+ * MIXGCN_ARITH_BF16X3.  Calls that use the same one must not overlap: issue them on one stream, or order the
+ * streams with events (the layer and pipeline entry points do).
  */
 int mixgcn_update(int op, int dtype, const void* A, int64_t lda, const void* B, int64_t ldb,
                   void* C, int64_t ldc, int64_t n_rows, int32_t k, int32_t m,

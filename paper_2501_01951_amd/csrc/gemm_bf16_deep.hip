@@ -1,5 +1,5 @@
-// Forward product and data gradient of bf16 features whose weights do not fit LDS (more than 256 reduction
-// indices of 128 output columns, 640 of 64): tiles of 128 x 128 or 128 x 32 on the bf16 matrix cores
+// Forward product and data gradient of bf16 features whose weights do not fit LDS (more than 320 reduction
+// indices of 128 output columns, 640 of 64, 1280 of 32, 2560 of 16): tiles of 128 x 128 or 128 x 32 on the bf16 matrix cores
 // (v_mfma_f32_32x32x16_bf16, fp32 accumulation), both operands staged through LDS.
 //
 // Every call first splits W = hi + lo into two bf16 terms (|W - hi - lo| < 2^-16 |W|) in the layout the B

@@ -9,8 +9,8 @@
 // (|W - hi - lo| < 2^-16 |W|).
 //
 // Work split.  The weights of 128 output columns stay in LDS, in MFMA operand order, for as long as the
-// workgroup lives (one per compute unit: three terms of up to 160 reduction indices, or two of 256, fill
-// 120 to 128 KB); its eight wavefronts then walk 32-row tiles of their own without a barrier, each with
+// workgroup lives (one per compute unit; what fits is kRowsLds: three terms of up to 192 reduction indices, 144 KB,
+// or two of up to 320, 160 KB, and of fewer output columns twice as many each time); its eight wavefronts then walk 32-row tiles of their own without a barrier, each with
 // the rows of the next two steps in flight from global memory straight to registers (16 rows of 64 bytes
 // per load: such a read runs at the streaming rate, 6.1 TB/s).  No other wavefront needs a row, so
 // nothing is gained from LDS, and a term split happens once.  Deeper fp32 products stream the weights

@@ -62,11 +62,15 @@ def test_fp32_forward_sums_are_the_fp32_chain(mg, n, k, m):
         assert torch.equal(out[:, :m], ref) and out[:, m:].isnan().all()
 
 
-# rows: one, around a tile and a workgroup's rows; depths: below, at and past a step, the most that keeps
-# 128 columns of weights in LDS (fp32 160, bf16 256) and beyond; columns: around every tile width
+# rows: one, around a tile and a workgroup's rows; depths: below, at and past a step; columns: around every tile width
 SHAPES = [(1, 1, 1), (31, 3, 16), (32, 32, 17), (33, 31, 33), (255, 33, 64), (257, 64, 65), (64, 160, 128),
           (100, 161, 129), (300, 256, 127), (290, 257, 100), (520, 320, 47), (45, 602, 41), (8200, 16, 96),
           (129, 1027, 130)]
+# the deepest products whose weights stay in LDS and the next deeper ones, for every tile width: fp32 192, 416, 832 and
+# 1696 indices of 128, 64, 32 and 16 columns (data gradient), bf16 320, 640, 1280 and 2560 (both)
+SHAPES += [(150, k, m + d) for k, m in ((128, 192), (50, 416), (20, 832), (9, 1696), (100, 320), (60, 640), (20, 1280),
+                                        (10, 2560)) for d in (0, 1)]
+SHAPES += [(150, k + d, m) for k, m in ((320, 100), (640, 60), (1280, 20), (2560, 10)) for d in (0, 1)]
 # more column tiles than compute units of an XCD: several rounds of workgroups
 SHAPES += [(20000, 32, 4130), (20000, 4130, 32)]
 
