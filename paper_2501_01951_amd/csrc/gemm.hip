@@ -23,17 +23,6 @@ constexpr int BK = 16;          // reduction depth staged per step
 constexpr int kRowblockMinBlocks = 3;
 constexpr int kLdsPad = 4;      // row stride of the staged tiles = tile width + 4 floats
 
-// Tile shape: WM x WN waves (4 in total), each owning TM x TN accumulator tiles of 32 x 32.
-template <int WM_, int WN_, int TM_, int TN_>
-struct Shape {
-    static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_;
-    static constexpr int BM = WM * TM * 32;  // extent along the A-operand free dimension
-    static constexpr int BN = WN * TN * 32;  // extent along the B-operand free dimension
-    static_assert(WM * WN == 4, "four waves per block");
-};
-using Shape128x128 = Shape<2, 2, 2, 2>;
-using Shape128x32 = Shape<4, 1, 1, 1>;
-
 // acc += As[kk][a-rows] (x) Bs[kk][b-cols] over the BK staged reduction steps.  The operand
 // registers of step k2 + 2 are read from LDS before the MFMAs of step k2 are issued.
 // MFMA 32x32x2 operand layout: lane l supplies A[i = l % 32][k = l / 32] and B[k = l / 32][j = l % 32].

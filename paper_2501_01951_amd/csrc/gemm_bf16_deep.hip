@@ -11,34 +11,11 @@
 //
 // MFMA 32x32x16 operand layout: lane l supplies A[i = l % 32][k = 8 (l / 32) + 0..7] and
 // B[k = 8 (l / 32) + 0..7][j = l % 32] as eight consecutive bf16; D as for the fp32 32x32 MFMA.
-#include "gemm_common.h"
+#include "gemm_bf16_tiles.h"
 #include "internal.h"
 
 namespace mixgcn {
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-
-constexpr int BKB = 32;       // reduction depth staged per step (bf16 elements)
-constexpr int LDT = BKB + 8;  // LDS row stride: 80 bytes, so 16-byte reads of 16 rows hit all banks
-
-template <int WM_, int WN_, int TM_, int TN_>
-struct Shape {
-    static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_;
-    static constexpr int BM = WM * TM * 32;
-    static constexpr int BN = WN * TN * 32;
-    static_assert(WM * WN == 4, "four waves per block");
-};
-using Shape128x128 = Shape<2, 2, 2, 2>;
-using Shape128x32 = Shape<4, 1, 1, 1>;
-
-__device__ inline uint16_t bf16_rne(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7F800000u) != 0x7F800000u) u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
 
 // Operand element (j, kk) = transpose ? W[kk][j] : W[j][kk], zero outside W, as bf16 hi and lo
 // parts, in the order the row-block kernel walks them: [column tile j / bn][step kk / BKB]
@@ -56,58 +33,11 @@ __global__ __launch_bounds__(kBlock) void split_weights_kernel(
     const int j = idx / out_cols, kk = idx % out_cols;
     const int r = transpose ? kk : j, c = transpose ? j : kk;
     const float x = (r < rows_w && c < cols_w) ? W[(int64_t)r * ldw + c] : 0.f;
-    const uint16_t h = bf16_rne(x);
-    const float rest = x - __uint_as_float((uint32_t)h << 16);
+    const uint16_t h = (uint16_t)pack_bf16(x, 0.f);
+    const float rest = x - low_half(h);
     const size_t o = split_weight_index(j, kk, bn, out_cols / BKB);
     hi[o] = h;
-    lo[o] = (rest == rest && fabsf(rest) <= 3.0e38f) ? bf16_rne(rest) : (uint16_t)0;
-}
-
-// Eight bf16 of a feature tile on their way from global memory to LDS: issue() starts the
-// loads from an address clamped into the matrix, value() zeroes what lies outside it and, with
-// MASK, what the ReLU-derivative mask 1[R > 0] removes.
-template <bool MASK>
-struct Piece8 {
-    uint4 v, m;
-    int nvalid;  // leading elements inside the matrix (0..8)
-
-    __device__ inline void issue(const uint16_t* __restrict__ M, int64_t ld, int64_t r, int c,
-                                 int64_t rows, int cols, const uint16_t* __restrict__ R,
-                                 int64_t ldr)
-    {
-        const bool ok = r < rows && c < cols;
-        nvalid = ok ? (cols - c < 8 ? cols - c : 8) : 0;
-        const int64_t rr = r < rows ? r : rows - 1;
-        const int cc = c < cols ? c : 0;
-        v = *reinterpret_cast<const uint4*>(M + rr * ld + cc);
-        if (MASK) m = *reinterpret_cast<const uint4*>(R + rr * ldr + cc);
-        else m = make_uint4(0u, 0u, 0u, 0u);
-    }
-    __device__ static inline uint32_t keep_word(uint32_t x, uint32_t r, int left)
-    {
-        uint32_t keep = 0;
-        if (left > 0) keep |= 0x0000FFFFu;
-        if (left > 1) keep |= 0xFFFF0000u;
-        if (MASK) {
-            if (!(__uint_as_float(r << 16) > 0.f)) keep &= 0xFFFF0000u;
-            if (!(__uint_as_float(r & 0xFFFF0000u) > 0.f)) keep &= 0x0000FFFFu;
-        }
-        return x & keep;
-    }
-    __device__ inline uint4 value() const
-    {
-        uint4 o;
-        o.x = keep_word(v.x, m.x, nvalid);
-        o.y = keep_word(v.y, m.y, nvalid - 2);
-        o.z = keep_word(v.z, m.z, nvalid - 4);
-        o.w = keep_word(v.w, m.w, nvalid - 6);
-        return o;
-    }
-};
-
-__device__ inline bf16x8 lds_operand(const uint16_t* p)
-{
-    return *reinterpret_cast<const bf16x8*>(p);
+    lo[o] = fabsf(rest) <= 3.0e38f ? (uint16_t)pack_bf16(rest, 0.f) : (uint16_t)0;
 }
 
 // ---- fast path of the row-block kernel ----------------------------------------------------------
@@ -118,29 +48,6 @@ __device__ inline bf16x8 lds_operand(const uint16_t* p)
 // scalar base plus a fixed per-thread offset to a fixed LDS position (the split weights are
 // padded to whole tiles with zeros).  What is left per step is the ReLU mask, three packed 16-bit
 // integer instructions and an AND per 32-bit word.
-typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) uintx4 lds_uintx4;
-__device__ inline void lds_store16(uint16_t* p, const uint4& v)
-{
-    const uintx4 q = {v.x, v.y, v.z, v.w};
-    *(lds_uintx4*)p = q;
-}
-
-// two fp32 -> two bf16 (round to nearest even, the conversion instruction of this part), first
-// argument in the low half
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) uintx2 lds_uintx2;
-__device__ inline uint32_t pack_bf16_pair(float a, float b)
-{
-    const floatx2 v = {a, b};
-    const bf16x2 h = __builtin_convertvector(v, bf16x2);
-    uint32_t u;
-    __builtin_memcpy(&u, &h, 4);
-    return u;
-}
-
 // Tile row of a thread's 16-byte pieces: rows are dealt so that the 16 lanes of one LDS write
 // cycle (four rows of 64 bytes) take rows q, q + 4, q + 8, q + 12 of a group of 16, which at 20
 // banks per row start 16 banks apart (0, 16, 32, 48 of 64) and do not collide.
@@ -438,8 +345,8 @@ __global__ __launch_bounds__(kBlock)
                     e2 = fmaxf(e2, 0.f);
                     e3 = fmaxf(e3, 0.f);
                 }
-                const uint32_t w0 = pack_bf16_pair(e0, e1);
-                const uint32_t w1 = pack_bf16_pair(e2, e3);
+                const uint32_t w0 = pack_bf16(e0, e1);
+                const uint32_t w1 = pack_bf16(e2, e3);
                 const uintx2 v = {w0, w1};
                 *(lds_uintx2*)(smem + ((wm * S::TM + tm) * 32 + li) * LDC + (wn * S::TN + tn) * 32 +
                                8 * g + 4 * lk) = v;

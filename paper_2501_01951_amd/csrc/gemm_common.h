@@ -4,6 +4,17 @@
 
 namespace mixgcn {
 
+// Tile shape: WM x WN waves (4 in total), each owning TM x TN accumulator tiles of 32 x 32.
+template <int WM_, int WN_, int TM_, int TN_>
+struct Shape {
+    static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_;
+    static constexpr int BM = WM * TM * 32;  // extent along the A-operand free dimension
+    static constexpr int BN = WN * TN * 32;  // extent along the B-operand free dimension
+    static_assert(WM * WN == 4, "four waves per block");
+};
+using Shape128x128 = Shape<2, 2, 2, 2>;
+using Shape128x32 = Shape<4, 1, 1, 1>;
+
 // Workgroups are dealt round-robin to the 8 XCDs.  This maps the hardware block index to a
 // logical one such that consecutive logical indices run on the same XCD, so tiles that share
 // an operand (the column tiles of one row block) find it in that XCD's L2.
@@ -27,6 +38,38 @@ __device__ inline uint32_t pack_bf16(float a, float b)
 }
 __device__ inline float low_half(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ inline float high_half(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
+
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) uintx2 lds_uintx2;
+
+// Four fp32 of a row on their way to LDS: the three bf16 planes of the (masked, negated) values.
+template <bool MASK, bool NEGATE>
+__device__ inline void split_store(const float4& a, const float4& r, uint16_t* p0, uint16_t* p1,
+                                   uint16_t* p2)
+{
+    float4 x = a;
+    if (MASK) {
+        x.x = r.x > 0.f ? x.x : 0.f;
+        x.y = r.y > 0.f ? x.y : 0.f;
+        x.z = r.z > 0.f ? x.z : 0.f;
+        x.w = r.w > 0.f ? x.w : 0.f;
+    }
+    if (NEGATE) x = make_float4(-x.x, -x.y, -x.z, -x.w);
+    const uintx2 t0 = {pack_bf16(x.x, x.y), pack_bf16(x.z, x.w)};
+    x.x -= low_half(t0.x);
+    x.y -= high_half(t0.x);
+    x.z -= low_half(t0.y);
+    x.w -= high_half(t0.y);
+    const uintx2 t1 = {pack_bf16(x.x, x.y), pack_bf16(x.z, x.w)};
+    x.x -= low_half(t1.x);
+    x.y -= high_half(t1.x);
+    x.z -= low_half(t1.y);
+    x.w -= high_half(t1.y);
+    const uintx2 t2 = {pack_bf16(x.x, x.y), pack_bf16(x.z, x.w)};
+    *(lds_uintx2*)p0 = t0;
+    *(lds_uintx2*)p1 = t1;
+    *(lds_uintx2*)p2 = t2;
+}
 
 // x with the halves zeroed whose reference half (bf16 bits) is not > 0: 1 .. 0x7F80 are the positive values up
 // to +inf.  r - 1 is then below 0x7F80, and 0x7F80 less that, saturated, positive exactly for them; its negation

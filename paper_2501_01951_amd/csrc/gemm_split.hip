@@ -31,41 +31,10 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) uintx2 lds_uintx2;
 
 constexpr int BKS = 16;       // node rows per step = the reduction depth of one MFMA
 constexpr int kPlanes = 3;
-
-// Four fp32 of a row on their way to LDS: the three bf16 planes of the (masked, negated) values.
-template <bool MASK, bool NEGATE>
-__device__ inline void split_store(const float4& a, const float4& r, uint16_t* p0, uint16_t* p1,
-                                   uint16_t* p2)
-{
-    float4 x = a;
-    if (MASK) {
-        x.x = r.x > 0.f ? x.x : 0.f;
-        x.y = r.y > 0.f ? x.y : 0.f;
-        x.z = r.z > 0.f ? x.z : 0.f;
-        x.w = r.w > 0.f ? x.w : 0.f;
-    }
-    if (NEGATE) x = make_float4(-x.x, -x.y, -x.z, -x.w);
-    const uintx2 t0 = {pack_bf16(x.x, x.y), pack_bf16(x.z, x.w)};
-    x.x -= low_half(t0.x);
-    x.y -= high_half(t0.x);
-    x.z -= low_half(t0.y);
-    x.w -= high_half(t0.y);
-    const uintx2 t1 = {pack_bf16(x.x, x.y), pack_bf16(x.z, x.w)};
-    x.x -= low_half(t1.x);
-    x.y -= high_half(t1.x);
-    x.z -= low_half(t1.y);
-    x.w -= high_half(t1.y);
-    const uintx2 t2 = {pack_bf16(x.x, x.y), pack_bf16(x.z, x.w)};
-    *(lds_uintx2*)p0 = t0;
-    *(lds_uintx2*)p1 = t1;
-    *(lds_uintx2*)p2 = t2;
-}
 
 // ---- weight gradient: P[slab][KD x MD] = A[rows of slab][KD]^T * (B (.) 1[R > 0])[rows][MD] -----
 // The reduction runs over node rows, the slow index of both operands in memory, while the bf16

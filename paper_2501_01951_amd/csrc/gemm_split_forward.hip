@@ -34,9 +34,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) uintx2 lds_uintx2;
 typedef __attribute__((address_space(3))) uintx4 lds_uintx4;
 
 constexpr int BKS = 16;       // reduction depth per step = one MFMA
@@ -68,25 +66,6 @@ __global__ __launch_bounds__(kBlock) void split3_weights_kernel(
     }
 }
 
-// Four fp32 of a row on their way to LDS: the three bf16 planes.
-__device__ inline void split_store(float4 x, uint16_t* p0, uint16_t* p1, uint16_t* p2)
-{
-    const uintx2 t0 = {pack_bf16(x.x, x.y), pack_bf16(x.z, x.w)};
-    x.x -= low_half(t0.x);
-    x.y -= high_half(t0.x);
-    x.z -= low_half(t0.y);
-    x.w -= high_half(t0.y);
-    const uintx2 t1 = {pack_bf16(x.x, x.y), pack_bf16(x.z, x.w)};
-    x.x -= low_half(t1.x);
-    x.y -= high_half(t1.x);
-    x.z -= low_half(t1.y);
-    x.w -= high_half(t1.y);
-    const uintx2 t2 = {pack_bf16(x.x, x.y), pack_bf16(x.z, x.w)};
-    *(lds_uintx2*)p0 = t0;
-    *(lds_uintx2*)p1 = t1;
-    *(lds_uintx2*)p2 = t2;
-}
-
 // What one thread moves per step: two 16-byte pieces of the A tile (rows prow and prow + 64,
 // four columns) and one 16-byte piece of each weight plane.
 struct Stage {
@@ -108,7 +87,7 @@ struct Stage {
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             uint16_t* q = as + apos + p * 64 * LDR;
-            split_store(a[p], q, q + BM * LDR, q + 2 * BM * LDR);
+            split_store<false, false>(a[p], a[p], q, q + BM * LDR, q + 2 * BM * LDR);
         }
 #pragma unroll
         for (int p = 0; p < kPlanes; ++p) {
