@@ -40,6 +40,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0       # MI355X published HBM3E bandwidth
 MFMA_F32_TFLOPS = 157.3     # published dense fp32 matrix rate
+MFMA_BF16_TFLOPS = 2500.0   # published dense bf16 matrix rate
 KIND_NAMES = ["agg_g4", "agg_g8", "agg_g16", "agg_g32", "agg_g64", "update_fwd", "update_dgrad",
               "update_wgrad"]
 # rocprofv3 --pmc summaries (committed) that hold the HBM traffic of the dominant kernel
@@ -195,6 +196,14 @@ def kernels_compact(kinds):
     return {k: [v["avg_ms"], v["launches"]] for k, v in kinds.items()}
 
 
+def update_rate(kind, tflops, arith):
+    """Rate of an update product of fp32 features against the matrix rate of its arithmetic: the fp32 MFMA
+    for the forward product, a sixth of the bf16 MFMA for six products of bf16 terms each."""
+    if kind == "update_fwd" and arith == "fp32":
+        return {"tflops": tflops, "frac_of_fp32_mfma_peak": tflops / MFMA_F32_TFLOPS}
+    return {"tflops": tflops, "frac_of_sixth_of_bf16_mfma_peak": tflops / (MFMA_BF16_TFLOPS / 6.0)}
+
+
 def aggregation_roofline(config, kinds, nnz, n, esz, chunks=1):
     """Roofline block of the aggregation launch that takes the most time of the step."""
     agg = {k: v for k, v in kinds.items() if k.startswith("agg")}
@@ -328,9 +337,7 @@ def bench_single_layer(args, mg, dev, config):
         "kernels_avg_ms_launches": kernels_compact(kinds),
         "roofline": aggregation_roofline(config, kinds, nnz, n, 4, args.chunks),
         "update_products": {
-            kk: {"tflops": 2.0 * n * k * m / (kinds[kk]["avg_ms"] * 1e-3) / 1e12,
-                 "frac_of_fp32_mfma_peak": 2.0 * n * k * m / (kinds[kk]["avg_ms"] * 1e-3) / 1e12 /
-                 MFMA_F32_TFLOPS}
+            kk: update_rate(kk, 2.0 * n * k * m / (kinds[kk]["avg_ms"] * 1e-3) / 1e12, args.update_arith)
             for kk in ("update_fwd", "update_dgrad", "update_wgrad") if kk in kinds},
     }
     if pipelined:
@@ -412,8 +419,9 @@ def bench_model(args, mg, dev, config, with_bf16x3=True):
         out["update_products_ms_per_step"] = upd
         flops = sum(2.0 * n * dims[l] * dims[l + 1] * (3 if l > 0 else 2) for l in range(len(dims) - 1))
         out["update_products_tflops"] = flops / (upd * 1e-3) / 1e12
-    # the same steps with the opt-in update arithmetic (fp32 operands as three bf16 terms on the
-    # bf16 matrix cores), after and outside the timed region above: reported beside the result
+    # the same steps with the opt-in arithmetic of the forward product (fp32 operands as three bf16 terms
+    # on the bf16 matrix cores, as the gradients always have them), after and outside the timed region
+    # above: reported beside the result
     if with_bf16x3 and args.update_arith == "fp32" and not bf16 and not args.hip_graph:
         mg.set_update_arith(mg.ARITH_BF16X3)
         try:
@@ -612,9 +620,9 @@ def main():
                     help="measurement aid: aggregations without column slices, the gather a fused "
                          "aggregate->update kernel would do (not the benchmark line)")
     ap.add_argument("--update-arith", default="fp32", choices=["fp32", "bf16x3"],
-                    help="matrix-core arithmetic of the update products of fp32 features: fp32 MFMA "
-                         "(the benchmark line) or three bf16 terms per operand, six bf16 MFMAs per "
-                         "product (forward and data gradient of wide layers)")
+                    help="matrix-core arithmetic of the forward product of fp32 features: fp32 MFMA "
+                         "(the benchmark line) or, for wide layers, three bf16 terms per operand and "
+                         "six bf16 MFMAs per product, as the gradients of fp32 features always run")
     args = ap.parse_args()
     if args.gpus != 1:
         sys.exit("bench.py: this build runs on exactly one GPU (no collectives are part of it); "

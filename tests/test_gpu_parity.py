@@ -1640,7 +1640,7 @@ def test_update_with_pitches_beyond_32_bit_tile_offsets(mg, bf16):
     """The fast paths of the update kernels address a tile with 32-bit offsets from a scalar base
     and therefore only take pitches below 2^22 elements; beyond that the generic paths must give
     the same bits as the packed case (the arithmetic does not depend on the pitch).  The
-    three-term bf16 arithmetic has the same limit and hands such operands to the fp32 MFMA
+    three-term forward product has the same limit and hands such operands to the fp32 MFMA
     kernels: switched on, it must give the fp32 path's bits here."""
     n, k, m = 300, 64, 128
     big = (1 << 22) + 8

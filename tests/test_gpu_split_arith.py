@@ -1,8 +1,9 @@
-"""GPU parity of the opt-in update arithmetic MIXGCN_ARITH_BF16X3 (fp32 operands as three bf16
-terms, six bf16 MFMAs per product; forward, data gradient and weight gradient): the same oracle
+"""GPU parity of fp32 products of three bf16 terms per operand, six bf16 MFMAs per product (the forward
+product under the opt-in MIXGCN_ARITH_BF16X3, the data and weight gradients in both modes): the same oracle
 and the same tolerance as the fp32 MFMA path,
 two exactness pins (inputs whose terms and sums are exact must come out bit-exact), a check that
-its error is not above the fp32 path's, and the products that must not change with the mode."""
+the error of the opt-in forward product is not above the fp32 one's, and the products that must not change
+with the mode."""
 import numpy as np
 import pytest
 
@@ -33,9 +34,8 @@ def split(mg):
         mg.set_update_arith(mg.ARITH_FP32)
 
 
-# (n, k, m): forward needs m > 64 and k a multiple of 16 from 64 up, the data gradient k > 64 and
-# the same of m; ragged row counts, 4 to 17 reduction steps (the loop takes two per trip and
-# finishes with one to three), several column tiles, a ragged last column tile
+# (n, k, m): forward needs m > 64 and k a multiple of 16 from 64 up; ragged row counts, 4 to 17 reduction steps
+# (its loop takes two per trip and finishes with one to three), several column tiles, a ragged last column tile
 SPLIT_SHAPES = [(1000, 64, 128), (2048, 128, 256), (4133, 256, 256), (130, 256, 256), (1, 128, 128),
                 (5000, 128, 1024), (777, 96, 160), (256, 112, 128), (384, 80, 144), (1500, 128, 172),
                 (640, 176, 96), (129, 272, 80), (16, 128, 128), (47, 256, 128), (20000, 384, 128)]
@@ -68,8 +68,7 @@ def test_split_forward_and_data_gradient(split, n, k, m):
         o = dz.cpu().numpy()
         assert_close(o[:, :k], oracle.update_dgrad(dp, w64), RTOL_F32, "dgrad")
         assert np.all(o[:, k:] == 9.0)
-        # the weight gradient takes the path for whole 128 x 128 tiles (rows beyond the last
-        # multiple of 16 go to the fp32 kernel and are added)
+        # the weight gradient: tiles of 128 x 128, rows beyond the last multiple of 16 read as zeros
         for beta in (0.0, 1.0):
             dw = torch.full((k, ldm), 2.0, device="cuda")
             mg.update(mg.OP_WGRAD, zd, gd, dw, n, k, m, relu_ref=ref_t, beta=beta)
@@ -129,9 +128,9 @@ def _worst_error(got, a64, w64):
 
 
 def test_split_error_is_not_above_the_fp32_path(mg):
-    """max |C - A W| / (|A| |W|) of both paths against fp64, on inputs with a wide spread of
-    magnitudes: the three-term path must stay within 1.5 times the fp32 MFMA path's error and
-    below 2^-20."""
+    """max |C - A W| / (|A| |W|) of the forward product against fp64 in both modes, on inputs with a wide
+    spread of magnitudes: in three terms it must stay within 1.5 times the error of the fp32 MFMA and below
+    2^-20."""
     rng = np.random.default_rng(9)
     n, k, m = 4096, 256, 256
     a = (rng.standard_normal((n, k)) * np.exp2(rng.integers(-12, 13, size=(n, k)))).astype(np.float32)
@@ -154,8 +153,8 @@ def test_split_error_is_not_above_the_fp32_path(mg):
 
 @pytest.mark.parametrize("n,k,m", [(1000, 100, 128), (1000, 64, 32), (900, 128, 200), (500, 48, 128)])
 def test_products_outside_the_split_path_do_not_change(mg, n, k, m):
-    """Reduction depths that are not whole steps, narrow outputs and the weight gradient keep the
-    fp32 MFMA kernels: bit-identical results in both modes."""
+    """Forward products with a reduction depth that is not whole steps or a narrow output keep the fp32 MFMA
+    kernels, and the gradients take no notice of the mode: bit-identical results in both."""
     say(f"mode-independent products n={n} k={k} m={m}")
     z, w, gr = dev(gg.normal(43, 1, n, k)), dev(gg.glorot(43, 2, k, m)), dev(gg.normal(43, 3, n, m))
     res = {}
