@@ -292,11 +292,10 @@ int mixgcn_apply_bitmap(int dtype, void* X, int64_t ldx, int64_t n_rows, int32_t
  * bf16 matrix cores where the reduction has at least four terms: an operand is the exact sum of three bf16
  * terms and a product is accumulated in fp32 from the six partial products of order 2^-16 and above (the
  * others are together below 2^-23 |a| |b|).  Against 64 bits these results are closer than those of a chain of
- * fp32 multiply-adds (relative error 5.6e-8 against 2.0e-7 at depth 128).  Operands of a gradient below about
- * 1e-33 in magnitude carry fewer than 24 bits into a product (at 1e-35 a relative error of 3e-6).  bf16
+ * fp32 multiply-adds (relative error 5.6e-8 against 2.0e-7 at depth 128).  bf16
  * features enter as they are and the weights as two terms.  Infinities and NaN give what fp32 arithmetic gives:
- * fp32 products on the bf16 matrix cores compute every sum that is not finite again, one multiply-add at a
- * time (a tensor full of NaN takes many times as long).
+ * fp32 products on the bf16 matrix cores compute every sum that is not finite (a gradient's also where 2^32
+ * times it would not be) again, one multiply-add at a time: a tensor full of NaN takes many times as long.
  * Two per-device work buffers are shared by all calls: the slab partials of WGRAD, and the weight terms of
  * products that split them beforehand: bf16 FWD and DGRAD whose weights do not fit LDS (4 bytes for every
  * reduction index, rounded up to 64, and output column, rounded up to 16, 32, 64 or 128 and 128 at most, are
@@ -314,7 +313,8 @@ int mixgcn_update(int op, int dtype, const void* A, int64_t lda, const void* B, 
  * MIXGCN_ARITH_BF16X3 applies when the output is wider than 64 columns, the reduction depth k is a multiple of
  * 16 and at least 64, and the pitch of A is below 2^22 elements; every other product keeps the fp32 chain.
  * Its error per product term is bounded by 2^-23 |a| |b| (the three dropped partial products), the size of an
- * fp32 rounding.  Not thread safe: set it before launching work.  MIXGCN_EINVAL for an unknown mode.
+ * fp32 rounding; operands below about 1e-33 in magnitude carry fewer than 24 bits into it.  Not thread safe:
+ * set it before launching work.  MIXGCN_EINVAL for an unknown mode.
  */
 int mixgcn_set_update_arith(int mode);
 

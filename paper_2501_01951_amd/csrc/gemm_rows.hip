@@ -214,8 +214,11 @@ __global__ __launch_bounds__(kRowsBlock) __attribute__((amdgpu_waves_per_eu(2, 2
     };
     auto store_w = [&](uint16_t* chunk, int item, const float* w) {
         uint32_t t[4 * PB];
+        float x[8];
         item = fresh(item);
-        split8<PB, true>(w, t);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = DT == MIXGCN_F32 ? w[e] * kTermScale : w[e];
+        split8<PB, true>(x, t);
         uint16_t* dst = chunk + (item >> 6) * (PB * 512) + (item & 63) * 8;
 #pragma unroll
         for (int b = 0; b < PB; ++b) {
@@ -332,6 +335,8 @@ __global__ __launch_bounds__(kRowsBlock) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
                     for (int e = 0; e < 8; ++e) v[e] = r[e] > 0.f ? v[e] : 0.f;
                 }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] *= kTermScale;
                 split8<PA, false>(v, o.w[tm]);
             } else {
                 __builtin_memcpy(o.w[tm], x.a[tm], 32);
@@ -507,6 +512,12 @@ __global__ __launch_bounds__(kRowsBlock) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
                     for (int v = 0; v < 4; ++v) z = fmaf(acc[tm][t][v], 0.f, z);
             bad = __any(!(z == 0.f));
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                for (int t = 0; t < TN; ++t)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[tm][t][v] *= 1.f / (kTermScale * kTermScale);
         }
         write(tile);
         if (__builtin_expect(bad, 0)) repair(tile * kWaveRows);

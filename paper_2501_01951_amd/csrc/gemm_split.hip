@@ -176,12 +176,13 @@ __global__ __launch_bounds__(kBlock, 2) void wgrad_split_kernel(
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             uint16_t* qa = as + spos + p * 8 * LDW;
-            split_store<false, decltype(odd)::value>(g.a[p], g.a[p], qa, qa + kWPlane, qa + 2 * kWPlane);
+            split_store<false>(g.a[p], g.a[p], decltype(odd)::value ? -kTermScale : kTermScale, qa, qa + kWPlane,
+                               qa + 2 * kWPlane);
         }
 #pragma unroll
         for (int p = 0; p < PB; ++p) {
             uint16_t* qb = bs + tpos + p * 8 * LDW;
-            split_store<MASK, false>(g.b[p], g.r[MASK ? p : 0], qb, qb + kWPlane, qb + 2 * kWPlane);
+            split_store<MASK>(g.b[p], g.r[MASK ? p : 0], kTermScale, qb, qb + kWPlane, qb + 2 * kWPlane);
         }
     };
     // operand reads: lane -> 16-lane group (feature block, reduction half), place in the group
@@ -254,12 +255,14 @@ __global__ __launch_bounds__(kBlock, 2) void wgrad_split_kernel(
                 const bool in = iw + tm * 32 + 8 * (v / 4) + 4 * lk + (v % 4) < KD && jw + tn * 32 + li < MD;
                 z = fmaf(in ? acc[tm][tn][v] : 0.f, 0.f, z);
             }
+    float unscale = 1.f / (kTermScale * kTermScale);
     if (__builtin_expect(r_end - r_begin < 4 || __any(!(z == 0.f)), 0)) {
         // A sum that is not finite (a term of an infinity is NaN, a value next to the largest float rounds
         // up to an infinity), or fewer than four rows, over which a chain of fp32 multiply-adds is closer to
         // 64 bits: the wavefront's tile again on the fp32 matrix cores, straight from memory.
         // 32x32x2: lane l supplies column l % 32 of reduction index l / 32.
         clear();
+        unscale = 1.f;
         int ca[TM], cb[TN];
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) ca[tm] = iw + tm * 32 + li < KD ? iw + tm * 32 + li : i0;
@@ -296,7 +299,7 @@ __global__ __launch_bounds__(kBlock, 2) void wgrad_split_kernel(
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int i = iw + tm * 32 + 8 * (v / 4) + 4 * lk + (v % 4);
-                if (i < KD && j < MD) out[(size_t)i * MD + j] = acc[tm][tn][v];
+                if (i < KD && j < MD) out[(size_t)i * MD + j] = acc[tm][tn][v] * unscale;
             }
         }
 }

@@ -87,7 +87,7 @@ struct Stage {
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             uint16_t* q = as + apos + p * 64 * LDR;
-            split_store<false, false>(a[p], a[p], q, q + BM * LDR, q + 2 * BM * LDR);
+            split_store<false>(a[p], a[p], 1.f, q, q + BM * LDR, q + 2 * BM * LDR);
         }
 #pragma unroll
         for (int p = 0; p < kPlanes; ++p) {

@@ -193,6 +193,36 @@ def test_fp32_gradients_are_no_further_from_64_bits_than_the_chain(mg, depth, va
     assert error(dw, a, w) <= 1.05 * error(chain(a, w), a, w)
 
 
+@pytest.mark.parametrize("size", [1e-33, 1e-35, 1e-37, 1e-39, 1e20, 1e30, 1e35])
+@pytest.mark.parametrize("depth", [4, 33, 200])
+def test_fp32_gradients_keep_their_accuracy_at_every_magnitude(mg, depth, size):
+    """The smallest bf16 is 2^-133: terms of a float below 1e-33 end above its last bits, unless it is scaled.
+    Subnormal operands and results, a small operand next to a large one, and sums that a scaling carries past
+    the largest float; error as above."""
+    gen = torch.Generator(device="cuda").manual_seed(depth)
+    rows, cols = 1000, 100
+    g = torch.randn(rows, depth, device="cuda", generator=gen) * size
+    w = torch.randn(depth, (cols + 3) // 4 * 4, device="cuda", generator=gen) * 0.1
+
+    def aligned(t):
+        out = torch.zeros(t.shape[0], (t.shape[1] + 3) // 4 * 4, device="cuda")
+        out[:, :t.shape[1]] = t
+        return out[:, :t.shape[1]]
+
+    def error(x, a, b):
+        ref = a.double() @ b.double()
+        return ((x.double() - ref).norm() / ref.norm()).item()
+
+    for a, b in ((g, w), (g * 1e10, w * 1e-10) if size < 1 else (g * 1e-10, w * 1e10)):
+        dz = torch.empty(rows, cols, device="cuda")
+        mg.update(mg.OP_DGRAD, aligned(a), aligned(b.t()), dz, rows, cols, depth)
+        assert error(dz, a, b) <= 1.05 * error(chain(a, b), a, b)
+        z = a[:cols].contiguous()
+        dw = torch.empty(cols, cols, device="cuda")
+        mg.update(mg.OP_WGRAD, aligned(z.t()), aligned(b), dw, depth, cols, cols)
+        assert error(dw, z, b) <= 1.05 * error(chain(z, b), z, b)
+
+
 @pytest.mark.parametrize("n,k,m", [(1, 1, 1), (1000, 3, 2), (777, 64, 3), (333, 129, 1), (2048, 256, 2), (50, 602, 3),
                                    (40, 1100, 2), (2200003, 1, 3)])
 def test_fp32_data_gradient_of_few_columns_is_the_fp32_chain(mg, n, k, m):
