@@ -13,7 +13,7 @@ CSRC = os.path.join(_HERE, "csrc")
 BUILD_DIR = os.path.join(_HERE, "_build")
 LIB_PATH = os.path.join(_HERE, "libmixgcn.so")
 
-SOURCES = ["abi.hip", "pool.hip", "scan.hip", "sort.hip", "csr.hip", "spmm.hip", "rowgroups.hip", "gemm.hip", "gemm_rows.hip",
+SOURCES = ["abi.hip", "pool.hip", "scan.hip", "sort.hip", "csr.hip", "spmm.hip", "rowgroups.hip", "gemm.hip", "gemm_rows.hip", "gemm_rows_f32.hip",
            "gemm_bf16.hip", "gemm_bf16_deep.hip", "gemm_split.hip", "gemm_split_forward.hip", "loss.hip", "peaks.hip",
            "reorder.hip"]
 

@@ -1,5 +1,5 @@
 // Dispatch of the update products (paper Algorithm 2, update phase), the forward product H' = sigma(Z W) of
-// fp32 features on the fp32 matrix cores (v_mfma_f32_32x32x2_f32), and the reduction of the slabs of a weight
+// fp32 features on the fp32 matrix cores (v_mfma_f32_32x32x2_f32) where gemm_rows_f32.hip does not take it, and the reduction of the slabs of a weight
 // gradient.  A row-block kernel's workgroup owns 128 node rows: the node dimension is the long one, the
 // feature dimensions are at most a few hundred.
 //
@@ -518,6 +518,8 @@ int launch_rowblock(bool relu, const float* A, int64_t lda, const float* B, int6
 int forward_f32(bool relu, const float* A, int64_t lda, const float* W, int64_t ldw, float* C, int64_t ldc,
                 int64_t n, int32_t k, int32_t m, hipStream_t s)
 {
+    if (forward_rows_applies(n, k, m))
+        return launch_forward_rows(relu, A, lda, W, ldw, C, ldc, n, k, m, s);
     return m > 64 ? launch_rowblock<Shape128x128>(relu, A, lda, W, ldw, C, ldc, n, k, m, s)
                   : launch_rowblock<Shape128x32>(relu, A, lda, W, ldw, C, ldc, n, k, m, s);
 }

@@ -1,6 +1,7 @@
 // Device helpers shared by the kernels of the update products.
 #pragma once
 #include "device_utils.h"
+#include "internal.h"
 
 namespace mixgcn {
 
@@ -122,6 +123,40 @@ __device__ inline void repair_sums(float* C, int64_t ldc, int64_t row0, int64_t 
         }
         *c = RELU ? fmaxf(x, 0.f) : x;
     }
+}
+
+// Workgroups of a product whose weights stay in LDS and whose wavefronts walk tiles of rows: row_groups groups of
+// rows (a multiple of 8, one XCD each), one workgroup per group and column tile, `waves` walking wavefronts each.
+struct RowWalk {
+    int row_groups, waves;
+    unsigned grid;
+};
+inline RowWalk plan_row_walk(int64_t tiles, int n_col_tiles, int most_waves, bool all_waves)
+{
+    // One workgroup per compute unit.  Where there are fewer tiles than wavefronts the workgroups get
+    // fewer wavefronts rather than the chip fewer workgroups (4096 rows 64 -> 32: 16 workgroups of 8 took
+    // 8.2 us, 128 of one take 5.0).
+    int64_t per_xcd = 32 / n_col_tiles;
+    if (per_xcd < 1) per_xcd = 1;
+    // Where the column tiles leave compute units of an XCD idle that way (11 of them take 22 of 32), more
+    // groups of rows and several rounds of workgroups, if that saves a tenth: a round costs a wavefront its
+    // tiles, and the weights about another.  us at 2^17 rows 128 -> 1408, 2176, 4224, one round : several, bf16
+    // 134 : 124, 252 : 190, 524 : 380, fp32 data gradient 321 : 300, 598 : 455, 1257 : 887; with 384 to 1280 columns
+    // several rounds took up to a sixth longer.
+    const auto cost = [&](int64_t groups) {
+        return ceil_div(groups * n_col_tiles, 32) * (ceil_div(tiles, 8 * most_waves * groups) + 1);
+    };
+    int64_t least = cost(per_xcd) * 9 / 10;
+    for (int64_t p = per_xcd + 1; p <= 32; ++p)
+        if (cost(p) < least) {
+            least = cost(p);
+            per_xcd = p;
+        }
+    const int64_t per_group = ceil_div(tiles, 8 * per_xcd);
+    const int waves = all_waves || per_group > most_waves ? most_waves : (int)per_group;
+    const int64_t need = ceil_div(ceil_div(tiles, waves), 8);
+    if (per_xcd > need) per_xcd = need;
+    return RowWalk{(int)per_xcd * 8, waves, (unsigned)(8 * per_xcd * n_col_tiles)};
 }
 
 }  // namespace mixgcn

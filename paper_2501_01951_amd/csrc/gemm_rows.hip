@@ -611,31 +611,10 @@ int launch_rows_tn(bool relu, const RowsArgs& args, hipStream_t s)
                                        a.n, a.KD, a.MD, (const uint16_t*)a.R, a.ldr, s);
     a.n_col_tiles = (int)ceil_div(a.MD, TN * 16);
     const int64_t tiles = ceil_div(a.n, kWaveRows);
-    // One workgroup per compute unit.  Where there are fewer tiles than wavefronts the workgroups get
-    // fewer wavefronts rather than the chip fewer workgroups (4096 rows 64 -> 32: 16 workgroups of 8 took
-    // 8.2 us, 128 of one take 5.0).
-    int64_t per_xcd = 32 / a.n_col_tiles;
-    if (per_xcd < 1) per_xcd = 1;
-    // Where the column tiles leave compute units of an XCD idle that way (11 of them take 22 of 32), more
-    // groups of rows and several rounds of workgroups, if that saves a tenth: a round costs a wavefront its
-    // tiles, and the weights about another.  us at 2^17 rows 128 -> 1408, 2176, 4224, one round : several, bf16
-    // 134 : 124, 252 : 190, 524 : 380, fp32 data gradient 321 : 300, 598 : 455, 1257 : 887; with 384 to 1280 columns
-    // several rounds took up to a sixth longer.
-    const auto cost = [&](int64_t groups) {
-        return ceil_div(groups * a.n_col_tiles, 32) * (ceil_div(tiles, 8 * kRowsWaves * groups) + 1);
-    };
-    int64_t least = cost(per_xcd) * 9 / 10;
-    for (int64_t p = per_xcd + 1; p <= 32; ++p)
-        if (cost(p) < least) {
-            least = cost(p);
-            per_xcd = p;
-        }
-    const int64_t per_group = ceil_div(tiles, 8 * per_xcd);
-    a.waves = !resident || per_group > kRowsWaves ? kRowsWaves : (int)per_group;
-    const int64_t need = ceil_div(ceil_div(tiles, a.waves), 8);
-    if (per_xcd > need) per_xcd = need;
-    a.row_groups = (int)per_xcd * 8;
-    const unsigned grid = (unsigned)(8 * per_xcd * a.n_col_tiles);
+    const RowWalk w = plan_row_walk(tiles, a.n_col_tiles, kRowsWaves, !resident);
+    a.row_groups = w.row_groups;
+    a.waves = w.waves;
+    const unsigned grid = w.grid;
     const unsigned lds = (unsigned)((resident ? nch : 2) * kChunkBytes);
 #define MIXGCN_ROWS(RELU, MASK)                                                                       \
     do {                                                                                              \

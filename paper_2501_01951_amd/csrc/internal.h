@@ -269,6 +269,11 @@ int launch_update_bf16_deep(bool w_is_kd_major, bool relu, const uint16_t* A, in
                             int64_t ldw, uint16_t* C, int64_t ldc, int64_t n, int KD, int MD,
                             const uint16_t* R, int64_t ldr, hipStream_t s);
 
+// forward product of fp32 features on the fp32 matrix cores, weights that fit LDS
+bool forward_rows_applies(int64_t n, int KD, int MD);
+int launch_forward_rows(bool relu, const float* A, int64_t lda, const float* W, int64_t ldw, float* C, int64_t ldc,
+                        int64_t n, int KD, int MD, hipStream_t s);
+
 // forward product of fp32 features, every operand as three bf16 terms; chosen by mixgcn_set_update_arith, and
 // only where forward_split_applies says so
 extern int g_update_arith;

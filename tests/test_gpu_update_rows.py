@@ -48,7 +48,11 @@ def chain(a, w):
 
 # around tiles of 128 rows, 32 and 128 columns and steps of 16: tiles inside the matrices and tiles at their edges
 @pytest.mark.parametrize("n,k,m", [(1, 1, 1), (128, 16, 32), (129, 15, 33), (256, 64, 128), (300, 100, 64),
-                                   (255, 128, 65), (384, 256, 256), (260, 602, 129)])
+                                   (255, 128, 65), (384, 256, 256), (260, 602, 129),
+                                   # weights in LDS: the deepest and the next ones of 32 columns, column tiles of 64
+                                   # with rows and columns left over, tiles of 128 (32 of them), 47 columns
+                                   (70, 1280, 31), (70, 1281, 31), (20003, 37, 250), (16397, 160, 4001),
+                                   (262150, 200, 47)])
 def test_fp32_forward_sums_are_the_fp32_chain(mg, n, k, m):
     """Bit for bit: the sums of a forward product decide the sign of an activation, so they keep their
     rounding from release to release."""
