@@ -577,21 +577,25 @@ __device__ inline void finish_row(float* t, void* Z, int64_t ldz, uint32_t row, 
 }
 
 // Eight lanes of 16 bytes hold a feature row's slice, one 128-byte line.
-// The pipeline is that of the entry-balanced kernel: the entries of four gathers arrive with one
+// The pipeline is that of the entry-balanced kernel: the entries of D gathers arrive with one
 // coalesced load two rounds ahead and are handed out with lane shuffles, the feature rows are
-// gathered one round (four loads) ahead, two rounds are written out per trip so that no register
+// gathered one round (D loads) ahead, two rounds are written out per trip so that no register
 // of a load in flight is copied, and the loop has no side exit.
 // EPI: an epilogue other than a plain store is wanted.  OFF32: offsets into H fit 32 bits and
-// column indices 24 bits.
-template <bool EPI, bool OFF32>
-__global__ __launch_bounds__(kBlock, 6) void aggregate_groups_kernel(
+// column indices 24 bits.  D: gathers in flight per wavefront, a batch each, at 4 (D = 8) or 6 wavefronts per SIMD.
+// In bands a row is read from Z before it is added to, and the gathers behind that read wait for it: eight of them
+// outlast it, where there are enough wavefronts.  us, D = 4 : 8, 128 columns, entries per band: power law, 233 k nodes of
+// 492, 13 M 3570 : 3440; 150 k of 200, 5 M 1022 : 994; uniform, 60 k of 300, 6 M 467 : 462; 100 k of 100, 2.5 M 351 : 360
+// (at 256 columns 693 : 677), at 20 columns 111 : 126.
+template <bool EPI, bool OFF32, int D>
+__global__ __launch_bounds__(kBlock, D == 8 ? 4 : 6) void aggregate_groups_kernel(
     const uint2* __restrict__ ent, const uint32_t* __restrict__ rows,
     const uint32_t* __restrict__ kind, const uint2* __restrict__ tab, int64_t n_tab, int tab_per_wave, int64_t n_waves, const void* __restrict__ H, int64_t ldh,
     void* __restrict__ Z, int64_t ldz, int c0, int width, int n_slices,
     float* __restrict__ partials, int part_stride, int epi, const uint32_t* __restrict__ mask,
     int64_t ldm, int c_lo, int c_hi)
 {
-    constexpr int D = 4;  // gathers in flight per wavefront, a batch each
+    constexpr int NC = 4;  // chains of a row's sum; batch b adds to chain b % 4
     const int lane = threadIdx.x & (kWave - 1);
     const int sub = lane / kSliceLanes, lj = lane % kSliceLanes;
     // Workgroups are dealt round-robin to the 8 XCDs.  1, 2, 4 or 8 slices are dealt with them, so
@@ -617,9 +621,9 @@ __global__ __launch_bounds__(kBlock, 6) void aggregate_groups_kernel(
     const uint32_t lane_off = (uint32_t)(c_load * F::ES);
     const char* const hbase = reinterpret_cast<const char*>(H) + c_load * F::ES;
 
-    float acc[D][kVec];  // of the gathers of a slot
+    float acc[NC][kVec];
 #pragma unroll
-    for (int u = 0; u < D; ++u)
+    for (int u = 0; u < NC; ++u)
 #pragma unroll
         for (int i = 0; i < kVec; ++i) acc[u][i] = 0.f;
     constexpr int RE = D * kGroupRows;  // entries per round
@@ -670,7 +674,7 @@ __global__ __launch_bounds__(kBlock, 6) void aggregate_groups_kernel(
         if (row != kNoRow && active)
             finish_row<EPI>(t, Z, ldz, row, c, epi, zraw, mask != nullptr, mbits, c_lo, c_hi);
 #pragma unroll
-        for (int u = 0; u < D; ++u)
+        for (int u = 0; u < NC; ++u)
 #pragma unroll
             for (int i = 0; i < kVec; ++i) acc[u][i] = 0.f;
         ++k;
@@ -693,7 +697,7 @@ __global__ __launch_bounds__(kBlock, 6) void aggregate_groups_kernel(
             if (b + u >= nb) end = 0;  // a batch of the next wavefront
             if (real) {
 #pragma unroll
-                for (int i = 0; i < kVec; ++i) acc[u][i] = fmaf(av, x[i], acc[u][i]);
+                for (int i = 0; i < kVec; ++i) acc[u % NC][i] = fmaf(av, x[i], acc[u % NC][i]);
             }
             if (__builtin_expect(end != 0, 0)) finish(end);
             fill(u, en);
@@ -992,10 +996,17 @@ int launch_groups(const Band& g, const uint2* ent, int64_t n_nodes, const void* 
     const bool off32 = n_nodes * ldh * F::ES + (int64_t)(c0 + width) * F::ES < (1ll << 32) &&
                        ldh * F::ES < (1ll << 24) && n_nodes <= (1ll << 24);
     if (timer) MIXGCN_TRY(timer->begin(timer_kind, s));
-#define MIXGCN_GROUPS(EPI, O32)                                                                   \
-    hipLaunchKernelGGL((aggregate_groups_kernel<EPI, O32>), dim3((unsigned)grid), dim3(kBlock), 0, s, \
+    // the sums do not depend on D (see there)
+    const bool deep = g.n_batches * n_slices >= 2400000;
+#define MIXGCN_GROUPS_D(EPI, O32, D)                                                              \
+    hipLaunchKernelGGL((aggregate_groups_kernel<EPI, O32, D>), dim3((unsigned)grid), dim3(kBlock), 0, s, \
                        ent, g.rows, g.kind, g.tab, g.n_tab, per_wave, n_waves, H, ldh, Z, ldz, c0, width, \
                        n_slices, P, part_stride, epi, mask, ldm, c_lo, c_hi)
+#define MIXGCN_GROUPS(EPI, O32)              \
+    do {                                     \
+        if (deep) MIXGCN_GROUPS_D(EPI, O32, 8); \
+        else MIXGCN_GROUPS_D(EPI, O32, 4);   \
+    } while (0)
     if (epilogue) {
         if (off32) MIXGCN_GROUPS(true, true);
         else MIXGCN_GROUPS(true, false);
@@ -1004,6 +1015,7 @@ int launch_groups(const Band& g, const uint2* ent, int64_t n_nodes, const void* 
         else MIXGCN_GROUPS(false, false);
     }
 #undef MIXGCN_GROUPS
+#undef MIXGCN_GROUPS_D
     if (timer) MIXGCN_TRY(timer->end(s));
     if (g.n_cut > 0)
         hipLaunchKernelGGL(sum_pieces_kernel, dim3((unsigned)g.n_cut), dim3(kWave), 0, s, g.cut_row, g.piece0,
