@@ -184,27 +184,51 @@ __global__ __launch_bounds__(kBlock) void degree_kernel(const int64_t* __restric
     else dinv[r] = d ? (float)(1.0 / sqrt((double)d)) : 0.0f;
 }
 
-// One thread per stored entry, its row found by binary search in rowptr.
+// One thread per stored entry, a block per group of kGroupNnz: the row of an entry is one of those that the group
+// covers, so the search starts from a handful of row pointers that the block has in its L1 (over all of them it took
+// most of the time).  Four groups per block, so that the columns and scales of four entries are on their way together.
+// What is left are the gathers of dinv.  33.0 M entries of 2^20 rows: 656 -> 225 us; without the hints, with which the streams leave the L2s to dinv, 279.
+constexpr int kValueGroups = 4;
+static_assert(kGroupNnz == kBlock, "a thread per entry of a group");
 __global__ __launch_bounds__(kBlock) void values_kernel(const int64_t* __restrict__ rowptr,
+                                                        const uint32_t* __restrict__ grp_row,
                                                         const uint32_t* __restrict__ col,
                                                         const float* __restrict__ dinv,
-                                                        uint32_t n, int64_t nnz, int mode,
+                                                        int64_t n_groups, int64_t nnz, int mode,
                                                         float eps, int swapped,
                                                         float* __restrict__ val,
                                                         uint2* __restrict__ cv)
 {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= nnz) return;
-    int64_t lo = 0, hi = (int64_t)n + 1;
-    while (lo < hi) {
-        const int64_t mid = lo + (hi - lo) / 2;
-        if (rowptr[mid] <= e) lo = mid + 1;
-        else hi = mid;
+    const int64_t g0 = (int64_t)blockIdx.x * kValueGroups;
+    uint32_t c[kValueGroups], row[kValueGroups];
+#pragma unroll
+    for (int j = 0; j < kValueGroups; ++j) {
+        const int64_t e = (g0 + j) * kGroupNnz + threadIdx.x;
+        c[j] = __builtin_nontemporal_load(col + (e < nnz ? e : nnz - 1));
     }
-    const uint32_t row = (uint32_t)(lo - 1);
-    const float v = entry_value(mode, eps, swapped, row, col[e], dinv[row], dinv);
-    val[e] = v;
-    cv[e].y = __float_as_uint(v);
+#pragma unroll
+    for (int j = 0; j < kValueGroups; ++j) {
+        const int64_t g = g0 + j < n_groups ? g0 + j : n_groups - 1;
+        int64_t e = g * kGroupNnz + threadIdx.x;
+        if (e >= nnz) e = nnz - 1;
+        // the last row in [lo, hi] with rowptr <= e (rowptr[lo] <= e: the row of the group's first entry)
+        uint32_t lo = grp_row[g], hi = grp_row[g + 1];
+        while (lo < hi) {
+            const uint32_t mid = hi - (hi - lo) / 2;
+            if (rowptr[mid] <= e) lo = mid;
+            else hi = mid - 1;
+        }
+        row[j] = lo;
+    }
+#pragma unroll
+    for (int j = 0; j < kValueGroups; ++j) {
+        const int64_t e = (g0 + j) * kGroupNnz + threadIdx.x;
+        if (e >= nnz) continue;
+        const float drow = mode == MIXGCN_NORM_SUM ? 0.f : dinv[row[j]];
+        const float v = entry_value(mode, eps, swapped, row[j], c[j], drow, dinv);
+        __builtin_nontemporal_store(v, val + e);
+        __builtin_nontemporal_store(__float_as_uint(v), &cv[e].y);
+    }
 }
 
 // cv_t = cv with the value words left for values_kernel to fill (same columns and row marks)
@@ -357,14 +381,14 @@ int csr_from_edges(const uint32_t* d_src, const uint32_t* d_dst, uint64_t n_edge
 namespace {
 
 // Values of the matrix (swapped: of its transpose on the same pattern) in all stored forms.
-int fill_values(const Csr& c, uint32_t n, const float* dinv, int mode, float eps, int swapped,
+int fill_values(const Csr& c, const float* dinv, int mode, float eps, int swapped,
                 bool transposed, float* val, uint2* cv, hipStream_t s)
 {
     if (c.nnz == 0) return MIXGCN_OK;
     if (!c.groups.bands.empty() && (!transposed || c.groups.bands.back().ent_t))
         return rowgroups_fill(c, c.groups, dinv, mode, eps, swapped, transposed, val, cv, s);
-    hipLaunchKernelGGL(values_kernel, dim3((unsigned)ceil_div(c.nnz, kBlock)), dim3(kBlock), 0, s,
-                       c.rowptr, c.col, dinv, n, c.nnz, mode, eps, swapped, val, cv);
+    hipLaunchKernelGGL(values_kernel, dim3((unsigned)ceil_div(c.n_groups, kValueGroups)), dim3(kBlock), 0, s,
+                       c.rowptr, c.grp_row, c.col, dinv, c.n_groups, c.nnz, mode, eps, swapped, val, cv);
     return MIXGCN_OK;
 }
 
@@ -382,7 +406,7 @@ int normalize_graph(mixgcn_graph* g, int mode, float eps, hipStream_t s)
     for (Csr* c : mats) {
         if (!c) continue;
         if (!c->val) MIXGCN_TRY(dmalloc_async(&c->val, (size_t)c->nnz, s));
-        MIXGCN_TRY(fill_values(*c, n, g->dinv, mode, eps, c == &g->tr ? 1 : 0, false, c->val, c->cv, s));
+        MIXGCN_TRY(fill_values(*c, g->dinv, mode, eps, c == &g->tr ? 1 : 0, false, c->val, c->cv, s));
     }
     // A symmetrised graph stores one pattern for the matrix and its transpose.  The mean
     // weights are not symmetric, so the transpose gets value arrays of its own on that pattern.
@@ -393,7 +417,7 @@ int normalize_graph(mixgcn_graph* g, int mode, float eps, hipStream_t s)
         MIXGCN_TRY(rowgroups_alloc_transpose(&f.groups, s));
         hipLaunchKernelGGL(copy_entries_kernel, dim3((unsigned)ceil_div(f.nnz_padded, kBlock)),
                            dim3(kBlock), 0, s, f.cv, f.cv_t, f.nnz_padded);
-        MIXGCN_TRY(fill_values(f, n, g->dinv, mode, eps, 1, true, f.val_t, f.cv_t, s));
+        MIXGCN_TRY(fill_values(f, g->dinv, mode, eps, 1, true, f.val_t, f.cv_t, s));
     }
     MIXGCN_HIP_TRY(hipGetLastError());
     g->normalized = true;
