@@ -279,10 +279,18 @@ void csr_free(Csr* c)
     pool_free(c->cv_t);
     pool_free(c->val_t);
     pool_free(c->grp_row);
+    host_free(c->h_rowptr);
     rowgroups_free(&c->groups);
     *c = Csr();
 }
 
+int csr_copy_rowptr(const Csr& c, uint32_t n, hipStream_t s)
+{
+    MIXGCN_HIP_TRY(hipMemcpyAsync(c.h_rowptr, c.rowptr, ((size_t)n + 1) * 8, hipMemcpyDeviceToHost, s));
+    return MIXGCN_OK;
+}
+
+// The row pointers are not copied to the host yet (csr_copy_rowptr).
 int csr_from_edges(const uint32_t* d_src, const uint32_t* d_dst, uint64_t n_edges, uint32_t n,
                    bool symmetrize, bool self_loops, bool transposed, Csr* out, hipStream_t s)
 {
@@ -359,10 +367,8 @@ int csr_from_edges(const uint32_t* d_src, const uint32_t* d_dst, uint64_t n_edge
                                t.flags + 1);
         hipLaunchKernelGGL(group_rows_kernel, dim3((unsigned)ceil_div(c.n_groups + 1, kBlock)),
                            dim3(kBlock), 0, s, c.rowptr, n, nnz, c.n_groups, c.grp_row);
-        c.h_rowptr.resize((size_t)n + 1);
-        if (hipMemcpyAsync(c.h_rowptr.data(), c.rowptr, ((size_t)n + 1) * 8, hipMemcpyDeviceToHost,
-                           s) != hipSuccess ||
-            hipMemcpyAsync(h_flags, t.flags, 16, hipMemcpyDeviceToHost, s) != hipSuccess ||
+        if ((rc = host_alloc((void**)&c.h_rowptr, ((size_t)n + 1) * 8)) != MIXGCN_OK) break;
+        if (hipMemcpyAsync(h_flags, t.flags, 16, hipMemcpyDeviceToHost, s) != hipSuccess ||
             hipStreamSynchronize(s) != hipSuccess || hipGetLastError() != hipSuccess) {
             rc = fail(MIXGCN_EHIP, "CSR fill failed");
             break;

@@ -97,7 +97,7 @@ struct Csr {
     float* val_t = nullptr;          // [nnz]
     uint32_t* grp_row = nullptr;     // [n_groups + 1] row that holds entry g * kGroupNnz
     RowGroups groups;
-    std::vector<int64_t> h_rowptr;   // host copy of rowptr
+    int64_t* h_rowptr = nullptr;     // host copy of rowptr (host_alloc)
     bool has_empty_rows = false;
 };
 
@@ -196,6 +196,9 @@ int pool_malloc(void** p, size_t bytes);
 void pool_free(void* p);
 void pool_free_on(void* p, hipStream_t s);
 void pool_release();
+// Host memory, pinned where the runtime grants it; nothing on the device may still use a block that is freed.
+int host_alloc(void** p, size_t bytes);
+void host_free(void* p);
 
 // ---- scratch shared by entry points without a handle --------------------------------------------
 int get_scratch(int which, size_t bytes, void** out);
@@ -204,6 +207,8 @@ int get_scratch(int which, size_t bytes, void** out);
 int csr_from_edges(const uint32_t* d_src, const uint32_t* d_dst, uint64_t n_edges, uint32_t n,
                    bool symmetrize, bool self_loops, bool transposed, Csr* out, hipStream_t s);
 void csr_free(Csr* c);
+// Queues the host copy of the row pointers; it is there once the stream has been waited for.
+int csr_copy_rowptr(const Csr& c, uint32_t n, hipStream_t s);
 int normalize_graph(mixgcn_graph* g, int mode, float eps, hipStream_t s);
 
 int rowgroups_build(const Csr& m, uint32_t n, RowGroups* out, hipStream_t s);

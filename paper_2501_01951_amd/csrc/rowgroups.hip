@@ -882,6 +882,34 @@ int build_band(const int64_t* rowptr, uint32_t n, int64_t nnz, const uint32_t* b
     return MIXGCN_OK;
 }
 
+// Host copy of the popularity histogram, and an event behind it.
+struct HostHist {
+    unsigned long long* p = nullptr;
+    hipEvent_t ev = nullptr;
+    int copy(const unsigned long long* d, hipStream_t s)
+    {
+        MIXGCN_TRY(host_alloc((void**)&p, 2 * kBins * sizeof(*p)));
+        MIXGCN_HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+        MIXGCN_HIP_TRY(hipMemcpyAsync(p, d, 2 * kBins * sizeof(*p), hipMemcpyDeviceToHost, s));
+        MIXGCN_HIP_TRY(hipEventRecord(ev, s));
+        queued = true;
+        return MIXGCN_OK;
+    }
+    int wait()
+    {
+        MIXGCN_HIP_TRY(hipEventSynchronize(ev));
+        queued = false;
+        return MIXGCN_OK;
+    }
+    bool queued = false;
+    ~HostHist()
+    {
+        if (queued) (void)hipEventSynchronize(ev);
+        if (ev) (void)hipEventDestroy(ev);
+        host_free(p);
+    }
+};
+
 int build_bands(const Csr& m, uint32_t n, RowGroups* out, hipStream_t s)
 {
     Tmp t(s);
@@ -891,10 +919,12 @@ int build_bands(const Csr& m, uint32_t n, RowGroups* out, hipStream_t s)
     MIXGCN_HIP_TRY(hipMemsetAsync(t.hist, 0, 2 * kBins * sizeof(unsigned long long), s));
     hipLaunchKernelGGL(popularity_kernel, dim3(blocks(n) < 512u ? blocks(n) : 512u), dim3(kBlock), 0, s,
                        m.rowptr, n, t.keys, t.hist, t.hist + kBins);
-    unsigned long long h[2 * kBins];
-    MIXGCN_HIP_TRY(hipMemcpyAsync(h, t.hist, sizeof(h), hipMemcpyDeviceToHost, s));
-    MIXGCN_HIP_TRY(hipStreamSynchronize(s));
-    const int n_bands = plan_bands(h, h + kBins, (double)n, (double)m.nnz, out);
+    // the row pointers are on their way to the host while the bands are planned
+    HostHist h;
+    MIXGCN_TRY(h.copy(t.hist, s));
+    MIXGCN_TRY(csr_copy_rowptr(m, n, s));
+    MIXGCN_TRY(h.wait());
+    const int n_bands = plan_bands(h.p, h.p + kBins, (double)n, (double)m.nnz, out);
     if (n_bands == 1) return MIXGCN_OK;
     out->bands.resize((size_t)n_bands);
 
@@ -939,11 +969,12 @@ int build_bands(const Csr& m, uint32_t n, RowGroups* out, hipStream_t s)
 
 // The bands and groups of a matrix with a symmetric pattern (row lengths are then the popularities of
 // the columns): everything that depends on the pattern only.  None where they cannot pay, and where
-// there is no memory for them.  Waits for the stream.
+// there is no memory for them.  Queues the host copy of the row pointers too, and waits for the stream where there
+// was anything to plan.
 int rowgroups_build(const Csr& m, uint32_t n, RowGroups* out, hipStream_t s)
 {
     if (n <= (uint32_t)kBandColumns || n >= kRowMask || m.nnz < 2 * kBandRow * (int64_t)n || m.nnz > kMostEntries)
-        return MIXGCN_OK;
+        return csr_copy_rowptr(m, n, s);
     RowGroups g;
     int rc = build_bands(m, n, &g, s);
     if (rc == MIXGCN_OK && hipStreamSynchronize(s) != hipSuccess) rc = fail(MIXGCN_EHIP, "bands of the columns");
@@ -951,7 +982,7 @@ int rowgroups_build(const Csr& m, uint32_t n, RowGroups* out, hipStream_t s)
         (void)hipStreamSynchronize(s);  // the arrays may have work queued on them
         rowgroups_free(&g);
         if (rc == MIXGCN_ENOMEM) (void)hipGetLastError();
-        return rc == MIXGCN_ENOMEM ? MIXGCN_OK : rc;
+        return rc == MIXGCN_ENOMEM ? csr_copy_rowptr(m, n, s) : rc;  // (the copy may have been queued or not)
     }
     *out = std::move(g);
     return MIXGCN_OK;

@@ -179,3 +179,56 @@ def test_first_normalisation_can_be_captured(n, degree, mean):
         z.zero_()
     g.free()
     want.free()
+
+
+@pytest.mark.parametrize("n,degree", [(1000, 3), (30_000, 30), (200_000, 8)])
+def test_row_pointers_on_the_host_belong_to_their_graph(n, degree):
+    """The pinned host copies of row pointers go from one graph to the next: calls over row ranges, which take their
+    first and last entries from them, while graphs of the same size come and go (and after the cache has been emptied)."""
+    import paper_2501_01951_amd as mg
+
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    held = []
+    for i in range(4):
+        src, dst = (torch.randint(0, n, (n * degree // 2,), device="cuda", dtype=torch.int32, generator=gen)
+                    for _ in range(2))
+        g = mg.build_csr(src, dst, n)
+        mg.normalize(g)
+        held.append(g)
+        if i == 1:
+            held.pop(0).free()
+        if i == 2:
+            mg.release_memory()
+        for k in held:
+            h = torch.randn(n, 8, device="cuda", generator=gen)
+            z, parts = torch.empty_like(h), torch.empty_like(h)
+            mg.aggregate(k, h, z)
+            for r0, r1 in ((0, 1), (1, n // 3), (n // 3, n)):
+                mg.aggregate(k, h, parts, row_begin=r0, row_end=r1)
+            assert torch.allclose(z, parts, rtol=1e-5, atol=1e-6)  # (spans of another length: sums in another order)
+    for k in held:
+        k.free()
+
+
+@pytest.mark.parametrize("mode", ["sym", "mean", "sum"])
+@pytest.mark.parametrize("first,last,n", [(0, 300, 301), (100_000, 100_257, 400_000), (399_000, 400_000, 400_000)])
+def test_values_of_rows_between_empty_ones(mode, first, last, n):
+    """Groups of 256 entries that cover one row, many rows, and long runs of empty rows; a last group that is not full."""
+    import paper_2501_01951_amd as mg
+
+    gen = torch.Generator(device="cuda").manual_seed(last)
+    src = torch.randint(first, last, (3001,), device="cuda", dtype=torch.int32, generator=gen)
+    dst = torch.cat([src.new_full((700,), last - 1),
+                     torch.randint(first, last, (2301,), device="cuda", dtype=torch.int32, generator=gen)])
+    g = mg.build_csr(src, dst, n, mg.SYMMETRIZE)
+    mg.normalize(g, {"sym": mg.NORM_SYM, "mean": mg.NORM_MEAN, "sum": mg.NORM_SUM}[mode], eps=0.25)
+    for transpose in (False, True):
+        a = g.arrays(transpose)
+        deg = a["rowptr"][1:] - a["rowptr"][:-1]
+        row = torch.repeat_interleave(torch.arange(n, device="cuda"), deg)
+        col = a["col"].long()
+        root = (1 / deg.double().sqrt()).float()
+        want = {"sym": root[row] * root[col], "sum": torch.ones_like(a["val"]),
+                "mean": (1 / deg.double()).float()[col if transpose else row]}[mode]
+        assert torch.equal(a["val"], want)
+    g.free()
