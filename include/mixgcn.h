@@ -338,7 +338,9 @@ int mixgcn_layer_fwd(const mixgcn_graph* g, const mixgcn_layer_desc* d, const vo
  *                         H is not read (may be NULL).
  *   MIXGCN_UPDATE_FIRST:  dQ = A_hat^T dP [n x f_out] (written to the workspace Z);
  *                         dW = H^T dQ;   dH = dQ W^T.  H is the layer's input [n x f_in, ld_h].
- * G may be overwritten.  dH == NULL skips the input gradient (first layer when none is wanted).
+ * G may be overwritten.  dH == NULL skips the input gradient (first layer when none is wanted); its rows may hold
+ * other values until they are written (wide fp32 layers keep 1[Hout > 0] there as bits, unless dH shares memory with
+ * Z, G, Hout, W or dW).
  * dW is fp32 [f_in x f_out] with leading dimension d->ld_w.
  * The backward pass is not cut into row chunks: with d->n_chunks > 1 and two streams the two
  * dense products run on the secondary stream and the transposed aggregation, which needs all

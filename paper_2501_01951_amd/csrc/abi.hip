@@ -457,7 +457,7 @@ int mixgcn_relu_bitmap(int dtype, const void* X, int64_t ldx, int64_t n_rows, in
 static int update_impl(int op, int dtype, const void* A, int64_t lda, const void* B, int64_t ldb,
                        void* C, int64_t ldc, int64_t n_rows, int32_t k, int32_t m,
                        const void* relu_ref, int64_t ldr, float beta, hipStream_t stream,
-                       Timer* timer)
+                       Timer* timer, ReluBits bits = {})
 {
     if (op < MIXGCN_OP_FWD || op > MIXGCN_OP_WGRAD) return fail(MIXGCN_EINVAL, "update: op");
     if (dtype != MIXGCN_F32 && dtype != MIXGCN_BF16) return fail(MIXGCN_EINVAL, "update: dtype");
@@ -485,7 +485,7 @@ static int update_impl(int op, int dtype, const void* A, int64_t lda, const void
         break;
     }
     return launch_update(op, dtype, A, lda, B, ldb, C, ldc, n_rows, k, m, relu_ref,
-                         ldr, beta, stream, timer);
+                         ldr, beta, stream, timer, bits);
 }
 
 int mixgcn_apply_bitmap(int dtype, void* X, int64_t ldx, int64_t n_rows, int32_t n_cols,
@@ -761,12 +761,30 @@ int mixgcn_layer_bwd(const mixgcn_graph* g, const mixgcn_layer_desc* d, const vo
         MIXGCN_HIP_TRY(hipEventRecord(p->ev_start, p->primary));
         MIXGCN_HIP_TRY(hipStreamWaitEvent(p->secondary, p->ev_start, 0));
     }
+    // The rows of dH, which nothing holds before the transposed aggregation writes it, take the ReLU derivative as bits
+    // from the weight to the data gradient, which then reads a sixteenth of Hout.  Not where dH shares memory with what
+    // is still to be read, nor for narrow layers, where making the bits costs more (both gradients and the aggregation
+    // of one entry per row, us, Hout read twice : bits; 2^21 rows 128 -> 1024 8800 : 8310, 2^20 256 -> 256 2510 : 2450,
+    // 20 k 128 -> 512 128 : 125; 2^18 128 -> 256 373 : 379, 300 k 256 -> 33 401 : 421).
+    ReluBits bits;
+    if (R && dH && d->dtype == MIXGCN_F32 && (d->f_out >= 512 || (d->f_out >= 256 && d->f_in >= 256)) &&
+        relu_bits_row(d->f_out) <= (int64_t)d->f_in * 4 &&
+        relu_bits_apply(d->ld_z, d->ld_out, d->ld_out, d->ld_h * 4) &&
+        check_matrix("layer_bwd: dH", dH, d->ld_h, d->f_in, 4) == MIXGCN_OK) {
+        const auto apart = [&](const void* q, int64_t rows, int64_t ld) {
+            const char* const a = (const char*)dH, * const b = (const char*)q;
+            return a + n * d->ld_h * 4 <= b || b + rows * ld * 4 <= a;
+        };
+        if (apart(Z, n, d->ld_z) && apart(G, n, d->ld_out) && apart(R, n, d->ld_out) && apart(W, d->f_in, d->ld_w) &&
+            apart(dW, d->f_in, d->ld_w))
+            bits = ReluBits{(uint8_t*)dH, d->ld_h * 4};
+    }
     // dW = Z^T dP must read Z before dZ overwrites it
     MIXGCN_TRY(update_impl(MIXGCN_OP_WGRAD, d->dtype, Z, d->ld_z, G, d->ld_out, dW, d->ld_w, n,
-                           d->f_in, d->f_out, R, d->ld_out, 0.f, dense, tm));
+                           d->f_in, d->f_out, R, d->ld_out, 0.f, dense, tm, bits));
     if (dH) {
         MIXGCN_TRY(update_impl(MIXGCN_OP_DGRAD, d->dtype, G, d->ld_out, W, d->ld_w, Z, d->ld_z, n,
-                               d->f_in, d->f_out, R, d->ld_out, 0.f, dense, tm));
+                               d->f_in, d->f_out, R, d->ld_out, 0.f, dense, tm, bits));
         if (two) {
             MIXGCN_HIP_TRY(hipEventRecord(p->ev_done, p->secondary));
             MIXGCN_HIP_TRY(hipStreamWaitEvent(p->primary, p->ev_done, 0));

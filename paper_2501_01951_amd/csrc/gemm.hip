@@ -576,7 +576,7 @@ int launch_wgrad_reduce(const float* P, int64_t n_slabs, int64_t cells, int32_t 
 
 int launch_update(int op, int dtype, const void* A, int64_t lda, const void* B, int64_t ldb,
                   void* C, int64_t ldc, int64_t n, int32_t k, int32_t m, const void* R,
-                  int64_t ldr, float beta, hipStream_t s, Timer* timer)
+                  int64_t ldr, float beta, hipStream_t s, Timer* timer, ReluBits bits)
 {
     if (op != MIXGCN_OP_WGRAD) {
         const bool fwd = op != MIXGCN_OP_DGRAD, relu = op == MIXGCN_OP_FWD_RELU;
@@ -586,7 +586,7 @@ int launch_update(int op, int dtype, const void* A, int64_t lda, const void* B, 
                                      (const float*)R, ldr, s));
         else if (!fwd || dtype != MIXGCN_F32)
             MIXGCN_TRY(launch_update_rows(dtype, fwd, relu, A, lda, (const float*)B, ldb, C, ldc, n, fwd ? k : m,
-                                          fwd ? m : k, fwd ? nullptr : R, ldr, s));
+                                          fwd ? m : k, fwd ? nullptr : R, ldr, s, bits));
         else if (g_update_arith == MIXGCN_ARITH_BF16X3 && forward_split_applies(lda, n, k, m))
             MIXGCN_TRY(launch_forward_split(relu, (const float*)A, lda, (const float*)B, ldb, (float*)C, ldc, n, k,
                                             m, s));
@@ -599,7 +599,7 @@ int launch_update(int op, int dtype, const void* A, int64_t lda, const void* B, 
         return launch_wgrad_bf16((const uint16_t*)A, lda, (const uint16_t*)B, ldb, (float*)C, ldc, n, k, m,
                                  (const uint16_t*)R, ldr, beta, s, timer);
     return launch_wgrad_split((const float*)A, lda, (const float*)B, ldb, (float*)C, ldc, n, k, m, (const float*)R, ldr,
-                              beta, s, timer);
+                              beta, s, timer, bits);
 }
 
 }  // namespace mixgcn

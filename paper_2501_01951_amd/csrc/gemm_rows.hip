@@ -134,10 +134,14 @@ __device__ inline int fresh(int v)
     return v;
 }
 
-template <int DT, bool MASK>
+// How the rows are masked: not, by 1[R > 0], or by the bits that the weight gradient has made of it (fp32).
+constexpr int kNoMask = 0, kMaskRef = 1, kMaskBits = 2;
+
+template <int DT, int MASK>
 struct RawRows {
     uint4 a[TM][2];
-    uint4 r[TM][MASK ? 2 : 1];
+    uint4 r[TM][MASK == kMaskRef ? 2 : 1];
+    uint2 bits[TM];
 };
 
 struct RowsArgs {
@@ -153,9 +157,10 @@ struct RowsArgs {
     int64_t ldr;
     int n_col_tiles, row_groups;
     int waves;  // wavefronts of a workgroup that walk rows (streamed weights: all); all load the weights
+    ReluBits bits;
 };
 
-template <int DT, int TN, bool WT, bool RELU, bool MASK, bool RESIDENT>
+template <int DT, int TN, bool WT, bool RELU, int MASK, bool RESIDENT>
 __global__ __launch_bounds__(kRowsBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void update_rows_kernel(RowsArgs p)
 {
     using T = Terms<DT>;
@@ -256,10 +261,11 @@ __global__ __launch_bounds__(kRowsBlock) __attribute__((amdgpu_waves_per_eu(2, 2
     }
     // Rows in flight: two steps, or one with a mask, which loads twice the bytes per step (and two would
     // not fit the registers).
-    constexpr int kAhead = MASK ? 1 : 2;
+    constexpr int kAhead = MASK == kMaskRef ? 1 : 2;
     RawRows<DT, MASK> raw[kAhead];
     const char* arow[TM];
     const char* rrow[TM];
+    const char* brow[TM];
     int lc = 0;             // chunk the load cursor stands at
     int64_t lt = first;     // its tile
     auto point = [&]() {
@@ -268,7 +274,8 @@ __global__ __launch_bounds__(kRowsBlock) __attribute__((amdgpu_waves_per_eu(2, 2
             int64_t row = lt * kWaveRows + tm * 16 + li;
             if (row > p.n - 1) row = p.n - 1;
             arow[tm] = reinterpret_cast<const char*>(p.A) + row * p.lda * ES + g * 16;
-            if (MASK) rrow[tm] = reinterpret_cast<const char*>(p.R) + row * p.ldr * ES + g * 16;
+            if (MASK == kMaskRef) rrow[tm] = reinterpret_cast<const char*>(p.R) + row * p.ldr * ES + g * 16;
+            if (MASK == kMaskBits) brow[tm] = reinterpret_cast<const char*>(p.bits.p) + row * p.bits.pitch;
         }
     };
     const bool ragged = p.KD % KC != 0;
@@ -283,8 +290,12 @@ __global__ __launch_bounds__(kRowsBlock) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
             for (int tm = 0; tm < TM; ++tm) {
                 x.a[tm][h] = load_from(out ? zero : arow[tm] + off + h * 64);
-                if (MASK) x.r[tm][h] = load_from(out ? zero : rrow[tm] + off + h * 64);
+                if (MASK == kMaskRef) x.r[tm][h] = load_from(out ? zero : rrow[tm] + off + h * 64);
             }
+        }
+        if (MASK == kMaskBits) {  // the 32 columns of the step: a byte for each piece of 4, all lanes of a row the same
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm) x.bits[tm] = *reinterpret_cast<const uint2*>(brow[tm] + lc * 8);
         }
         if (++lc == nch) {
             lc = 0;
@@ -329,11 +340,19 @@ __global__ __launch_bounds__(kRowsBlock) __attribute__((amdgpu_waves_per_eu(2, 2
             if (DT == MIXGCN_F32) {
                 float v[8];
                 __builtin_memcpy(v, x.a[tm], 32);
-                if (MASK) {
+                if (MASK == kMaskRef) {
                     float r[8];
                     __builtin_memcpy(r, x.r[tm], 32);
 #pragma unroll
                     for (int e = 0; e < 8; ++e) v[e] = r[e] > 0.f ? v[e] : 0.f;
+                }
+                if (MASK == kMaskBits) {
+                    const uint32_t w[2] = {x.bits[tm].x >> (8 * g), x.bits[tm].y >> (8 * g)};
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const uint32_t keep = (uint32_t)((int)(w[e >> 2] << (31 - (e & 3))) >> 31);
+                        v[e] = __uint_as_float(__float_as_uint(v[e]) & keep);
+                    }
                 }
 #pragma unroll
                 for (int e = 0; e < 8; ++e) v[e] *= kTermScale;
@@ -626,11 +645,17 @@ int launch_rows_tn(bool relu, const RowsArgs& args, hipStream_t s)
                                dim3(grid), dim3(kRowsBlock), lds, s, a);                              \
     } while (0)
     if constexpr (WT) {
-        if (relu) MIXGCN_ROWS(true, false);
-        else MIXGCN_ROWS(false, false);
+        if (relu) MIXGCN_ROWS(true, kNoMask);
+        else MIXGCN_ROWS(false, kNoMask);
     } else {
-        if (a.R) MIXGCN_ROWS(false, true);
-        else MIXGCN_ROWS(false, false);
+        if constexpr (DT == MIXGCN_F32) {
+            if (a.R && a.bits.p) {
+                MIXGCN_ROWS(false, kMaskBits);
+                return MIXGCN_OK;
+            }
+        }
+        if (a.R) MIXGCN_ROWS(false, kMaskRef);
+        else MIXGCN_ROWS(false, kNoMask);
     }
 #undef MIXGCN_ROWS
     MIXGCN_HIP_TRY(hipGetLastError());
@@ -652,10 +677,10 @@ int launch_rows_wt(bool relu, const RowsArgs& a, hipStream_t s)
 // features the data gradient alone
 int launch_update_rows(int dtype, bool w_is_kd_major, bool relu, const void* A, int64_t lda, const float* W,
                        int64_t ldw, void* C, int64_t ldc, int64_t n, int KD, int MD, const void* R,
-                       int64_t ldr, hipStream_t s)
+                       int64_t ldr, hipStream_t s, ReluBits bits)
 {
     if (n <= 0) return MIXGCN_OK;
-    RowsArgs a{A, lda, W, ldw, C, ldc, n, KD, MD, R, ldr, 0, 0, 0};
+    RowsArgs a{A, lda, W, ldw, C, ldc, n, KD, MD, R, ldr, 0, 0, 0, bits};
     if (dtype == MIXGCN_F32) return launch_rows_wt<MIXGCN_F32, false>(relu, a, s);
     return w_is_kd_major ? launch_rows_wt<MIXGCN_BF16, true>(relu, a, s)
                          : launch_rows_wt<MIXGCN_BF16, false>(relu, a, s);

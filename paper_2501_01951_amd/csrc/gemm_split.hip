@@ -77,13 +77,23 @@ __device__ inline __amdgpu_buffer_rsrc_t rows_at(const char* first, int bytes)
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(first), 0, bytes, 0x00020000);
 }
 
+// 2 b + on: one instruction with the comparison's lane mask as its carry.
+__device__ inline int shift_in(int b, bool on)
+{
+    const uint64_t lanes = __builtin_amdgcn_ballot_w64(on);
+    asm("v_addc_co_u32 %0, vcc, %0, %0, %1" : "+v"(b) : "s"(lanes) : "vcc");
+    return b;
+}
+
 // FAR: a step of 16 rows does not fit a buffer with 32-bit offsets (pitches of 2^22 elements and more).  The
 // same tiles, slabs and order with 64-bit addresses: the arithmetic does not depend on the pitch.
-template <int BN, bool MASK, bool FAR>
+// BITS: the mask goes to `bits` too (see ReluBits), each byte once, by the tiles of the first 128 features (2^21 rows
+// 128 x 1024 3900 -> 4200 us; the data gradient that reads it instead of R 4580 -> 3780).
+template <int BN, bool MASK, bool FAR, bool BITS>
 __global__ __launch_bounds__(kBlock, 2) void wgrad_split_kernel(
     const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
     const float* __restrict__ R, int64_t ldr, float* __restrict__ P, int KD, int MD,
-    int64_t rows_per_slab, int64_t n_rows, int n_i_tiles, int n_j_tiles)
+    int64_t rows_per_slab, int64_t n_rows, int n_i_tiles, int n_j_tiles, ReluBits bits)
 {
     // tile of 128 x BN: 2 x 2 wavefronts of 64 x BN / 2, or (32 columns) four of 32 x 32
     constexpr int WN = BN > 32 ? 2 : 1, TM = BN > 32 ? 2 : 1, TN = BN / WN / 32;
@@ -172,7 +182,27 @@ __global__ __launch_bounds__(kBlock, 2) void wgrad_split_kernel(
         bp += (int64_t)BKS * pb;
         left -= BKS;
     };
+    // The bytes of a step's mask.  What lies past the slab's end or the columns is outside the buffer: not stored.
+    int bits_left = BITS && i0 == 0 ? left : 0;  // rows from the store cursor on
+    char* bits_row = BITS ? reinterpret_cast<char*>(bits.p + r_begin * bits.pitch) : nullptr;
+    const int bits_col = j0 + tcol < MD ? (j0 + tcol) / 4 : 0x7FFF0000;
+    auto put_bits = [&](const Regs& g) {
+        const int rows = __builtin_amdgcn_readfirstlane(bits_left >= BKS ? BKS : bits_left > 0 ? bits_left : 0);
+        const auto out = rows_at(bits_row, rows * (int)bits.pitch);
+#pragma unroll
+        for (int p = 0; p < PB; ++p) {
+            const float4 r = g.r[MASK ? p : 0];
+            int b = r.w > 0.f ? 1 : 0;
+            b = shift_in(b, r.z > 0.f);
+            b = shift_in(b, r.y > 0.f);
+            b = shift_in(b, r.x > 0.f);
+            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)b, out, (trow + 8 * p) * (int)bits.pitch + bits_col, 0, 0);
+        }
+        bits_row += BKS * bits.pitch;
+        bits_left -= BKS;
+    };
     auto store = [&](const Regs& g, uint16_t* as, uint16_t* bs, auto odd) {
+        if (BITS) put_bits(g);
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             uint16_t* qa = as + spos + p * 8 * LDW;
@@ -308,7 +338,7 @@ __global__ __launch_bounds__(kBlock, 2) void wgrad_split_kernel(
 
 // dW[k x m] = beta dW + A[n x k]^T (B (.) mask)[n x m]
 int launch_wgrad_split(const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc, int64_t n,
-                       int32_t k, int32_t m, const float* R, int64_t ldr, float beta, hipStream_t s, Timer* timer)
+                       int32_t k, int32_t m, const float* R, int64_t ldr, float beta, hipStream_t s, Timer* timer, ReluBits bits)
 {
     // The narrowest tile that holds the columns (2^20 rows 256 x 47: 508 us with 128 columns, 360 with 64;
     // 256 x 16: 333 with 64, 282 with 32).
@@ -325,24 +355,21 @@ int launch_wgrad_split(const float* A, int64_t lda, const float* B, int64_t ldb,
     float* P = (float*)scratch;
     const unsigned grid = (unsigned)(n_slabs * tiles);
     if (timer) MIXGCN_TRY(timer->begin(kTimeUpdateWgrad, s));
-#define MIXGCN_WGRAD(BN, MASK, FAR)                                                                              \
-    hipLaunchKernelGGL((wgrad_split_kernel<BN, MASK, FAR>), dim3(grid), dim3(kBlock), 0, s, A, lda, B, ldb, R, ldr, \
-                       P, k, m, rows_per_slab, n, nit, njt)
-#define MIXGCN_WGRAD_FAR(BN, MASK)                \
-    do {                                          \
-        if (far) MIXGCN_WGRAD(BN, MASK, true);    \
-        else MIXGCN_WGRAD(BN, MASK, false);       \
-    } while (0)
-#define MIXGCN_WGRAD_MASK(BN)                     \
-    do {                                          \
-        if (R) MIXGCN_WGRAD_FAR(BN, true);        \
-        else MIXGCN_WGRAD_FAR(BN, false);         \
+#define MIXGCN_WGRAD(BN, MASK, FAR, BITS)                                                                        \
+    hipLaunchKernelGGL((wgrad_split_kernel<BN, MASK, FAR, BITS>), dim3(grid), dim3(kBlock), 0, s, A, lda, B, ldb, R, \
+                       ldr, P, k, m, rows_per_slab, n, nit, njt, bits)
+#define MIXGCN_WGRAD_MASK(BN)                                            \
+    do {                                                                 \
+        if (R && bits.p && !far) MIXGCN_WGRAD(BN, true, false, true);    \
+        else if (R && far) MIXGCN_WGRAD(BN, true, true, false);          \
+        else if (R) MIXGCN_WGRAD(BN, true, false, false);                \
+        else if (far) MIXGCN_WGRAD(BN, false, true, false);              \
+        else MIXGCN_WGRAD(BN, false, false, false);                      \
     } while (0)
     if (bn == 128) MIXGCN_WGRAD_MASK(128);
     else if (bn == 64) MIXGCN_WGRAD_MASK(64);
     else MIXGCN_WGRAD_MASK(32);
 #undef MIXGCN_WGRAD_MASK
-#undef MIXGCN_WGRAD_FAR
 #undef MIXGCN_WGRAD
     if (timer) MIXGCN_TRY(timer->end(s));
     MIXGCN_TRY(launch_wgrad_reduce(P, n_slabs, cells, m, C, ldc, beta, s));

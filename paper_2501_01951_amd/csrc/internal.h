@@ -255,9 +255,21 @@ int launch_dropout_bitmap(uint64_t seed, int64_t n, int32_t cols, uint64_t thres
 int launch_relu_mask(int dtype, void* G, int64_t ldg, const void* R, int64_t ldr, int64_t n,
                      int32_t m, hipStream_t s);
 
+// The ReLU derivative 1[R > 0] of an n x m fp32 matrix as bits: column c of row r is bit c % 4 of byte r * pitch + c / 4.
+// The weight gradient writes it, the data gradient of the same layer reads it instead of R (each where p is set).
+struct ReluBits {
+    uint8_t* p = nullptr;
+    int64_t pitch = 0;  // bytes; rows hold whole groups of 8 bytes
+};
+inline int64_t relu_bits_row(int32_t m) { return ceil_div(m, 32) * 8; }
+// whether both products can take them
+inline bool relu_bits_apply(int64_t lda, int64_t ldb, int64_t ldr, int64_t pitch)
+{
+    return lda < (1 << 22) && ldb < (1 << 22) && ldr < (1 << 22) && pitch < (1 << 26);
+}
 int launch_update(int op, int dtype, const void* A, int64_t lda, const void* B, int64_t ldb,
                   void* C, int64_t ldc, int64_t n, int32_t k, int32_t m, const void* R,
-                  int64_t ldr, float beta, hipStream_t s, Timer* timer);
+                  int64_t ldr, float beta, hipStream_t s, Timer* timer, ReluBits bits);
 
 // dW[k x m] = beta dW + A[n x k]^T (B (.) 1[R > 0])[n x m] of bf16 features
 int launch_wgrad_bf16(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, float* C, int64_t ldc,
@@ -267,7 +279,7 @@ int launch_wgrad_bf16(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t
 // the same of fp32 features, every operand as three bf16 terms
 int launch_wgrad_split(const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc,
                        int64_t n, int32_t k, int32_t m, const float* R, int64_t ldr, float beta,
-                       hipStream_t s, Timer* timer);
+                       hipStream_t s, Timer* timer, ReluBits bits);
 
 // bf16 features and weights that do not fit LDS; launch_update_rows chooses it
 int launch_update_bf16_deep(bool w_is_kd_major, bool relu, const uint16_t* A, int64_t lda, const float* W,
@@ -290,7 +302,7 @@ int launch_forward_split(bool relu, const float* A, int64_t lda, const float* W,
 // features the data gradient alone
 int launch_update_rows(int dtype, bool w_is_kd_major, bool relu, const void* A, int64_t lda, const float* W,
                        int64_t ldw, void* C, int64_t ldc, int64_t n, int KD, int MD, const void* R,
-                       int64_t ldr, hipStream_t s);
+                       int64_t ldr, hipStream_t s, ReluBits bits = {});
 
 // Row slabs of a weight gradient of `tiles` output tiles over n rows: slabs of at most `most_rows`
 // rows (1024 workgroups at most), and on small inputs shorter ones until every compute unit has a

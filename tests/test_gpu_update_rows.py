@@ -378,3 +378,34 @@ def test_the_relu_derivative_of_nan_is_zero(mg, dtype, n, k, m):
         mg.update(mg.OP_WGRAD, z[:, :k], g[:, :m], dw, n, k, m, relu_ref=ref)
         out.append((dz[:, :k], dw))
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+# layers whose backward pass hands the ReLU derivative on as bits (512 columns, or 256 of both), widths that are no
+# multiple of 4 or 32, several column tiles and row tiles of the weight gradient, rows that fill no step or slab; too few
+# columns of dH for the bits; narrower layers
+@pytest.mark.parametrize("n,k,m", [(1, 128, 512), (31, 132, 601), (1000, 256, 256), (5000, 300, 259), (2500, 128, 1030),
+                                   (700, 20, 512), (700, 32, 513), (3000, 128, 128)])
+@pytest.mark.parametrize("share", ["nothing", "dH over G", "dH over Hout"])
+def test_layer_backward_is_its_two_products_and_the_aggregation(mg, n, k, m, share):
+    if share != "nothing" and k != m:
+        pytest.skip("dH has the shape of neither")
+    gen = torch.Generator(device="cuda").manual_seed(n + k + m)
+    ends = [torch.randint(0, n, (3 * n,), device="cuda", dtype=torch.int32, generator=gen) for _ in range(2)]
+    g = mg.build_csr(*ends, n)
+    mg.normalize(g)
+    z, hout, grad = padded(n, k, torch.float32, gen), padded(n, m, torch.float32, gen), padded(n, m, torch.float32, gen)
+    hout[:, :m].clamp_(min=0)
+    hout[0, 0], hout[-1, m - 1] = float("nan"), float("inf")
+    w = torch.randn(k, (m + 3) // 4 * 4, device="cuda", generator=gen)[:, :m]
+    dw, want_dw = torch.empty_strided(w.shape, w.stride(), device="cuda"), torch.empty_strided(w.shape, w.stride(), device="cuda")
+    want_z, want_dh = z.clone(), torch.full_like(z, 7.0)
+    mg.update(mg.OP_WGRAD, z[:, :k], grad[:, :m], want_dw, n, k, m, relu_ref=hout[:, :m])
+    mg.update(mg.OP_DGRAD, grad[:, :m], w, want_z[:, :k], n, k, m, relu_ref=hout[:, :m])
+    mg.aggregate(g, want_z[:, :k], want_dh[:, :k], transpose=True)
+    dh = {"nothing": torch.full_like(z, 7.0), "dH over G": grad, "dH over Hout": hout}[share]
+    past = dh[:, k:].clone()
+    mg.layer_bwd(g, z[:, :k], hout[:, :m], w, grad[:, :m], dw, dh[:, :k], mg.Pipeline(), relu=True)
+    same = lambda a, b: torch.equal(a.contiguous().view(torch.int32), b.contiguous().view(torch.int32))
+    assert same(dw, want_dw) and same(z[:, :k], want_z[:, :k]) and same(dh[:, :k], want_dh[:, :k])
+    assert same(dh[:, k:], past)
+    g.free()
