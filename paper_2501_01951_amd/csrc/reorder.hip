@@ -337,16 +337,18 @@ __global__ __launch_bounds__(kBlock) void narrow_levels_kernel(
 }
 
 // ---- wide levels ----------------------------------------------------------------------------
-// Three kernels and a scan per level, one wavefront per frontier node.  What bounds a level of a few
-// thousand nodes is the chain of dependent loads of each kernel (about 5 us) and the launches, so
+// Three kernels per level, one wavefront per frontier node.  What bounds a level of a few
+// thousand nodes is the chain of dependent loads of each kernel (about 4 us) and the launches, so
 // the levels follow each other without the host: the state of the walk goes from one slot to the
-// next on the device, and launches behind the last wide level return at once.
-// A 64 x 64 x 64 grid (about 95 wide levels): 3.8 ms; with one counter read back and a radix sort of
-// seven passes per level it was 17.4 ms.
+// next on the device, and launches behind the last wide level return at once.  A block owns consecutive
+// frontier nodes where their next-level nodes are counted and where these are placed: the counts are added up per block, and the
+// kernel that places the nodes adds up the sums of the blocks before its own (1024 words) instead of waiting for a scan
+// of all counts by one workgroup.
+// A 64 x 64 x 64 grid (about 106 wide levels): 3.3 ms; with that scan 3.6, with one counter read back and a radix
+// sort of seven passes per level 17.4 ms.
 constexpr int kMostChildren = 64;   // next-level nodes of one frontier node that a wavefront orders
 constexpr int kWideBlocks = 1024;
-constexpr int kScanThreads = 1024;
-constexpr int kScanPer = 16;        // counts per thread and step of the scan
+static_assert(kWideBlocks == 4 * kBlock, "four block sums per thread");
 
 struct WideState {
     uint32_t f_begin, f_count;  // the frontier is order[f_begin, f_begin + f_count)
@@ -409,6 +411,16 @@ __global__ __launch_bounds__(kBlock) void wide_offer_kernel(
     }
 }
 
+// Frontier nodes [first, end) of a block of the grid.
+struct BlockNodes {
+    uint32_t first, end;
+};
+__device__ inline BlockNodes block_nodes(uint32_t f_count)
+{
+    const uint32_t per = (f_count - 1) / gridDim.x + 1, first = blockIdx.x * per;  // (f_count > 0, at most 2^30)
+    return BlockNodes{first, first + per < f_count ? first + per : f_count};
+}
+
 // Lanes whose neighbor w of the frontier node u with queue index qi is placed by it.  Only a root has
 // its own index for a parent.
 __device__ inline uint64_t children(uint32_t w, uint32_t p, bool valid, uint32_t u, uint32_t qi)
@@ -420,13 +432,17 @@ __device__ inline uint64_t children(uint32_t w, uint32_t p, bool valid, uint32_t
 __global__ __launch_bounds__(kBlock) void wide_count_kernel(
     const int64_t* __restrict__ rowptr, const uint32_t* __restrict__ col,
     const uint32_t* __restrict__ order, const WideState* __restrict__ st,
-    const uint32_t* __restrict__ parent, uint32_t* __restrict__ cnt, uint32_t* __restrict__ many)
+    const uint32_t* __restrict__ parent, uint32_t* __restrict__ cnt, uint32_t* __restrict__ block_sum,
+    uint32_t* __restrict__ many)
 {
     const WideState a = *st;
     if (a.stop != kWideGo) return;
+    __shared__ uint32_t sum;
+    if (threadIdx.x == 0) sum = 0;
+    __syncthreads();
     const uint32_t lane = threadIdx.x & (kWave - 1);
-    for (uint32_t i = blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6); i < a.f_count;
-         i += gridDim.x * (kBlock / kWave)) {
+    const BlockNodes own = block_nodes(a.f_count);
+    for (uint32_t i = own.first + (threadIdx.x >> 6); i < own.end; i += kBlock / kWave) {
         const uint32_t qi = a.f_begin + i;
         const uint32_t u = order[qi];
         uint32_t c = 0;
@@ -436,109 +452,98 @@ __global__ __launch_bounds__(kBlock) void wide_count_kernel(
         });
         if (lane == 0) {
             cnt[i] = c;
+            atomicAdd(&sum, c);
             if (c > (uint32_t)kMostChildren) atomicOr(many, 1u);
         }
     }
+    __syncthreads();
+    if (threadIdx.x == 0) block_sum[blockIdx.x] = sum;
 }
 
-// Exclusive prefix sums of the counts, and the state after the level.  One workgroup.
-__global__ __launch_bounds__(kScanThreads) void wide_scan_kernel(
-    const WideState* __restrict__ st, WideState* __restrict__ next, const uint32_t* __restrict__ cnt,
-    uint32_t* __restrict__ off, const uint32_t* __restrict__ many)
-{
-    __shared__ uint32_t sums[kScanThreads / kWave];
-    const WideState a = *st;
-    const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid >> 6;
-    if (a.stop != kWideGo) {
-        if (tid == 0) *next = a;
-        return;
-    }
-    uint32_t run = 0;
-    for (uint32_t i0 = 0; i0 < a.f_count; i0 += kScanThreads * kScanPer) {
-        const uint32_t first = i0 + tid * kScanPer;
-        uint32_t v[kScanPer], mine = 0;
-#pragma unroll
-        for (int j = 0; j < kScanPer; ++j) {
-            v[j] = first + j < a.f_count ? cnt[first + j] : 0;
-            mine += v[j];
-        }
-        uint32_t inc = mine;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const uint32_t t = (uint32_t)__shfl_up((int)inc, o, kWave);
-            if (lane >= (uint32_t)o) inc += t;
-        }
-        if (lane == kWave - 1) sums[wv] = inc;
-        __syncthreads();
-        uint32_t before = run, total = 0;
-#pragma unroll
-        for (uint32_t k = 0; k < kScanThreads / kWave; ++k) {
-            const uint32_t x = sums[k];
-            if (k < wv) before += x;
-            total += x;
-        }
-        __syncthreads();
-        before += inc - mine;
-#pragma unroll
-        for (int j = 0; j < kScanPer; ++j) {
-            if (first + j < a.f_count) off[first + j] = before;
-            before += v[j];
-        }
-        run += total;
-    }
-    if (tid == 0) {
-        WideState b;
-        if (*many) {
-            b = a;
-            b.m = run;
-            b.stop = kWideSort;
-        } else {
-            b.f_begin = a.count;
-            b.f_count = run;
-            b.count = a.count + run;
-            b.m = 0;
-            b.stop = run == 0 ? kWideEnd : run <= (uint32_t)kNarrowFrontier ? kWideNarrow : kWideGo;
-        }
-        *next = b;
-    }
-}
-
-// Every frontier node places its next-level nodes in their (degree, id) order.
+// Every frontier node places its next-level nodes in their (degree, id) order; in a level that is to be sorted, the
+// places of its first ones go to off instead.  Block 0 writes the state after the level.
 __global__ __launch_bounds__(kBlock) void wide_place_kernel(
     const int64_t* __restrict__ rowptr, const uint32_t* __restrict__ col,
     const uint32_t* __restrict__ bydeg, const uint32_t* __restrict__ degrank, uint32_t* order,
-    const WideState* __restrict__ st, const WideState* __restrict__ next,
+    const WideState* __restrict__ st, WideState* __restrict__ next,
     const uint32_t* __restrict__ parent, const uint32_t* __restrict__ cnt,
-    const uint32_t* __restrict__ off, uint32_t* __restrict__ cm_idx)
+    const uint32_t* __restrict__ block_sum, uint32_t* __restrict__ off, const uint32_t* __restrict__ many,
+    uint32_t* __restrict__ cm_idx)
 {
     __shared__ uint32_t ranks[kBlock / kWave][kMostChildren];
+    __shared__ uint32_t at0[kBlock];  // places of the first next-level nodes of a block's nodes
+    __shared__ uint32_t lds[kBlock / kWave];
     const WideState a = *st;
-    if (a.stop != kWideGo || next->stop == kWideSort) return;
-    const uint32_t lane = threadIdx.x & (kWave - 1);
-    volatile uint32_t* const mine = ranks[threadIdx.x >> 6];
-    for (uint32_t i = blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6); i < a.f_count;
-         i += gridDim.x * (kBlock / kWave)) {
-        const uint32_t c = cnt[i];  // at most kMostChildren
-        if (c == 0) continue;
-        const uint32_t qi = a.f_begin + i;
-        const uint32_t u = order[qi];
-        uint32_t found = 0;
-        walk_row(col, parent, rowptr[u], rowptr[u + 1], lane, [&](uint32_t w, uint32_t p, bool valid) {
-            const uint64_t m = children(w, p, valid, u, qi);
-            if ((m >> lane) & 1) mine[found + __popcll(m & ((1ull << lane) - 1))] = degrank[w];
-            found += (uint32_t)__popcll(m);
-            return found < c;
-        });
-        __builtin_amdgcn_wave_barrier();  // LDS operations of a wavefront complete in order
-        const uint32_t key = lane < c ? mine[lane] : 0;
-        uint32_t rank = 0;
-        for (uint32_t j = 0; j < c; ++j) rank += mine[j] < key ? 1u : 0u;
-        if (lane < c) {
-            const uint32_t w = bydeg[key], at = a.count + off[i] + rank;
-            order[at] = w;
-            cm_idx[w] = at;
+    const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid >> 6;
+    if (a.stop != kWideGo) {
+        if (blockIdx.x == 0 && tid == 0) *next = a;
+        return;
+    }
+    const bool sort = *many != 0;
+    // nodes that the blocks before this one place
+    uint32_t base, all;
+    {
+        const uint4 q = reinterpret_cast<const uint4*>(block_sum)[tid];
+        const uint32_t k = 4 * tid, b = blockIdx.x;
+        block_scan_u32((k < b ? q.x : 0) + (k + 1 < b ? q.y : 0) + (k + 2 < b ? q.z : 0) + (k + 3 < b ? q.w : 0), &base,
+                       lds);
+        if (b == 0) {
+            block_scan_u32(q.x + q.y + q.z + q.w, &all, lds);
+            if (tid == 0) {
+                WideState w;
+                if (sort) {
+                    w = a;
+                    w.m = all;
+                    w.stop = kWideSort;
+                } else {
+                    w.f_begin = a.count;
+                    w.f_count = all;
+                    w.count = a.count + all;
+                    w.m = 0;
+                    w.stop = all == 0 ? kWideEnd : all <= (uint32_t)kNarrowFrontier ? kWideNarrow : kWideGo;
+                }
+                *next = w;
+            }
         }
-        __builtin_amdgcn_wave_barrier();
+    }
+    const BlockNodes own = block_nodes(a.f_count);
+    volatile uint32_t* const mine = ranks[wv];
+    for (uint32_t i0 = own.first; i0 < own.end; i0 += kBlock) {  // (uniform over the block)
+        const uint32_t here = own.end - i0 < (uint32_t)kBlock ? own.end - i0 : (uint32_t)kBlock;
+        uint32_t total;
+        const uint32_t before = block_scan_u32(tid < here ? cnt[i0 + tid] : 0, &total, lds);
+        if (sort) {
+            if (tid < here) off[i0 + tid] = base + before;
+            base += total;
+            continue;
+        }
+        at0[tid] = a.count + base + before;
+        base += total;
+        __syncthreads();
+        for (uint32_t j = wv; j < here; j += kBlock / kWave) {
+            const uint32_t c = cnt[i0 + j];  // at most kMostChildren
+            if (c == 0) continue;
+            const uint32_t qi = a.f_begin + i0 + j;
+            const uint32_t u = order[qi];
+            uint32_t found = 0;
+            walk_row(col, parent, rowptr[u], rowptr[u + 1], lane, [&](uint32_t w, uint32_t p, bool valid) {
+                const uint64_t m = children(w, p, valid, u, qi);
+                if ((m >> lane) & 1) mine[found + __popcll(m & ((1ull << lane) - 1))] = degrank[w];
+                found += (uint32_t)__popcll(m);
+                return found < c;
+            });
+            __builtin_amdgcn_wave_barrier();  // LDS operations of a wavefront complete in order
+            const uint32_t key = lane < c ? mine[lane] : 0;
+            uint32_t rank = 0;
+            for (uint32_t k = 0; k < c; ++k) rank += mine[k] < key ? 1u : 0u;
+            if (lane < c) {
+                const uint32_t w = bydeg[key], at = at0[j] + rank;
+                order[at] = w;
+                cm_idx[w] = at;
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        __syncthreads();  // at0 is written again
     }
 }
 
@@ -678,7 +683,7 @@ int mixgcn_reorder_rcm(const mixgcn_graph* g, uint32_t* pos, void* stream)
     const Csr& m = g->fwd;
     DevMem mem(s);
     uint64_t *keys, *alt;
-    uint32_t *bydeg, *degrank, *single, *cm_idx, *parent, *order, *cnt, *off, *many;
+    uint32_t *bydeg, *degrank, *single, *cm_idx, *parent, *order, *cnt, *off, *block_sum, *many;
     WideState* wide;
     void* tmp;
     MIXGCN_TRY(mem.alloc(&keys, n));
@@ -691,6 +696,7 @@ int mixgcn_reorder_rcm(const mixgcn_graph* g, uint32_t* pos, void* stream)
     MIXGCN_TRY(mem.alloc(&order, n));
     MIXGCN_TRY(mem.alloc(&cnt, n));
     MIXGCN_TRY(mem.alloc(&off, n));
+    MIXGCN_TRY(mem.alloc(&block_sum, kWideBlocks));
     MIXGCN_TRY(mem.alloc(&many, 1));
     MIXGCN_TRY(mem.alloc(&wide, 2));
     const size_t tmp_bytes = sort_tmp_bytes(n) > scan_tmp_bytes(n) ? sort_tmp_bytes(n) : scan_tmp_bytes(n);
@@ -733,11 +739,9 @@ int mixgcn_reorder_rcm(const mixgcn_graph* g, uint32_t* pos, void* stream)
                 hipLaunchKernelGGL(wide_offer_kernel, grid, block, 0, s, m.rowptr, m.col, order,
                                    wide + at, parent, many);
                 hipLaunchKernelGGL(wide_count_kernel, grid, block, 0, s, m.rowptr, m.col, order,
-                                   wide + at, parent, cnt, many);
-                hipLaunchKernelGGL(wide_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, wide + at,
-                                   wide + (at ^ 1), cnt, off, many);
+                                   wide + at, parent, cnt, block_sum, many);
                 hipLaunchKernelGGL(wide_place_kernel, grid, block, 0, s, m.rowptr, m.col, bydeg, degrank,
-                                   order, wide + at, wide + (at ^ 1), parent, cnt, off, cm_idx);
+                                   order, wide + at, wide + (at ^ 1), parent, cnt, block_sum, off, many, cm_idx);
             }
             MIXGCN_HIP_TRY(hipMemcpyAsync(&w, wide + at, sizeof(w), hipMemcpyDeviceToHost, s));
             MIXGCN_HIP_TRY(hipStreamSynchronize(s));

@@ -50,3 +50,26 @@ def test_wide_levels(leaves, sym):
     got = mg.reorder_rcm(g).cpu().numpy().view(np.uint32)
     g.free()
     assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("wide", [262_144, 262_145, 300_000])
+def test_levels_of_more_nodes_than_a_block_takes_at_once(wide):
+    """A grid of 1024 blocks has 256 frontier nodes each up to 262,144: a hub's leaves, most of them with a node or two
+    of their own, one with 70 in the second level after them."""
+    import paper_2501_01951_amd as mg
+
+    rng = np.random.default_rng(wide)
+    leaf = np.arange(1, wide + 1)
+    second = wide + 1 + np.arange(wide // 2 * 3)
+    up = np.concatenate([leaf[: len(second) - wide // 2], leaf[: wide // 2]])
+    third = second[-1] + 1 + np.arange(70)
+    src = np.concatenate([np.zeros(wide, np.int64), up, np.full(70, second[wide // 3])])
+    dst = np.concatenate([leaf, second, third])
+    n = int(third[-1]) + 1
+    perm = rng.permutation(n).astype(np.uint32)
+    src, dst = perm[src], perm[dst]
+    want = oracle.rcm(oracle.build_csr(src, dst, n, True, True))
+    g = mg.build_csr(torch.from_numpy(src.view(np.int32)).cuda(), torch.from_numpy(dst.view(np.int32)).cuda(), n)
+    got = mg.reorder_rcm(g).cpu().numpy().view(np.uint32)
+    g.free()
+    assert np.array_equal(got, want)
