@@ -142,9 +142,10 @@ __global__ __launch_bounds__(kBlock) void wgrad_bf16_kernel(
 // i / 4 + 8 and i / 4 + 12, so with lane s of the group pointing at row s / 4, features
 // 4 (s % 4) .. + 3, every lane receives its own feature at four consecutive rows, and two such
 // reads are one MFMA operand.  Two groups are served per cycle from 64 banks (four rows of 64
-// bytes): a row pitch of 64 bytes modulo 256 keeps them apart.  Rows come in whole steps of 32
-// (the caller gives the last n % 32 rows to the kernel above); features beyond the matrices are
-// zeroed with per-thread masks that do not change from step to step.
+// bytes): a row pitch of 64 bytes modulo 256 keeps them apart.  Rows come in whole steps of 32; the last n % 32
+// rows are a slab of their own with one step, whose other rows are zeros (the kernel above in a launch of its own took
+// 6 us for them: a weight gradient of 100003 rows 128 x 128 25 -> 19.6 us, 128 x 16 17 -> 13).  Features beyond the matrices are zeroed with per-thread
+// masks that do not change from step to step.
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 typedef short shortx8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) shortx4 lds_shortx4;
@@ -161,9 +162,9 @@ __device__ inline bf16x8 read_transposed(const uint16_t* p)
 }
 
 template <class S, bool MASK>
-__global__ __launch_bounds__(kBlock) void wgrad_bf16_tr_kernel(
+__global__ __launch_bounds__(kBlock, S::BN == 128 ? 3 : 5) void wgrad_bf16_tr_kernel(
     const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ B, int64_t ldb,
-    const uint16_t* __restrict__ R, int64_t ldr, float* __restrict__ P, int64_t n, int KD, int MD,
+    const uint16_t* __restrict__ R, int64_t ldr, float* __restrict__ P, int64_t n_main, int64_t n, int KD, int MD,
     int64_t rows_per_slab, int n_i_tiles, int n_j_tiles)
 {
     static_assert(S::BM == 128 && (S::BN == 128 || S::BN == 32), "tile shapes of the staging");
@@ -178,12 +179,15 @@ __global__ __launch_bounds__(kBlock) void wgrad_bf16_tr_kernel(
     const int wm = wave / S::WN, wn = wave % S::WN;
     const int tiles = n_i_tiles * n_j_tiles;
     const unsigned lid = xcd_local_index(blockIdx.x, gridDim.x);
-    const int64_t slab = lid / tiles;
-    const int t = (int)(lid % tiles);
+    const int slab = __builtin_amdgcn_readfirstlane((int)(lid / (unsigned)tiles));
+    const int t = (int)(lid % (unsigned)tiles);
     const int i0 = (t / n_j_tiles) * S::BM, j0 = (t % n_j_tiles) * S::BN;
-    const int64_t r_begin = slab * rows_per_slab;
-    const int64_t r_end = (r_begin + rows_per_slab) < n ? (r_begin + rows_per_slab) : n;
-    const int nk = (int)((r_end - r_begin) / BKB);  // whole steps: the caller sees to it
+    // n_main rows in whole steps, then the slab of the others
+    const int64_t first = slab * rows_per_slab;
+    const int rest = first < n_main ? 0 : (int)(n - n_main);
+    const int64_t r_begin = rest ? n_main : first;
+    const int64_t r_end = (r_begin + rows_per_slab) < n_main ? (r_begin + rows_per_slab) : n_main;
+    const int nk = rest ? 0 : (int)((r_end - r_begin) / BKB);  // whole steps: the caller sees to it
 
     floatx16 acc[S::TM][S::TN];
 #pragma unroll
@@ -320,6 +324,27 @@ __global__ __launch_bounds__(kBlock) void wgrad_bf16_tr_kernel(
         }
     }
 
+    if (rest) {
+        Regs g;
+        // (a row that does not exist: the first one, times zero)
+        auto piece = [](const char* first, size_t at, uint32_t off, bool in) {
+            const uint4 v = *reinterpret_cast<const uint4*>(first + (in ? at + off : (size_t)0));
+            const uint32_t k = in ? ~0u : 0u;
+            return make_uint4(v.x & k, v.y & k, v.z & k, v.w & k);
+        };
+#pragma unroll
+        for (int p = 0; p < 2; ++p) g.a[p] = piece(a0, (size_t)p * 16 * 2 * (size_t)lda, a_off, arow + p * 16 < rest);
+#pragma unroll
+        for (int p = 0; p < B_PASSES; ++p) {
+            const bool in = brow_c + p * B_RPP < rest;
+            g.b[p] = piece(b0, (size_t)p * B_RPP * 2 * (size_t)ldb, b_off, in);
+            if (MASK) g.r[p] = piece(m0, (size_t)p * B_RPP * 2 * (size_t)ldr, r_off, in);
+        }
+        store(g, As[0], Bs[0]);
+        __syncthreads();
+        step_mma(As[0], Bs[0]);
+    }
+
     const int li = lane & 31, lk = lane >> 5;
     float* out = P + (size_t)slab * KD * MD;
 #pragma unroll
@@ -342,8 +367,8 @@ int launch_wgrad_bf16(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t
                       int64_t n, int32_t k, int32_t m, const uint16_t* R, int64_t ldr, float beta,
                       hipStream_t s, Timer* timer)
 {
-    // C[k x m] = beta C + A[n x k]^T (B (.) mask)[n x m]: whole steps of 32 rows with the
-    // transposing LDS reads, the last n % 32 rows with the scattering kernel
+    // C[k x m] = beta C + A[n x k]^T (B (.) mask)[n x m]: with the transposing LDS reads, the last n % 32 rows too where
+    // their slab fits the scratch; pitches that 32-bit offsets do not reach with the scattering kernel
     const bool wide = m > 64;
     const int bm = 128, bn = wide ? 128 : 32;
     const int nit = (int)ceil_div(k, bm), njt = (int)ceil_div(m, bn);
@@ -375,38 +400,42 @@ int launch_wgrad_bf16(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t
     MIXGCN_TRY(get_scratch(0, (size_t)(together ? all : most) * cells * sizeof(float), &scratch));
     float* const P0 = (float*)scratch;
     if (timer) MIXGCN_TRY(timer->begin(kTimeUpdateWgrad, s));
+    // the rest in the launch of the whole steps: one more slab
+    const bool one_launch = pitches_ok && together && n % BKB != 0;
     auto slabs = [&](bool transposing_reads, int64_t row0, const Part& p, float* P) {
-        const int64_t rows = p.rows, rows_per_slab = p.rows_per_slab, n_slabs = p.slabs;
+        const int64_t rows = p.rows, rows_per_slab = p.rows_per_slab;
+        const int64_t n_slabs = p.slabs + (transposing_reads && one_launch ? 1 : 0);
         const unsigned grid = (unsigned)(n_slabs * tiles);
+        const int64_t n_all = one_launch ? n : rows;
         const uint16_t* a = A + row0 * lda;
         const uint16_t* b = B + row0 * ldb;
         const uint16_t* r = R ? R + row0 * ldr : nullptr;
-#define MIXGCN_WGRAD(KERNEL, SHAPE, MASK)                                                        \
-    hipLaunchKernelGGL((KERNEL<SHAPE, MASK>), dim3(grid), dim3(kBlock), 0, s, a, lda, b, ldb, r,  \
-                   ldr, P, rows, k, m, rows_per_slab, nit, njt)
-#define MIXGCN_WGRAD_SHAPES(KERNEL)                                                              \
-    do {                                                                                         \
-    if (wide) {                                                                              \
-        if (r) MIXGCN_WGRAD(KERNEL, Shape128x128, true);                                     \
-        else MIXGCN_WGRAD(KERNEL, Shape128x128, false);                                      \
-    } else {                                                                                 \
-        if (r) MIXGCN_WGRAD(KERNEL, Shape128x32, true);                                      \
-        else MIXGCN_WGRAD(KERNEL, Shape128x32, false);                                       \
-    }                                                                                        \
+#define MIXGCN_WGRAD(SHAPE, MASK)                                                                             \
+    do {                                                                                                      \
+        if (transposing_reads)                                                                                \
+            hipLaunchKernelGGL((wgrad_bf16_tr_kernel<SHAPE, MASK>), dim3(grid), dim3(kBlock), 0, s, a, lda, b, ldb, r, \
+                               ldr, P, rows, n_all, k, m, rows_per_slab, nit, njt);                           \
+        else                                                                                                  \
+            hipLaunchKernelGGL((wgrad_bf16_kernel<SHAPE, MASK>), dim3(grid), dim3(kBlock), 0, s, a, lda, b, ldb, r, \
+                               ldr, P, rows, k, m, rows_per_slab, nit, njt);                                  \
     } while (0)
-        if (transposing_reads) MIXGCN_WGRAD_SHAPES(wgrad_bf16_tr_kernel);
-        else MIXGCN_WGRAD_SHAPES(wgrad_bf16_kernel);
-#undef MIXGCN_WGRAD_SHAPES
+        if (wide) {
+            if (r) MIXGCN_WGRAD(Shape128x128, true);
+            else MIXGCN_WGRAD(Shape128x128, false);
+        } else {
+            if (r) MIXGCN_WGRAD(Shape128x32, true);
+            else MIXGCN_WGRAD(Shape128x32, false);
+        }
 #undef MIXGCN_WGRAD
     };
-    if (main_part.slabs) {
+    if (main_part.slabs || one_launch) {
         slabs(true, 0, main_part, P0);
         if (!together) {
             MIXGCN_TRY(launch_wgrad_reduce(P0, main_part.slabs, cells, m, C, ldc, beta, s));
             beta = 1.f;
         }
     }
-    if (rest.slabs) slabs(false, n_main, rest, together ? P0 + main_part.slabs * cells : P0);
+    if (rest.slabs && !one_launch) slabs(false, n_main, rest, together ? P0 + main_part.slabs * cells : P0);
     if (together || rest.slabs)
         MIXGCN_TRY(launch_wgrad_reduce(P0, together ? all : rest.slabs, cells, m, C, ldc, beta, s));
     if (timer) MIXGCN_TRY(timer->end(s));

@@ -409,3 +409,24 @@ def test_layer_backward_is_its_two_products_and_the_aggregation(mg, n, k, m, sha
     assert same(dw, want_dw) and same(z[:, :k], want_z[:, :k]) and same(dh[:, :k], want_dh[:, :k])
     assert same(dh[:, k:], past)
     g.free()
+
+
+@pytest.mark.parametrize("k,m", [(128, 128), (100, 50), (130, 20), (300, 200)])
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 2079, 40001])
+def test_bf16_weight_gradient_of_any_number_of_rows(mg, n, k, m):
+    """The last n % 32 rows are a slab of their own; what lies past the rows and the columns is NaN.  Element by
+    element: products of bf16 are exact in fp32, a slab adds at most 2048 rows in MFMAs of 16 (their sums lose less than
+    2^-23 of the running sum each), the slabs are added in 64 bits and rounded once."""
+    gen = torch.Generator(device="cuda").manual_seed(n + k + m)
+    a, g, h = (padded(n + 40, c, torch.bfloat16, gen) for c in (k, m, m))
+    for t in (a, g, h):
+        t[n:] = float("nan")
+    a, g, h = a[:n, :k], g[:n, :m], h[:n, :m]
+    dw = torch.empty(k, (m + 3) // 4 * 4, device="cuda")[:, :m]
+    for ref in (None, h):
+        dp = g if ref is None else torch.where(ref > 0, g, torch.zeros_like(g))
+        want, mag = a.double().t() @ dp.double(), a.double().abs().t() @ dp.double().abs()
+        bound = mag * (2048 / 16 + 2) * 2.0 ** -23
+        for beta in (0.0, 1.0):
+            mg.update(mg.OP_WGRAD, a, g, dw, n, k, m, relu_ref=ref, beta=beta)
+            assert ((dw.double() - (1 + beta) * want).abs() <= (1 + 2 * beta) * bound + 1e-30).all()
