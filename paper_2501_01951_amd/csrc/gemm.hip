@@ -518,7 +518,10 @@ int launch_rowblock(bool relu, const float* A, int64_t lda, const float* B, int6
 int forward_f32(bool relu, const float* A, int64_t lda, const float* W, int64_t ldw, float* C, int64_t ldc,
                 int64_t n, int32_t k, int32_t m, hipStream_t s)
 {
-    if (forward_rows_applies(n, k, m))
+    // (a product written over its features has to read all of a row's before any of its sums are written, which several
+    // narrow column tiles do not)
+    const bool apart = (const float*)C + n * ldc <= A || A + n * lda <= C;
+    if (apart && forward_rows_applies(n, k, m))
         return launch_forward_rows(relu, A, lda, W, ldw, C, ldc, n, k, m, s);
     return m > 64 ? launch_rowblock<Shape128x128>(relu, A, lda, W, ldw, C, ldc, n, k, m, s)
                   : launch_rowblock<Shape128x32>(relu, A, lda, W, ldw, C, ldc, n, k, m, s);

@@ -19,7 +19,7 @@
 // What bounds it: memory on the wide layers (2^21 rows 128 x 1024 reads and masks 18.2 GB at 4.7 TB/s, a
 // streaming read reaches 5.7), vector work of the splits and the sums (175 instructions beside 24 MFMAs) where
 // a tile has both operands to itself.  us, fp32 MFMAs -> now: 2^20 rows 128 x 256 761 -> 619, 256 x 256
-// 1280 -> 1020, 256 x 47 574 -> 365, 256 x 16 315 -> 282; 2^21 rows 128 x 1024 5100 -> 3900; 11.1 M rows
+// 1280 -> 863, 256 x 47 574 -> 365, 256 x 16 315 -> 282; 2^21 rows 128 x 1024 5100 -> 3900; 11.1 M rows
 // 128 x 128 3170 -> 2520; 232965 rows 602 x 128 458 -> 331; 4096 rows 64 x 100 19.7 -> 15.2.
 #include <type_traits>
 

@@ -33,6 +33,8 @@ namespace {
 constexpr size_t kMaxCached = (size_t)4 << 30;
 constexpr int kPoolDevices = 16;
 constexpr size_t kMaxHostCached = (size_t)512 << 20;
+// Smaller blocks are ordinary memory: one staging buffer, and pinning takes 100 us and more where none is cached.
+constexpr size_t kLeastPinned = (size_t)1 << 20;
 
 struct Block {
     void* p = nullptr;
@@ -250,8 +252,8 @@ int host_alloc(void** p, size_t bytes)
         P.host_cached.erase(best);
     } else {
         b.bytes = want;
-        if (hipHostMalloc(&b.p, want, hipHostMallocPortable) != hipSuccess) {
-            (void)hipGetLastError();
+        if (want < kLeastPinned || hipHostMalloc(&b.p, want, hipHostMallocPortable) != hipSuccess) {
+            if (want >= kLeastPinned) (void)hipGetLastError();
             *p = malloc(want);
             return *p ? MIXGCN_OK : fail(MIXGCN_ENOMEM, "host memory");
         }

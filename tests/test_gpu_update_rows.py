@@ -430,3 +430,15 @@ def test_bf16_weight_gradient_of_any_number_of_rows(mg, n, k, m):
         for beta in (0.0, 1.0):
             mg.update(mg.OP_WGRAD, a, g, dw, n, k, m, relu_ref=ref, beta=beta)
             assert ((dw.double() - (1 + beta) * want).abs() <= (1 + 2 * beta) * bound + 1e-30).all()
+
+
+@pytest.mark.parametrize("n,k", [(5000, 128), (20003, 100), (300, 32)])
+def test_fp32_forward_written_over_its_features(mg, n, k):
+    """Up to 128 columns a row's features are all read before its sums are written, whatever the number of rows."""
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    z = padded(n, k, torch.float32, gen)
+    w = torch.randn(k, k, device="cuda", generator=gen)
+    out = torch.empty(n, k, device="cuda")
+    mg.update(mg.OP_FWD_RELU, z[:, :k], w, out, n, k, k)
+    mg.update(mg.OP_FWD_RELU, z[:, :k], w, z[:, :k], n, k, k)
+    assert torch.equal(z[:, :k], out)
