@@ -77,14 +77,6 @@ __device__ inline __amdgpu_buffer_rsrc_t rows_at(const char* first, int bytes)
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(first), 0, bytes, 0x00020000);
 }
 
-// 2 b + on: one instruction with the comparison's lane mask as its carry.
-__device__ inline int shift_in(int b, bool on)
-{
-    const uint64_t lanes = __builtin_amdgcn_ballot_w64(on);
-    asm("v_addc_co_u32 %0, vcc, %0, %0, %1" : "+v"(b) : "s"(lanes) : "vcc");
-    return b;
-}
-
 // FAR: a step of 16 rows does not fit a buffer with 32-bit offsets (pitches of 2^22 elements and more).  The
 // same tiles, slabs and order with 64-bit addresses: the arithmetic does not depend on the pitch.
 // BITS: the mask goes to `bits` too (see ReluBits), each byte once, by the tiles of the first 128 features (2^21 rows
@@ -185,18 +177,16 @@ __global__ __launch_bounds__(kBlock, 2) void wgrad_split_kernel(
     // The bytes of a step's mask.  What lies past the slab's end or the columns is outside the buffer: not stored.
     int bits_left = BITS && i0 == 0 ? left : 0;  // rows from the store cursor on
     char* bits_row = BITS ? reinterpret_cast<char*>(bits.p + r_begin * bits.pitch) : nullptr;
-    const int bits_col = j0 + tcol < MD ? (j0 + tcol) / 4 : 0x7FFF0000;
+    const uint32_t bits_col = j0 + tcol < MD ? (uint32_t)(j0 + tcol) / 4 : 0x7FFF0000u;
     auto put_bits = [&](const Regs& g) {
         const int rows = __builtin_amdgcn_readfirstlane(bits_left >= BKS ? BKS : bits_left > 0 ? bits_left : 0);
         const auto out = rows_at(bits_row, rows * (int)bits.pitch);
 #pragma unroll
         for (int p = 0; p < PB; ++p) {
             const float4 r = g.r[MASK ? p : 0];
-            int b = r.w > 0.f ? 1 : 0;
-            b = shift_in(b, r.z > 0.f);
-            b = shift_in(b, r.y > 0.f);
-            b = shift_in(b, r.x > 0.f);
-            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)b, out, (trow + 8 * p) * (int)bits.pitch + bits_col, 0, 0);
+            const int b = (r.x > 0.f ? 1 : 0) | (r.y > 0.f ? 2 : 0) | (r.z > 0.f ? 4 : 0) | (r.w > 0.f ? 8 : 0);
+            __builtin_amdgcn_raw_buffer_store_b8(
+                (uint8_t)b, out, (int)((uint32_t)(trow + 8 * p) * (uint32_t)bits.pitch + bits_col), 0, 0);
         }
         bits_row += BKS * bits.pitch;
         bits_left -= BKS;
@@ -338,7 +328,8 @@ __global__ __launch_bounds__(kBlock, 2) void wgrad_split_kernel(
 
 // dW[k x m] = beta dW + A[n x k]^T (B (.) mask)[n x m]
 int launch_wgrad_split(const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc, int64_t n,
-                       int32_t k, int32_t m, const float* R, int64_t ldr, float beta, hipStream_t s, Timer* timer, ReluBits bits)
+                       int32_t k, int32_t m, const float* R, int64_t ldr, float beta, hipStream_t s, Timer* timer,
+                       ReluBits bits)
 {
     // The narrowest tile that holds the columns (2^20 rows 256 x 47: 508 us with 128 columns, 360 with 64;
     // 256 x 16: 333 with 64, 282 with 32).
