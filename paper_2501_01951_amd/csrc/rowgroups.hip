@@ -5,7 +5,7 @@
 // popular lines.  So where a graph is dense enough the columns are dealt to bands by popularity, 26 k
 // columns each and the rest in the last, and the bands are aggregated one after the other; the later
 // ones add to what the earlier ones left in Z.  How many bands pay is estimated from the degree histogram
-// (plan_bands).  Power law, 233 k nodes, 492 entries per row, 128 columns, 9 bands: 7.19 -> 3.57 ms, 52 -> 11
+// (plan_bands).  Power law, 233 k nodes, 492 entries per row, 128 columns, 9 bands: 7.19 -> 3.44 ms, 52 -> 11
 // GB read, 18 -> 83 % L2 hits (the entries that stream through the same L2 push out some of a band's lines).
 //
 // Groups.  Within a band rows are short, and closing them one at a time (three rounds of lane
