@@ -333,26 +333,70 @@ bool fits(int KD)
     return 2 * ceil_div(KD, 2 * KC) * Walk<TN>::CHUNK * (int64_t)sizeof(float) <= kWeightsLds;
 }
 
-// Column tiles of a product in units of 32 columns, 0 for the tiles of gemm.hip.  us, those tiles : here.
+// Tiles that a wavefront walks one after another, and whether they keep at least `percent` of the time of all the
+// wavefronts that the chip holds.
+struct Passes {
+    int64_t n;
+    bool full(int percent) const { return 100 * used >= percent * n * slots; }
+    int64_t used, slots;
+};
+template <int TN>
+Passes passes(int64_t n, int MD)
+{
+    const int64_t tiles = ceil_div(n, kTileRows), n_col_tiles = ceil_div(MD, TN * 32);
+    const RowWalk w = plan_row_walk(tiles, (int)n_col_tiles, Walk<TN>::WAVES, false);
+    return Passes{ceil_div(w.grid, 256) * ceil_div(tiles, (int64_t)w.row_groups * w.waves), tiles * n_col_tiles,
+                  256 * Walk<TN>::WAVES};
+}
+
+// Column tiles of a product in units of 32 columns, 0 for the tiles of gemm.hip.  Figures: us, those tiles : here, or how
+// many times as fast it is here.
 int column_tiles(int64_t n, int KD, int MD)
 {
     const int64_t tiles = ceil_div(n, kTileRows), blocks = ceil_div(n, 128);
-    if (MD <= 32) return fits<1>(KD) ? 1 : 0;
-    const int wide = MD > 64 ? 4 : 2;
-    // Where 128-row tiles leave a fifth of the compute units idle, narrow column tiles for more wavefronts: 20 k rows
-    // 256 -> 128 27.7 : 19.6, 5000 602 -> 128 56.8 : 17.4, 2500 600 -> 64 25.2 : 17.0 (33 k 128 -> 128, more tiles than
-    // units: 21.5 : 24.6).
-    if (blocks * ceil_div(MD, wide * 32) <= 200) {
-        const int tn = wide == 4 && tiles * ceil_div(MD, 64) >= 2048 ? 2 : 1;
-        return tn == 2 && fits<2>(KD) ? 2 : fits<1>(KD) ? 1 : 0;
+    // gemm.hip: its workgroups, and whether none has a tile at an edge of the columns, or at any edge.  A small launch takes
+    // as long as its slowest workgroup, and one with an edge takes half as long again.
+    const int64_t grid = blocks * ceil_div(MD, MD > 64 ? 128 : 32);
+    const bool even = MD % (MD > 64 ? 128 : 32) == 0 && KD % KC == 0, whole = even && n % 128 == 0;
+    if (MD > 64) {
+        // Where its tiles leave a fifth of the compute units idle, with none at an edge half of them, 32 columns each for
+        // more wavefronts: 20 k rows 256 -> 128 27.7 : 19.6, 5000 602 -> 128 56.8 : 17.4; no edge, 16384 64 -> 128 1.06,
+        // 5120 64 -> 512 0.93, 25600 256 -> 128 0.89.  As long as none of them walks two tiles (5000 rows 256 -> 602
+        // 0.65) or the workgroups of the second round are few (1000 64 -> 1500 1.33, 2500 64 -> 2048 0.95).  Shallow
+        // depths gain by it where few compute units have a tile at all (8000 48 -> 256 1.22, 12 k 0.98; 16 -> 128 of 8000
+        // 1.31, 20 k 0.90; no edge, 5120 32 -> 256 1.02, 10 k 0.86), or one or two
+        // column tiles have columns left over (25 k 16 -> 80 1.06, 4096 48 -> 602 0.89).
+        if (grid <= 200) {
+            const Passes p = passes<1>(n, MD);
+            const int64_t most = whole ? (KD < 32 ? 0 : KD < 64 ? 64 : KD < 96 ? 110 : 128)
+                                 : MD % 128 == 0 || MD > 256 ? (KD < 32 ? 64 : KD < 64 ? 130 : 200) : 200;
+            const bool few = p.n == 1 || (p.n == 2 && p.used <= 2048 && KD >= (whole ? 128 : 32));
+            return grid <= most && few && fits<1>(KD) ? 1 : 0;
+        }
+        // Otherwise 128 columns, where wavefronts walk eight tiles each that keep 93 % of their time (267 k rows 256 ->
+        // 384, 87 %, 0.94; 100 k 160 -> 640, 85 %, 0.92; 2 M 256 -> 384, 93 %, 1.02), deep enough to pay for the weights,
+        // and no odd step that is filled up with zeros: 2^20 rows 256 -> 256 1188 : 1110, 2^18 128 -> 256 171 : 164 (200 k
+        // rows 128 -> 128, three tiles each, 75 : 82; 100 k 90 -> 768 154 : 165; 700 k 100 -> 90 212 : 215).
+        const Passes p = passes<4>(n, MD);
+        return KD >= 128 && ceil_div(KD, KC) % 2 == 0 && p.n >= 8 && p.full(93) && fits<4>(KD) ? 4 : 0;
     }
-    // Otherwise wavefronts that walk eight tiles each, so that their last one is a small part, deep enough to pay
-    // for the weights, and no odd step that is filled up with zeros: 2^20 rows 256 -> 256 1188 : 1110, 256 -> 47 412 :
-    // 327, 2^18 128 -> 256 171 : 164 (200 k rows 128 -> 128, three tiles each, 75 : 82; 100 k 90 -> 768 154 : 165;
-    // 700 k 100 -> 90 212 : 215; 233 k 128 -> 41 47 : 54).
-    if (wide == 2) return KD >= 192 && tiles >= 8192 && fits<2>(KD) ? 2 : 0;
-    const int64_t groups = 8 * (ceil_div(MD, 128) < 32 ? 32 / ceil_div(MD, 128) : 1);
-    return KD >= 128 && ceil_div(KD, KC) % 2 == 0 && tiles >= 64 * groups && fits<4>(KD) ? 4 : 0;
+    // 64 columns in four tiles and more that keep 85 % of the time: 2^20 rows 256 -> 47 412 : 327, 300 k 1.08 (270 k 200 ->
+    // 47, 82 %, 0.94; 233 k 128 -> 41 47 : 54).
+    if (MD > 32 && KD >= 192 && tiles >= 8192) return passes<2>(n, MD).full(85) && fits<2>(KD) ? 2 : 0;
+    // 32 columns.  A step is 32 indices deep here, 16 in gemm.hip: not where the last one is mostly zeros (100 k rows
+    // 47 -> 32 0.80, 80 -> 24 0.95), nor for shallow depths (100 k 16 -> 32 0.72).
+    if (KD < 64 || 9 * KD < 8 * 32 * ceil_div(KD, 32) || !fits<1>(KD)) return 0;
+    const Passes p = passes<1>(n, MD);
+    // Nearly all wavefronts with two to four tiles each: 2^18 rows 256 -> 16 1.26, 256 -> 32 1.04, 2^19 256 -> 16 1.04,
+    // 2^20 no faster; 135 k rows, one tile and a little, 0.73, 400 k, three and a little, 0.85.
+    if (p.n > 1) return MD <= 32 && p.n <= (even ? 2 : 4) && p.full(95) ? 1 : 0;
+    // One tile each at most: not without an edge (4096 rows 64 -> 32 0.85, 12 k 256 -> 64 0.82).  10 k rows 256 -> 16 1.31,
+    // 64 -> 32 1.0; past 200 of its workgroups with columns left over from 96 indices on (100 k 128 -> 16 1.09, 66 k 64 -> 8
+    // 0.97), with rows alone where the workgroup at the edge is not among others of a second round, from 128 on (30 k
+    // 128 -> 32 1.04, 33 k 0.85, 50 k 1.01, 66 k 0.93; 26 k 64 -> 32 0.93).
+    if (whole || (MD > 32 && blocks > 200)) return 0;
+    if (grid <= 200) return 1;
+    return even ? KD >= 128 && grid <= 512 && (grid <= 256 || grid > 300) : KD >= 96;
 }
 
 }  // namespace

@@ -1,0 +1,34 @@
+"""Which forward products of fp32 features take the kernel with the weights in LDS: host arithmetic on the sizes."""
+import ctypes
+
+import pytest
+
+import paper_2501_01951_amd as mg
+
+
+@pytest.fixture(scope="module")
+def in_lds():
+    f = mg.load_library()._ZN6mixgcn20forward_rows_appliesElii  # mixgcn::forward_rows_applies(n, k, m)
+    f.argtypes, f.restype = [ctypes.c_int64, ctypes.c_int, ctypes.c_int], ctypes.c_bool
+    return f
+
+
+# (rows, depth, columns) at which the tiles of the general kernel measured 5 to 40 % faster: shallow depths, a last step
+# mostly of zeros, a last tile that few wavefronts have, no tile of the general kernel at an edge, workgroups that do not
+# fit the chip at once, column tiles that leave compute units idle
+@pytest.mark.parametrize("n,k,m", [
+    (33_000, 16, 32), (100_000, 47, 24), (66_000, 80, 8), (135_000, 256, 16), (400_000, 256, 4), (1_500_000, 64, 32),
+    (33_000, 128, 32), (4_096, 64, 32), (16_384, 256, 64), (25_600, 256, 128), (12_032, 96, 256), (270_000, 200, 47),
+    (5_000, 256, 602), (16_384, 16, 128), (300, 64, 4096), (1_500, 64, 2048), (1_000, 16, 2048), (267_000, 256, 384),
+    (100_000, 160, 640), (67_000, 128, 1024)])
+def test_sizes_of_the_general_kernel(in_lds, n, k, m):
+    assert not in_lds(n, k, m)
+
+
+@pytest.mark.parametrize("n,k,m", [
+    (1, 64, 1), (10_000, 256, 16), (4_096, 256, 16), (20_000, 602, 32), (100_000, 128, 16), (50_000, 256, 32),
+    (262_144, 256, 16), (20_000, 256, 64), (12_000, 128, 48), (1 << 20, 256, 47), (300_000, 256, 64), (5_000, 602, 128),
+    (20_000, 256, 128), (4_096, 64, 128), (5_000, 16, 128), (1_000, 64, 1500), (16_000, 16, 80), (1 << 18, 128, 256),
+    (1 << 20, 256, 256), (1 << 21, 128, 1024)])
+def test_sizes_with_the_weights_in_lds(in_lds, n, k, m):
+    assert in_lds(n, k, m)
