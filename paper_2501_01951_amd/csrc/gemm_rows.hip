@@ -648,14 +648,9 @@ int launch_rows_tn(bool relu, const RowsArgs& args, hipStream_t s)
         if (relu) MIXGCN_ROWS(true, kNoMask);
         else MIXGCN_ROWS(false, kNoMask);
     } else {
-        if constexpr (DT == MIXGCN_F32) {
-            if (a.R && a.bits.p) {
-                MIXGCN_ROWS(false, kMaskBits);
-                return MIXGCN_OK;
-            }
-        }
-        if (a.R) MIXGCN_ROWS(false, kMaskRef);
-        else MIXGCN_ROWS(false, kNoMask);
+        if (!a.R) MIXGCN_ROWS(false, kNoMask);
+        else if (DT != MIXGCN_F32 || !a.bits.p) MIXGCN_ROWS(false, kMaskRef);
+        else if constexpr (DT == MIXGCN_F32) MIXGCN_ROWS(false, kMaskBits);
     }
 #undef MIXGCN_ROWS
     MIXGCN_HIP_TRY(hipGetLastError());

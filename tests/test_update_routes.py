@@ -1,7 +1,9 @@
-"""Which forward products of fp32 features take the kernel with the weights in LDS: host arithmetic on the sizes."""
+"""Host side of the update products: which forward products of fp32 features take the kernel with the weights in LDS, and
+launches that fail."""
 import ctypes
 
 import pytest
+import torch
 
 import paper_2501_01951_amd as mg
 
@@ -32,3 +34,19 @@ def test_sizes_of_the_general_kernel(in_lds, n, k, m):
     (1 << 20, 256, 256), (1 << 21, 128, 1024)])
 def test_sizes_with_the_weights_in_lds(in_lds, n, k, m):
     assert in_lds(n, k, m)
+
+
+class ReluBits(ctypes.Structure):
+    _fields_ = [("p", ctypes.c_void_p), ("pitch", ctypes.c_int64)]
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="the launches have to fail: no device")
+@pytest.mark.parametrize("k,m", [(256, 256), (32, 512), (64, 512)])
+@pytest.mark.parametrize("ref,bits", [(None, None), (4096, None), (4096, 4096)])
+def test_a_data_gradient_that_is_not_launched_is_an_error(k, m, ref, bits):
+    # mixgcn::launch_update_rows(dtype, w_is_kd_major, relu, A, lda, W, ldw, C, ldc, n, KD, MD, R, ldr, s, bits); nothing
+    # reads the addresses on the host
+    f = mg.load_library()._ZN6mixgcn18launch_update_rowsEibbPKvlPKflPvlliiS1_lP12ihipStream_tNS_8ReluBitsE
+    i, l, v, b = ctypes.c_int, ctypes.c_int64, ctypes.c_void_p, ctypes.c_bool
+    f.argtypes, f.restype = [i, b, b, v, l, v, l, v, l, l, i, i, v, l, v, ReluBits], i
+    assert f(mg.F32, False, False, 4096, m, 4096, m, 4096, k, 32, m, k, ref, m, None, ReluBits(bits, 4 * k)) == -3
