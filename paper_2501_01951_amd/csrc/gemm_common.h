@@ -25,6 +25,21 @@ __device__ inline unsigned xcd_local_index(unsigned bid, unsigned grid)
     return x * q + (x < rem ? x : rem) + bid / 8;
 }
 
+// What a lane reads whose piece of a row lies past the reduction depth (nothing writes it; not const, so that the read
+// stays an ordinary load from a selected address).
+[[maybe_unused]] static __device__ uint4 g_zero_piece = {0u, 0u, 0u, 0u};
+
+// (The address is settled before the load: left to itself the compiler turns a selected address into two loads behind
+// branches, and waits for them where the branches meet.)
+template <class V>
+__device__ inline V load_piece(const char* p)
+{
+    typedef __attribute__((address_space(1))) const V global_piece;
+    uint64_t a = (uint64_t)p;
+    asm("" : "+v"(a));
+    return *(global_piece*)a;
+}
+
 // two fp32 -> two bf16 (round to nearest even, the conversion instruction of this part), first argument
 // in the low half
 __device__ inline uint32_t pack_bf16(float a, float b)

@@ -111,18 +111,9 @@ __device__ inline void split8(const float* x, uint32_t* out)
     }
 }
 
-// What a lane reads whose piece of a row lies past the reduction depth (nothing writes it; not const, so
-// that the read stays an ordinary load from a selected address).
-__device__ uint4 g_zero_piece = {0u, 0u, 0u, 0u};
-
-// (The address is settled before the load: left to itself the compiler turns a selected address into two
-// loads behind branches, and waits for them where the branches meet.)
 __device__ inline uint4 load_from(const char* p)
 {
-    typedef __attribute__((address_space(1))) const uintx4 global_piece;
-    uint64_t a = (uint64_t)p;
-    asm("" : "+v"(a));
-    const uintx4 v = *(global_piece*)a;
+    const uintx4 v = load_piece<uintx4>(p);
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
@@ -623,6 +614,7 @@ int launch_rows_tn(bool relu, const RowsArgs& args, hipStream_t s)
     RowsArgs a = args;
     constexpr int KC = Terms<DT>::KC;
     constexpr int kChunkBytes = TN * Terms<DT>::NB * Terms<DT>::PB * 1024;
+    constexpr bool kBits = DT == MIXGCN_F32 && TN > 1;  // (rows of 16 columns hold no bits of 256)
     const int nch = (a.KD + KC - 1) / KC;
     const bool resident = nch * kChunkBytes <= kRowsLds;
     if (DT == MIXGCN_BF16 && !resident)
@@ -649,8 +641,8 @@ int launch_rows_tn(bool relu, const RowsArgs& args, hipStream_t s)
         else MIXGCN_ROWS(false, kNoMask);
     } else {
         if (!a.R) MIXGCN_ROWS(false, kNoMask);
-        else if (DT != MIXGCN_F32 || !a.bits.p) MIXGCN_ROWS(false, kMaskRef);
-        else if constexpr (DT == MIXGCN_F32) MIXGCN_ROWS(false, kMaskBits);
+        else if (!kBits || !a.bits.p) MIXGCN_ROWS(false, kMaskRef);
+        else if constexpr (kBits) MIXGCN_ROWS(false, kMaskBits);
     }
 #undef MIXGCN_ROWS
     MIXGCN_HIP_TRY(hipGetLastError());

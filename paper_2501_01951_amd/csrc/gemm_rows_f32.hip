@@ -26,7 +26,6 @@ namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) floatx4 lds_floatx4;
 
 constexpr int KC = 16;         // reduction indices per step: 64 bytes of a row
@@ -52,20 +51,6 @@ struct ForwardArgs {
     int n_col_tiles, row_groups;
     int waves;  // wavefronts of a workgroup that walk rows; all load the weights
 };
-
-// What a lane reads whose piece of a row lies past the reduction depth (nothing writes it; not const, so that the
-// read stays an ordinary load from a selected address).
-__device__ uint4 g_zero_quad = {0u, 0u, 0u, 0u};
-
-// (The address is settled before the load: left to itself the compiler turns a selected address into two loads
-// behind branches.)
-__device__ inline floatx4 load_quad(const char* p)
-{
-    typedef __attribute__((address_space(1))) const floatx4 global_quad;
-    uint64_t a = (uint64_t)p;
-    asm("" : "+v"(a));
-    return *(global_quad*)a;
-}
 
 // x: its odd groups of 16 lanes exchanged with the even ones of y
 __device__ inline void swap16(float& x, float& y)
@@ -127,14 +112,14 @@ void forward_rows_kernel(ForwardArgs p)
         }
     };
     const int whole = p.KD / KC;  // steps wholly inside the depth
-    const char* zero = reinterpret_cast<const char*>(&g_zero_quad);
+    const char* zero = reinterpret_cast<const char*>(&g_zero_piece);
     asm("" : "+s"(zero));  // (not looked up again in every step)
     auto load = [&](Rows& x) {
         const char* from[2] = {arow[0] + lc * (KC * 4), arow[1] + lc * (KC * 4)};
         if (lc >= whole && lc * KC + 4 * g >= p.KD)
             from[0] = from[1] = zero;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) x.a[h] = load_quad(from[h]);
+        for (int h = 0; h < 2; ++h) x.a[h] = load_piece<floatx4>(from[h]);
         if (++lc == nch) {
             lc = 0;
             lt += stride;

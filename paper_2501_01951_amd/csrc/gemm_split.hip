@@ -340,6 +340,7 @@ int launch_wgrad_split(const float* A, int64_t lda, const float* B, int64_t ldb,
     if (rows_per_slab < BKS) rows_per_slab = BKS;
     n_slabs = n > 0 ? ceil_div(n, rows_per_slab) : 1;  // without rows: one slab of zeros
     const bool far = lda >= (1 << 22) || ldb >= (1 << 22) || (R && ldr >= (1 << 22));
+    if (bits.p && (!R || far || bn < 128)) return fail(MIXGCN_EINVAL, "update: mask bits");
     const int64_t cells = (int64_t)k * m;
     void* scratch = nullptr;
     MIXGCN_TRY(get_scratch(0, (size_t)n_slabs * cells * sizeof(float), &scratch));
@@ -351,13 +352,13 @@ int launch_wgrad_split(const float* A, int64_t lda, const float* B, int64_t ldb,
                        ldr, P, k, m, rows_per_slab, n, nit, njt, bits)
 #define MIXGCN_WGRAD_MASK(BN)                                            \
     do {                                                                 \
-        if (R && bits.p && !far) MIXGCN_WGRAD(BN, true, false, true);    \
-        else if (R && far) MIXGCN_WGRAD(BN, true, true, false);          \
+        if (R && far) MIXGCN_WGRAD(BN, true, true, false);               \
         else if (R) MIXGCN_WGRAD(BN, true, false, false);                \
         else if (far) MIXGCN_WGRAD(BN, false, true, false);              \
         else MIXGCN_WGRAD(BN, false, false, false);                      \
     } while (0)
-    if (bn == 128) MIXGCN_WGRAD_MASK(128);
+    if (bits.p) MIXGCN_WGRAD(128, true, false, true);
+    else if (bn == 128) MIXGCN_WGRAD_MASK(128);
     else if (bn == 64) MIXGCN_WGRAD_MASK(64);
     else MIXGCN_WGRAD_MASK(32);
 #undef MIXGCN_WGRAD_MASK
