@@ -285,6 +285,8 @@ int mixgcn_apply_bitmap(int dtype, void* X, int64_t ldx, int64_t n_rows, int32_t
  *   relu_ref   : R, the stored layer output H' whose sign gives the ReLU derivative
  *                (1[R > 0], 0 at 0); NULL = no mask.  Only DGRAD and WGRAD read it.
  *   beta       : WGRAD only, 0 or 1.
+ * C must not overlap A, B or R, with one exception: FWD and FWD_RELU of fp32 features under MIXGCN_ARITH_FP32 may be
+ * written over A (the same pointer and pitch) where m <= 128.  A and C may be column blocks of one buffer.
  * FWD, FWD_RELU, DGRAD: B is the weight matrix W[k x m], fp32, row-major.  WGRAD: A = Z
  * [n x k], B = the upstream gradient [n x m], C = dW [k x m] fp32.
  * The forward product of fp32 features is a chain of fp32 multiply-adds over the reduction index, on the

@@ -514,17 +514,24 @@ int launch_rowblock(bool relu, const float* A, int64_t lda, const float* B, int6
     return MIXGCN_OK;
 }
 
+// Whether C holds other columns than A of the rows of one buffer.
+bool column_blocks(const float* A, int64_t lda, int32_t k, const float* C, int64_t ldc, int32_t m)
+{
+    const int64_t off = ((intptr_t)C - (intptr_t)A) / (int64_t)sizeof(float) % lda, col = off < 0 ? off + lda : off;
+    return lda == ldc && col >= k && col + m <= lda;
+}
+
 // C[n x m] = act(A[n x k] W[k x m])
 int forward_f32(bool relu, const float* A, int64_t lda, const float* W, int64_t ldw, float* C, int64_t ldc,
                 int64_t n, int32_t k, int32_t m, hipStream_t s)
 {
-    // (a product written over its features has to read all of a row's before any of its sums are written, which several
-    // narrow column tiles do not)
-    const bool apart = (const float*)C + n * ldc <= A || A + n * lda <= C;
+    // A product written over its features has to read all of a row's before any of its sums are written: one column
+    // tile, of up to 128 columns, by a workgroup that reads its own rows alone.
+    const bool apart = C + n * ldc <= A || A + n * lda <= C || column_blocks(A, lda, k, C, ldc, m);
     if (apart && forward_rows_applies(n, k, m))
         return launch_forward_rows(relu, A, lda, W, ldw, C, ldc, n, k, m, s);
-    return m > 64 ? launch_rowblock<Shape128x128>(relu, A, lda, W, ldw, C, ldc, n, k, m, s)
-                  : launch_rowblock<Shape128x32>(relu, A, lda, W, ldw, C, ldc, n, k, m, s);
+    return m > (apart ? 64 : 32) ? launch_rowblock<Shape128x128>(relu, A, lda, W, ldw, C, ldc, n, k, m, s)
+                                 : launch_rowblock<Shape128x32>(relu, A, lda, W, ldw, C, ldc, n, k, m, s);
 }
 
 int shallow_dgrad(const float* G, int64_t ldg, const float* W, int64_t ldw, float* Z, int64_t ldz, int64_t n, int32_t k,

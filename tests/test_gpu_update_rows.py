@@ -431,13 +431,27 @@ def test_bf16_weight_gradient_of_any_number_of_rows(mg, n, k, m):
             assert ((dw.double() - (1 + beta) * want).abs() <= (1 + 2 * beta) * bound + 1e-30).all()
 
 
-@pytest.mark.parametrize("n,k", [(5000, 128), (20003, 100), (300, 32)])
+@pytest.mark.parametrize("n,k", [(5000, 128), (20003, 100), (300, 32), (5000, 48), (20003, 64), (8192, 64), (300, 33)])
 def test_fp32_forward_written_over_its_features(mg, n, k):
     """Up to 128 columns a row's features are all read before its sums are written, whatever the number of rows."""
     gen = torch.Generator(device="cuda").manual_seed(n)
     z = padded(n, k, torch.float32, gen)
-    w = torch.randn(k, k, device="cuda", generator=gen)
-    out = torch.empty(n, k, device="cuda")
-    mg.update(mg.OP_FWD_RELU, z[:, :k], w, out, n, k, k)
+    w = torch.randn(k, (k + 3) // 4 * 4, device="cuda", generator=gen)[:, :k]
+    out = padded(n, k, torch.float32, gen)
+    mg.update(mg.OP_FWD_RELU, z[:, :k], w, out[:, :k], n, k, k)
     mg.update(mg.OP_FWD_RELU, z[:, :k], w, z[:, :k], n, k, k)
-    assert torch.equal(z[:, :k], out)
+    assert torch.equal(z[:, :k], out[:, :k])
+
+
+@pytest.mark.parametrize("n,k,m", [(5000, 128, 64), (20003, 100, 256), (300, 37, 47), (8192, 64, 32)])
+@pytest.mark.parametrize("left", [False, True])
+def test_fp32_forward_into_other_columns_of_its_buffer(mg, n, k, m, left):
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    wide = [(c + 3) // 4 * 4 for c in (k, m)]
+    both = torch.randn(n, sum(wide), device="cuda", generator=gen)
+    z, c = (both[:, wide[1]:][:, :k], both[:, :m]) if left else (both[:, :k], both[:, wide[0]:][:, :m])
+    w = torch.randn(k, wide[1], device="cuda", generator=gen)[:, :m]
+    out, before = padded(n, m, torch.float32, gen), z.clone()
+    mg.update(mg.OP_FWD, z, w, out[:, :m], n, k, m)
+    mg.update(mg.OP_FWD, z, w, c, n, k, m)
+    assert torch.equal(c, out[:, :m]) and torch.equal(z, before)
