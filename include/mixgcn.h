@@ -403,8 +403,9 @@ int mixgcn_graph_info(const mixgcn_graph* g, mixgcn_graph_view* out);
 int mixgcn_graph_free(mixgcn_graph* g);
 /*
  * Device memory of freed graphs and of the work arrays of mixgcn_build_csr and mixgcn_reorder_rcm stays
- * cached for the next such call, up to 4 GiB per device.  It goes back to the driver where an allocation
- * of the library itself finds no memory, and all of it with mixgcn_release_memory, which a program calls
+ * cached for the next such call, up to 4 GiB per device, and so does pinned host memory of freed graphs (8 bytes per
+ * node), up to 512 MiB per process.  Device memory goes back to the driver where an allocation
+ * of the library itself finds none, and all of both with mixgcn_release_memory, which a program calls
  * before it allocates the last gigabytes of a device elsewhere.  Thread safe.
  */
 int mixgcn_release_memory(void);

@@ -1,5 +1,6 @@
 """Reuse of the memory of freed graphs and finished builds: blocks pass between sizes, streams and
 threads, and the results are those of first builds."""
+import ctypes
 import threading
 
 import numpy as np
@@ -232,3 +233,64 @@ def test_values_of_rows_between_empty_ones(mode, first, last, n):
                 "mean": (1 / deg.double()).float()[col if transpose else row]}[mode]
         assert torch.equal(a["val"], want)
     g.free()
+
+
+@pytest.fixture
+def host_memory():
+    """mixgcn::host_alloc and host_free, and whether an address is pinned host memory."""
+    import paper_2501_01951_amd as mg
+
+    lib = mg.load_library()
+    alloc, free = lib._ZN6mixgcn10host_allocEPPvm, lib._ZN6mixgcn9host_freeEPv
+    alloc.argtypes, free.argtypes, free.restype = [ctypes.c_void_p, ctypes.c_size_t], [ctypes.c_void_p], None
+    with open("/proc/self/maps") as maps:
+        runtime = ctypes.CDLL(next(line.split()[-1] for line in maps if "libamdhip64" in line))
+
+    def take(size):
+        p = ctypes.c_void_p()
+        assert alloc(ctypes.byref(p), size) == 0
+        return p
+
+    def pinned(p):
+        attr = (ctypes.c_int * 64)()  # the memory type comes first; 1 is host memory
+        ok = runtime.hipPointerGetAttributes(attr, p) == 0 and attr[0] == 1
+        runtime.hipGetLastError()
+        return ok
+
+    mg.release_memory()
+    yield take, free, pinned
+    mg.release_memory()
+
+
+def test_pinned_memory_that_is_too_large_to_keep(host_memory):
+    """A block above the bound of 512 MB goes back alone; others leave when they are together more, the oldest first."""
+    take, free, pinned = host_memory
+    blocks = [take(size << 20) for size in (8, 300, 9, 600, 300)]
+    assert all(pinned(p) for p in blocks)
+    for p in blocks[:4]:
+        free(p)
+    assert [pinned(p) for p in blocks[:4]] == [True, True, True, False]
+    free(blocks[4])
+    assert [pinned(p) for p in blocks] == [False, False, True, False, True]
+    assert take(9 << 20).value == blocks[2].value
+    free(blocks[2])
+
+
+@pytest.mark.parametrize("thread", [False, True])
+def test_pinned_memory_goes_back_while_a_stream_is_captured(host_memory, thread):
+    """Freeing a graph is allowed then in every mode of capture: a release that the runtime refuses would end it."""
+    take, free, pinned = host_memory
+    large, x = take(600 << 20), torch.zeros(8, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, capture_error_mode="global"):
+        x.add_(1)
+        if thread:
+            t = threading.Thread(target=free, args=(large,))
+            t.start()
+            t.join()
+        else:
+            free(large)
+    for _ in range(3):
+        graph.replay()
+    assert (x == 3).all() and not pinned(large)
