@@ -1,6 +1,8 @@
 """The update products (forward, data gradient, fp32 weight gradient) at the edges of their kernels: 32-row tiles, reduction steps
 of 128 bytes of a row, weights that stay in LDS and weights that stream through it, output tiles of 16, 32,
 64 and 128 columns; what rows hold past their columns, infinities and NaN."""
+import ctypes
+
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -39,23 +41,38 @@ def check(got, a, w, dtype, steps, what):
 
 
 def chain(a, w):
-    """Multiply-adds of fp32 in the order of the reduction index: a product of two floats is exact in 64 bits."""
+    """Multiply-adds of fp32 in the order of the reduction index.  A product of two floats is exact in 64 bits; the sum is
+    rounded to odd there (what it loses, exactly, says which way), so that rounding it once more is rounding it once."""
     s = torch.zeros(a.shape[0], w.shape[1], device="cuda")
     for k in range(a.shape[1]):
-        s = (a[:, k:k + 1].double() * w[k:k + 1].double() + s.double()).float()
+        p, q = a[:, k:k + 1].double() * w[k:k + 1].double(), s.double()
+        t = p + q
+        lost = (p - (t - (t - p))) + (q - (t - p))
+        bits = t.view(torch.int64)
+        even = (bits & 1 == 0) & ((lost > 0) | (lost < 0))  # (not a NaN)
+        s = torch.where(even, bits + torch.where((lost > 0) == (t > 0), 1, -1), bits).view(torch.float64).float()
     return s
 
 
-# around tiles of 128 rows, 32 and 128 columns and steps of 16: tiles inside the matrices and tiles at their edges
-@pytest.mark.parametrize("n,k,m", [(1, 1, 1), (128, 16, 32), (129, 15, 33), (256, 64, 128), (300, 100, 64),
-                                   (255, 128, 65), (384, 256, 256), (260, 602, 129),
-                                   # weights in LDS: the deepest and the next ones of 32 columns, column tiles of 64
-                                   # with rows and columns left over, tiles of 128 (32 of them), 47 columns
-                                   (70, 1280, 31), (70, 1281, 31), (20003, 37, 250), (16397, 160, 4001),
-                                   (262150, 200, 47)])
-def test_fp32_forward_sums_are_the_fp32_chain(mg, n, k, m):
+# The general kernel: tiles of 128 rows, 32 and 128 columns and steps of 16, inside the matrices and at their edges; every
+# tile inside (its fast path) alone, and beside others of the last rows.
+GENERAL = [(1, 1, 1), (128, 16, 32), (129, 15, 33), (300, 100, 64), (70, 1281, 31), (20003, 37, 250), (4096, 64, 32),
+           (33000, 64, 64), (16512, 64, 256), (33000, 128, 256), (262150, 200, 47), (16397, 160, 4001)]
+# The weights in LDS.  Column tiles of 32: below, at and past a tile of 32 rows and a step of 32 indices, the deepest,
+# several column tiles, the last one whole or not, two rounds of workgroups, two tiles to a wavefront; of 64, whole and
+# not, rows left over; of 128, 32 of them, rows and columns left over
+IN_LDS = [(1, 64, 1), (256, 64, 128), (255, 128, 65), (384, 256, 256), (260, 602, 129), (70, 1280, 31), (4000, 96, 40),
+          (12000, 70, 120), (300, 64, 1500), (262144, 64, 31), (262144, 192, 64), (300010, 200, 47), (17900, 160, 4001),
+          (131072, 128, 512)]
+
+
+@pytest.mark.parametrize("n,k,m,in_lds", [(*c, False) for c in GENERAL] + [(*c, True) for c in IN_LDS])
+def test_fp32_forward_sums_are_the_fp32_chain(mg, n, k, m, in_lds):
     """Bit for bit: the sums of a forward product decide the sign of an activation, so they keep their
     rounding from release to release."""
+    applies = mg.load_library()._ZN6mixgcn20forward_rows_appliesElii
+    applies.argtypes, applies.restype = [ctypes.c_int64, ctypes.c_int, ctypes.c_int], ctypes.c_bool
+    assert applies(n, k, m) == in_lds
     gen = torch.Generator(device="cuda").manual_seed(n + k)
     z = padded(n, k, torch.float32, gen)
     w = torch.randn(k, (m + 3) // 4 * 4 + 4, device="cuda", generator=gen)[:, :m]
@@ -386,24 +403,39 @@ def test_the_relu_derivative_of_nan_is_zero(mg, dtype, n, k, m):
 @pytest.mark.parametrize("n,k,m,share", [
     (1, 128, 512, "nothing"), (31, 132, 601, "nothing"), (1000, 256, 256, "nothing"), (5000, 300, 259, "nothing"),
     (2500, 128, 1030, "nothing"), (700, 20, 512, "nothing"), (700, 32, 513, "nothing"), (3000, 128, 128, "nothing"),
-    (1000, 256, 256, "dH over G"), (1000, 256, 256, "dH over Hout"), (3000, 128, 128, "dH over G")])
-def test_layer_backward_is_its_two_products_and_the_aggregation(mg, n, k, m, share):
+    (1000, 256, 256, "dH over G"), (1000, 256, 256, "dH over Hout"), (3000, 128, 128, "dH over G"),
+    (1000, 256, 259, "columns beside Z"), (1000, 300, 256, "columns beside G"), (1000, 256, 256, "columns beside Hout"),
+    (700, 32, 513, "columns beside Hout")])
+@pytest.mark.parametrize("streams", [1, 2])
+def test_layer_backward_is_its_two_products_and_the_aggregation(mg, n, k, m, share, streams):
     gen = torch.Generator(device="cuda").manual_seed(n + k + m)
     ends = [torch.randint(0, n, (3 * n,), device="cuda", dtype=torch.int32, generator=gen) for _ in range(2)]
     g = mg.build_csr(*ends, n)
     mg.normalize(g)
-    z, hout, grad = padded(n, k, torch.float32, gen), padded(n, m, torch.float32, gen), padded(n, m, torch.float32, gen)
+
+    def features(cols, *names):
+        """A buffer of its own, or one with the columns of dH before them (the pitch of G is that of Hout)."""
+        extra = (k + 3) // 4 * 4 if share in [f"columns beside {x}" for x in names] else 0
+        t = padded(n, extra + cols, torch.float32, gen)
+        return t[:, extra:], t[:, :extra]
+
+    (z, by_z), (hout, by_hout), (grad, by_g) = features(k, "Z"), features(m, "Hout", "G"), features(m, "Hout", "G")
     hout[:, :m].clamp_(min=0)
     hout[0, 0], hout[-1, m - 1] = float("nan"), float("inf")
     w = torch.randn(k, (m + 3) // 4 * 4, device="cuda", generator=gen)[:, :m]
     dw, want_dw = torch.empty_strided(w.shape, w.stride(), device="cuda"), torch.empty_strided(w.shape, w.stride(), device="cuda")
-    want_z, want_dh = z.clone(), torch.full_like(z, 7.0)
+    want_z, want_dh = z.clone(), torch.full((n, (k + 3) // 4 * 4), 7.0, device="cuda")
     mg.update(mg.OP_WGRAD, z[:, :k], grad[:, :m], want_dw, n, k, m, relu_ref=hout[:, :m])
     mg.update(mg.OP_DGRAD, grad[:, :m], w, want_z[:, :k], n, k, m, relu_ref=hout[:, :m])
     mg.aggregate(g, want_z[:, :k], want_dh[:, :k], transpose=True)
-    dh = {"nothing": torch.full_like(z, 7.0), "dH over G": grad, "dH over Hout": hout}[share]
+    dh = {"nothing": torch.full_like(z, 7.0), "dH over G": grad, "dH over Hout": hout, "columns beside Z": by_z,
+          "columns beside Hout": by_hout, "columns beside G": by_g}[share]
     past = dh[:, k:].clone()
-    mg.layer_bwd(g, z[:, :k], hout[:, :m], w, grad[:, :m], dw, dh[:, :k], mg.Pipeline(), relu=True)
+    side = (torch.cuda.Stream(), torch.cuda.Stream())
+    pipe = mg.Pipeline() if streams == 1 else mg.Pipeline(*side)
+    torch.cuda.synchronize()
+    mg.layer_bwd(g, z[:, :k], hout[:, :m], w, grad[:, :m], dw, dh[:, :k], pipe, relu=True, n_chunks=streams)
+    torch.cuda.synchronize()
     same = lambda a, b: torch.equal(a.contiguous().view(torch.int32), b.contiguous().view(torch.int32))
     assert same(dw, want_dw) and same(z[:, :k], want_z[:, :k]) and same(dh[:, :k], want_dh[:, :k])
     assert same(dh[:, k:], past)
