@@ -214,18 +214,14 @@ int mixgcn_build_csr(const uint32_t* src, const uint32_t* dst, uint64_t n_edges,
         g->n = n_nodes;
         g->flags = flags;
         rc = csr_from_edges(use_src, use_dst, n_edges, n_nodes, sym, loops, false, &g->fwd, s);
-        if (rc == MIXGCN_OK)
-            rc = sym ? rowgroups_build(g->fwd, n_nodes, &g->fwd.groups, s) : csr_copy_rowptr(g->fwd, n_nodes, s);
+        if (rc == MIXGCN_OK && sym) rc = rowgroups_build(g->fwd, n_nodes, &g->fwd.groups, s);
         if (rc != MIXGCN_OK) break;
         if ((flags & MIXGCN_BUILD_TRANSPOSE) && !sym) {
             rc = csr_from_edges(use_src, use_dst, n_edges, n_nodes, false, loops, true, &g->tr, s);
-            if (rc == MIXGCN_OK) rc = csr_copy_rowptr(g->tr, n_nodes, s);
             if (rc != MIXGCN_OK) break;
             g->has_transpose = true;
         }
     } while (0);
-    // the host copies of the row pointers
-    if (hipStreamSynchronize(s) != hipSuccess && rc == MIXGCN_OK) rc = fail(MIXGCN_EHIP, "build_csr: row pointers");
     pool_free_on(d_src, s);
     pool_free_on(d_dst, s);
     if (rc != MIXGCN_OK) {

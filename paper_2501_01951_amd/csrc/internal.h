@@ -211,6 +211,8 @@ void csr_free(Csr* c);
 int csr_copy_rowptr(const Csr& c, uint32_t n, hipStream_t s);
 int normalize_graph(mixgcn_graph* g, int mode, float eps, hipStream_t s);
 
+// Whether the bands of a matrix with a symmetric pattern are planned: it is large and dense enough for them to pay.
+bool rowgroups_planned(uint32_t n, int64_t nnz);
 int rowgroups_build(const Csr& m, uint32_t n, RowGroups* out, hipStream_t s);
 int rowgroups_alloc_transpose(RowGroups* g, hipStream_t s);
 int rowgroups_fill(const Csr& m, const RowGroups& g, const float* dinv, int mode, float eps,

@@ -967,22 +967,29 @@ int build_bands(const Csr& m, uint32_t n, RowGroups* out, hipStream_t s)
 
 }  // namespace
 
+bool rowgroups_planned(uint32_t n, int64_t nnz)
+{
+    return n > (uint32_t)kBandColumns && n < kRowMask && nnz >= 2 * kBandRow * (int64_t)n && nnz <= kMostEntries;
+}
+
 // The bands and groups of a matrix with a symmetric pattern (row lengths are then the popularities of
 // the columns): everything that depends on the pattern only.  None where they cannot pay, and where
-// there is no memory for them.  Queues the host copy of the row pointers too, and waits for the stream where there
-// was anything to plan.
+// there is no memory for them.  Where they are planned it copies the row pointers to the host meanwhile, and waits for
+// the stream.
 int rowgroups_build(const Csr& m, uint32_t n, RowGroups* out, hipStream_t s)
 {
-    if (n <= (uint32_t)kBandColumns || n >= kRowMask || m.nnz < 2 * kBandRow * (int64_t)n || m.nnz > kMostEntries)
-        return csr_copy_rowptr(m, n, s);
+    if (!rowgroups_planned(n, m.nnz)) return MIXGCN_OK;
     RowGroups g;
     int rc = build_bands(m, n, &g, s);
     if (rc == MIXGCN_OK && hipStreamSynchronize(s) != hipSuccess) rc = fail(MIXGCN_EHIP, "bands of the columns");
     if (rc != MIXGCN_OK) {
         (void)hipStreamSynchronize(s);  // the arrays may have work queued on them
         rowgroups_free(&g);
-        if (rc == MIXGCN_ENOMEM) (void)hipGetLastError();
-        return rc == MIXGCN_ENOMEM ? csr_copy_rowptr(m, n, s) : rc;  // (the copy may have been queued or not)
+        if (rc != MIXGCN_ENOMEM) return rc;
+        (void)hipGetLastError();
+        MIXGCN_TRY(csr_copy_rowptr(m, n, s));  // (it may have been queued or not)
+        MIXGCN_HIP_TRY(hipStreamSynchronize(s));
+        return MIXGCN_OK;
     }
     *out = std::move(g);
     return MIXGCN_OK;
