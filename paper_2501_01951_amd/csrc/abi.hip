@@ -759,11 +759,9 @@ int mixgcn_layer_bwd(const mixgcn_graph* g, const mixgcn_layer_desc* d, const vo
     }
     // The rows of dH, which nothing holds before the transposed aggregation writes it, take the ReLU derivative as bits
     // from the weight to the data gradient, which then reads a sixteenth of Hout.  Not where dH shares memory with what
-    // is still to be read, nor for narrow layers, where making the bits costs more (both gradients and the aggregation
-    // of one entry per row, us, Hout read twice : bits; 2^21 rows 128 -> 1024 8800 : 8310, 2^20 256 -> 256 2510 : 2450,
-    // 20 k 128 -> 512 128 : 125; 2^18 128 -> 256 373 : 379, 300 k 256 -> 33 401 : 421).
+    // is still to be read.
     ReluBits bits;
-    if (R && dH && d->dtype == MIXGCN_F32 && (d->f_out >= 512 || (d->f_out >= 256 && d->f_in >= 256)) &&
+    if (R && dH && d->dtype == MIXGCN_F32 && relu_bits_pay(n, d->f_in, d->f_out) &&
         relu_bits_row(d->f_out) <= (int64_t)d->f_in * 4 &&
         relu_bits_apply(d->ld_z, d->ld_out, d->ld_out, d->ld_h * 4) &&
         check_matrix("layer_bwd: dH", dH, d->ld_h, d->f_in, 4) == MIXGCN_OK) {

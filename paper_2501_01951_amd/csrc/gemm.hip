@@ -584,6 +584,19 @@ int launch_wgrad_reduce(const float* P, int64_t n_slabs, int64_t cells, int32_t 
     return MIXGCN_OK;
 }
 
+// Making the bits costs the weight gradient a twentieth; the data gradient gains where its column tiles are full and it
+// waits for memory.  Times as fast with bits as with Hout read twice, both gradients and an aggregation of three entries
+// per row: 128 -> 1024 1.06 of 2500 rows, 1.05 of 100 k, 1.00 of 10^6 (2^21 rows 8800 -> 8310 us); 64 -> 768 1.09, 1.06,
+// 1.05; 256 -> 512 1.03, 1.04, 1.03; 32 -> 512 1.01, 1.10, 1.11.  96 -> 640 1.03, 1.03, 0.97.  Fewer or uneven columns,
+// 256 -> 256 0.99, 1.03, 1.01, 384 -> 600 1.01, 1.04, 1.02 (0.98 of 20 k); column tiles that are not full, 320 -> 600
+// 0.98, 1.00, 0.99, 192 -> 768 1.00, 1.01, 1.00 (0.98 of 20 k), 48 -> 600 1.02, 0.98, 0.94.
+bool relu_bits_pay(int64_t n, int32_t k, int32_t m)
+{
+    const bool full = k == 32 || k == 64 || k % 128 == 0;
+    if (m >= 512 && m % 128 == 0) return full || (k > 64 && k < 128 && n < (1 << 19));
+    return m >= 256 && k >= 256 && full && n >= (1 << 16);
+}
+
 int launch_update(int op, int dtype, const void* A, int64_t lda, const void* B, int64_t ldb,
                   void* C, int64_t ldc, int64_t n, int32_t k, int32_t m, const void* R,
                   int64_t ldr, float beta, hipStream_t s, Timer* timer, ReluBits bits)

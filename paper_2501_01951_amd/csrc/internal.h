@@ -269,6 +269,8 @@ inline bool relu_bits_apply(int64_t lda, int64_t ldb, int64_t ldr, int64_t pitch
 {
     return lda < (1 << 22) && ldb < (1 << 22) && ldr < (1 << 22) && pitch < (1 << 26);
 }
+// whether a layer's backward pass of fp32 features is faster with them (k -> m columns)
+bool relu_bits_pay(int64_t n, int32_t k, int32_t m);
 int launch_update(int op, int dtype, const void* A, int64_t lda, const void* B, int64_t ldb,
                   void* C, int64_t ldc, int64_t n, int32_t k, int32_t m, const void* R,
                   int64_t ldr, float beta, hipStream_t s, Timer* timer, ReluBits bits);

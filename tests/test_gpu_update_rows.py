@@ -397,17 +397,26 @@ def test_the_relu_derivative_of_nan_is_zero(mg, dtype, n, k, m):
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
 
 
-# layers whose backward pass hands the ReLU derivative on as bits (512 columns, or 256 of both), widths that are no
-# multiple of 4 or 32, several column tiles and row tiles of the weight gradient, rows that fill no step or slab; too few
-# columns of dH for the bits; narrower layers
-@pytest.mark.parametrize("n,k,m,share", [
-    (1, 128, 512, "nothing"), (31, 132, 601, "nothing"), (1000, 256, 256, "nothing"), (5000, 300, 259, "nothing"),
-    (2500, 128, 1030, "nothing"), (700, 20, 512, "nothing"), (700, 32, 513, "nothing"), (3000, 128, 128, "nothing"),
-    (1000, 256, 256, "dH over G"), (1000, 256, 256, "dH over Hout"), (3000, 128, 128, "dH over G"),
-    (1000, 256, 259, "columns beside Z"), (1000, 300, 256, "columns beside G"), (1000, 256, 256, "columns beside Hout"),
-    (700, 32, 513, "columns beside Hout")])
+# layers whose backward pass hands the ReLU derivative on as bits: rows that fill no step or slab, several column and row
+# tiles of the weight gradient, widths that are no multiple of 4 or 32, memory that dH shares; and layers that read the
+# derivative twice
+BITS = [(1, 128, 512, "nothing"), (31, 100, 640, "nothing"), (2500, 128, 1024, "nothing"), (700, 32, 512, "nothing"),
+        (1000, 256, 512, "nothing"), (65537, 256, 259, "nothing"), (65600, 384, 601, "nothing"),
+        (1000, 256, 512, "dH over Hout"), (1000, 512, 512, "dH over G"), (1000, 256, 512, "columns beside Z"),
+        (1000, 384, 512, "columns beside G"), (1000, 256, 640, "columns beside Hout"),
+        (700, 32, 512, "columns beside Hout")]
+NO_BITS = [(31, 132, 601, "nothing"), (1000, 256, 256, "nothing"), (5000, 300, 259, "nothing"),
+           (2500, 128, 1030, "nothing"), (700, 20, 512, "nothing"), (700, 32, 513, "nothing"), (3000, 128, 128, "nothing"),
+           (1000, 256, 256, "dH over G"), (1000, 256, 256, "dH over Hout"), (3000, 128, 128, "dH over G"),
+           (1000, 300, 256, "columns beside G")]
+
+
+@pytest.mark.parametrize("n,k,m,share,bits", [(*c, True) for c in BITS] + [(*c, False) for c in NO_BITS])
 @pytest.mark.parametrize("streams", [1, 2])
-def test_layer_backward_is_its_two_products_and_the_aggregation(mg, n, k, m, share, streams):
+def test_layer_backward_is_its_two_products_and_the_aggregation(mg, n, k, m, share, bits, streams):
+    pay = mg.load_library()._ZN6mixgcn13relu_bits_payElii
+    pay.argtypes, pay.restype = [ctypes.c_int64, ctypes.c_int, ctypes.c_int], ctypes.c_bool
+    assert pay(n, k, m) == bits
     gen = torch.Generator(device="cuda").manual_seed(n + k + m)
     ends = [torch.randint(0, n, (3 * n,), device="cuda", dtype=torch.int32, generator=gen) for _ in range(2)]
     g = mg.build_csr(*ends, n)

@@ -36,6 +36,15 @@ def test_sizes_with_the_weights_in_lds(in_lds, n, k, m):
     assert in_lds(n, k, m)
 
 
+# (rows, input columns, output columns) at which reading the activations twice measured 2 to 6 % faster
+@pytest.mark.parametrize("n,k,m", [(20_000, 300, 400), (20_000, 200, 600), (1_000_000, 48, 600), (20_000, 256, 256),
+                                   (20_000, 192, 768), (1_000_000, 96, 640), (1_000_000, 128, 600)])
+def test_layers_that_read_the_relu_derivative_twice(n, k, m):
+    f = mg.load_library()._ZN6mixgcn13relu_bits_payElii  # mixgcn::relu_bits_pay(n, k, m)
+    f.argtypes, f.restype = [ctypes.c_int64, ctypes.c_int, ctypes.c_int], ctypes.c_bool
+    assert not f(n, k, m) and f(n, 128, 1024)
+
+
 class ReluBits(ctypes.Structure):
     _fields_ = [("p", ctypes.c_void_p), ("pitch", ctypes.c_int64)]
 
