@@ -187,7 +187,8 @@ __global__ __launch_bounds__(kBlock) void degree_kernel(const int64_t* __restric
 // One thread per stored entry, a block per group of kGroupNnz: the row of an entry is one of those that the group
 // covers, so the search starts from a handful of row pointers that the block has in its L1 (over all of them it took
 // most of the time).  Four groups per block, so that the columns and scales of four entries are on their way together.
-// What is left are the gathers of dinv.  33.0 M entries of 2^20 rows: 656 -> 225 us; without the hints, with which the streams leave the L2s to dinv, 279.
+// What is left are the gathers of dinv.  33.0 M entries of 2^20 rows: 656 -> 225 us; without the hints, with which the
+// streams leave the L2s to dinv, 279.
 constexpr int kValueGroups = 4;
 static_assert(kGroupNnz == kBlock, "a thread per entry of a group");
 __global__ __launch_bounds__(kBlock) void values_kernel(const int64_t* __restrict__ rowptr,

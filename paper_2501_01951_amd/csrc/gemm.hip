@@ -1,7 +1,7 @@
 // Dispatch of the update products (paper Algorithm 2, update phase), the forward product H' = sigma(Z W) of
-// fp32 features on the fp32 matrix cores (v_mfma_f32_32x32x2_f32) where gemm_rows_f32.hip does not take it, and the reduction of the slabs of a weight
-// gradient.  A row-block kernel's workgroup owns 128 node rows: the node dimension is the long one, the
-// feature dimensions are at most a few hundred.
+// fp32 features on the fp32 matrix cores (v_mfma_f32_32x32x2_f32) where gemm_rows_f32.hip does not take it, and the
+// reduction of the slabs of a weight gradient.  A row-block kernel's workgroup owns 128 node rows: the node dimension
+// is the long one, the feature dimensions are at most a few hundred.
 //
 // The sums of the forward product are chains of fp32 multiply-adds over the reduction index, bit for bit.
 // They decide which side of zero an activation falls on, so they keep this rounding: with another one

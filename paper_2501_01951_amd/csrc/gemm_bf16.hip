@@ -144,8 +144,8 @@ __global__ __launch_bounds__(kBlock) void wgrad_bf16_kernel(
 // reads are one MFMA operand.  Two groups are served per cycle from 64 banks (four rows of 64
 // bytes): a row pitch of 64 bytes modulo 256 keeps them apart.  Rows come in whole steps of 32; the last n % 32
 // rows are a slab of their own with one step, whose other rows are zeros (the kernel above in a launch of its own took
-// 6 us for them: a weight gradient of 100003 rows 128 x 128 25 -> 19.6 us, 128 x 16 17 -> 13).  Features beyond the matrices are zeroed with per-thread
-// masks that do not change from step to step.
+// 6 us for them: a weight gradient of 100003 rows 128 x 128 25 -> 19.6 us, 128 x 16 17 -> 13).  Features beyond the
+// matrices are zeroed with per-thread masks that do not change from step to step.
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 typedef short shortx8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) shortx4 lds_shortx4;

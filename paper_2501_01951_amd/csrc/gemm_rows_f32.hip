@@ -1,7 +1,7 @@
 // Node update H' = sigma(Z W) of fp32 features (paper Algorithm 2, update phase) on the fp32 matrix cores:
 // C[n x MD] = act(A[n x KD] W[KD x MD]) with few columns and very many rows.  The sums are chains of fp32
 // multiply-adds over the reduction index, bit for bit those of the tiles in gemm.hip, which remain for weights
-// that do not fit LDS.
+// that do not fit LDS and where they are faster (column_tiles).
 //
 // Work split.  The weights of 32 TN output columns stay in LDS, in MFMA operand order, for as long as the workgroup
 // lives (one per compute unit); its wavefronts then walk 32-row tiles of their own without a barrier, each with the
@@ -14,8 +14,8 @@
 // reads and vector instructions alone could keep busy for 94 %.  What is between them: without the stores 1009 instead
 // of 1109 us, without the row loads 1025; more or fewer wavefronts per SIMD (1, 2, 3) 1148, 1123, 1240; stores with the
 // non-temporal hint 1136 instead of 1101 (128 -> 1024 at 2^21 rows 5005 : 4596).  us, tiles through LDS with a barrier
-// per step (gemm.hip) : here: 2^20 rows 256 -> 256 1188 : 1110, 256 -> 47 412 : 327, 256 -> 16 252 : 245; 2^21 rows 128 ->
-// 1024 4974 : 4660; 2^18 rows 128 -> 256 171 : 164, 256 -> 16 61 : 51; 20 k rows 256 -> 128 27.7 : 19.6.
+// per step (gemm.hip) : here: 2^20 rows 256 -> 256 1188 : 1110, 256 -> 47 412 : 327; 2^21 rows 128 -> 1024 4974 : 4660; 2^18
+// rows 128 -> 256 171 : 164, 256 -> 16 61 : 51; 20 k rows 256 -> 128 27.7 : 19.6.
 #include <type_traits>
 
 #include "gemm_common.h"
@@ -349,8 +349,8 @@ int column_tiles(int64_t n, int KD, int MD)
         // 5120 64 -> 512 0.93, 25600 256 -> 128 0.89.  As long as none of them walks two tiles (5000 rows 256 -> 602
         // 0.65) or the workgroups of the second round are few (1000 64 -> 1500 1.33, 2500 64 -> 2048 0.95).  Shallow
         // depths gain by it where few compute units have a tile at all (8000 48 -> 256 1.22, 12 k 0.98; 16 -> 128 of 8000
-        // 1.31, 20 k 0.90; no edge, 5120 32 -> 256 1.02, 10 k 0.86), or one or two
-        // column tiles have columns left over (25 k 16 -> 80 1.06, 4096 48 -> 602 0.89).
+        // 1.31, 20 k 0.90; no edge, 5120 32 -> 256 1.02, 10 k 0.86), or one or two column tiles have columns left over
+        // (25 k 16 -> 80 1.06, 4096 48 -> 602 0.89).
         if (grid <= 200) {
             const Passes p = passes<1>(n, MD);
             const int64_t most = whole ? (KD < 32 ? 0 : KD < 64 ? 64 : KD < 96 ? 110 : 128)
