@@ -338,6 +338,7 @@ Passes passes(int64_t n, int MD)
 // many times as fast it is here.
 int column_tiles(int64_t n, int KD, int MD)
 {
+    if (n <= 0) return 0;
     const int64_t tiles = ceil_div(n, kTileRows), blocks = ceil_div(n, 128);
     // gemm.hip: its workgroups, and whether none has a tile at an edge of the columns, or at any edge.  A small launch takes
     // as long as its slowest workgroup, and one with an edge takes half as long again.
@@ -370,7 +371,7 @@ int column_tiles(int64_t n, int KD, int MD)
     if (MD > 32 && KD >= 192 && tiles >= 8192) return passes<2>(n, MD).full(85) && fits<2>(KD) ? 2 : 0;
     // 32 columns.  A step is 32 indices deep here, 16 in gemm.hip: not where the last one is mostly zeros (100 k rows
     // 47 -> 32 0.80, 80 -> 24 0.95), nor for shallow depths (100 k 16 -> 32 0.72).
-    if (KD < 64 || 9 * KD < 8 * 32 * ceil_div(KD, 32) || !fits<1>(KD)) return 0;
+    if (KD < 64 || !fits<1>(KD) || 9 * KD < 8 * 32 * ceil_div(KD, 32)) return 0;
     const Passes p = passes<1>(n, MD);
     // Nearly all wavefronts with two to four tiles each: 2^18 rows 256 -> 16 1.26, 256 -> 32 1.04, 2^19 256 -> 16 1.04,
     // 2^20 no faster; 135 k rows, one tile and a little, 0.73, 400 k, three and a little, 0.85.

@@ -45,6 +45,17 @@ def test_layers_that_read_the_relu_derivative_twice(n, k, m):
     assert not f(n, k, m) and f(n, 128, 1024)
 
 
+@pytest.mark.parametrize("dtype", [mg.F32, mg.BF16])
+@pytest.mark.parametrize("k,m", [(3, 2), (64, 16), (64, 47), (256, 47), (256, 256), (602, 1024)])
+def test_products_without_rows(in_lds, dtype, k, m):
+    """Nothing is launched, and nothing divides by the number of tiles."""
+    assert not in_lds(0, k, m)
+    for op in (mg.OP_FWD, mg.OP_FWD_RELU, mg.OP_DGRAD):
+        pitch = 1024
+        assert mg.load_library().mixgcn_update(op, dtype, 4096, pitch, 4096, pitch, 4096, pitch, 0, k, m, None, 0,
+                                               ctypes.c_float(0), None) == 0
+
+
 class ReluBits(ctypes.Structure):
     _fields_ = [("p", ctypes.c_void_p), ("pitch", ctypes.c_int64)]
 
